@@ -49,13 +49,16 @@ size_t scan_scratch_elems(int64_t n);
 int32_t exclusive_scan_i64(int64_t* data, int64_t n, int64_t* scratch, int64_t* total_out,
                            hipStream_t stream);
 
-// Stable least-significant-digit radix sort of (key, payload) records on the
-// key bits [lo_a, lo_a + nbits_a) then [lo_b, lo_b + nbits_b).  The result is
-// left in (keys, vals); (keys_alt, vals_alt) are scratch of the same size.
+// Stable least-significant-digit radix sort of (key, value) records on the low `nbits` bits of
+// min(key, limit); vals_in == null: keys alone.  The passes alternate between the output and the
+// alternate buffers and end in the output.  keys_in / vals_in are not written unless they are the
+// buffer of a later pass: they may be the alternate buffers when the number of passes is odd, the
+// output when it is even.  n < 2^32.
 size_t radix_sort_scratch_bytes(int64_t n);
-int32_t radix_sort_u64_u32(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                           int64_t n, int lo_a, int nbits_a, int lo_b, int nbits_b,
-                           void* scratch, hipStream_t stream);
+int radix_sort_passes(int nbits);
+template <typename K>
+int32_t radix_sort(const K* keys_in, const uint32_t* vals_in, K* keys_out, uint32_t* vals_out, K* keys_alt,
+                   uint32_t* vals_alt, int64_t n, K limit, int nbits, void* scratch, hipStream_t stream);
 
 // ---- device side -----------------------------------------------------------
 #if defined(__HIPCC__)

@@ -1,5 +1,5 @@
 // gs_csr_build: edge list -> CSR on the device (GraphScale Sec. 3.1: the
-// topology a trainer keeps).  Records (src << 32 | dst, input index) are sorted
+// topology a trainer keeps).  Records (src << id_bits | dst, weight) are sorted
 // stably, duplicates are flagged, and the survivors are compacted.
 #include "common.h"
 
@@ -7,9 +7,12 @@ namespace gs {
 
 constexpr uint64_t kDroppedKey = ~0ull;
 
+// The weight travels with its key (the sort is stable: among equal keys the one from the lowest
+// input index stays first), so nothing is gathered from the edge list afterwards; without weights
+// the keys travel alone, because equal keys cannot be told apart.
 __global__ void csr_keygen_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                  int64_t cap, int64_t num_nodes, uint32_t flags,
-                                  uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+                                  const float* __restrict__ w, int64_t cap, int64_t num_nodes, uint32_t flags,
+                                  int id_bits, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= cap) return;
   const bool sym = flags & GS_SYMMETRIZE;
@@ -18,33 +21,77 @@ __global__ void csr_keygen_kernel(const int32_t* __restrict__ src, const int32_t
   if (sym && (e & 1)) { int32_t t = s; s = d; d = t; }
   const bool ok = s >= 0 && d >= 0 && s < num_nodes && d < num_nodes &&
                   !((flags & GS_DROP_SELF_LOOPS) && s == d);
-  keys[e] = ok ? (((uint64_t)(uint32_t)s << 32) | (uint64_t)(uint32_t)d) : kDroppedKey;
-  vals[e] = (uint32_t)i;
+  keys[e] = ok ? (((uint64_t)(uint32_t)s << id_bits) | (uint64_t)(uint32_t)d) : kDroppedKey;
+  if (w != nullptr) vals[e] = __float_as_uint(w[i]);
 }
 
-__device__ __forceinline__ bool csr_keeps(const uint64_t* keys, int64_t e, bool dedupe) {
+// Compaction: a block takes kCompactTile consecutive records, counts the kept ones (first kernel)
+// and, once the counts of the tiles are summed, moves them (second kernel).  In both, a wave takes
+// its share 64 records at a time, so the place of a record is its rank among the lanes' votes.
+constexpr int kCompactThreads = 256;
+constexpr int kCompactWaves = kCompactThreads / 64;
+constexpr int kCompactItems = 8;                              // records per lane
+constexpr int kCompactTile = kCompactThreads * kCompactItems;
+
+__device__ __forceinline__ bool csr_keeps(const uint64_t* __restrict__ keys, int64_t e, int64_t cap, bool dedupe) {
+  if (e >= cap) return false;
   const uint64_t k = keys[e];
   if (k == kDroppedKey) return false;
   return !(dedupe && e > 0 && keys[e - 1] == k);
 }
 
-__global__ void csr_flag_kernel(const uint64_t* __restrict__ keys, int64_t cap, uint32_t flags,
-                                int64_t* __restrict__ pos) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < cap) pos[e] = csr_keeps(keys, e, flags & GS_DEDUPE) ? 1 : 0;
+__global__ __launch_bounds__(kCompactThreads) void csr_count_kernel(const uint64_t* __restrict__ keys, int64_t cap,
+                                                                    uint32_t flags, int64_t* __restrict__ tile_counts) {
+  __shared__ uint32_t wave_kept[kCompactWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * kCompactTile + wave * (64 * kCompactItems) + lane;
+  uint32_t kept = 0;
+#pragma unroll
+  for (int c = 0; c < kCompactItems; ++c)
+    kept += (uint32_t)__popcll(__ballot(csr_keeps(keys, first + c * 64, cap, flags & GS_DEDUPE)));
+  if (lane == 0) wave_kept[wave] = kept;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t sum = 0;
+#pragma unroll
+    for (int w = 0; w < kCompactWaves; ++w) sum += wave_kept[w];
+    tile_counts[blockIdx.x] = sum;
+  }
 }
 
-__global__ void csr_compact_kernel(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals,
-                                   const int64_t* __restrict__ pos, int64_t cap, uint32_t flags,
-                                   const float* __restrict__ w, int32_t* __restrict__ nbrs_out,
-                                   float* __restrict__ w_out, int32_t* __restrict__ row_of) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= cap || !csr_keeps(keys, e, flags & GS_DEDUPE)) return;
-  const int64_t p = pos[e];
-  const uint64_t k = keys[e];
-  nbrs_out[p] = (int32_t)(uint32_t)k;
-  row_of[p] = (int32_t)(uint32_t)(k >> 32);
-  if (w != nullptr) w_out[p] = w[vals[e]];
+__global__ __launch_bounds__(kCompactThreads) void csr_compact_kernel(
+    const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals, const int64_t* __restrict__ tile_first,
+    int64_t cap, uint32_t flags, int id_bits, int32_t* __restrict__ nbrs_out, float* __restrict__ w_out,
+    int32_t* __restrict__ row_of) {
+  __shared__ uint32_t wave_kept[kCompactWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * kCompactTile + wave * (64 * kCompactItems) + lane;
+  const uint64_t below = (1ull << lane) - 1ull;
+  uint32_t place[kCompactItems];                              // among the wave's kept records
+  bool keep[kCompactItems];
+  uint32_t kept = 0;
+#pragma unroll
+  for (int c = 0; c < kCompactItems; ++c) {
+    keep[c] = csr_keeps(keys, first + c * 64, cap, flags & GS_DEDUPE);
+    const uint64_t votes = __ballot(keep[c]);
+    place[c] = kept + (uint32_t)__popcll(votes & below);
+    kept += (uint32_t)__popcll(votes);
+  }
+  if (lane == 0) wave_kept[wave] = kept;
+  __syncthreads();
+  int64_t at = tile_first[blockIdx.x];
+#pragma unroll
+  for (int w = 0; w < kCompactWaves; ++w)
+    if (w < wave) at += wave_kept[w];
+#pragma unroll
+  for (int c = 0; c < kCompactItems; ++c) {
+    if (!keep[c]) continue;
+    const int64_t e = first + c * 64, p = at + place[c];
+    const uint64_t k = keys[e];
+    nbrs_out[p] = (int32_t)(k & ((1ull << id_bits) - 1ull));
+    row_of[p] = (int32_t)(k >> id_bits);
+    if (vals != nullptr) w_out[p] = __uint_as_float(vals[e]);
+  }
 }
 
 // offsets[v] = number of kept entries whose row is < v  (lower bound in row_of)
@@ -70,8 +117,8 @@ static int bits_for(int64_t n) {  // bits needed for ids in [0, n)
 
 struct CsrPlan {
   uint64_t *keys, *keys_alt;
-  uint32_t *vals, *vals_alt;
-  int64_t *pos, *scan_scratch;
+  uint32_t *vals, *vals_alt;     // weighted graphs only use them
+  int64_t *tile_first, *scan_scratch;
   int32_t* row_of;
   void* sort_scratch;
   size_t bytes;
@@ -81,12 +128,13 @@ static CsrPlan plan_csr(void* ws, int64_t cap) {
   Carver cv(ws);
   CsrPlan p;
   const size_t c = (size_t)(cap > 0 ? cap : 1);
+  const int64_t tiles = ceil_div((int64_t)c, kCompactTile);
   p.keys = cv.take<uint64_t>(c);
   p.keys_alt = cv.take<uint64_t>(c);
   p.vals = cv.take<uint32_t>(c);
   p.vals_alt = cv.take<uint32_t>(c);
-  p.pos = cv.take<int64_t>(c);
-  p.scan_scratch = cv.take<int64_t>(scan_scratch_elems((int64_t)c));
+  p.tile_first = cv.take<int64_t>((size_t)tiles);
+  p.scan_scratch = cv.take<int64_t>(scan_scratch_elems(tiles));
   p.row_of = cv.take<int32_t>(c);
   p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)c));
   p.bytes = cv.used;
@@ -124,24 +172,28 @@ extern "C" int32_t gs_csr_build(const int32_t* src, const int32_t* dst, const fl
   if (ws_bytes < p.bytes) return GS_EWORKSPACE;
 
   const int threads = 256;
+  const int64_t tiles = ceil_div(cap, kCompactTile);
+  const int nb = bits_for(num_nodes);
   if (cap > 0) {
-    const unsigned blocks = (unsigned)ceil_div(cap, threads);
-    csr_keygen_kernel<<<blocks, threads, 0, stream>>>(src, dst, cap, num_nodes, flags, p.keys, p.vals);
+    // ids take nb bits, and the key has one bit more than two ids, so dropped records sort last.
+    // The passes go back and forth between two buffers and end in (keys, vals).
+    const bool odd = radix_sort_passes(2 * nb + 1) & 1;
+    uint64_t* made = odd ? p.keys_alt : p.keys;
+    uint32_t* made_vals = w == nullptr ? nullptr : (odd ? p.vals_alt : p.vals);
+    csr_keygen_kernel<<<(unsigned)ceil_div(cap, threads), threads, 0, stream>>>(src, dst, w, cap, num_nodes, flags, nb,
+                                                                               made, made_vals);
     GS_LAUNCH_CHECK();
-    const int nb = bits_for(num_nodes);
-    // dst field first, then src field with one extra bit so dropped records sort last
-    int32_t rc = radix_sort_u64_u32(p.keys, p.vals, p.keys_alt, p.vals_alt, cap, 0, nb, 32, nb + 1,
-                                    p.sort_scratch, stream);
+    const int32_t rc = radix_sort<uint64_t>(made, made_vals, p.keys, p.vals, p.keys_alt, p.vals_alt, cap, kDroppedKey,
+                                            2 * nb + 1, p.sort_scratch, stream);
     if (rc != GS_OK) return rc;
-    csr_flag_kernel<<<blocks, threads, 0, stream>>>(p.keys, cap, flags, p.pos);
+    csr_count_kernel<<<(unsigned)tiles, kCompactThreads, 0, stream>>>(p.keys, cap, flags, p.tile_first);
     GS_LAUNCH_CHECK();
   }
-  int32_t rc = exclusive_scan_i64(p.pos, cap, p.scan_scratch, num_entries_out, stream);
+  const int32_t rc = exclusive_scan_i64(p.tile_first, tiles, p.scan_scratch, num_entries_out, stream);
   if (rc != GS_OK) return rc;
   if (cap > 0) {
-    const unsigned blocks = (unsigned)ceil_div(cap, threads);
-    csr_compact_kernel<<<blocks, threads, 0, stream>>>(p.keys, p.vals, p.pos, cap, flags, w, nbrs_out,
-                                                       w_out, p.row_of);
+    csr_compact_kernel<<<(unsigned)tiles, kCompactThreads, 0, stream>>>(
+        p.keys, w != nullptr ? p.vals : nullptr, p.tile_first, cap, flags, nb, nbrs_out, w_out, p.row_of);
     GS_LAUNCH_CHECK();
   }
   const unsigned oblocks = (unsigned)ceil_div(num_nodes + 1, threads);

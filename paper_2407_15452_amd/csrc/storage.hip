@@ -13,33 +13,29 @@ constexpr int kRowLanes = 16;                       // lanes per row, 16 bytes e
 constexpr int kRowThreads = 256;
 constexpr int kRowsPerBlock = kRowThreads / kRowLanes;
 
-// id -> sort key; ids that are not rows get the key num_nodes and sort last
-__global__ void unique_keys_kernel(const int32_t* __restrict__ ids, int64_t n, int64_t num_nodes,
-                                   uint64_t* __restrict__ keys, uint32_t* __restrict__ index) {
+__global__ void index_kernel(int64_t n, uint32_t* __restrict__ index) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int32_t v = ids[i];
-  keys[i] = (v >= 0 && (int64_t)v < num_nodes) ? (uint64_t)v : (uint64_t)num_nodes;
-  index[i] = (uint32_t)i;
+  if (i < n) index[i] = (uint32_t)i;
 }
 
-// head[j] = 1 where a new valid id starts in the sorted keys
-__global__ void unique_heads_kernel(const uint64_t* __restrict__ keys, int64_t n, int64_t num_nodes,
+// head[j] = 1 where a new valid id starts in the sorted ids (those that are not rows come last, in
+// any order)
+__global__ void unique_heads_kernel(const uint32_t* __restrict__ keys, int64_t n, int64_t num_nodes,
                                     int64_t* __restrict__ head) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
-  const uint64_t k = keys[j];
-  head[j] = (k < (uint64_t)num_nodes && (j == 0 || keys[j - 1] != k)) ? 1 : 0;
+  const uint32_t k = keys[j];
+  head[j] = ((int64_t)k < num_nodes && (j == 0 || keys[j - 1] != k)) ? 1 : 0;
 }
 
 // before[j] = number of heads before j (exclusive scan of head)
-__global__ void unique_emit_kernel(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ index,
+__global__ void unique_emit_kernel(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ index,
                                    const int64_t* __restrict__ before, int64_t n, int64_t num_nodes,
                                    int32_t* __restrict__ unique_out, int32_t* __restrict__ inverse_out) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
-  const uint64_t k = keys[j];
-  const bool valid = k < (uint64_t)num_nodes;
+  const uint32_t k = keys[j];
+  const bool valid = (int64_t)k < num_nodes;
   const bool is_head = valid && (j == 0 || keys[j - 1] != k);
   const int64_t b = before[j];
   if (is_head) unique_out[b] = (int32_t)k;
@@ -181,19 +177,6 @@ __global__ __launch_bounds__(kRowThreads) void put_rows16_kernel(
   }
 }
 
-// pairs in sorted order: entry j comes from input position index[j]
-__global__ void sort_pairs_gather_kernel(const uint32_t* __restrict__ index,
-                                         const int32_t* __restrict__ centers,
-                                         const int32_t* __restrict__ contexts, int64_t n,
-                                         int32_t* __restrict__ centers_out,
-                                         int32_t* __restrict__ contexts_out) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const uint32_t from = index[j];
-  centers_out[j] = centers[from];
-  contexts_out[j] = contexts[from];
-}
-
 // ---- dense operations over a whole table: 16 bytes per lane, grid-stride ----------------
 __global__ __launch_bounds__(256) void table_mult_f32_kernel(float4* __restrict__ t, int64_t n4,
                                                              float factor) {
@@ -279,7 +262,7 @@ BitmapPlan plan_bitmap(void* ws, int64_t num_nodes) {
 }
 
 struct UniquePlan {
-  uint64_t *keys, *keys_alt;
+  uint32_t *keys, *keys_alt;
   uint32_t *index, *index_alt;
   int64_t *head, *scan_scratch;
   void* sort_scratch;
@@ -290,8 +273,8 @@ UniquePlan plan_unique(void* ws, int64_t n) {
   Carver cv(ws);
   UniquePlan p;
   const size_t m = (size_t)(n > 0 ? n : 1);
-  p.keys = cv.take<uint64_t>(m);
-  p.keys_alt = cv.take<uint64_t>(m);
+  p.keys = cv.take<uint32_t>(m);
+  p.keys_alt = cv.take<uint32_t>(m);
   p.index = cv.take<uint32_t>(m);
   p.index_alt = cv.take<uint32_t>(m);
   p.head = cv.take<int64_t>(m);
@@ -302,8 +285,7 @@ UniquePlan plan_unique(void* ws, int64_t n) {
 }
 
 struct SortPairsPlan {
-  uint64_t *keys, *keys_alt;
-  uint32_t *index, *index_alt;
+  uint32_t *keys_alt, *vals_alt;
   void* sort_scratch;
   size_t bytes;
 };
@@ -312,10 +294,8 @@ SortPairsPlan plan_sort_pairs(void* ws, int64_t n) {
   Carver cv(ws);
   SortPairsPlan p;
   const size_t m = (size_t)(n > 0 ? n : 1);
-  p.keys = cv.take<uint64_t>(m);
-  p.keys_alt = cv.take<uint64_t>(m);
-  p.index = cv.take<uint32_t>(m);
-  p.index_alt = cv.take<uint32_t>(m);
+  p.keys_alt = cv.take<uint32_t>(m);
+  p.vals_alt = cv.take<uint32_t>(m);
   p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)m));
   p.bytes = cv.used;
   return p;
@@ -385,10 +365,12 @@ extern "C" int32_t gs_unique_ids(const int32_t* ids, int64_t n, int64_t num_node
   if (ws_bytes < p.bytes) return GS_EWORKSPACE;
   const unsigned blocks = (unsigned)ceil_div(n, 256);
   if (n > 0) {
-    unique_keys_kernel<<<blocks, 256, 0, stream>>>(ids, n, num_nodes, p.keys, p.index);
+    const int nbits = bits_for((uint64_t)num_nodes);
+    uint32_t* index = (radix_sort_passes(nbits) & 1) ? p.index_alt : p.index;
+    index_kernel<<<blocks, 256, 0, stream>>>(n, index);
     GS_LAUNCH_CHECK();
-    int32_t rc = radix_sort_u64_u32(p.keys, p.index, p.keys_alt, p.index_alt, n, 0,
-                                    bits_for((uint64_t)num_nodes), 0, 0, p.sort_scratch, stream);
+    const int32_t rc = radix_sort<uint32_t>(reinterpret_cast<const uint32_t*>(ids), index, p.keys, p.index, p.keys_alt,
+                                            p.index_alt, n, (uint32_t)num_nodes, nbits, p.sort_scratch, stream);
     if (rc != GS_OK) return rc;
     unique_heads_kernel<<<blocks, 256, 0, stream>>>(p.keys, n, num_nodes, p.head);
     GS_LAUNCH_CHECK();
@@ -502,14 +484,9 @@ extern "C" int32_t gs_sort_pairs(const int32_t* centers, const int32_t* contexts
   SortPairsPlan p = plan_sort_pairs(ws, n);
   if (ws_bytes < p.bytes) return GS_EWORKSPACE;
   if (n == 0) return GS_OK;
-  const unsigned blocks = (unsigned)ceil_div(n, 256);
-  unique_keys_kernel<<<blocks, 256, 0, stream>>>(centers, n, num_nodes, p.keys, p.index);
-  GS_LAUNCH_CHECK();
-  const int32_t rc = radix_sort_u64_u32(p.keys, p.index, p.keys_alt, p.index_alt, n, 0,
-                                        bits_for((uint64_t)num_nodes), 0, 0, p.sort_scratch, stream);
-  if (rc != GS_OK) return rc;
-  sort_pairs_gather_kernel<<<blocks, 256, 0, stream>>>(p.index, centers, contexts, n, centers_out,
-                                                       contexts_out);
-  GS_LAUNCH_CHECK();
-  return GS_OK;
+  // the pair itself is the record: a source id that is not a row sorts as num_nodes, i.e. last
+  return radix_sort<uint32_t>(reinterpret_cast<const uint32_t*>(centers), reinterpret_cast<const uint32_t*>(contexts),
+                              reinterpret_cast<uint32_t*>(centers_out), reinterpret_cast<uint32_t*>(contexts_out),
+                              p.keys_alt, p.vals_alt, n, (uint32_t)num_nodes, bits_for((uint64_t)num_nodes),
+                              p.sort_scratch, stream);
 }

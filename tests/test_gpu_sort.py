@@ -1,0 +1,71 @@
+"""The device radix sort through the calls that use it: tile edges (2048 and 8192 records), the
+size from which the large tiles are taken (2^21), and odd and even numbers of passes."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def gs():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_15452_amd import binding
+    binding.lib()
+    return binding
+
+
+def _t(a):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(DEV)
+
+
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, (1 << 21) - 1, (1 << 21) + 8191])
+@pytest.mark.parametrize("num_nodes", [1, 200, 60_000, 5_000_000, (1 << 31) - 1])    # 1, 1, 2, 3 and 4 passes
+def test_sort_pairs_sizes(gs, n, num_nodes):
+    rng = np.random.default_rng(n + num_nodes)
+    c = rng.integers(0, num_nodes, n).astype(np.int32)
+    c[rng.integers(0, n, n // 3)] = c[0]                   # one long run of equal sources
+    c[rng.integers(0, n, n // 50)] = -7                    # not rows: last, in input order
+    o = np.arange(n, dtype=np.int32)                       # shows whether the order is stable
+    at = np.argsort(np.where(c < 0, num_nodes, c.astype(np.int64)), kind="stable")
+    got_c, got_o = gs.gs_sort_pairs(_t(c), _t(o), num_nodes)
+    np.testing.assert_array_equal(got_o.cpu().numpy(), o[at])
+    np.testing.assert_array_equal(got_c.cpu().numpy(), c[at])
+
+
+@pytest.mark.parametrize("m,num_nodes", [(1, 1), (1023, 9), (1024, 300), (40_000, 5000), (40_001, 70_000),
+                                         ((1 << 20) + 17, 3_000_000)])     # 1, 2, 3, 4, 5 and 6 passes
+@pytest.mark.parametrize("weighted", [False, True])
+def test_csr_sizes(gs, oracle, m, num_nodes, weighted):
+    rng = np.random.default_rng(m)
+    src = rng.integers(-1, num_nodes + 1, m).astype(np.int32)
+    dst = rng.integers(0, num_nodes, m).astype(np.int32)
+    dup = rng.integers(0, m, m // 4)
+    src[dup], dst[dup] = src[0], dst[0]                    # one entry many times over
+    w = rng.random(m).astype(np.float32) if weighted else None
+    flags = gs.GS_SYMMETRIZE | gs.GS_DEDUPE
+    off, nb, wo = oracle.csr_build(src, dst, w, num_nodes, flags, 32)
+    g = gs.gs_csr_build(_t(src), _t(dst), _t(w) if weighted else None, num_nodes, flags)
+    np.testing.assert_array_equal(g.offsets.cpu().numpy(), off)
+    np.testing.assert_array_equal(g.nbrs.cpu().numpy(), nb)
+    if weighted:
+        np.testing.assert_array_equal(g.weights.cpu().numpy(), wo)
+
+
+@pytest.mark.parametrize("n,num_nodes", [(1, 1 << 20), (2049, 1 << 24), (5000, (1 << 31) - 1)])
+def test_unique_ids_by_sorting(gs, n, num_nodes):
+    """Graphs far larger than the batch: the ids are sorted (3 and 4 passes)."""
+    rng = np.random.default_rng(n)
+    ids = rng.integers(0, num_nodes, n).astype(np.int32)
+    ids[rng.integers(0, n, n // 2)] = ids[0]
+    ids[rng.integers(0, n, n // 10)] = -1
+    want, inverse = np.unique(ids[ids >= 0], return_inverse=True)
+    u, count, inv = gs.gs_unique_ids(_t(ids), num_nodes)
+    assert int(count.item()) == want.size
+    np.testing.assert_array_equal(u.cpu().numpy()[:want.size], want)
+    got = inv.cpu().numpy()
+    np.testing.assert_array_equal(got[ids >= 0], inverse)
+    assert (got[ids < 0] == -1).all()
