@@ -35,6 +35,9 @@
 //   finish     table[row] = round(old + side buffer) for the longer rows; one
 //              extra block sums the per-block loss partials in a fixed order
 //
+// Small batches take two launches instead (forward, and one kernel for the rest): see
+// sgns_small_update_kernel.
+//
 // delta is accumulated exactly: every product coef * element is rounded once to
 // a multiple of 2^-36 (one fp64 fused multiply-add against 1.5 * 2^52, whose
 // result bits hold the integer) and the 64-bit integers are added.  Integer
@@ -451,12 +454,12 @@ __global__ void sgns_clear_kernel(uint4* __restrict__ cnt4, int64_t n4, uint4* _
 // order.  Slot numbers are fixed by position (first pair of the chunk + flush
 // number), so no counter is shared between groups; unused slots of a chunk are
 // marked with centre -1.
-template <typename T, int VPL>
+template <typename T, int VPL, bool kRank>
 __device__ __forceinline__ void stage_flush(const SgnsArgs& a, int64_t slot, int32_t center, int l16,
                                             const float4 (&du)[VPL]) {
   if (l16 == 0) {
     a.stage_center[slot] = center;
-    a.stage_rank[slot] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)a.num_nodes + (uint32_t)center), 1u);
+    if constexpr (kRank) a.stage_rank[slot] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)a.num_nodes + (uint32_t)center), 1u);
   }
   float4* out = reinterpret_cast<float4*>(a.stage_delta + slot * (int64_t)a.dim);
   const int dim4 = a.dim >> 2;
@@ -477,25 +480,41 @@ __device__ __forceinline__ float row_peak(const float4 (&r)[VPL]) {
   return m;
 }
 
-template <typename T, int VPL, int RB>
-__global__ __launch_bounds__(kSgnsThreads) void sgns_forward_kernel(SgnsArgs a) {
-  extern __shared__ int32_t idx_s[];              // per group: centres[16], rows[16][K+1]
-  __shared__ float loss_s[kGroupsPerBlock];
+//
+// kRank = false: the step of a small batch (below), whose update kernel groups the terms itself.
+// Nothing is counted, and a bad id or an out-of-range product turns the block's loss partial into
+// NaN (there is no flag that an earlier kernel would have cleared).
+template <typename T, int VPL, int RB, bool kRank, int kThreads>
+__global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
+  constexpr int kGroups = kThreads / kGroupLanes;
+  extern __shared__ int32_t idx_s[];              // per group: centres[chunk], rows[chunk][K+1]
+  __shared__ float loss_s[kGroups];
   // Rank counters of rows that many terms hit at once are same-address atomics in
   // memory, which serialise.  Each block therefore counts up to kHotSlots rows
   // locally first (whichever rows reach a slot of this small LDS table first):
   // a term of such a row takes a block-local rank, the block adds its total to
   // the row's global counter once, and the ranks are completed afterwards.
-  __shared__ int32_t hot_key[kHotSlots];
-  __shared__ uint32_t hot_cnt[kHotSlots];
-  __shared__ uint32_t hot_base[kHotSlots];
+  __shared__ int32_t hot_key[kRank ? kHotSlots : 1];
+  __shared__ uint32_t hot_cnt[kRank ? kHotSlots : 1];
+  __shared__ uint32_t hot_base[kRank ? kHotSlots : 1];
+  bool bad = false;
+  auto row_of = [&](int32_t id) -> int32_t {
+    if constexpr (kRank) return checked_row(a, id);
+    if ((uint32_t)id < (uint32_t)a.num_nodes) return id;
+    bad = true;
+    return 0;
+  };
+  auto report = [&]() {
+    if constexpr (kRank) *a.bad_ids = 1u;
+    else bad = true;
+  };
   const T* __restrict__ w_in = static_cast<const T*>(a.w_in);
   const T* __restrict__ w_out = static_cast<const T*>(a.w_out);
   const int l16 = threadIdx.x & (kGroupLanes - 1);
   const int group_in_block = threadIdx.x / kGroupLanes;
   const int64_t block = xcd_contiguous_block(blockIdx.x, a.forward_blocks_per_xcd);
   const int K = a.k, K1 = a.k + 1;
-  const int64_t group = block * kGroupsPerBlock + group_in_block;
+  const int64_t group = block * kGroups + group_in_block;
   const int64_t first = group * a.chunk_pairs;
   const bool block_live = block < a.forward_blocks;
   const int64_t last = block_live ? min(first + a.chunk_pairs, a.num_pairs) : first;
@@ -503,7 +522,8 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_forward_kernel(SgnsArgs a) 
 
   int32_t* cen_s = idx_s + group_in_block * (a.chunk_pairs * (K1 + 1));
   int32_t* rows_s = cen_s + a.chunk_pairs;
-  for (int h = threadIdx.x; h < kHotSlots; h += kSgnsThreads) { hot_key[h] = -1; hot_cnt[h] = 0u; }
+  if constexpr (kRank)
+    for (int h = threadIdx.x; h < kHotSlots; h += kThreads) { hot_key[h] = -1; hot_cnt[h] = 0u; }
   if (a.walks != nullptr) {
     if (l16 < count) {                      // lane p derives pair p of the chunk from its walk
       int32_t c = 0, o = 0;
@@ -522,32 +542,32 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_forward_kernel(SgnsArgs a) 
           c = row[at];
           o = row[other];
         } else {
-          *a.bad_ids = 1u;                  // pair_offsets does not belong to these walks
+          report();                         // pair_offsets does not belong to these walks
         }
       } else {
-        *a.bad_ids = 1u;                    // the walks do not hold that many pairs
+        report();                           // the walks do not hold that many pairs
       }
       a.gen_centers[first + l16] = c;
       a.gen_contexts[first + l16] = o;
-      cen_s[l16] = checked_row(a, c);
-      rows_s[l16 * K1] = checked_row(a, o);
+      cen_s[l16] = row_of(c);
+      rows_s[l16 * K1] = row_of(o);
     }
   } else if (l16 < count) {
-    cen_s[l16] = checked_row(a, a.centers[first + l16]);
+    cen_s[l16] = row_of(a.centers[first + l16]);
   }
   for (int t = l16; t < count * K1; t += kGroupLanes) {
     const int p = t / K1, j = t - p * K1;
     int32_t row;
     if (j == 0) {
       if (a.walks != nullptr) continue;     // set above
-      row = checked_row(a, a.contexts[first + p]);
+      row = row_of(a.contexts[first + p]);
     } else if (a.draw_negs) {
       const Block4 b = philox_at(a.neg_seed, a.neg_pair_base + (uint64_t)(first + p), (uint32_t)(j - 1),
                                  0x80000000u);
       row = (int32_t)table_draw(a.noise_prob, a.noise_alias, a.noise_packed, (uint64_t)a.num_nodes, b);
       a.negs_draw[(first + p) * (int64_t)K + (j - 1)] = row;
     } else {
-      row = checked_row(a, a.negs[(first + p) * (int64_t)K + (j - 1)]);
+      row = row_of(a.negs[(first + p) * (int64_t)K + (j - 1)]);
     }
     rows_s[t] = row;
   }
@@ -569,7 +589,7 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_forward_kernel(SgnsArgs a) 
     if (c != cur_c) {
       if (cur_c >= 0) {
         peak = fmaxf(peak, row_peak<VPL>(du));
-        stage_flush<T, VPL>(a, first + flushes++, cur_c, l16, du);
+        stage_flush<T, VPL, kRank>(a, first + flushes++, cur_c, l16, du);
       }
       load_row<VPL>(w_in, c, a.dim, l16, u);
       peak = fmaxf(peak, row_peak<VPL>(u));
@@ -589,7 +609,7 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_forward_kernel(SgnsArgs a) 
       const int my_j = j0 + l16;
       const bool mine = l16 < RB && my_j <= K;
       uint32_t rk = 0;
-      if (mine) {
+      if (kRank && mine) {
         const int32_t row = prow[my_j];
         const uint32_t h = ((uint32_t)row * 2654435761u) >> (32 - kHotBits);
         const int32_t seen = atomicCAS(&hot_key[h], -1, row);
@@ -616,34 +636,40 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_forward_kernel(SgnsArgs a) 
 #pragma unroll
       for (int b = 0; b < RB; ++b)
         if (j0 + b <= K) axpy<VPL>(du, __shfl(g_mine, b, kGroupLanes), vv[b]);
-      if (mine) { a.g[e0 + my_j] = g_mine; a.rank[e0 + my_j] = rk; }
+      if (mine) {
+        a.g[e0 + my_j] = g_mine;
+        if constexpr (kRank) a.rank[e0 + my_j] = rk;
+      }
     }
   }
   if (cur_c >= 0) {
     peak = fmaxf(peak, row_peak<VPL>(du));
-    stage_flush<T, VPL>(a, first + flushes++, cur_c, l16, du);
+    stage_flush<T, VPL, kRank>(a, first + flushes++, cur_c, l16, du);
   }
   if (l16 >= flushes && l16 < count) a.stage_center[first + l16] = -1;
-  if (!(peak * fabsf(a.lr) < kFixPeak)) *a.bad_ids = 1u;   // (also taken for NaN)
+  if (!(peak * fabsf(a.lr) < kFixPeak)) report();   // (also taken for NaN)
+  if (!kRank && bad) loss = __uint_as_float(0x7fc00000u);
 
   loss = row_sum16(loss);
   if (l16 == 0) loss_s[group_in_block] = loss;
   __syncthreads();
-  // one global update per locally counted row, then complete the pending ranks
-  for (int h = threadIdx.x; h < kHotSlots; h += kSgnsThreads)
-    if (hot_key[h] >= 0) hot_base[h] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)hot_key[h]), hot_cnt[h]);
-  __syncthreads();
-  for (int t = l16; t < count * K1; t += kGroupLanes) {
-    const int64_t e = first * (int64_t)K1 + t;
-    // written above by another lane of this group: read it back past the L1
-    const uint32_t rk = __hip_atomic_load(a.rank + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (rk & kRankPending)
-      a.rank[e] = hot_base[rk & (kHotSlots - 1)] + ((rk & ~kRankPending) >> kHotBits);
+  if constexpr (kRank) {
+    // one global update per locally counted row, then complete the pending ranks
+    for (int h = threadIdx.x; h < kHotSlots; h += kThreads)
+      if (hot_key[h] >= 0) hot_base[h] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)hot_key[h]), hot_cnt[h]);
+    __syncthreads();
+    for (int t = l16; t < count * K1; t += kGroupLanes) {
+      const int64_t e = first * (int64_t)K1 + t;
+      // written above by another lane of this group: read it back past the L1
+      const uint32_t rk = __hip_atomic_load(a.rank + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (rk & kRankPending)
+        a.rank[e] = hot_base[rk & (kHotSlots - 1)] + ((rk & ~kRankPending) >> kHotBits);
+    }
   }
   if (threadIdx.x == 0 && block_live) {
     double s = 0.0;
 #pragma unroll
-    for (int gidx = 0; gidx < kGroupsPerBlock; ++gidx) s += (double)loss_s[gidx];
+    for (int gidx = 0; gidx < kGroups; ++gidx) s += (double)loss_s[gidx];
     a.loss_partials[block] = s;
   }
 }
@@ -943,52 +969,30 @@ __device__ __forceinline__ int64_t next_segment_start(const Term* __restrict__ s
   return limit;
 }
 
-// Ownership: the terms of a key are cut into segments of S = 2^seg_shift consecutive
-// positions (pos = 0..S-1, S..2S-1, ...); a wave handles the segments whose first term lies
-// in its slice, reading on past the slice's end to finish the last one.  A row of at most S
-// terms is one segment: it is written once, as round(old + sum).  The partial sums of a row
-// with more segments meet in the side buffer at slot (position of the row's first term) >>
-// seg_shift, which no two such rows can share because each spans more than S positions.
-// kStage = false: context-table keys, positions [0, num_terms), source rows from the input
-// table; kStage = true: input-table keys, the positions after them, source rows = staged
-// gradients (fp32, natural element order).
-template <typename T, int WPP, int PPL, int UB, bool kSq, bool kStage>
-__global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
+// What one wave does with the positions [begin, end) of key-major terms: begin and end are the
+// starts of segments (or the end of the terms).  kStage = false: context-table keys, source rows
+// from the input table; kStage = true: input-table keys, source rows = staged gradients (fp32,
+// natural element order).  kSegments = false: every key is one segment.
+template <typename T, int WPP, int PPL, int UB, bool kSq, bool kStage, bool kSegments>
+__device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __restrict__ sorted, int64_t begin,
+                                             int64_t end, int64_t pos_hi, int lane) {
   static_assert(!kSq || std::is_same<T, float>::value, "second-moment tables are fp32");
-  constexpr int kWaves = kSgnsThreads / 64;
   constexpr int EPP = WPP * Words<T>::kPerWord;          // elements per piece
   constexpr int EPL = EPP * PPL;                         // elements per lane
   constexpr int SW = kStage ? EPP : WPP;                 // 32-bit words of a source piece
-  // source rows: the input table, or the copies the forward kernel kept (one-table mode),
-  // or the staged gradients
+  // source rows: the input table, or the copies the forward kernel kept (one-table mode, small
+  // batches), or the staged gradients
   const uint32_t* __restrict__ src_base = reinterpret_cast<const uint32_t*>(
       kStage ? static_cast<const void*>(a.stage_delta) : (a.snap != nullptr ? a.snap : a.w_in));
   uint32_t* dst_base = reinterpret_cast<uint32_t*>(kStage ? a.dst_in : a.dst_out);
   uint32_t* sq_base = reinterpret_cast<uint32_t*>(kStage ? a.sq_in : a.sq_out);
   const uint32_t key_base = kStage ? (uint32_t)a.num_nodes : 0u;
-  const int64_t pos_lo = kStage ? a.num_terms : 0;
-  // (scalars that come out of memory are made wave-uniform explicitly: loop bounds and the
-  // lane numbers of the broadcasts below must live in scalar registers)
-  const int64_t pos_hi = kStage ? (int64_t)uniform_u32(a.cnt[a.cnt_last]) : a.num_terms;
-  const int lane = threadIdx.x & 63;
-  const int64_t first_wave = (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int slice = kStage ? kStageSlice : a.slice_terms;
-  const Term* __restrict__ sorted = a.sorted;
   const int64_t src_row_words = kStage ? (int64_t)a.dim : (int64_t)a.dim / Words<T>::kPerWord;
   const int64_t dst_row_words = (int64_t)a.dim / Words<T>::kPerWord;
+  const uint32_t seg_mask = kSegments ? (1u << a.seg_shift) - 1u : ~0u;
   bool piece_ok[PPL];                                    // piece p of this lane lies inside the row
 #pragma unroll
   for (int p = 0; p < PPL; ++p) piece_ok[p] = (p * 64 + lane) * EPP < a.dim;
-
-  const uint32_t seg_mask = (1u << a.seg_shift) - 1u;
-  // a wave takes the slices first_wave, first_wave + (waves of the launch), ...: the launch of
-  // the input-table pass is sized for the few slots a batch normally uses, not for one per pair
-  for (int64_t wave = first_wave;; wave += (int64_t)gridDim.x * kWaves) {
-  const int64_t slice_begin = pos_lo + wave * slice;
-  if (slice_begin >= pos_hi) break;
-  const int64_t slice_end = min(slice_begin + slice, pos_hi);
-  const int64_t begin = next_segment_start(sorted, slice_begin, pos_hi, lane, seg_mask);   // what lies before is an earlier wave's
-  const int64_t end = next_segment_start(sorted, slice_end, pos_hi, lane, seg_mask);       // finish the segment we started
 
   unsigned long long acc[EPL];
   uint32_t old[PPL][WPP];
@@ -1039,9 +1043,11 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
   // continues: the next term belongs to the same key (the row has a further segment)
   auto flush = [&](bool continues) {
     settle();
-    if (cur_seg > 0 || continues) {
-      flush_long();
-      return;
+    if constexpr (kSegments) {
+      if (cur_seg > 0 || continues) {
+        flush_long();
+        return;
+      }
     }
     const int64_t r = (int64_t)(cur_row - key_base);
     uint32_t* row_words = dst_base + r * dst_row_words;
@@ -1101,8 +1107,10 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
             const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)t.row, b0 + b);
             if (cur_row != kNoRow) flush(row == cur_row);
             cur_row = row;
-            cur_seg = pos >> a.seg_shift;
-            seg_first = q + b0 + b;
+            if constexpr (kSegments) {
+              cur_seg = pos >> a.seg_shift;
+              seg_first = q + b0 + b;
+            }
             cur_terms = 0;
 #pragma unroll
             for (int x = 0; x < EPL; ++x) acc[x] = 0;
@@ -1129,7 +1137,37 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
     }
   }
   // last pending segment: the row goes on if the term after the range has the same key
-  if (cur_row != kNoRow) flush(end < pos_hi && uniform_u32(sorted[end].row) == cur_row);
+  if (cur_row != kNoRow) flush(kSegments && end < pos_hi && uniform_u32(sorted[end].row) == cur_row);
+}
+
+// Ownership: the terms of a key are cut into segments of S = 2^seg_shift consecutive
+// positions (pos = 0..S-1, S..2S-1, ...); a wave handles the segments whose first term lies
+// in its slice, reading on past the slice's end to finish the last one.  A row of at most S
+// terms is one segment: it is written once, as round(old + sum).  The partial sums of a row
+// with more segments meet in the side buffer at slot (position of the row's first term) >>
+// seg_shift, which no two such rows can share because each spans more than S positions.
+// Context-table keys take the positions [0, num_terms), input-table keys the positions after them.
+template <typename T, int WPP, int PPL, int UB, bool kSq, bool kStage>
+__global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
+  constexpr int kWaves = kSgnsThreads / 64;
+  const int64_t pos_lo = kStage ? a.num_terms : 0;
+  // (scalars that come out of memory are made wave-uniform explicitly: loop bounds and the
+  // lane numbers of the broadcasts must live in scalar registers)
+  const int64_t pos_hi = kStage ? (int64_t)uniform_u32(a.cnt[a.cnt_last]) : a.num_terms;
+  const int lane = threadIdx.x & 63;
+  const int64_t first_wave = (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int slice = kStage ? kStageSlice : a.slice_terms;
+  const Term* __restrict__ sorted = a.sorted;
+  const uint32_t seg_mask = (1u << a.seg_shift) - 1u;
+  // a wave takes the slices first_wave, first_wave + (waves of the launch), ...: the launch of
+  // the input-table pass is sized for the few slots a batch normally uses, not for one per pair
+  for (int64_t wave = first_wave;; wave += (int64_t)gridDim.x * kWaves) {
+    const int64_t slice_begin = pos_lo + wave * slice;
+    if (slice_begin >= pos_hi) break;
+    const int64_t slice_end = min(slice_begin + slice, pos_hi);
+    const int64_t begin = next_segment_start(sorted, slice_begin, pos_hi, lane, seg_mask);   // what lies before is an earlier wave's
+    const int64_t end = next_segment_start(sorted, slice_end, pos_hi, lane, seg_mask);       // finish the segment we started
+    update_range<T, WPP, PPL, UB, kSq, kStage, true>(a, sorted, begin, end, pos_hi, lane);
   }
 }
 
@@ -1198,6 +1236,277 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, i
     elem_store(dst, e, (float)((double)elem_load(dst, e) + fix_value(src[e])));
 }
 
+// ---- small batches: the whole step in two launches -----------------------------------------
+// Bound by latency: the kernels above are a chain of seven dependent launches, each a few microseconds
+// for a batch of a few thousand pairs (2048 pairs, 5 negatives, 128 columns on 1 M nodes: 82 us; the
+// two launches here: 25 us, 9 in the forward kernel and 17 in the update kernel).  Here the forward kernel counts nothing, and one kernel of
+// kSmallBlocks workgroups does the rest: a workgroup owns the keys whose hash names it, reads all
+// ids of the batch (they fit the L2), counts its keys in an LDS table, brings its terms together
+// in LDS and sums and writes its rows.  Both kinds of keys are handled at once, because the source
+// rows of the context-table keys are the copies the forward kernel kept, not the input table.
+// Rows of more than kSmallRow terms are summed by the whole workgroup, which picks their terms from
+// the ids as it goes.  Should the keys of a workgroup not fit its table or its terms their place in
+// LDS (ids that share a hash, rows of just under kSmallRow terms), it sums all its rows that way.
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
+constexpr int kSmallBlockBits = 8, kSmallBlocks = 1 << kSmallBlockBits;
+constexpr int kSmallSlotBits = 10, kSmallSlots = 1 << kSmallSlotBits;
+constexpr int kSmallTerms = 2048;
+constexpr uint32_t kSmallRow = 64;
+constexpr int kSmallMaxDim = 512;
+constexpr int kSmallMaxRowBytes = 1024;
+constexpr int kSmallChunkPairs = 2;              // consecutive pairs per 16-lane group in forward
+constexpr int kSmallForwardThreads = 64;
+static_assert(kSmallThreads == kSmallSlots, "the prefix sum takes one slot per lane");
+
+// entry e of the batch: contexts, then negatives, then staging slots; its key (kNoRow: none)
+__device__ __forceinline__ uint32_t small_key(const SgnsArgs& a, uint32_t e, uint32_t pairs, uint32_t terms) {
+  if (e < terms) {
+    const int32_t id = e < pairs ? a.contexts[e] : a.negs[e - pairs];
+    return (uint32_t)id < (uint32_t)a.num_nodes ? (uint32_t)id : 0u;
+  }
+  if (e >= terms + pairs) return kNoRow;
+  const int32_t c = a.stage_center[e - terms];
+  return c < 0 ? kNoRow : (uint32_t)a.num_nodes + (uint32_t)c;
+}
+// its source row and coefficient
+__device__ __forceinline__ void small_source(const SgnsArgs& a, uint32_t e, uint32_t pairs, uint32_t terms,
+                                             int32_t& center, float& coef) {
+  if (e >= terms) {
+    center = (int32_t)(e - terms);
+    coef = -a.lr;
+    return;
+  }
+  const uint32_t k = (uint32_t)a.k;
+  const uint32_t i = e < pairs ? e : (e - pairs) / k;
+  const uint32_t j = e < pairs ? 0u : e - pairs - i * k + 1u;
+  center = a.pair_slot[i];
+  coef = -a.lr * a.g[i * (k + 1u) + j];
+}
+__device__ __forceinline__ uint32_t small_hash(uint32_t key) { return key * 2654435761u; }
+__device__ __forceinline__ bool small_owns(uint32_t key) {
+  return key != kNoRow && (small_hash(key) >> (32 - kSmallBlockBits)) == blockIdx.x;
+}
+__device__ __forceinline__ uint32_t small_home(uint32_t key) {
+  return (small_hash(key) >> (32 - kSmallBlockBits - kSmallSlotBits)) & (uint32_t)(kSmallSlots - 1);
+}
+
+// LDS accesses of one wave complete in order; this keeps the compiler from moving them
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The row of `key`, summed by the whole workgroup: every wave picks the key's entries out of its
+// share of the ids, 64 at a time, and adds their source rows; the waves' sums meet in row_acc.
+template <typename T, int WPP, int UB, bool kStage>
+__device__ void small_long_row(const SgnsArgs& a, uint32_t key, uint32_t pairs, uint32_t terms,
+                               unsigned long long* row_acc, uint32_t* found) {
+  constexpr int EPP = WPP * Words<T>::kPerWord;
+  constexpr int SW = kStage ? EPP : WPP;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t entries = terms + pairs;
+  const uint32_t* __restrict__ src_base = static_cast<const uint32_t*>(kStage ? static_cast<const void*>(a.stage_delta) : a.snap);
+  const int64_t src_row_words = kStage ? (int64_t)a.dim : (int64_t)a.dim / Words<T>::kPerWord;
+  const bool piece_ok = lane * EPP < a.dim;
+  if (tid < a.dim) row_acc[tid] = 0ull;
+  __syncthreads();
+  unsigned long long acc[EPP];
+#pragma unroll
+  for (int i = 0; i < EPP; ++i) acc[i] = 0ull;
+  uint32_t summed = 0;
+  auto add = [&](int n) {                                 // the first n entries of `found`
+    int32_t center = 0;
+    float coef = 0.f;
+    if (lane < n) small_source(a, found[lane], pairs, terms, center, coef);
+#pragma unroll 1
+    for (int b0 = 0; b0 < n; b0 += UB) {
+      uint32_t u[UB][SW];
+#pragma unroll
+      for (int b = 0; b < UB; ++b) {
+        if (b0 + b < n) {
+          const uint32_t* row_words = src_base + (int64_t)__builtin_amdgcn_readlane(center, b0 + b) * src_row_words;
+          if (piece_ok) load_words<SW>(row_words + (int64_t)lane * SW, u[b]);
+          else
+#pragma unroll
+            for (int w = 0; w < SW; ++w) u[b][w] = 0u;
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < UB; ++b) {
+        if (b0 + b < n) {
+          const double c = (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(coef), b0 + b)) * kFixScale;
+#pragma unroll
+          for (int i = 0; i < EPP; ++i)
+            fix_add(acc[i], c, kStage ? __uint_as_float(u[b][i]) : piece_elem<T, SW>(u[b], i));
+        }
+      }
+    }
+    summed += (uint32_t)n;
+  };
+  int held = 0;
+  for (uint32_t e0 = wave * 64u; e0 < entries; e0 += kSmallThreads) {
+    const bool match = small_key(a, e0 + (uint32_t)lane, pairs, terms) == key;
+    const uint64_t votes = __ballot(match);
+    if (votes == 0ull) continue;
+    if (match) found[held + __popcll(votes & ((1ull << lane) - 1ull))] = e0 + (uint32_t)lane;
+    held += __popcll(votes);
+    wave_fence();
+    if (held >= 64) {
+      add(64);
+      held -= 64;
+      const uint32_t rest = found[64 + lane];
+      wave_fence();
+      if (lane < held) found[lane] = rest;
+      wave_fence();
+    }
+  }
+  if (held > 0) add(held);
+  if (summed > 0 && piece_ok) {
+    const unsigned long long off = (unsigned long long)(summed * (uint32_t)(kFixMagicBits >> 32)) << 32;
+#pragma unroll
+    for (int i = 0; i < EPP; ++i) atomicAdd(row_acc + lane * EPP + i, acc[i] - off);
+  }
+  __syncthreads();
+  if (tid < a.dim) {
+    T* row = static_cast<T*>(kStage ? a.dst_in : a.dst_out) + (int64_t)(kStage ? key - (uint32_t)a.num_nodes : key) * a.dim;
+    elem_store(row, tid, (float)((double)elem_load(row, tid) + fix_value(row_acc[tid])));
+  }
+  __syncthreads();
+}
+
+template <typename T, int WPP, int UB>
+__global__ __launch_bounds__(kSmallThreads) void sgns_small_update_kernel(SgnsArgs a) {
+  __shared__ uint32_t keys[kSmallSlots], cnt[kSmallSlots], off[kSmallSlots];
+  __shared__ uint32_t long_keys[kSmallSlots];
+  __shared__ Term terms_s[kSmallTerms];
+  __shared__ uint2 owned[kSmallTerms];                    // entry; slot and position among the terms of its key
+  __shared__ unsigned long long row_acc[kSmallMaxDim];
+  __shared__ uint32_t found[kSmallWaves][128];
+  __shared__ uint32_t wave_tot[2][kSmallWaves];
+  __shared__ uint32_t n_long, n_owned, failed, next_key;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (blockIdx.x == kSmallBlocks) {                       // the loss: partials added in a fixed order
+    double* sum_s = reinterpret_cast<double*>(terms_s);
+    double sum = 0.0;
+    for (int64_t i = tid; i < a.forward_blocks; i += kSmallThreads) sum += a.loss_partials[i];
+    sum_s[tid] = sum;
+    __syncthreads();
+    for (int w = kSmallThreads / 2; w > 0; w >>= 1) {
+      if (tid < w) sum_s[tid] += sum_s[tid + w];
+      __syncthreads();
+    }
+    if (tid == 0) *a.loss_out = sum_s[0];
+    return;
+  }
+  const uint32_t pairs = (uint32_t)a.num_pairs, terms = (uint32_t)a.num_terms, entries = terms + pairs;
+  const uint32_t nodes = (uint32_t)a.num_nodes;
+  keys[tid] = kNoRow;
+  cnt[tid] = 0u;
+  if (tid == 0) { n_long = 0u; n_owned = 0u; failed = 0u; }
+  __syncthreads();
+
+  constexpr int kBatch = 8;                               // ids in flight per lane
+  for (uint32_t e0 = 0; e0 < entries; e0 += kBatch * kSmallThreads) {
+    uint32_t key[kBatch];
+#pragma unroll
+    for (int c = 0; c < kBatch; ++c) key[c] = small_key(a, e0 + c * kSmallThreads + tid, pairs, terms);
+#pragma unroll
+    for (int c = 0; c < kBatch; ++c) {
+      if (!small_owns(key[c])) continue;
+      uint32_t at = small_home(key[c]);
+      int probes = 0;
+      for (; probes < kSmallSlots; ++probes, at = (at + 1u) & (kSmallSlots - 1)) {
+        const uint32_t seen = atomicCAS(&keys[at], kNoRow, key[c]);
+        if (seen == kNoRow || seen == key[c]) break;
+      }
+      if (probes == kSmallSlots) { failed = 1u; continue; }
+      const uint32_t pos = atomicAdd(&cnt[at], 1u);
+      if (pos >= kSmallRow) continue;                     // (a long row: its terms are picked later)
+      const uint32_t i = atomicAdd(&n_owned, 1u);
+      if (i < (uint32_t)kSmallTerms) owned[i] = make_uint2(e0 + c * kSmallThreads + tid, (at << 8) | pos);
+    }
+  }
+  __syncthreads();
+  // places: the short context rows first, then the short input rows
+  uint32_t n_out = 0, n_in = 0;
+  {
+    const uint32_t c = cnt[tid], key = keys[tid];
+    const bool is_short = c <= kSmallRow;
+    const uint32_t c_out = is_short && key < nodes ? c : 0u, c_in = is_short && key >= nodes ? c : 0u;
+    if (!is_short) long_keys[atomicAdd(&n_long, 1u)] = key;
+    uint32_t i_out = c_out, i_in = c_in;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t u0 = __shfl_up(i_out, d, 64), u1 = __shfl_up(i_in, d, 64);
+      if (lane >= d) { i_out += u0; i_in += u1; }
+    }
+    if (lane == 63) { wave_tot[0][wave] = i_out; wave_tot[1][wave] = i_in; }
+    __syncthreads();
+    uint32_t b_out = 0, b_in = 0;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+      if (w < wave) { b_out += wave_tot[0][w]; b_in += wave_tot[1][w]; }
+      n_out += wave_tot[0][w];
+      n_in += wave_tot[1][w];
+    }
+    off[tid] = !is_short ? kNoRow : (key < nodes ? b_out + i_out - c_out : n_out + b_in + i_in - c_in);
+    __syncthreads();
+  }
+  n_out = uniform_u32(n_out);
+  n_in = uniform_u32(n_in);
+  uint32_t* my_found = found[wave];
+  if (failed != 0u || n_owned > (uint32_t)kSmallTerms) {
+    // does not fit: every key of this workgroup on its own, in ascending order
+    for (uint32_t lowest = 0;;) {
+      if (tid == 0) next_key = kNoRow;
+      __syncthreads();
+      uint32_t best = kNoRow;
+      for (uint32_t e = tid; e < entries; e += kSmallThreads) {
+        const uint32_t key = small_key(a, e, pairs, terms);
+        if (key >= lowest && key < best && small_owns(key)) best = key;
+      }
+      if (best != kNoRow) atomicMin(&next_key, best);
+      __syncthreads();
+      const uint32_t key = uniform_u32(next_key);
+      if (key == kNoRow) return;
+      if (key < nodes) small_long_row<T, WPP, UB, false>(a, key, pairs, terms, row_acc, my_found);
+      else small_long_row<T, WPP, UB, true>(a, key, pairs, terms, row_acc, my_found);
+      lowest = key + 1u;
+    }
+  }
+  for (uint32_t i = tid; i < n_owned; i += kSmallThreads) {
+    const uint2 o = owned[i];
+    const uint32_t at = o.y >> 8;
+    if (off[at] == kNoRow) continue;
+    Term t;
+    t.row = keys[at];
+    t.pos = o.y & 255u;
+    small_source(a, o.x, pairs, terms, t.center, t.coef);
+    terms_s[off[at] + t.pos] = t;
+  }
+  __syncthreads();
+  const uint32_t s_out = min(64u, (n_out + kSmallWaves - 1) / kSmallWaves), s_in = min(64u, (n_in + kSmallWaves - 1) / kSmallWaves);
+  for (uint32_t at = (uint32_t)wave * s_out; at < n_out; at += kSmallWaves * s_out) {
+    const int64_t begin = next_segment_start(terms_s, at, n_out, lane, ~0u);
+    const int64_t end = next_segment_start(terms_s, min(at + s_out, n_out), n_out, lane, ~0u);
+    update_range<T, WPP, 1, UB, false, false, false>(a, terms_s, begin, end, n_out, lane);
+  }
+  const uint32_t n_all = n_out + n_in;
+  for (uint32_t at = n_out + (uint32_t)wave * s_in; at < n_all; at += kSmallWaves * s_in) {
+    const int64_t begin = next_segment_start(terms_s, at, n_all, lane, ~0u);
+    const int64_t end = next_segment_start(terms_s, min(at + s_in, n_all), n_all, lane, ~0u);
+    update_range<T, WPP, 1, UB, false, true, false>(a, terms_s, begin, end, n_all, lane);
+  }
+  const uint32_t longs = uniform_u32(n_long);
+  for (uint32_t l = 0; l < longs; ++l) {
+    const uint32_t key = uniform_u32(long_keys[l]);
+    if (key < nodes) small_long_row<T, WPP, UB, false>(a, key, pairs, terms, row_acc, my_found);
+    else small_long_row<T, WPP, UB, true>(a, key, pairs, terms, row_acc, my_found);
+  }
+}
+
 // ---- host side -----------------------------------------------------------------------------
 // Work per 16-lane group: large batches fill the chip many times over, so long runs per
 // group amortise the row loads of a run of equal centres; small batches are cut finer so
@@ -1234,6 +1543,9 @@ struct SgnsPlan {
   float* stage_delta;
   int64_t long_slots;
   int32_t seg_shift;
+  bool small = false;       // the two-launch step of a small batch, which keeps copies of the input rows
+  void* snap = nullptr;
+  int32_t* pair_slot = nullptr;
   size_t bytes;
 };
 
@@ -1282,6 +1594,52 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
   return p;
 }
 
+// Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every
+// workgroup of its update kernel reads all of them, so its time grows with the ids (about 0.8 us
+// per 1000) while that of the seven launches hardly does.  Measured, seven launches against two, with
+// 5 negatives and 128 fp32 columns on 1 M nodes: 2048 pairs (14 k ids) 82 / 25 us, 6000 (42 k) 81 /
+// 46, 12,000 (84 k) 89 / 105; 64 columns on 10 k nodes: 4096 (29 k) 50 / 38, 6000 53 / 46, 8192 (57 k)
+// 54 / 59; 10 negatives, 256 bf16 columns on 500 k nodes: 4096 (49 k) 123 / 64, 8192 (98 k) 117 / 125.
+constexpr int64_t kSmallMaxEntries = 3 << 14;
+
+static bool small_batch(int64_t num_pairs, int32_t k, int32_t dim, int32_t dtype) {
+  return num_pairs * (int64_t)(k + 2) <= kSmallMaxEntries && dim * (dtype == GS_F32 ? 4 : 2) <= kSmallMaxRowBytes;
+}
+static int64_t small_forward_blocks(int64_t num_pairs) {
+  return ceil_div(ceil_div(num_pairs, kSmallChunkPairs), kSmallForwardThreads / kGroupLanes);
+}
+
+static SgnsPlan plan_small(void* ws, int64_t num_pairs, int32_t k, int32_t dim, int32_t dtype) {
+  Carver cv(ws);
+  SgnsPlan p = {};
+  const size_t b = (size_t)(num_pairs > 0 ? num_pairs : 1);
+  p.small = true;
+  p.loss_partials = cv.take<double>((size_t)small_forward_blocks((int64_t)b));
+  p.g = cv.take<float>(b * (size_t)(k + 1));
+  p.stage_center = cv.take<int32_t>(b);
+  p.stage_delta = cv.take<float>(b * (size_t)dim);
+  p.snap = cv.take<char>(b * (size_t)dim * (dtype == GS_F32 ? 4 : 2));
+  p.pair_slot = cv.take<int32_t>(b);
+  p.bytes = cv.used;
+  return p;
+}
+
+// The plan of a step in a workspace of ws_bytes, of which the call's own arrays take `extra` bytes
+// behind the plan: the two-launch step where the batch is small and the workspace holds it.
+static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int64_t num_pairs, int64_t num_nodes,
+                      int32_t k, int32_t dim, int32_t dtype, bool force_compact = false) {
+  if (small_batch(num_pairs, k, dim, dtype)) {
+    p = plan_small(ws, num_pairs, k, dim, dtype);
+    if (p.bytes + extra <= ws_bytes) return true;
+  }
+  p = plan_sgns(ws, num_pairs, num_nodes, k, dim, force_compact);
+  return p.bytes + extra <= ws_bytes;
+}
+static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
+  const size_t large = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
+  return small_batch(num_pairs, k, dim, dtype) ? max(large, plan_small(nullptr, num_pairs, k, dim, dtype).bytes) : large;
+}
+
 // the two update passes (context-table keys, then input-table keys) in the piece layout that
 // fits the row: 64 lanes x WPP words x PPL pieces cover the row, UB source rows in flight
 template <typename T, int WPP, int PPL, int UB>
@@ -1309,7 +1667,26 @@ static int32_t launch_updates(const SgnsArgs& a, hipStream_t stream) {
 }
 
 template <typename T, int VPL, int RB>
-static int32_t launch_sgns(const SgnsArgs& a, hipStream_t stream) {
+static int32_t launch_small(const SgnsArgs& a, hipStream_t stream) {
+  const size_t idx_lds = (size_t)(kSmallForwardThreads / kGroupLanes) * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
+  sgns_forward_kernel<T, VPL, RB, false, kSmallForwardThreads>
+      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSmallForwardThreads, idx_lds, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  const int row_bytes = a.dim * (int)sizeof(T);            // one block more adds up the loss
+  if (row_bytes <= 256) sgns_small_update_kernel<T, 1, 8><<<kSmallBlocks + 1, kSmallThreads, 0, stream>>>(a);
+  else if (row_bytes <= 512) sgns_small_update_kernel<T, 2, 8><<<kSmallBlocks + 1, kSmallThreads, 0, stream>>>(a);
+  else sgns_small_update_kernel<T, 4, 4><<<kSmallBlocks + 1, kSmallThreads, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+
+template <typename T, int VPL, int RB>
+static int32_t launch_sgns(const SgnsArgs& a, bool small, hipStream_t stream) {
+  if (small) {
+    // (row_bytes <= kSmallMaxRowBytes)
+    if constexpr (VPL * 64 * sizeof(T) <= (size_t)kSmallMaxRowBytes) return launch_small<T, VPL, RB>(a, stream);
+    return GS_EINVAL;
+  }
   const int64_t keys1 = a.cnt_last + 1;
   const int64_t tiles = ceil_div(keys1, kScanTile);
   const int64_t keys4 = ceil_div(keys1, 4);
@@ -1318,8 +1695,8 @@ static int32_t launch_sgns(const SgnsArgs& a, hipStream_t stream) {
       (uint4*)a.cnt, keys4, (uint4*)a.key_table, table4, a.bad_ids);
   GS_LAUNCH_CHECK();
   const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
-  sgns_forward_kernel<T, VPL, RB><<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds,
-                                   stream>>>(a);
+  sgns_forward_kernel<T, VPL, RB, true, kSgnsThreads>
+      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds, stream>>>(a);
   GS_LAUNCH_CHECK();
   if (keys1 <= kScanSmallMax) {
     scan_small_kernel<<<1, 1024, 0, stream>>>(a.cnt, keys1);
@@ -1491,8 +1868,8 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   a.neg_pair_base = x.neg_pair_base;
   a.negs_draw = x.negs_draw;
   if (a.draw_negs) negs = x.negs_draw;
-  a.snap = x.snap;
-  a.pair_slot = x.pair_slot;
+  a.snap = p.small ? p.snap : x.snap;
+  a.pair_slot = p.small ? p.pair_slot : x.pair_slot;
   a.walks = x.walks;
   a.pair_offsets = x.pair_offsets;
   a.num_walks = x.num_walks;
@@ -1536,32 +1913,32 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   a.stage_center = p.stage_center;
   a.stage_rank = p.stage_rank;
   a.stage_delta = p.stage_delta;
-  a.chunk_pairs = chunk_pairs_for(num_pairs);
+  a.chunk_pairs = p.small ? kSmallChunkPairs : chunk_pairs_for(num_pairs);
   a.slice_terms = slice_terms_for(num_pairs);
   a.loss_partials = p.loss_partials;
-  a.forward_blocks = forward_blocks_for(num_pairs);
+  a.forward_blocks = p.small ? small_forward_blocks(num_pairs) : forward_blocks_for(num_pairs);
   a.forward_blocks_per_xcd = ceil_div(a.forward_blocks, 8);
   a.loss_out = loss_sum_out;
   // float4 registers per lane for one row: 16 lanes x 4 floats = 64 elements each
   const int vpl = (dim + 63) / 64;
   if (dtype == GS_F32) {
-    if (vpl <= 1) return launch_sgns<float, 1, 6>(a, stream);
-    if (vpl <= 2) return launch_sgns<float, 2, 6>(a, stream);
-    if (vpl <= 4) return launch_sgns<float, 4, 3>(a, stream);
-    if (vpl <= 8) return launch_sgns<float, 8, 2>(a, stream);
-    return launch_sgns<float, 16, 1>(a, stream);
+    if (vpl <= 1) return launch_sgns<float, 1, 6>(a, p.small, stream);
+    if (vpl <= 2) return launch_sgns<float, 2, 6>(a, p.small, stream);
+    if (vpl <= 4) return launch_sgns<float, 4, 3>(a, p.small, stream);
+    if (vpl <= 8) return launch_sgns<float, 8, 2>(a, p.small, stream);
+    return launch_sgns<float, 16, 1>(a, p.small, stream);
   }
   // 16-bit rows: a 16-byte piece is 8 elements = two float4, so the register count is even
   if (dtype == GS_BF16) {
-    if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, stream);
-    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, stream);
-    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, stream);
-    return launch_sgns<bf16_t, 16, 2>(a, stream);
+    if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, p.small, stream);
+    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, p.small, stream);
+    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, p.small, stream);
+    return launch_sgns<bf16_t, 16, 2>(a, p.small, stream);
   }
-  if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, stream);
-  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, stream);
-  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, stream);
-  return launch_sgns<f16_t, 16, 2>(a, stream);
+  if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, p.small, stream);
+  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, p.small, stream);
+  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, p.small, stream);
+  return launch_sgns<f16_t, 16, 2>(a, p.small, stream);
 }
 
 }  // namespace gs
@@ -1570,9 +1947,8 @@ using namespace gs;
 
 extern "C" size_t gs_sgns_step_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k,
                                                int32_t dim, int32_t dtype) {
-  (void)dtype;
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
-  return plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
+  return step_bytes(num_pairs, num_nodes, k, dim, dtype);
 }
 
 extern "C" int32_t gs_sgns_step(void* w_in, void* w_out, int64_t num_nodes, int32_t dim,
@@ -1583,8 +1959,8 @@ extern "C" int32_t gs_sgns_step(void* w_in, void* w_out, int64_t num_nodes, int3
   const int32_t bad = check_sgns_args(w_in, w_out, num_nodes, dim, dtype, centers, contexts, negs,
                                       num_pairs, k, loss_sum_out, ws);
   if (bad != GS_OK) return bad;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-  if (ws_bytes < p.bytes) return GS_EWORKSPACE;
+  SgnsPlan p;
+  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -1637,8 +2013,8 @@ extern "C" int32_t gs_sgns_step_static(void* w_in, void* w_out, int64_t num_node
   const int32_t bad = check_sgns_args(w_in, w_out, num_nodes, dim, dtype, centers, contexts, negs,
                                       num_pairs, k, loss_sum_out, ws);
   if (bad != GS_OK) return bad;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim, true);
-  if (p.bytes > kStaticScratchBytes) return GS_EWORKSPACE;
+  SgnsPlan p;
+  if (!plan_step(p, ws, kStaticScratchBytes, 0, num_pairs, num_nodes, k, dim, dtype, true)) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -1655,9 +2031,8 @@ static size_t fused_negs_bytes(int64_t num_pairs, int32_t k) {
 
 extern "C" size_t gs_sgns_step_fused_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k,
                                                      int32_t dim, int32_t dtype) {
-  (void)dtype;
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
-  return plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes + fused_negs_bytes(num_pairs, k);
+  return step_bytes(num_pairs, num_nodes, k, dim, dtype) + fused_negs_bytes(num_pairs, k);
 }
 
 extern "C" int32_t gs_sgns_step_fused(void* w_in, void* w_out, int64_t num_nodes, int32_t dim,
@@ -1671,8 +2046,8 @@ extern "C" int32_t gs_sgns_step_fused(void* w_in, void* w_out, int64_t num_nodes
                                       static_cast<const int32_t*>(ws), num_pairs, k, loss_sum_out, ws);
   if (bad != GS_OK) return bad;
   if (noise != nullptr && noise->prob != nullptr && !noise->alias) return GS_EINVAL;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-  if (ws_bytes < p.bytes + fused_negs_bytes(num_pairs, k)) return GS_EWORKSPACE;
+  SgnsPlan p;
+  if (!plan_step(p, ws, ws_bytes, fused_negs_bytes(num_pairs, k), num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -1695,9 +2070,8 @@ static size_t walk_ids_bytes(int64_t num_pairs) {
 
 extern "C" size_t gs_sgns_step_from_walks_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k,
                                                           int32_t dim, int32_t dtype) {
-  (void)dtype;
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
-  return plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes + fused_negs_bytes(num_pairs, k) +
+  return step_bytes(num_pairs, num_nodes, k, dim, dtype) + fused_negs_bytes(num_pairs, k) +
          2 * walk_ids_bytes(num_pairs);
 }
 
@@ -1718,9 +2092,9 @@ extern "C" int32_t gs_sgns_step_from_walks(void* w_in, void* w_out, int64_t num_
                                       num_pairs, k, loss_sum_out, ws);
   if (bad != GS_OK) return bad;
   if (noise != nullptr && noise->prob != nullptr && !noise->alias) return GS_EINVAL;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
   const size_t negs_bytes = fused_negs_bytes(num_pairs, k), ids_bytes = walk_ids_bytes(num_pairs);
-  if (ws_bytes < p.bytes + negs_bytes + 2 * ids_bytes) return GS_EWORKSPACE;
+  SgnsPlan p;
+  if (!plan_step(p, ws, ws_bytes, negs_bytes + 2 * ids_bytes, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -1795,8 +2169,8 @@ extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, vo
   if (!m_in || !m_out || !aligned(m_in, 16) || !aligned(m_out, 16)) return GS_EINVAL;
   if (m_in == w_in || m_in == w_out || m_out == w_in || m_out == w_out || m_in == m_out)
     return GS_EINVAL;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-  if (ws_bytes < p.bytes) return GS_EWORKSPACE;
+  SgnsPlan p;
+  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
   const int per16 = (dtype == GS_F32) ? 4 : 8;
   const int64_t pieces = num_nodes * (int64_t)dim / per16;
   const unsigned blocks = (unsigned)min((int64_t)(256 * 64), ceil_div(pieces, 256));
