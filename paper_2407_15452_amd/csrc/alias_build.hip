@@ -1,14 +1,37 @@
 // gs_alias_build: alias tables, one per segment, in the canonical first-in
 // first-out construction order stated in gs.h (Walker 1977 / Vose 1991).
-// The order of the fp64 operations is part of the definition of the table, so
-// each short segment is built sequentially by one lane; parallelism is across
-// segments (per-row tables of a weighted graph).  Long segments (the noise
-// table, the rows of hub nodes) are built by one workgroup each, see
-// alias_build_long_kernel.
+// The order of the fp64 operations is part of the definition of the table; what
+// can run side by side without changing it:
+//
+//  * The sequential loop pairs the oldest small with the oldest large and appends the
+//    large to the back of one of the two lists.  If both lists hold at least m
+//    entries, the next m iterations use exactly the first m entries of each list
+//    as they stand now (appends go to the back), touch 2m distinct entries, and
+//    are independent of each other: they can run side by side, and appending
+//    their larges in iteration order (a rank over the "became small" flags)
+//    leaves both lists exactly as the sequential loop would.
+//  * S, the index-order fp64 sum of the weights: while the running sum stays in one binade,
+//    [2^e, 2^(e+1)), it is a whole number N of units u = 2^(e-52), and adding a weight w >= 0 adds
+//    round(w / u) to it, where only an exact tie depends on N, and only on whether N is even.  A run of
+//    weights is therefore the pair of whole numbers it adds to an even and to an odd N, and such
+//    pairs combine in any grouping that keeps their order.  Stretches in which the sum leaves its
+//    binade (at most one per doubling of the sum) are added one by one.
+//
+// Segments of up to kLaneSegment entries are built by one lane each, up to kWaveSegment by one wave
+// in LDS, longer ones (the noise table, the rows of hub nodes) by a workgroup of 1024 lanes.  All are
+// bound by latency, so the limits lie where the next larger team finishes the longest segment sooner.
+// Measured on a 1 M-node graph of 22 M weighted entries: row tables 2.65 ms (lanes 0.29, waves 0.20 +
+// 0.45, workgroups 1.70), against 9.5 ms with one lane per row up to 8191 entries; the noise table of
+// 1 M entries 5.8 ms, against 18.0 ms with the sum and the narrow stretches run by one lane from global
+// memory and 1024 iterations per trip.
 #include "common.h"
 
 namespace gs {
 
+constexpr int64_t kLaneSegment = 32;
+constexpr int kWaveSegment = 2048;
+
+// ---- one lane per segment ------------------------------------------------------------------
 template <typename OffT>
 __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict__ seg_offsets,
                                                          int64_t num_segments,
@@ -17,14 +40,13 @@ __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict_
                                                          int32_t* __restrict__ alias_out,
                                                          double* __restrict__ mass_ws,
                                                          int32_t* __restrict__ small_ws,
-                                                         int32_t* __restrict__ large_ws,
-                                                         int64_t skip_from) {
+                                                         int32_t* __restrict__ large_ws) {
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= num_segments) return;
   const int64_t begin = (int64_t)seg_offsets[s];
   const int64_t n = (int64_t)seg_offsets[s + 1] - begin;
-  if (n <= 0 || n >= skip_from) return;        // long segments are left to the workgroup kernel
+  if (n <= 0 || n > kLaneSegment) return;
   const float* w = weights + begin;
   float* prob = prob_out + begin;
   int32_t* alias = alias_out + begin;
@@ -75,63 +97,228 @@ __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict_
   }
 }
 
-// ---------------------------------------------------------------------------
-// A long segment (the noise table, a hub row): the same construction, same order,
-// run by one workgroup of 1024 lanes.
-//
-// The sequential loop pairs the oldest small with the oldest large and appends
-// the large to the back of one of the two lists.  If both lists hold at least m
-// entries, the next m iterations use exactly the first m entries of each list
-// as they stand now (appends go to the back), touch 2m distinct entries, and
-// are independent of each other: they can run side by side, and appending
-// their larges in iteration order (a prefix sum over the "became small" flags)
-// leaves both lists exactly as the sequential loop would.  So the workgroup
-// advances in rounds of m = min(|small|, |large|) iterations; when m is small
-// (a few very heavy entries left) lane 0 runs the plain loop instead.
-// S is still the index-order fp64 sum: lanes stage 1024 weights in LDS, lane 0
-// adds them one by one.
-// ---------------------------------------------------------------------------
-constexpr int kLongThreads = 1024;
-constexpr int64_t kLongSegment = 8192;      // segments at least this long use the workgroup
-constexpr int kSerialBelow = 64;            // rounds narrower than this are run by lane 0
-
-// loads that must see what other lanes of the workgroup stored earlier (bypass the L1)
-__device__ __forceinline__ int32_t ld_i32(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double ld_f64(const double* p) {
-  return __longlong_as_double((long long)__hip_atomic_load(
-      reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+// LDS accesses of one wave complete in order; this keeps the compiler from moving them
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Ranks of the set flags among the 1024 lanes, in lane order, and their total.
-__device__ __forceinline__ void block_rank(bool flag, uint32_t* wave_tot, int& rank, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t votes = __ballot(flag);
-  const int before = __popcll(votes & ((1ull << lane) - 1ull));
-  if (lane == 0) wave_tot[wave] = (uint32_t)__popcll(votes);
-  __syncthreads();
-  int base = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < kLongThreads / 64; ++w) {
-    const int c = (int)wave_tot[w];
-    if (w < wave) base += c;
-    all += c;
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// ---- one wave per segment --------------------------------------------------------------------
+// Segments of MIN_N .. MAX_N entries: masses and both lists in LDS, up to 64 iterations at a time.  A
+// wave looks at `per_wave` consecutive segments and takes those of its size.
+template <typename OffT, int MIN_N, int MAX_N>
+__global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __restrict__ seg_offsets,
+                                                              int64_t num_segments, int per_wave,
+                                                              const float* __restrict__ weights,
+                                                              float* __restrict__ prob_out,
+                                                              int32_t* __restrict__ alias_out) {
+#pragma clang fp contract(off)  // every fp64 operation below must round on its own
+  static_assert((MAX_N & (MAX_N - 1)) == 0, "the list of larges wraps by a mask");
+  __shared__ double mass[MAX_N];
+  __shared__ uint16_t small_q[MAX_N];          // every entry enters at most once: no wrap
+  __shared__ uint16_t large_q[MAX_N];
+  const int lane = threadIdx.x;
+  const uint64_t below = (1ull << lane) - 1ull;
+  const int64_t first = (int64_t)blockIdx.x * per_wave;
+  int64_t my_begin = 0, my_n = 0;
+  if (lane < per_wave && first + lane < num_segments) {
+    my_begin = (int64_t)seg_offsets[first + lane];
+    my_n = (int64_t)seg_offsets[first + lane + 1] - my_begin;
   }
-  __syncthreads();
-  rank = base + before;
-  total = all;
+  uint64_t todo = __ballot(my_n >= MIN_N && my_n <= MAX_N);
+  while (todo != 0ull) {
+    const int who = __ffsll((unsigned long long)todo) - 1;
+    todo &= todo - 1ull;
+    const int n = __builtin_amdgcn_readlane((int)my_n, who);
+    const int64_t begin = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(my_begin >> 32), who) << 32) |
+                                    (uint32_t)__builtin_amdgcn_readlane((int)my_begin, who));
+    const float* w = weights + begin;
+    float* prob = prob_out + begin;
+    int32_t* alias = alias_out + begin;
+    const double dn = (double)n;
+    double S = 0.0;
+    for (int base = 0; base < n; base += 64) {
+      const double v = base + lane < n ? (double)w[base + lane] : 0.0;
+#pragma unroll 16
+      for (int k = 0; k < 64; ++k) S += lane_value(v, k);       // (+ 0.0 behind the end changes nothing)
+      if (base + lane < n) mass[base + lane] = v * dn;
+    }
+    int sh = 0, st = 0, lh = 0, lt = 0;        // heads and tails of the lists, the same in every lane
+    wave_fence();
+    for (int base = 0; base < n; base += 64) {
+      const bool valid = base + lane < n;
+      const bool is_small = valid && mass[base + lane] < S;
+      const uint64_t smalls = __ballot(is_small), larges = __ballot(valid && !is_small);
+      if (is_small) small_q[st + __popcll(smalls & below)] = (uint16_t)(base + lane);
+      else if (valid) large_q[lt + __popcll(larges & below)] = (uint16_t)(base + lane);
+      st += __popcll(smalls);
+      lt += __popcll(larges);
+    }
+    wave_fence();
+    while (sh < st && lh < lt) {
+      const int m = min(64, min(st - sh, lt - lh));
+      int b = 0;
+      bool demoted = false;
+      if (lane < m) {
+        const int a = small_q[sh + lane];
+        b = large_q[(lh + lane) & (MAX_N - 1)];
+        const double ma = mass[a];
+        prob[a] = (float)(ma / S);
+        alias[a] = b;
+        const double mb = (mass[b] + ma) - S;
+        mass[b] = mb;
+        demoted = mb < S;
+      }
+      const uint64_t down = __ballot(lane < m && demoted), stay = __ballot(lane < m && !demoted);
+      sh += m;
+      lh += m;
+      wave_fence();
+      if (lane < m) {
+        if (demoted) small_q[st + __popcll(down & below)] = (uint16_t)b;
+        else large_q[(lt + __popcll(stay & below)) & (MAX_N - 1)] = (uint16_t)b;
+      }
+      st += __popcll(down);
+      lt += __popcll(stay);
+      wave_fence();
+    }
+    for (int i = sh + lane; i < st; i += 64) {
+      const int x = small_q[i];
+      prob[x] = 1.0f;
+      alias[x] = x;
+    }
+    for (int i = lh + lane; i < lt; i += 64) {
+      const int x = large_q[i & (MAX_N - 1)];
+      prob[x] = 1.0f;
+      alias[x] = x;
+    }
+    wave_fence();
+  }
 }
 
-// the segments the workgroup kernel takes, in any order
+// ---- one workgroup per long segment --------------------------------------------------------
+// The lists live in global memory (all of a workgroup's accesses go through one compute unit's
+// cache, so a barrier is all that orders them).  Rounds of at least kNarrow iterations are run by
+// the workgroup, kLongTrip iterations at a time; narrower ones by one wave that keeps the heads of
+// both lists in LDS.
+constexpr int kLongThreads = 1024, kLongWaves = kLongThreads / 64;
+constexpr int kLongItems = 4;                                  // iterations per lane and trip
+constexpr int kLongTrip = kLongThreads * kLongItems;
+constexpr int kSumItems = 8;                                   // consecutive weights per lane of the sum
+constexpr int kSumChunk = 64 * kSumItems;                      // per wave
+constexpr int64_t kNarrow = 512;
+constexpr int kRing = 1024;                                    // list entries kept in LDS
+
+struct Runs { long long even, odd; };          // what a run of weights adds to an even / odd whole number of units
+__device__ __forceinline__ Runs then(const Runs& a, const Runs& b) {
+  Runs r;
+  r.even = a.even + ((a.even & 1) ? b.odd : b.even);
+  r.odd = a.odd + ((a.odd & 1) ? b.even : b.odd);
+  return r;
+}
+
+// index-order fp64 sum of w[0..n); every lane gets it
+__device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_s, uint32_t* bad_s, double* sum_s) {
+#pragma clang fp contract(off)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double S = 0.0;
+  int64_t pos = 0;
+  while (pos < n) {
+    int taken = 0;                             // waves whose chunk has been added
+    if (S >= 0x1p-200 && S < 0x1p+200) {
+      const int e = (int)(((uint64_t)__double_as_longlong(S) >> 52) & 2047u) - 1023;
+      const double per_unit = __longlong_as_double((long long)(uint64_t)(52 - e + 1023) << 52);
+      const double unit = __longlong_as_double((long long)(uint64_t)(e - 52 + 1023) << 52);
+      const int64_t at = pos + wave * kSumChunk + lane * kSumItems;
+      float v[kSumItems];
+#pragma unroll
+      for (int k = 0; k < kSumItems; ++k) v[k] = at + k < n ? w[at + k] : 0.f;
+      Runs r = {0, 0};
+      bool bad = false;
+#pragma unroll
+      for (int k = 0; k < kSumItems; ++k) {
+        const double t = (double)v[k] * per_unit;              // exact: a power of two
+        if (!(t >= 0.0 && t < 0x1p52)) { bad = true; continue; }
+        const double fl = floor(t), rest = t - fl;
+        const long long whole = (long long)fl;
+        const long long tie = rest == 0.5, up = rest > 0.5;
+        // N + whole + rest, rounded to the nearest whole number, ties to even
+        r.even += whole + (up | (tie & (r.even + whole)));
+        r.odd += whole + (up | (tie & (r.odd + 1 + whole)));
+      }
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {                        // lane l: the run of lanes l .. l + d - 1
+        Runs next;
+        next.even = __shfl_down(r.even, d, 64);
+        next.odd = __shfl_down(r.odd, d, 64);
+        r = then(r, next);
+      }
+      const uint64_t any_bad = __ballot(bad);
+      if (lane == 0) { run_s[wave] = r; bad_s[wave] = any_bad != 0ull; }
+      __syncthreads();
+      long long N = (long long)(S * per_unit);                  // in [2^52, 2^53)
+      for (; taken < kLongWaves; ++taken) {
+        if (bad_s[taken] != 0u) break;
+        const long long more = N + ((N & 1) ? run_s[taken].odd : run_s[taken].even);
+        if (more >= (1ll << 53)) break;
+        N = more;
+      }
+      S = (double)N * unit;
+      pos += (int64_t)taken * kSumChunk;
+    }
+    if (taken < kLongWaves && pos < n) {       // the sum leaves its binade in this chunk (or starts): one by one
+      if (tid == 0) {
+        const int64_t end = min(n, pos + kSumChunk);
+        double run = S;
+        for (int64_t i = pos; i < end; i += 8) {
+          float v[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) v[k] = i + k < end ? w[i + k] : 0.f;
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (i + k < end) run += (double)v[k];
+        }
+        *sum_s = run;
+      }
+      __syncthreads();
+      S = *sum_s;
+      pos += kSumChunk;
+    }
+    __syncthreads();
+  }
+  return S;
+}
+
+// places of the wave's votes in the workgroup's order, for two kinds of votes at once: c0 and c1
+// are the wave's totals; returns the totals of the waves before, and all of them
+__device__ __forceinline__ void block_before(int c0, int c1, int (*tot)[kLongWaves], int& before0, int& before1,
+                                             int& all0, int& all1) {
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { tot[0][wave] = c0; tot[1][wave] = c1; }
+  __syncthreads();
+  before0 = before1 = all0 = all1 = 0;
+#pragma unroll
+  for (int v = 0; v < kLongWaves; ++v) {
+    if (v < wave) { before0 += tot[0][v]; before1 += tot[1][v]; }
+    all0 += tot[0][v];
+    all1 += tot[1][v];
+  }
+}
+
 template <typename OffT>
 __global__ void alias_find_long_kernel(const OffT* __restrict__ seg_offsets, int64_t num_segments,
                                        int64_t* __restrict__ long_ids, int64_t capacity,
                                        unsigned long long* __restrict__ long_count) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= num_segments) return;
-  if ((int64_t)seg_offsets[s + 1] - (int64_t)seg_offsets[s] >= kLongSegment) {
-    // capacity = total_entries / kLongSegment bounds the count when the offsets add up to
+  if ((int64_t)seg_offsets[s + 1] - (int64_t)seg_offsets[s] > kWaveSegment) {
+    // capacity = total_entries / (kWaveSegment + 1) bounds the count when the offsets add up to
     // total_entries; an inconsistent pair of arguments must still not write out of bounds
     const unsigned long long at = atomicAdd(long_count, 1ull);
     if (at < (unsigned long long)capacity) long_ids[at] = s;
@@ -140,7 +327,38 @@ __global__ void alias_find_long_kernel(const OffT* __restrict__ seg_offsets, int
 
 __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 
-// One workgroup per long segment.  long_ids == null: the single segment 0.
+// The head of a list as one wave keeps it: entries [head, loaded) of the list in a ring in LDS.
+struct Window {
+  int32_t* id;
+  double* mass;
+  int64_t head, loaded, tail;                  // the list itself is [head, tail)
+};
+__device__ __forceinline__ void refill(Window& q, const int32_t* list, const double* mass, int lane) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");       // what this wave appended has to be there
+  const int64_t end = min(q.tail, q.head + kRing);
+  for (int64_t i = q.loaded + lane; i < end; i += 64) {
+    const int32_t x = list[i];
+    q.id[i & (kRing - 1)] = x;
+    q.mass[i & (kRing - 1)] = mass[x];
+  }
+  q.loaded = end;
+  wave_fence();
+}
+// appends the lanes with `mine` set, in lane order, to the list and, if the ring reaches that far, to the ring
+__device__ __forceinline__ void append(Window& q, int32_t* list, bool mine, int32_t x, double m, int lane) {
+  const uint64_t votes = __ballot(mine);
+  const int count = __popcll(votes);
+  const bool in_ring = q.loaded == q.tail && q.tail + count <= q.head + kRing;
+  if (mine) {
+    const int64_t at = q.tail + __popcll(votes & ((1ull << lane) - 1ull));
+    list[at] = x;
+    if (in_ring) { q.id[at & (kRing - 1)] = x; q.mass[at & (kRing - 1)] = m; }
+  }
+  q.tail += count;
+  if (in_ring) q.loaded = q.tail;
+}
+
+// long_ids == null: the single segment 0.
 // Scratch per entry of the segment, at the segment's own offsets: mass, the
 // small list (n entries), the large list (2n: appended without wrapping).
 template <typename OffT>
@@ -150,11 +368,15 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
     float* __restrict__ prob_out, int32_t* __restrict__ alias_out, double* mass_ws,
     int32_t* small_ws, int32_t* large_ws) {
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
-  __shared__ double tile_s[kLongThreads];
-  __shared__ uint32_t wave_tot[kLongThreads / 64];
-  __shared__ double S_s;
-  __shared__ int64_t q_s[4];                  // small head/tail, large head/tail after a serial stretch
-  const int tid = threadIdx.x;
+  __shared__ Runs run_s[kLongWaves];
+  __shared__ uint32_t bad_s[kLongWaves];
+  __shared__ double sum_s;
+  __shared__ int tot[2][2][kLongWaves];        // (two sets, used in turn: one barrier per use)
+  __shared__ int64_t q_s[4];                   // small head/tail, large head/tail after a narrow stretch
+  __shared__ int32_t ring_id[2][kRing];
+  __shared__ double ring_mass[2][kRing];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
   if (long_ids != nullptr && (unsigned long long)blockIdx.x >= *long_count) return;
   const int64_t seg = long_ids != nullptr ? long_ids[blockIdx.x] : 0;
   const int64_t begin = (int64_t)seg_offsets[seg];
@@ -167,99 +389,136 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
   int32_t* small_q = small_ws + begin;
   int32_t* large_q = large_ws + 2 * begin;
 
-  // S: index-order sum
-  double run = 0.0;
-  for (int64_t base = 0; base < n; base += kLongThreads) {
-    tile_s[tid] = (base + tid < n) ? (double)w[base + tid] : 0.0;
-    __syncthreads();
-    if (tid == 0) {
-      const int cnt = (int)min((int64_t)kLongThreads, n - base);
-      for (int k = 0; k < cnt; ++k) run += tile_s[k];
-    }
-    __syncthreads();
-  }
-  if (tid == 0) S_s = run;
-  __syncthreads();
-  const double S = S_s;
+  const double S = ordered_sum(w, n, run_s, bad_s, &sum_s);
   const double dn = (double)n;
+  int turn = 0;
 
-  // initial lists, in index order
+  // initial lists, in index order (a wave takes 64 * kLongItems consecutive entries of a trip)
   int64_t sh = 0, st = 0, lh = 0, lt = 0;     // heads and tails, identical in every lane
-  for (int64_t base = 0; base < n; base += kLongThreads) {
-    const int64_t i = base + tid;
-    const bool valid = i < n;
-    double m = 0.0;
-    if (valid) { m = (double)w[i] * dn; mass[i] = m; }
-    const bool is_small = valid && m < S;
-    int rs, ts, rl, tl;
-    block_rank(is_small, wave_tot, rs, ts);
-    block_rank(valid && !is_small, wave_tot, rl, tl);
-    if (is_small) small_q[st + rs] = (int32_t)i;
-    else if (valid) large_q[lt + rl] = (int32_t)i;
-    st += ts;
-    lt += tl;
+  for (int64_t base = 0; base < n; base += kLongTrip, turn ^= 1) {
+    const int64_t first = base + wave * (64 * kLongItems) + lane;
+    float v[kLongItems];
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) v[c] = first + c * 64 < n ? w[first + c * 64] : 0.f;
+    uint64_t smalls[kLongItems], larges[kLongItems];
+    int cs = 0, cl = 0;
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      const bool valid = first + c * 64 < n;
+      const double m = (double)v[c] * dn;
+      if (valid) mass[first + c * 64] = m;
+      smalls[c] = __ballot(valid && m < S);
+      larges[c] = __ballot(valid && !(m < S));
+      cs += __popcll(smalls[c]);
+      cl += __popcll(larges[c]);
+    }
+    int bs, bl, as, al;
+    block_before(cs, cl, tot[turn], bs, bl, as, al);
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      const int32_t i = (int32_t)(first + c * 64);
+      if ((smalls[c] >> lane) & 1ull) small_q[st + bs + __popcll(smalls[c] & below)] = i;
+      else if ((larges[c] >> lane) & 1ull) large_q[lt + bl + __popcll(larges[c] & below)] = i;
+      bs += __popcll(smalls[c]);
+      bl += __popcll(larges[c]);
+    }
+    st += as;
+    lt += al;
   }
 
   while (true) {
-    __threadfence();
     __syncthreads();
     const int64_t m = min(st - sh, lt - lh);
     if (m <= 0) break;
-    if (m < kSerialBelow) {
-      // few entries on one side: the plain loop, for a bounded stretch
-      if (tid == 0) {
-        int64_t a_sh = sh, a_st = st, a_lh = lh, a_lt = lt;
-        for (int it = 0; it < 4096 && a_sh < a_st && a_lh < a_lt; ++it) {
-          const int32_t a = ld_i32(small_q + a_sh++);
-          const int32_t b = ld_i32(large_q + a_lh++);
-          const double ma = ld_f64(mass + a);
-          prob[a] = (float)(ma / S);
-          alias[a] = b;
-          const double mb = (ld_f64(mass + b) + ma) - S;
-          mass[b] = mb;
-          if (mb < S) small_q[a_st++] = b; else large_q[a_lt++] = b;
+    if (m < kNarrow) {
+      if (wave == 0) {
+        Window s = {ring_id[0], ring_mass[0], sh, sh, st}, l = {ring_id[1], ring_mass[1], lh, lh, lt};
+        while (true) {
+          const int64_t both = min(s.tail - s.head, l.tail - l.head);
+          if (both <= 0 || both >= 2 * kNarrow) break;
+          if (s.head == s.loaded) refill(s, small_q, mass, lane);
+          if (l.head == l.loaded) refill(l, large_q, mass, lane);
+          const int k = (int)min((int64_t)64, min(s.loaded - s.head, l.loaded - l.head));
+          int32_t b = 0;
+          double mb = 0.0;
+          if (lane < k) {
+            const int at_s = (int)((s.head + lane) & (kRing - 1)), at_l = (int)((l.head + lane) & (kRing - 1));
+            const int32_t a = s.id[at_s];
+            const double ma = s.mass[at_s];
+            b = l.id[at_l];
+            mb = (l.mass[at_l] + ma) - S;
+            prob[a] = (float)(ma / S);
+            alias[a] = b;
+            mass[b] = mb;
+          }
+          s.head += k;
+          l.head += k;
+          wave_fence();
+          const bool demoted = mb < S;
+          append(s, small_q, lane < k && demoted, b, mb, lane);
+          append(l, large_q, lane < k && !demoted, b, mb, lane);
+          wave_fence();
         }
-        q_s[0] = a_sh; q_s[1] = a_st; q_s[2] = a_lh; q_s[3] = a_lt;
+        if (lane == 0) { q_s[0] = s.head; q_s[1] = s.tail; q_s[2] = l.head; q_s[3] = l.tail; }
       }
       __syncthreads();
       sh = q_s[0]; st = q_s[1]; lh = q_s[2]; lt = q_s[3];
       continue;
     }
     int64_t add_s = 0, add_l = 0;
-    for (int64_t base = 0; base < m; base += kLongThreads) {
-      const int64_t i = base + tid;
-      const bool valid = i < m;
-      int32_t b = 0;
-      bool demoted = false;
-      if (valid) {
-        const int32_t a = ld_i32(small_q + sh + i);
-        b = ld_i32(large_q + lh + i);
-        const double ma = ld_f64(mass + a);
-        prob[a] = (float)(ma / S);
-        alias[a] = b;
-        const double mb = (ld_f64(mass + b) + ma) - S;
-        mass[b] = mb;
-        demoted = mb < S;
+    for (int64_t base = 0; base < m; base += kLongTrip, turn ^= 1) {
+      const int64_t first = base + wave * (64 * kLongItems) + lane;
+      int32_t a[kLongItems], b[kLongItems];
+      double ma[kLongItems], mb[kLongItems];
+#pragma unroll
+      for (int c = 0; c < kLongItems; ++c) {
+        const bool valid = first + c * 64 < m;
+        a[c] = valid ? small_q[sh + first + c * 64] : 0;
+        b[c] = valid ? large_q[lh + first + c * 64] : 0;
       }
-      int rs, ts, rl, tl;
-      block_rank(valid && demoted, wave_tot, rs, ts);
-      block_rank(valid && !demoted, wave_tot, rl, tl);
-      if (valid) {
-        if (demoted) small_q[st + add_s + rs] = b;
-        else large_q[lt + add_l + rl] = b;
+#pragma unroll
+      for (int c = 0; c < kLongItems; ++c) {
+        const bool valid = first + c * 64 < m;
+        ma[c] = valid ? mass[a[c]] : 0.0;
+        mb[c] = valid ? mass[b[c]] : 0.0;
       }
-      add_s += ts;
-      add_l += tl;
+      uint64_t down[kLongItems], stay[kLongItems];
+      int cd = 0, cs = 0;
+#pragma unroll
+      for (int c = 0; c < kLongItems; ++c) {
+        const bool valid = first + c * 64 < m;
+        mb[c] = (mb[c] + ma[c]) - S;
+        if (valid) {
+          prob[a[c]] = (float)(ma[c] / S);
+          alias[a[c]] = b[c];
+          mass[b[c]] = mb[c];
+        }
+        down[c] = __ballot(valid && mb[c] < S);
+        stay[c] = __ballot(valid && !(mb[c] < S));
+        cd += __popcll(down[c]);
+        cs += __popcll(stay[c]);
+      }
+      int bd, bs, ad, as;
+      block_before(cd, cs, tot[turn], bd, bs, ad, as);
+#pragma unroll
+      for (int c = 0; c < kLongItems; ++c) {
+        if ((down[c] >> lane) & 1ull) small_q[st + add_s + bd + __popcll(down[c] & below)] = b[c];
+        else if ((stay[c] >> lane) & 1ull) large_q[lt + add_l + bs + __popcll(stay[c] & below)] = b[c];
+        bd += __popcll(down[c]);
+        bs += __popcll(stay[c]);
+      }
+      add_s += ad;
+      add_l += as;
     }
     sh += m; lh += m;
     st += add_s; lt += add_l;
   }
   for (int64_t i = sh + tid; i < st; i += kLongThreads) {
-    const int32_t x = ld_i32(small_q + i);
+    const int32_t x = small_q[i];
     prob[x] = 1.0f; alias[x] = x;
   }
   for (int64_t i = lh + tid; i < lt; i += kLongThreads) {
-    const int32_t x = ld_i32(large_q + i);
+    const int32_t x = large_q[i];
     prob[x] = 1.0f; alias[x] = x;
   }
 }
@@ -286,7 +545,7 @@ static AliasPlan plan_alias(void* ws, int64_t total_entries) {
   p.mass = cv.take<double>(t);
   p.small_q = cv.take<int32_t>(t);
   p.large_q = cv.take<int32_t>(2 * t);   // the workgroup variant appends without wrapping
-  p.max_long = (int64_t)(t / (size_t)kLongSegment) + 1;
+  p.max_long = (int64_t)(t / (size_t)(kWaveSegment + 1)) + 1;
   p.long_ids = cv.take<int64_t>((size_t)p.max_long);
   p.long_count = cv.take<unsigned long long>(1);
   p.bytes = cv.used;
@@ -297,22 +556,31 @@ template <typename OffT>
 static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments, int64_t total_entries,
                                   const float* weights, float* prob_out, int32_t* alias_out,
                                   const AliasPlan& p, hipStream_t stream) {
-  if (num_segments == 1) {
-    if (total_entries >= kLongSegment) {
-      alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(
-          seg_offsets, nullptr, nullptr, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q);
-      GS_LAUNCH_CHECK();
-      return GS_OK;
-    }
+  if (num_segments == 1 && total_entries > kWaveSegment) {
+    alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(
+        seg_offsets, nullptr, nullptr, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q);
+    GS_LAUNCH_CHECK();
+    return GS_OK;
   }
   const int threads = 64;
-  const unsigned blocks = (unsigned)ceil_div(num_segments, threads);
-  // at most this many segments can be long; none: the lane kernel alone
-  const int64_t max_long = min(num_segments, total_entries / kLongSegment);
-  alias_build_kernel<OffT><<<blocks, threads, 0, stream>>>(
-      seg_offsets, num_segments, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q,
-      max_long > 0 ? kLongSegment : INT64_MAX);
+  alias_build_kernel<OffT><<<(unsigned)ceil_div(num_segments, threads), threads, 0, stream>>>(
+      seg_offsets, num_segments, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q);
   GS_LAUNCH_CHECK();
+  // few segments: a wave each; many: up to 64 per wave, so that the short ones cost one look
+  const int per_wave = (int)max((int64_t)1, min((int64_t)64, num_segments / 16384));
+  const unsigned waves = (unsigned)ceil_div(num_segments, per_wave);
+  if (total_entries > kLaneSegment) {
+    alias_build_wave_kernel<OffT, (int)kLaneSegment + 1, 256><<<waves, 64, 0, stream>>>(
+        seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
+    GS_LAUNCH_CHECK();
+  }
+  if (total_entries > 256) {
+    alias_build_wave_kernel<OffT, 257, kWaveSegment><<<waves, 64, 0, stream>>>(
+        seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
+    GS_LAUNCH_CHECK();
+  }
+  // at most this many segments can be longer
+  const int64_t max_long = min(num_segments, total_entries / (kWaveSegment + 1));
   if (max_long > 0) {
     zero_u64_kernel<<<1, 1, 0, stream>>>(p.long_count);
     GS_LAUNCH_CHECK();
