@@ -102,14 +102,30 @@ struct Term {      // one contribution to a destination row
   uint32_t pos;    // position of this term among the terms of its key
 };
 
+// The optimizer behind the sparse update (a template argument of the kernels that write rows).  With
+// delta D, the exact sum of a row's terms (computed with step -1, so D is the row's gradient):
+//   kPlain     row = round(row + D)
+//   kMomentum  m = round(round(mu * m) + D), w = round(w - lr * m)
+//   kAdam      m = round(round(beta1 * m) + (1 - beta1) * D), v = round(round(beta2 * v) + (1 - beta2) * D * D),
+//              w = round(w - adam_move(m, v))
+// The rows that the batch does not name get the same with D = 0, in a pass over whole tables that
+// leaves the others alone.
+enum : int { kPlain, kMomentum, kAdam };
+struct OptRates {
+  float decay1, decay2;     // mu, or beta1 and beta2
+  float c1, c2;             // Adam: 1 - beta1, 1 - beta2
+  float lr;                 // of the model update (Adam: lr / (1 - beta1^t))
+  float root_c2, eps;
+};
+
 struct SgnsArgs {
   void* w_in;               // tables the logits are computed from
   void* w_out;
   void* dst_in;             // tables that receive round(old + delta): the same two for plain
   void* dst_out;            // SGD, the momentum tables for the momentum step
-  float* sq_in;             // Adam only (else null): with delta D of a row, the destination row
-  float* sq_out;            // gets c1 * D and this second-moment row gets c2 * D * D (fp32 tables)
-  float c1, c2;
+  float* sq_in;             // Adam only (else null): the second-moment tables (fp32)
+  float* sq_out;
+  OptRates opt;             // momentum and Adam: the rates of the optimizer
   // negatives drawn inside the step (draw_negs != 0): entry (i, j) is the draw of
   // gs_sample_negatives for pair index neg_pair_base + i, written to negs_draw
   // (which `negs` then points to) for the later kernels
@@ -948,6 +964,41 @@ __device__ __forceinline__ float piece_elem(const uint32_t (&w)[WORDS], int i) {
   else return (i & 1) ? T::hi(w[i >> 1]) : T::lo(w[i >> 1]);
 }
 
+// elements back into words of storage type T (16-bit: rounded)
+template <typename T, int WORDS>
+__device__ __forceinline__ void pack_piece(const float* x, uint32_t (&w)[WORDS]) {
+#pragma unroll
+  for (int i = 0; i < WORDS; ++i) {
+    if constexpr (std::is_same<T, float>::value) w[i] = __float_as_uint(x[i]);
+    else w[i] = pack16<T>(x[2 * i], x[2 * i + 1]);
+  }
+}
+
+// x as a table of type T holds it
+template <typename T>
+__device__ __forceinline__ float as_stored(float x) {
+  if constexpr (std::is_same<T, float>::value) return x;
+  else return T::lo(T::round(x));
+}
+
+// one element of the optimizers' rows (d = 0 for the rows outside the batch); w comes back unrounded
+template <typename T>
+__device__ __forceinline__ void momentum_elem(const OptRates& o, float& m, float& w, double d) {
+  m = as_stored<T>(m * o.decay1);
+  m = as_stored<T>((float)((double)m + d));
+  w = w - o.lr * m;
+}
+__device__ __forceinline__ float adam_move(float m, float v, float step, float root_c2, float eps) {
+  return step * m / (sqrtf(v) / root_c2 + eps);
+}
+__device__ __forceinline__ void adam_elem(const OptRates& o, float& m, float& v, float& w, double d) {
+  m *= o.decay1;
+  v *= o.decay2;
+  m = (float)((double)m + (double)o.c1 * d);
+  v = (float)((double)v + (double)o.c2 * d * d);
+  w -= adam_move(m, v, o.lr, o.root_c2, o.eps);
+}
+
 // the exact sum as a double: net integer (terms * magic bits taken off) times 2^-36
 __device__ __forceinline__ double fix_value(unsigned long long acc) {
   return (double)(long long)acc * kFixInvScale;
@@ -973,10 +1024,10 @@ __device__ __forceinline__ int64_t next_segment_start(const Term* __restrict__ s
 // starts of segments (or the end of the terms).  kStage = false: context-table keys, source rows
 // from the input table; kStage = true: input-table keys, source rows = staged gradients (fp32,
 // natural element order).  kSegments = false: every key is one segment.
-template <typename T, int WPP, int PPL, int UB, bool kSq, bool kStage, bool kSegments>
+template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage, bool kSegments>
 __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __restrict__ sorted, int64_t begin,
                                              int64_t end, int64_t pos_hi, int lane) {
-  static_assert(!kSq || std::is_same<T, float>::value, "second-moment tables are fp32");
+  static_assert(kOpt != kAdam || std::is_same<T, float>::value, "second-moment tables are fp32");
   constexpr int EPP = WPP * Words<T>::kPerWord;          // elements per piece
   constexpr int EPL = EPP * PPL;                         // elements per lane
   constexpr int SW = kStage ? EPP : WPP;                 // 32-bit words of a source piece
@@ -986,6 +1037,7 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
       kStage ? static_cast<const void*>(a.stage_delta) : (a.snap != nullptr ? a.snap : a.w_in));
   uint32_t* dst_base = reinterpret_cast<uint32_t*>(kStage ? a.dst_in : a.dst_out);
   uint32_t* sq_base = reinterpret_cast<uint32_t*>(kStage ? a.sq_in : a.sq_out);
+  uint32_t* model_base = reinterpret_cast<uint32_t*>(kStage ? a.w_in : a.w_out);   // momentum and Adam
   const uint32_t key_base = kStage ? (uint32_t)a.num_nodes : 0u;
   const int64_t src_row_words = kStage ? (int64_t)a.dim : (int64_t)a.dim / Words<T>::kPerWord;
   const int64_t dst_row_words = (int64_t)a.dim / Words<T>::kPerWord;
@@ -996,12 +1048,17 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
 
   unsigned long long acc[EPL];
   uint32_t old[PPL][WPP];
+  uint32_t old_w[kOpt != kPlain ? PPL : 1][WPP], old_v[kOpt == kAdam ? PPL : 1][WPP];
 #pragma unroll
   for (int x = 0; x < EPL; ++x) acc[x] = 0;
 #pragma unroll
   for (int p = 0; p < PPL; ++p)
 #pragma unroll
-    for (int w = 0; w < WPP; ++w) old[p][w] = 0u;
+    for (int w = 0; w < WPP; ++w) {
+      old[p][w] = 0u;
+      if constexpr (kOpt != kPlain) old_w[p][w] = 0u;
+      if constexpr (kOpt == kAdam) old_v[p][w] = 0u;
+    }
   uint32_t cur_row = kNoRow;       // key of the segment being summed (table row: cur_row - key_base)
   uint32_t cur_seg = 0;            // its number within the key (pos >> seg_shift of its terms)
   int64_t seg_first = 0;           // position of its first term
@@ -1057,20 +1114,31 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
       double d[EPP];
 #pragma unroll
       for (int i = 0; i < EPP; ++i) d[i] = fix_value(acc[p * EPP + i]);
-      if constexpr (kSq) {
-        uint32_t* sq_words = sq_base + r * dst_row_words;
-        uint32_t old2[WPP];
-        load_words<WPP>(sq_words + (int64_t)(p * 64 + lane) * WPP, old2);
-        double d2[EPP];
-#pragma unroll
-        for (int i = 0; i < EPP; ++i) {
-          d2[i] = (double)a.c2 * d[i] * d[i];
-          d[i] *= (double)a.c1;
-        }
+      if constexpr (kOpt == kPlain) {
         write_piece(row_words, p, old[p], d);
-        write_piece(sq_words, p, old2, d2);
       } else {
-        write_piece(row_words, p, old[p], d);
+        const int64_t at = r * dst_row_words + (int64_t)(p * 64 + lane) * WPP;
+        float m[EPP], w[EPP];
+#pragma unroll
+        for (int i = 0; i < EPP; ++i) { m[i] = piece_elem<T, WPP>(old[p], i); w[i] = piece_elem<T, WPP>(old_w[p], i); }
+        if constexpr (kOpt == kMomentum) {
+#pragma unroll
+          for (int i = 0; i < EPP; ++i) momentum_elem<T>(a.opt, m[i], w[i], d[i]);
+        } else {
+          uint32_t v_out[WPP];
+#pragma unroll
+          for (int i = 0; i < EPP; ++i) {
+            float v = __uint_as_float(old_v[p][i]);
+            adam_elem(a.opt, m[i], v, w[i], d[i]);
+            v_out[i] = __float_as_uint(v);
+          }
+          store_words<WPP>(sq_base + at, v_out);
+        }
+        uint32_t m_out[WPP], w_out[WPP];
+        pack_piece<T, WPP>(m, m_out);
+        pack_piece<T, WPP>(w, w_out);
+        store_words<WPP>(dst_base + at, m_out);
+        store_words<WPP>(model_base + at, w_out);
       }
     }
   };
@@ -1117,8 +1185,15 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
             if (pos == 0u) {
               const uint32_t* row_words = dst_base + (int64_t)(cur_row - key_base) * dst_row_words;
 #pragma unroll
-              for (int p = 0; p < PPL; ++p)
-                if (piece_ok[p]) load_words<WPP>(row_words + (int64_t)(p * 64 + lane) * WPP, old[p]);
+              for (int p = 0; p < PPL; ++p) {
+                if (!piece_ok[p]) continue;
+                const int64_t in_row = (int64_t)(p * 64 + lane) * WPP;
+                load_words<WPP>(row_words + in_row, old[p]);
+                if constexpr (kOpt != kPlain)
+                  load_words<WPP>(model_base + (int64_t)(cur_row - key_base) * dst_row_words + in_row, old_w[p]);
+                if constexpr (kOpt == kAdam)
+                  load_words<WPP>(sq_base + (int64_t)(cur_row - key_base) * dst_row_words + in_row, old_v[p]);
+              }
             }
           }
           const double c =
@@ -1147,7 +1222,7 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
 // with more segments meet in the side buffer at slot (position of the row's first term) >>
 // seg_shift, which no two such rows can share because each spans more than S positions.
 // Context-table keys take the positions [0, num_terms), input-table keys the positions after them.
-template <typename T, int WPP, int PPL, int UB, bool kSq, bool kStage>
+template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage>
 __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
   constexpr int kWaves = kSgnsThreads / 64;
   const int64_t pos_lo = kStage ? a.num_terms : 0;
@@ -1167,7 +1242,7 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
     const int64_t slice_end = min(slice_begin + slice, pos_hi);
     const int64_t begin = next_segment_start(sorted, slice_begin, pos_hi, lane, seg_mask);   // what lies before is an earlier wave's
     const int64_t end = next_segment_start(sorted, slice_end, pos_hi, lane, seg_mask);       // finish the segment we started
-    update_range<T, WPP, PPL, UB, kSq, kStage, true>(a, sorted, begin, end, pos_hi, lane);
+    update_range<T, WPP, PPL, UB, kOpt, kStage, true>(a, sorted, begin, end, pos_hi, lane);
   }
 }
 
@@ -1189,7 +1264,7 @@ __device__ __forceinline__ void elem_store(T* row, int e, float v) { row[e].bits
 // 2 = input-table keys and the loss.  With one table on both sides a row can be long under
 // both of its keys, and its two read-modify-writes must not overlap: the context-table keys
 // are then finished before the input-table keys are summed.
-template <typename T>
+template <typename T, int kOpt>
 __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, int which) {
   if (blockIdx.x == gridDim.x - 1) {
     if (which == 1) return;
@@ -1222,13 +1297,20 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, i
   const int64_t row = input_row ? (int64_t)t.row - a.num_nodes : (int64_t)t.row;
   const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.long_acc) + s * (int64_t)a.dim;
   T* dst = static_cast<T*>(input_row ? a.dst_in : a.dst_out) + row * (int64_t)a.dim;
-  float* sq = input_row ? a.sq_in : a.sq_out;
-  if (sq != nullptr) {
-    sq += row * (int64_t)a.dim;
+  if constexpr (kOpt != kPlain) {
+    T* model = static_cast<T*>(input_row ? a.w_in : a.w_out) + row * (int64_t)a.dim;
     for (int e = l16; e < a.dim; e += kGroupLanes) {
-      const double d = fix_value(src[e]);
-      elem_store(dst, e, (float)((double)elem_load(dst, e) + (double)a.c1 * d));
-      sq[e] = (float)((double)sq[e] + (double)a.c2 * d * d);
+      float m = elem_load(dst, e), w = elem_load(model, e);
+      if constexpr (kOpt == kMomentum) {
+        momentum_elem<T>(a.opt, m, w, fix_value(src[e]));
+      } else {
+        float* sq = (input_row ? a.sq_in : a.sq_out) + row * (int64_t)a.dim + e;
+        float v = *sq;
+        adam_elem(a.opt, m, v, w, fix_value(src[e]));
+        *sq = v;
+      }
+      elem_store(dst, e, m);
+      elem_store(model, e, w);
     }
     return;
   }
@@ -1491,13 +1573,13 @@ __global__ __launch_bounds__(kSmallThreads) void sgns_small_update_kernel(SgnsAr
   for (uint32_t at = (uint32_t)wave * s_out; at < n_out; at += kSmallWaves * s_out) {
     const int64_t begin = next_segment_start(terms_s, at, n_out, lane, ~0u);
     const int64_t end = next_segment_start(terms_s, min(at + s_out, n_out), n_out, lane, ~0u);
-    update_range<T, WPP, 1, UB, false, false, false>(a, terms_s, begin, end, n_out, lane);
+    update_range<T, WPP, 1, UB, kPlain, false, false>(a, terms_s, begin, end, n_out, lane);
   }
   const uint32_t n_all = n_out + n_in;
   for (uint32_t at = n_out + (uint32_t)wave * s_in; at < n_all; at += kSmallWaves * s_in) {
     const int64_t begin = next_segment_start(terms_s, at, n_all, lane, ~0u);
     const int64_t end = next_segment_start(terms_s, min(at + s_in, n_all), n_all, lane, ~0u);
-    update_range<T, WPP, 1, UB, false, true, false>(a, terms_s, begin, end, n_all, lane);
+    update_range<T, WPP, 1, UB, kPlain, true, false>(a, terms_s, begin, end, n_all, lane);
   }
   const uint32_t longs = uniform_u32(n_long);
   for (uint32_t l = 0; l < longs; ++l) {
@@ -1642,7 +1724,7 @@ static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_
 
 // the two update passes (context-table keys, then input-table keys) in the piece layout that
 // fits the row: 64 lanes x WPP words x PPL pieces cover the row, UB source rows in flight
-template <typename T, int WPP, int PPL, int UB>
+template <typename T, int WPP, int PPL, int UB, int kOpt>
 static int32_t launch_updates(const SgnsArgs& a, hipStream_t stream) {
   constexpr int kWaves = kSgnsThreads / 64;
   // context-table keys: exactly num_terms positions; input-table keys: at most one per pair
@@ -1650,18 +1732,10 @@ static int32_t launch_updates(const SgnsArgs& a, hipStream_t stream) {
   const unsigned in_blocks = (unsigned)min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
   const size_t lds = 0;
   const unsigned finish_blocks = (unsigned)ceil_div(a.long_slots, kGroupsPerBlock) + 1;
-  const bool one_table = a.snap != nullptr;
-  if constexpr (std::is_same<T, float>::value) {
-    if (a.sq_out != nullptr) {
-      sgns_update_kernel<T, WPP, PPL, UB, true, false><<<out_blocks, kSgnsThreads, lds, stream>>>(a);
-      sgns_update_kernel<T, WPP, PPL, UB, true, true><<<in_blocks, kSgnsThreads, lds, stream>>>(a);
-      GS_LAUNCH_CHECK();
-      return GS_OK;
-    }
-  }
-  sgns_update_kernel<T, WPP, PPL, UB, false, false><<<out_blocks, kSgnsThreads, lds, stream>>>(a);
-  if (one_table) sgns_finish_kernel<T><<<finish_blocks, kSgnsThreads, 0, stream>>>(a, 1);
-  sgns_update_kernel<T, WPP, PPL, UB, false, true><<<in_blocks, kSgnsThreads, lds, stream>>>(a);
+  sgns_update_kernel<T, WPP, PPL, UB, kOpt, false><<<out_blocks, kSgnsThreads, lds, stream>>>(a);
+  if constexpr (kOpt == kPlain)
+    if (a.snap != nullptr) sgns_finish_kernel<T, kOpt><<<finish_blocks, kSgnsThreads, 0, stream>>>(a, 1);   // one table
+  sgns_update_kernel<T, WPP, PPL, UB, kOpt, true><<<in_blocks, kSgnsThreads, lds, stream>>>(a);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
@@ -1680,8 +1754,30 @@ static int32_t launch_small(const SgnsArgs& a, hipStream_t stream) {
   return GS_OK;
 }
 
+template <typename T, int kOpt>
+static int32_t launch_dense_rest(const SgnsArgs& a, bool any_named, hipStream_t stream);
+
+// everything behind the place kernel
+template <typename T, int kOpt>
+static int32_t launch_rows(const SgnsArgs& a, hipStream_t stream) {
+  const int row_bytes = a.dim * (int)sizeof(T);
+  int32_t rc;
+  if (row_bytes <= 256) rc = launch_updates<T, 1, 1, 16, kOpt>(a, stream);
+  else if (row_bytes <= 512) rc = launch_updates<T, 2, 1, 16, kOpt>(a, stream);
+  else if (row_bytes <= 1024) rc = launch_updates<T, 4, 1, 8, kOpt>(a, stream);
+  else if (row_bytes <= 2048) rc = launch_updates<T, 4, 2, 4, kOpt>(a, stream);
+  else rc = launch_updates<T, 4, 4, 2, kOpt>(a, stream);
+  if (rc != GS_OK) return rc;
+  // long rows (of both tables, unless the context-table ones are done); one more block sums the loss
+  const unsigned finish_blocks = (unsigned)ceil_div(a.long_slots, kGroupsPerBlock) + 1;
+  sgns_finish_kernel<T, kOpt><<<finish_blocks, kSgnsThreads, 0, stream>>>(a, a.snap != nullptr ? 2 : 0);
+  GS_LAUNCH_CHECK();
+  if constexpr (kOpt != kPlain) return launch_dense_rest<T, kOpt>(a, true, stream);
+  return GS_OK;
+}
+
 template <typename T, int VPL, int RB>
-static int32_t launch_sgns(const SgnsArgs& a, bool small, hipStream_t stream) {
+static int32_t launch_sgns(const SgnsArgs& a, bool small, int opt, hipStream_t stream) {
   if (small) {
     // (row_bytes <= kSmallMaxRowBytes)
     if constexpr (VPL * 64 * sizeof(T) <= (size_t)kSmallMaxRowBytes) return launch_small<T, VPL, RB>(a, stream);
@@ -1714,19 +1810,10 @@ static int32_t launch_sgns(const SgnsArgs& a, bool small, hipStream_t stream) {
   }
   sgns_place_kernel<<<(unsigned)ceil_div(a.num_terms + a.num_pairs, 256), 256, 0, stream>>>(a);
   GS_LAUNCH_CHECK();
-  const int row_bytes = a.dim * (int)sizeof(T);
-  int32_t rc;
-  if (row_bytes <= 256) rc = launch_updates<T, 1, 1, 16>(a, stream);
-  else if (row_bytes <= 512) rc = launch_updates<T, 2, 1, 16>(a, stream);
-  else if (row_bytes <= 1024) rc = launch_updates<T, 4, 1, 8>(a, stream);
-  else if (row_bytes <= 2048) rc = launch_updates<T, 4, 2, 4>(a, stream);
-  else rc = launch_updates<T, 4, 4, 2>(a, stream);
-  if (rc != GS_OK) return rc;
-  // long rows (of both tables, unless the context-table ones are done); one more block sums the loss
-  const unsigned finish_blocks = (unsigned)ceil_div(a.long_slots, kGroupsPerBlock) + 1;
-  sgns_finish_kernel<T><<<finish_blocks, kSgnsThreads, 0, stream>>>(a, a.snap != nullptr ? 2 : 0);
-  GS_LAUNCH_CHECK();
-  return GS_OK;
+  if (opt == kMomentum) return launch_rows<T, kMomentum>(a, stream);
+  if constexpr (std::is_same<T, float>::value)
+    if (opt == kAdam) return launch_rows<T, kAdam>(a, stream);
+  return launch_rows<T, kPlain>(a, stream);
 }
 
 __global__ void zero_double_kernel(double* p) { *p = 0.0; }
@@ -1781,35 +1868,98 @@ __global__ __launch_bounds__(256) void table_axpy16_kernel(uint4* __restrict__ w
   }
 }
 
-// Adam's dense passes over a whole fp32 table: decay of both moments, then the model update
-__global__ __launch_bounds__(256) void adam_decay_kernel(float4* __restrict__ m, float4* __restrict__ v,
-                                                         int64_t n4, float beta1, float beta2) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    float4 x = m[i], y = v[i];
-    x.x *= beta1; x.y *= beta1; x.z *= beta1; x.w *= beta1;
-    y.x *= beta2; y.y *= beta2; y.z *= beta2; y.w *= beta2;
-    m[i] = x;
-    v[i] = y;
+// Whether the batch named the row of `key`: its counter slot holds terms, or the key is in the table of
+// the batch's keys.
+__device__ __forceinline__ bool row_named(const SgnsArgs& a, uint32_t key) {
+  const KeyRegion r = key_region(a, key);
+  if (r.bits == 0) return a.cnt[r.slot_base + r.vertex] != a.cnt[r.slot_base + r.vertex + 1u];
+  const uint32_t mask = (1u << r.bits) - 1u;
+  uint32_t h = (key * 2654435761u) >> (32 - r.bits);
+  for (uint32_t probes = 0; probes <= mask; ++probes) {
+    const uint32_t seen = r.table[h];
+    if (seen == key) return true;
+    if (seen == kNoRow) return false;
+    h = (h + 1u) & mask;
+  }
+  return false;
+}
+
+// The optimizer on the rows outside the batch (the update and finish kernels have done the others): one
+// pass that reads and writes every table once, where decay, put and apply as passes of their own read
+// the moments twice and write them twice.  Bound by memory: with 1 M rows of 128 fp32 columns and
+// 262,144 pairs, the rest of both tables takes 0.65 ms (momentum) and 1.00 ms (Adam), 4.4 TB/s, against
+// 0.99 and 1.74 ms for the separate passes; the update kernels take 0.04 and 0.06 ms more for the rows of
+// the batch.  A row takes `pieces` lanes of 16 bytes; a lane has kDenseRows rows in flight.
+constexpr int kDenseRows = 4;
+template <typename T, int kOpt>
+__global__ __launch_bounds__(256) void dense_rest_kernel(SgnsArgs a, int pieces, bool any_named) {
+  const int rows_at_once = 256 / pieces;
+  const int in_iter = (int)threadIdx.x / pieces, piece = (int)threadIdx.x - in_iter * pieces;
+  if (in_iter >= rows_at_once) return;
+  const bool input_table = blockIdx.y != 0;
+  uint4* __restrict__ m_t = static_cast<uint4*>(input_table ? a.dst_in : a.dst_out);
+  uint4* __restrict__ w_t = static_cast<uint4*>(input_table ? a.w_in : a.w_out);
+  uint4* __restrict__ v_t = reinterpret_cast<uint4*>(input_table ? a.sq_in : a.sq_out);
+  const int64_t step = (int64_t)rows_at_once * kDenseRows;
+  for (int64_t first = (int64_t)blockIdx.x * step + in_iter; first < a.num_nodes; first += (int64_t)gridDim.x * step) {
+    bool mine[kDenseRows];
+#pragma unroll
+    for (int u = 0; u < kDenseRows; ++u) {
+      const int64_t row = first + (int64_t)u * rows_at_once;
+      mine[u] = row < a.num_nodes &&
+                !(any_named && row_named(a, (uint32_t)row + (input_table ? (uint32_t)a.num_nodes : 0u)));
+    }
+    uint4 m[kDenseRows], w[kDenseRows], v[kOpt == kAdam ? kDenseRows : 1];
+#pragma unroll
+    for (int u = 0; u < kDenseRows; ++u) {
+      if (!mine[u]) continue;
+      const int64_t at = (first + (int64_t)u * rows_at_once) * pieces + piece;
+      m[u] = m_t[at];
+      w[u] = w_t[at];
+      if constexpr (kOpt == kAdam) v[u] = v_t[at];
+    }
+#pragma unroll
+    for (int u = 0; u < kDenseRows; ++u) {
+      if (!mine[u]) continue;
+      const int64_t at = (first + (int64_t)u * rows_at_once) * pieces + piece;
+      constexpr int kElems = 4 * Words<T>::kPerWord;
+      const uint32_t mw[4] = {m[u].x, m[u].y, m[u].z, m[u].w}, ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+      float me[kElems], we[kElems];
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) { me[i] = piece_elem<T, 4>(mw, i); we[i] = piece_elem<T, 4>(ww, i); }
+      if constexpr (kOpt == kMomentum) {
+#pragma unroll
+        for (int i = 0; i < kElems; ++i) {
+          me[i] = as_stored<T>(me[i] * a.opt.decay1);
+          we[i] = we[i] - a.opt.lr * me[i];
+        }
+      } else {
+        float ve[4] = {__uint_as_float(v[u].x), __uint_as_float(v[u].y), __uint_as_float(v[u].z), __uint_as_float(v[u].w)};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          me[i] *= a.opt.decay1;
+          ve[i] *= a.opt.decay2;
+          we[i] -= adam_move(me[i], ve[i], a.opt.lr, a.opt.root_c2, a.opt.eps);
+        }
+        v_t[at] = make_uint4(__float_as_uint(ve[0]), __float_as_uint(ve[1]), __float_as_uint(ve[2]), __float_as_uint(ve[3]));
+      }
+      uint32_t mo[4], wo[4];
+      pack_piece<T, 4>(me, mo);
+      pack_piece<T, 4>(we, wo);
+      m_t[at] = make_uint4(mo[0], mo[1], mo[2], mo[3]);
+      w_t[at] = make_uint4(wo[0], wo[1], wo[2], wo[3]);
+    }
   }
 }
-__device__ __forceinline__ float adam_move(float m, float v, float step, float root_c2, float eps) {
-  return step * m / (sqrtf(v) / root_c2 + eps);
-}
-__global__ __launch_bounds__(256) void adam_apply_kernel(float4* __restrict__ w,
-                                                         const float4* __restrict__ m,
-                                                         const float4* __restrict__ v, int64_t n4,
-                                                         float step, float root_c2, float eps) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    float4 x = w[i];
-    const float4 a = m[i], b = v[i];
-    x.x -= adam_move(a.x, b.x, step, root_c2, eps);
-    x.y -= adam_move(a.y, b.y, step, root_c2, eps);
-    x.z -= adam_move(a.z, b.z, step, root_c2, eps);
-    x.w -= adam_move(a.w, b.w, step, root_c2, eps);
-    w[i] = x;
-  }
+
+template <typename T, int kOpt>
+static int32_t launch_dense_rest(const SgnsArgs& a, bool any_named, hipStream_t stream) {
+  const int pieces = a.dim * (int)sizeof(T) / 16;
+  const int64_t per_block = (int64_t)(256 / pieces) * kDenseRows;
+  const dim3 grid((unsigned)min((int64_t)(256 * 32), ceil_div(a.num_nodes, per_block)), 2);
+  dense_rest_kernel<T, kOpt><<<grid, 256, 0, stream>>>(a, pieces, any_named);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
 }
 
 static int32_t check_sgns_args(const void* w_in, const void* w_out, int64_t num_nodes, int32_t dim,
@@ -1831,9 +1981,10 @@ static int32_t check_sgns_args(const void* w_in, const void* w_out, int64_t num_
 
 // What the variants of the step add to the plain one.
 struct SgnsExtras {
-  float* sq_in = nullptr;          // Adam: second-moment tables and the two put coefficients
+  int opt = kPlain;                // the optimizer behind the update, its rates
+  OptRates rates = {};
+  float* sq_in = nullptr;          // Adam: second-moment tables
   float* sq_out = nullptr;
-  float c1 = 1.f, c2 = 0.f;
   const gs_alias* noise = nullptr; // negatives drawn inside the step (negs_draw != null)
   uint64_t neg_seed = 0, neg_pair_base = 0;
   int32_t* negs_draw = nullptr;
@@ -1857,8 +2008,7 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   SgnsArgs a;
   a.sq_in = x.sq_in;
   a.sq_out = x.sq_out;
-  a.c1 = x.c1;
-  a.c2 = x.c2;
+  a.opt = x.rates;
   a.draw_negs = x.negs_draw != nullptr ? 1 : 0;
   const bool weighted = x.noise != nullptr && x.noise->prob != nullptr;
   a.noise_prob = weighted ? x.noise->prob : nullptr;
@@ -1922,23 +2072,23 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   // float4 registers per lane for one row: 16 lanes x 4 floats = 64 elements each
   const int vpl = (dim + 63) / 64;
   if (dtype == GS_F32) {
-    if (vpl <= 1) return launch_sgns<float, 1, 6>(a, p.small, stream);
-    if (vpl <= 2) return launch_sgns<float, 2, 6>(a, p.small, stream);
-    if (vpl <= 4) return launch_sgns<float, 4, 3>(a, p.small, stream);
-    if (vpl <= 8) return launch_sgns<float, 8, 2>(a, p.small, stream);
-    return launch_sgns<float, 16, 1>(a, p.small, stream);
+    if (vpl <= 1) return launch_sgns<float, 1, 6>(a, p.small, x.opt, stream);
+    if (vpl <= 2) return launch_sgns<float, 2, 6>(a, p.small, x.opt, stream);
+    if (vpl <= 4) return launch_sgns<float, 4, 3>(a, p.small, x.opt, stream);
+    if (vpl <= 8) return launch_sgns<float, 8, 2>(a, p.small, x.opt, stream);
+    return launch_sgns<float, 16, 1>(a, p.small, x.opt, stream);
   }
   // 16-bit rows: a 16-byte piece is 8 elements = two float4, so the register count is even
   if (dtype == GS_BF16) {
-    if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, p.small, stream);
-    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, p.small, stream);
-    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, p.small, stream);
-    return launch_sgns<bf16_t, 16, 2>(a, p.small, stream);
+    if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, p.small, x.opt, stream);
+    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, p.small, x.opt, stream);
+    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, p.small, x.opt, stream);
+    return launch_sgns<bf16_t, 16, 2>(a, p.small, x.opt, stream);
   }
-  if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, p.small, stream);
-  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, p.small, stream);
-  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, p.small, stream);
-  return launch_sgns<f16_t, 16, 2>(a, p.small, stream);
+  if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, p.small, x.opt, stream);
+  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, p.small, x.opt, stream);
+  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, p.small, x.opt, stream);
+  return launch_sgns<f16_t, 16, 2>(a, p.small, x.opt, stream);
 }
 
 }  // namespace gs
@@ -2156,6 +2306,12 @@ extern "C" int32_t gs_line1_step(void* w, int64_t num_nodes, int32_t dim, int32_
                   loss_sum_out, p, stream, x);
 }
 
+// Small batches on small tables: the two-launch step between dense passes of their own; else the rows of
+// the batch get the whole optimizer in the update and one pass does the rest.  The single pass moves two
+// tables' worth of momentum less, 2 * table_bytes * 2 / 5 TB/s, and the step in front of it is up to 57
+// us slower (82 against 25 us for 2048 pairs on 1 M nodes): even at about 70 MB per table.
+constexpr int64_t kSeparatePassBytes = (int64_t)64 << 20;
+
 extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, void* m_out,
                                          int64_t num_nodes, int32_t dim, int32_t dtype,
                                          const int32_t* centers, const int32_t* contexts,
@@ -2171,6 +2327,17 @@ extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, vo
     return GS_EINVAL;
   SgnsPlan p;
   if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
+  const int64_t table_bytes = num_nodes * (int64_t)dim * (dtype == GS_F32 ? 4 : 2);
+  if (num_pairs > 0 && !(p.small && table_bytes <= kSeparatePassBytes)) {
+    p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
+    if (p.bytes > ws_bytes) return GS_EWORKSPACE;
+    SgnsExtras x;
+    x.opt = kMomentum;
+    x.rates.decay1 = mu;
+    x.rates.lr = lr;
+    return run_sgns(w_in, w_out, m_in, m_out, num_nodes, dim, dtype, centers, contexts, negs, num_pairs, k, -1.0f,
+                    loss_sum_out, p, stream, x);
+  }
   const int per16 = (dtype == GS_F32) ? 4 : 8;
   const int64_t pieces = num_nodes * (int64_t)dim / per16;
   const unsigned blocks = (unsigned)min((int64_t)(256 * 64), ceil_div(pieces, 256));
@@ -2230,33 +2397,33 @@ extern "C" int32_t gs_sgns_adam_step(float* w_in, float* w_out, float* m_in, flo
     return GS_EINVAL;
   SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
   if (ws_bytes < p.bytes) return GS_EWORKSPACE;
-  const int64_t pieces = num_nodes * (int64_t)dim / 4;
-  const unsigned blocks = (unsigned)min((int64_t)(256 * 64), ceil_div(pieces, 256));
-  // mult: both moments decay, every row
-  adam_decay_kernel<<<blocks, 256, 0, stream>>>((float4*)m_in, (float4*)v_in, pieces, beta1, beta2);
-  adam_decay_kernel<<<blocks, 256, 0, stream>>>((float4*)m_out, (float4*)v_out, pieces, beta1, beta2);
-  GS_LAUNCH_CHECK();
-  // put: m[r] += (1 - beta1) g[r], v[r] += (1 - beta2) g[r]^2 for the rows of the batch
+  SgnsExtras x;
+  x.opt = kAdam;
+  x.sq_in = v_in;
+  x.sq_out = v_out;
+  x.rates.decay1 = beta1;
+  x.rates.decay2 = beta2;
+  x.rates.c1 = 1.0f - beta1;
+  x.rates.c2 = 1.0f - beta2;
+  // w -= (lr / (1 - beta1^t)) * m / (sqrt(v) / sqrt(1 - beta2^t) + eps), every row
+  x.rates.lr = (float)((double)lr / (1.0 - pow((double)beta1, (double)t)));
+  x.rates.root_c2 = (float)sqrt(1.0 - pow((double)beta2, (double)t));
+  x.rates.eps = eps;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
-  } else {
-    SgnsExtras x;
-    x.sq_in = v_in;
-    x.sq_out = v_out;
-    x.c1 = 1.0f - beta1;
-    x.c2 = 1.0f - beta2;
-    const int32_t rc = run_sgns(w_in, w_out, m_in, m_out, num_nodes, dim, GS_F32, centers, contexts,
-                                negs, num_pairs, k, -1.0f, loss_sum_out, p, stream, x);
-    if (rc != GS_OK) return rc;
+    SgnsArgs a = {};
+    a.w_in = w_in;
+    a.w_out = w_out;
+    a.dst_in = m_in;
+    a.dst_out = m_out;
+    a.sq_in = v_in;
+    a.sq_out = v_out;
+    a.opt = x.rates;
+    a.num_nodes = num_nodes;
+    a.dim = dim;
+    return launch_dense_rest<float, kAdam>(a, false, stream);
   }
-  // apply: w -= (lr / (1 - beta1^t)) * m / (sqrt(v) / sqrt(1 - beta2^t) + eps), every row
-  const float step = (float)((double)lr / (1.0 - pow((double)beta1, (double)t)));
-  const float root_c2 = (float)sqrt(1.0 - pow((double)beta2, (double)t));
-  adam_apply_kernel<<<blocks, 256, 0, stream>>>((float4*)w_in, (const float4*)m_in,
-                                                (const float4*)v_in, pieces, step, root_c2, eps);
-  adam_apply_kernel<<<blocks, 256, 0, stream>>>((float4*)w_out, (const float4*)m_out,
-                                                (const float4*)v_out, pieces, step, root_c2, eps);
-  GS_LAUNCH_CHECK();
-  return GS_OK;
+  return run_sgns(w_in, w_out, m_in, m_out, num_nodes, dim, GS_F32, centers, contexts, negs, num_pairs, k, -1.0f,
+                  loss_sum_out, p, stream, x);
 }
