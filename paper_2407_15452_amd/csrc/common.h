@@ -56,9 +56,10 @@ int32_t exclusive_scan_i64(int64_t* data, int64_t n, int64_t* scratch, int64_t* 
 // output when it is even.  n < 2^32.
 size_t radix_sort_scratch_bytes(int64_t n);
 int radix_sort_passes(int nbits);
-template <typename K>
-int32_t radix_sort(const K* keys_in, const uint32_t* vals_in, K* keys_out, uint32_t* vals_out, K* keys_alt,
-                   uint32_t* vals_alt, int64_t n, K limit, int nbits, void* scratch, hipStream_t stream);
+// Records: (uint32_t, uint32_t), (uint32_t, uint2), (uint64_t, uint32_t).
+template <typename K, typename V>
+int32_t radix_sort(const K* keys_in, const V* vals_in, K* keys_out, V* vals_out, K* keys_alt, V* vals_alt, int64_t n,
+                   K limit, int nbits, void* scratch, hipStream_t stream);
 
 // ---- device side -----------------------------------------------------------
 #if defined(__HIPCC__)
@@ -92,6 +93,11 @@ __device__ __forceinline__ Block4 philox_at(uint64_t seed, uint64_t index, uint3
 
 __device__ __forceinline__ uint64_t slot_of(const Block4& b, uint64_t n) {
   return __umul64hi(((uint64_t)b.x0 << 32) | (uint64_t)b.x1, n);
+}
+
+// the same for n below 2^32: two 32 x 32 -> 64 bit products instead of four
+__device__ __forceinline__ uint32_t slot_of32(const Block4& b, uint32_t n) {
+  return (uint32_t)(((uint64_t)b.x0 * n + (((uint64_t)b.x1 * n) >> 32)) >> 32);
 }
 
 __device__ __forceinline__ float unit_float(uint32_t x) { return (float)(x >> 8) * 0x1p-24f; }

@@ -210,13 +210,16 @@ __global__ __launch_bounds__(256) void radix_scan_kernel(uint32_t* __restrict__ 
   if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-template <typename K, bool kValues, int ITEMS>
+template <typename K, typename V, bool kValues, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
-    const K* __restrict__ keys, const uint32_t* __restrict__ vals, K* __restrict__ keys_out,
-    uint32_t* __restrict__ vals_out, int64_t n, K limit, int shift, uint32_t mask, int64_t num_tiles,
+    const K* __restrict__ keys, const V* __restrict__ vals, K* __restrict__ keys_out,
+    V* __restrict__ vals_out, int64_t n, K limit, int shift, uint32_t mask, int64_t num_tiles,
     const uint32_t* __restrict__ counts, const uint32_t* __restrict__ totals) {
   constexpr int kTile = kSortThreads * ITEMS;
-  __shared__ K stage[kTile];                          // the tile in digit order (then its values)
+  // the tile in digit order: its keys, then its values
+  constexpr size_t kRecord = kValues && sizeof(V) > sizeof(K) ? sizeof(V) : sizeof(K);
+  __shared__ __align__(16) unsigned char stage_bytes[kTile * kRecord];
+  K* stage = reinterpret_cast<K*>(stage_bytes);
   __shared__ uint32_t wave_count[kSortWaves][kDigits];
   __shared__ uint32_t tile_start[kDigits];            // first place of a digit in the tile
   __shared__ uint32_t out_start[kDigits];             // first place of the tile's run of a digit in the output, minus tile_start
@@ -228,13 +231,13 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   const int64_t first = base + (int64_t)wave * (64 * ITEMS) + lane;
   const int live = (int)min((int64_t)kTile, n - base);
   K key[ITEMS];
-  uint32_t val[ITEMS];
+  V val[ITEMS];
   uint32_t rank[ITEMS];
 #pragma unroll
   for (int c = 0; c < ITEMS; ++c) {
     const int64_t i = first + c * 64;
     key[c] = (i < n) ? keys[i] : (K)0;
-    if (kValues) val[c] = (i < n) ? vals[i] : 0u;
+    if (kValues && i < n) val[c] = vals[i];
   }
   __syncthreads();
   // rank of every record among the wave's records of its digit, in index order
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     }
   }
   if (kValues) {
-    uint32_t* vstage = reinterpret_cast<uint32_t*>(stage);
+    V* vstage = reinterpret_cast<V*>(stage_bytes);
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c)
@@ -314,8 +317,8 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   }
 }
 
-template <typename K, bool kValues, int ITEMS>
-static int32_t radix_pass(const K* keys, const uint32_t* vals, K* keys_out, uint32_t* vals_out, int64_t n, K limit,
+template <typename K, typename V, bool kValues, int ITEMS>
+static int32_t radix_pass(const K* keys, const V* vals, K* keys_out, V* vals_out, int64_t n, K limit,
                           int shift, int bits, uint32_t* counts, uint32_t* totals, hipStream_t stream) {
   const int64_t tiles = ceil_div(n, kSortThreads * ITEMS);
   const uint32_t mask = (1u << bits) - 1u;
@@ -323,7 +326,7 @@ static int32_t radix_pass(const K* keys, const uint32_t* vals, K* keys_out, uint
   GS_LAUNCH_CHECK();
   radix_scan_kernel<<<1u << bits, 256, 0, stream>>>(counts, tiles, totals);
   GS_LAUNCH_CHECK();
-  radix_scatter_kernel<K, kValues, ITEMS><<<(unsigned)tiles, kSortThreads, 0, stream>>>(
+  radix_scatter_kernel<K, V, kValues, ITEMS><<<(unsigned)tiles, kSortThreads, 0, stream>>>(
       keys, vals, keys_out, vals_out, n, limit, shift, mask, tiles, counts, totals);
   GS_LAUNCH_CHECK();
   return GS_OK;
@@ -343,9 +346,9 @@ size_t radix_sort_scratch_bytes(int64_t n) {
 
 int radix_sort_passes(int nbits) { return (nbits + kDigitBits - 1) / kDigitBits; }
 
-template <typename K>
-int32_t radix_sort(const K* keys_in, const uint32_t* vals_in, K* keys_out, uint32_t* vals_out, K* keys_alt,
-                   uint32_t* vals_alt, int64_t n, K limit, int nbits, void* scratch, hipStream_t stream) {
+template <typename K, typename V>
+int32_t radix_sort(const K* keys_in, const V* vals_in, K* keys_out, V* vals_out, K* keys_alt, V* vals_alt, int64_t n,
+                   K limit, int nbits, void* scratch, hipStream_t stream) {
   if (n <= 0) return GS_OK;
   if (n > (int64_t)UINT32_MAX) return GS_EOVERFLOW;      // (places are 32-bit)
   const bool large = n >= kSortLarge;
@@ -353,16 +356,16 @@ int32_t radix_sort(const K* keys_in, const uint32_t* vals_in, K* keys_out, uint3
   const int64_t tile = kSortThreads * (large ? kSortItemsLarge : kSortItemsSmall);
   uint32_t* counts = cv.take<uint32_t>((size_t)ceil_div(n, tile) * kDigits);
   uint32_t* totals = cv.take<uint32_t>(kDigits);
-  auto pass = vals_in != nullptr ? (large ? radix_pass<K, true, kSortItemsLarge> : radix_pass<K, true, kSortItemsSmall>)
-                                 : (large ? radix_pass<K, false, kSortItemsLarge> : radix_pass<K, false, kSortItemsSmall>);
+  auto pass = vals_in != nullptr ? (large ? radix_pass<K, V, true, kSortItemsLarge> : radix_pass<K, V, true, kSortItemsSmall>)
+                                 : (large ? radix_pass<K, V, false, kSortItemsLarge> : radix_pass<K, V, false, kSortItemsSmall>);
   const int passes = radix_sort_passes(nbits);
   const int width = (nbits + passes - 1) / passes;
   const K* k_from = keys_in;
-  const uint32_t* v_from = vals_in;
+  const V* v_from = vals_in;
   for (int p = 0; p < passes; ++p) {
     const bool to_alt = (passes - 1 - p) & 1;              // the last pass ends in the output
     K* k_to = to_alt ? keys_alt : keys_out;
-    uint32_t* v_to = to_alt ? vals_alt : vals_out;
+    V* v_to = to_alt ? vals_alt : vals_out;
     const int32_t rc = pass(k_from, v_from, k_to, v_to, n, limit, p * width, min(width, nbits - p * width), counts,
                             totals, stream);
     if (rc != GS_OK) return rc;
@@ -371,9 +374,11 @@ int32_t radix_sort(const K* keys_in, const uint32_t* vals_in, K* keys_out, uint3
   }
   return GS_OK;
 }
-template int32_t radix_sort<uint32_t>(const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*,
-                                      int64_t, uint32_t, int, void*, hipStream_t);
-template int32_t radix_sort<uint64_t>(const uint64_t*, const uint32_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*,
-                                      int64_t, uint64_t, int, void*, hipStream_t);
+template int32_t radix_sort(const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*, int64_t,
+                            uint32_t, int, void*, hipStream_t);
+template int32_t radix_sort(const uint32_t*, const uint2*, uint32_t*, uint2*, uint32_t*, uint2*, int64_t, uint32_t,
+                            int, void*, hipStream_t);
+template int32_t radix_sort(const uint64_t*, const uint32_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*, int64_t,
+                            uint64_t, int, void*, hipStream_t);
 
 }  // namespace gs

@@ -36,7 +36,8 @@
 //              extra block sums the per-block loss partials in a fixed order
 //
 // Small batches take two launches instead (forward, and one kernel for the rest): see
-// sgns_small_update_kernel.
+// sgns_small_update_kernel.  Large ones sort their context-table terms instead of counting and
+// placing them: see sgns_sorted_update_kernel.
 //
 // delta is accumulated exactly: every product coef * element is rounded once to
 // a multiple of 2^-36 (one fp64 fused multiply-add against 1.5 * 2^52, whose
@@ -185,7 +186,11 @@ struct SgnsArgs {
   int32_t out_bits, in_bits;
   uint32_t in_base;
   uint32_t* tile_sums;      // scan scratch
-  Term* sorted;             // [num_terms + num_pairs]
+  Term* sorted;             // [num_terms + num_pairs]; large batches: the input-table terms only
+  int64_t stage_base;       // position of the first input-table term in `sorted`
+  int64_t stage_long_base;  // first side-buffer slot of the input-table rows
+  uint32_t* term_key;       // large batches: [num_terms] row of the context table and
+  uint2* term_src;          // (source row, coefficient) of every term; after the sort: in order of the rows
   long long* long_acc;      // [long_slots][dim] exact sums of the long rows
   int32_t* stage_center;    // [num_pairs], -1 = unused slot
   uint32_t* stage_rank;     // [num_pairs] rank of the slot among the slots of its centre
@@ -466,16 +471,17 @@ __global__ void sgns_clear_kernel(uint4* __restrict__ cnt4, int64_t n4, uint4* _
 }
 
 // ---- forward ------------------------------------------------------------------------------
+enum : int { kByCounter, kBySort, kInLds };
 // Staged centre-row gradient of one run of equal centres, in natural element
 // order.  Slot numbers are fixed by position (first pair of the chunk + flush
 // number), so no counter is shared between groups; unused slots of a chunk are
 // marked with centre -1.
-template <typename T, int VPL, bool kRank>
+template <typename T, int VPL, int kGroup>
 __device__ __forceinline__ void stage_flush(const SgnsArgs& a, int64_t slot, int32_t center, int l16,
                                             const float4 (&du)[VPL]) {
   if (l16 == 0) {
     a.stage_center[slot] = center;
-    if constexpr (kRank) a.stage_rank[slot] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)a.num_nodes + (uint32_t)center), 1u);
+    if constexpr (kGroup != kInLds) a.stage_rank[slot] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)a.num_nodes + (uint32_t)center), 1u);
   }
   float4* out = reinterpret_cast<float4*>(a.stage_delta + slot * (int64_t)a.dim);
   const int dim4 = a.dim >> 2;
@@ -497,10 +503,13 @@ __device__ __forceinline__ float row_peak(const float4 (&r)[VPL]) {
 }
 
 //
-// kRank = false: the step of a small batch (below), whose update kernel groups the terms itself.
-// Nothing is counted, and a bad id or an out-of-range product turns the block's loss partial into
-// NaN (there is no flag that an earlier kernel would have cleared).
-template <typename T, int VPL, int RB, bool kRank, int kThreads>
+// kGroup: how the terms of a row come together afterwards.
+//   kByCounter  every term takes a rank from its row's counter (for the place kernel)
+//   kBySort     every term is written as a record for the sort; only staging slots are counted
+//   kInLds      the step of a small batch, whose update kernel groups the terms itself: nothing is
+//               counted, and a bad id or an out-of-range product turns the block's loss partial into
+//               NaN (there is no flag that an earlier kernel would have cleared)
+template <typename T, int VPL, int RB, int kGroup, int kThreads>
 __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
   constexpr int kGroups = kThreads / kGroupLanes;
   extern __shared__ int32_t idx_s[];              // per group: centres[chunk], rows[chunk][K+1]
@@ -510,18 +519,18 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
   // locally first (whichever rows reach a slot of this small LDS table first):
   // a term of such a row takes a block-local rank, the block adds its total to
   // the row's global counter once, and the ranks are completed afterwards.
-  __shared__ int32_t hot_key[kRank ? kHotSlots : 1];
-  __shared__ uint32_t hot_cnt[kRank ? kHotSlots : 1];
-  __shared__ uint32_t hot_base[kRank ? kHotSlots : 1];
+  __shared__ int32_t hot_key[kGroup == kByCounter ? kHotSlots : 1];
+  __shared__ uint32_t hot_cnt[kGroup == kByCounter ? kHotSlots : 1];
+  __shared__ uint32_t hot_base[kGroup == kByCounter ? kHotSlots : 1];
   bool bad = false;
   auto row_of = [&](int32_t id) -> int32_t {
-    if constexpr (kRank) return checked_row(a, id);
+    if constexpr (kGroup != kInLds) return checked_row(a, id);
     if ((uint32_t)id < (uint32_t)a.num_nodes) return id;
     bad = true;
     return 0;
   };
   auto report = [&]() {
-    if constexpr (kRank) *a.bad_ids = 1u;
+    if constexpr (kGroup != kInLds) *a.bad_ids = 1u;
     else bad = true;
   };
   const T* __restrict__ w_in = static_cast<const T*>(a.w_in);
@@ -538,7 +547,7 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
 
   int32_t* cen_s = idx_s + group_in_block * (a.chunk_pairs * (K1 + 1));
   int32_t* rows_s = cen_s + a.chunk_pairs;
-  if constexpr (kRank)
+  if constexpr (kGroup == kByCounter)
     for (int h = threadIdx.x; h < kHotSlots; h += kThreads) { hot_key[h] = -1; hot_cnt[h] = 0u; }
   if (a.walks != nullptr) {
     if (l16 < count) {                      // lane p derives pair p of the chunk from its walk
@@ -605,7 +614,7 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
     if (c != cur_c) {
       if (cur_c >= 0) {
         peak = fmaxf(peak, row_peak<VPL>(du));
-        stage_flush<T, VPL, kRank>(a, first + flushes++, cur_c, l16, du);
+        stage_flush<T, VPL, kGroup>(a, first + flushes++, cur_c, l16, du);
       }
       load_row<VPL>(w_in, c, a.dim, l16, u);
       peak = fmaxf(peak, row_peak<VPL>(u));
@@ -625,7 +634,7 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
       const int my_j = j0 + l16;
       const bool mine = l16 < RB && my_j <= K;
       uint32_t rk = 0;
-      if (kRank && mine) {
+      if (kGroup == kByCounter && mine) {
         const int32_t row = prow[my_j];
         const uint32_t h = ((uint32_t)row * 2654435761u) >> (32 - kHotBits);
         const int32_t seen = atomicCAS(&hot_key[h], -1, row);
@@ -653,23 +662,29 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
       for (int b = 0; b < RB; ++b)
         if (j0 + b <= K) axpy<VPL>(du, __shfl(g_mine, b, kGroupLanes), vv[b]);
       if (mine) {
-        a.g[e0 + my_j] = g_mine;
-        if constexpr (kRank) a.rank[e0 + my_j] = rk;
+        if constexpr (kGroup == kBySort) {
+          const int32_t src = a.snap != nullptr ? (int32_t)(first + flushes) : c;
+          a.term_key[e0 + my_j] = (uint32_t)prow[my_j];
+          a.term_src[e0 + my_j] = make_uint2((uint32_t)src, __float_as_uint(-a.lr * g_mine));
+        } else {
+          a.g[e0 + my_j] = g_mine;
+        }
+        if constexpr (kGroup == kByCounter) a.rank[e0 + my_j] = rk;
       }
     }
   }
   if (cur_c >= 0) {
     peak = fmaxf(peak, row_peak<VPL>(du));
-    stage_flush<T, VPL, kRank>(a, first + flushes++, cur_c, l16, du);
+    stage_flush<T, VPL, kGroup>(a, first + flushes++, cur_c, l16, du);
   }
   if (l16 >= flushes && l16 < count) a.stage_center[first + l16] = -1;
   if (!(peak * fabsf(a.lr) < kFixPeak)) report();   // (also taken for NaN)
-  if (!kRank && bad) loss = __uint_as_float(0x7fc00000u);
+  if (kGroup == kInLds && bad) loss = __uint_as_float(0x7fc00000u);
 
   loss = row_sum16(loss);
   if (l16 == 0) loss_s[group_in_block] = loss;
   __syncthreads();
-  if constexpr (kRank) {
+  if constexpr (kGroup == kByCounter) {
     // one global update per locally counted row, then complete the pending ranks
     for (int h = threadIdx.x; h < kHotSlots; h += kThreads)
       if (hot_key[h] >= 0) hot_base[h] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)hot_key[h]), hot_cnt[h]);
@@ -877,8 +892,9 @@ __global__ __launch_bounds__(1024) void scan_small_kernel(uint32_t* __restrict__
 // Entries [0, num_terms) are the (pair, j) terms, entries num_terms + s the staging slots.
 // The entry with position 2^seg_shift (it exists exactly in the rows of more than one
 // segment) also clears the row's slot of the side buffer.
-__global__ __launch_bounds__(256) void sgns_place_kernel(SgnsArgs a) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// (Large batches, whose terms are sorted: first_entry = num_terms, the staging slots alone.)
+__global__ __launch_bounds__(256) void sgns_place_kernel(SgnsArgs a, int64_t first_entry) {
+  const int64_t e = first_entry + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= a.num_terms + a.num_pairs) return;
   Term t;
   uint32_t rk;
@@ -903,7 +919,8 @@ __global__ __launch_bounds__(256) void sgns_place_kernel(SgnsArgs a) {
   t.pos = rk;
   a.sorted[begin + rk] = t;
   if (rk == (1u << a.seg_shift)) {
-    long long* acc = a.long_acc + (int64_t)(begin >> a.seg_shift) * a.dim;
+    const int64_t long_base = e < a.num_terms ? 0 : a.stage_long_base;
+    long long* acc = a.long_acc + (long_base + (int64_t)(begin >> a.seg_shift)) * a.dim;
     for (int x = 0; x < a.dim; ++x) acc[x] = 0;
   }
 }
@@ -1023,10 +1040,12 @@ __device__ __forceinline__ int64_t next_segment_start(const Term* __restrict__ s
 // What one wave does with the positions [begin, end) of key-major terms: begin and end are the
 // starts of segments (or the end of the terms).  kStage = false: context-table keys, source rows
 // from the input table; kStage = true: input-table keys, source rows = staged gradients (fp32,
-// natural element order).  kSegments = false: every key is one segment.
-template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage, bool kSegments>
+// natural element order).  kSegments = false: every key is one segment.  kSorted: the terms are the
+// sorted records (term_key, term_src), which do not hold their positions: these follow from
+// where the keys change, and from first_row, the first position of the row that `begin` lies in.
+template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage, bool kSegments, bool kSorted = false>
 __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __restrict__ sorted, int64_t begin,
-                                             int64_t end, int64_t pos_hi, int lane) {
+                                             int64_t end, int64_t pos_hi, int lane, int64_t first_row = 0) {
   static_assert(kOpt != kAdam || std::is_same<T, float>::value, "second-moment tables are fp32");
   constexpr int EPP = WPP * Words<T>::kPerWord;          // elements per piece
   constexpr int EPL = EPP * PPL;                         // elements per lane
@@ -1073,7 +1092,7 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
   auto flush_long = [&]() {
     const int64_t row_first = seg_first - ((int64_t)cur_seg << a.seg_shift);
     unsigned long long* dst = reinterpret_cast<unsigned long long*>(a.long_acc) +
-                              (row_first >> a.seg_shift) * a.dim;
+                              ((row_first >> a.seg_shift) + (kStage ? a.stage_long_base : 0)) * a.dim;
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
       if (piece_ok[p]) {
@@ -1143,11 +1162,29 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
     }
   };
 
+  uint32_t last_key = kNoRow;      // sorted records: key of the term before the 64 at hand
   for (int64_t q = begin; q < end; q += 64) {
     Term t;
     t.row = kNoRow; t.center = 0; t.coef = 0.f; t.pos = 0;
-    if (q + lane < end) t = sorted[q + lane];
     const int n = (int)min((int64_t)64, end - q);
+    if constexpr (kSorted) {
+      if (lane < n) {
+        t.row = a.term_key[q + lane];
+        const uint2 src = a.term_src[q + lane];
+        t.center = (int32_t)src.x;
+        t.coef = __uint_as_float(src.y);
+      }
+      uint32_t before = (uint32_t)__shfl_up((int)t.row, 1, 64);
+      if (lane == 0) before = (q == begin) ? t.row : last_key;
+      const unsigned long long changes = __builtin_amdgcn_ballot_w64(lane < n && t.row != before);
+      const unsigned long long upto = changes & ((2ull << lane) - 1ull);
+      const int64_t run_first = upto != 0ull ? q + 63 - __builtin_clzll(upto) : first_row;
+      t.pos = (uint32_t)(q + lane - run_first);
+      if (changes != 0ull) first_row = q + 63 - __builtin_clzll(changes);
+      last_key = (uint32_t)__builtin_amdgcn_readlane((int)t.row, n - 1);
+    } else {
+      if (lane < n) t = sorted[q + lane];
+    }
 #pragma unroll 1
     for (int b0 = 0; b0 < n; b0 += UB) {
       uint32_t u[UB][PPL][SW];
@@ -1212,7 +1249,8 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
     }
   }
   // last pending segment: the row goes on if the term after the range has the same key
-  if (cur_row != kNoRow) flush(kSegments && end < pos_hi && uniform_u32(sorted[end].row) == cur_row);
+  if (cur_row != kNoRow)
+    flush(kSegments && end < pos_hi && uniform_u32(kSorted ? a.term_key[end] : sorted[end].row) == cur_row);
 }
 
 // Ownership: the terms of a key are cut into segments of S = 2^seg_shift consecutive
@@ -1225,7 +1263,7 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
 template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage>
 __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
   constexpr int kWaves = kSgnsThreads / 64;
-  const int64_t pos_lo = kStage ? a.num_terms : 0;
+  const int64_t pos_lo = kStage ? a.stage_base : 0;
   // (scalars that come out of memory are made wave-uniform explicitly: loop bounds and the
   // lane numbers of the broadcasts must live in scalar registers)
   const int64_t pos_hi = kStage ? (int64_t)uniform_u32(a.cnt[a.cnt_last]) : a.num_terms;
@@ -1295,7 +1333,8 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, i
   const bool input_row = (int64_t)t.row >= a.num_nodes;
   if (which != 0 && input_row != (which == 2)) return;
   const int64_t row = input_row ? (int64_t)t.row - a.num_nodes : (int64_t)t.row;
-  const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.long_acc) + s * (int64_t)a.dim;
+  const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.long_acc) +
+                                  (s + (input_row ? a.stage_long_base : 0)) * (int64_t)a.dim;
   T* dst = static_cast<T*>(input_row ? a.dst_in : a.dst_out) + row * (int64_t)a.dim;
   if constexpr (kOpt != kPlain) {
     T* model = static_cast<T*>(input_row ? a.w_in : a.w_out) + row * (int64_t)a.dim;
@@ -1316,6 +1355,111 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, i
   }
   for (int e = l16; e < a.dim; e += kGroupLanes)
     elem_store(dst, e, (float)((double)elem_load(dst, e) + fix_value(src[e])));
+}
+
+// ---- large batches: the context-table terms as sorted records -------------------------------
+// With millions of terms the counters cost more than a sort: a random atomic per term in the forward
+// kernel, and in the place kernel a random read and a random 16-byte write per term, all of them whole
+// cache lines.  The forward kernel writes each term as a record (row; source row, coefficient)
+// instead, three or four passes of the radix sort bring the records into row order in streams, and
+// the update kernel reads them as they lie.  The few input-table terms keep their counters.
+// 12 million terms, 128 fp32 columns, 4 M nodes: forward 1016 -> 827 us, place and scan 420 -> three
+// passes of 106 us (count 28, prefix sums 5, scatter 73), update 944 -> 1000 us.
+
+// First position >= p (and <= num_terms) that starts a segment of its row, and the row's first
+// position.  back and ahead: the keys of the 64 positions before p (lane l: p - 1 - l) and of the 64
+// from p on (kNoRow outside), loaded by the caller so that the loads of both ends of a slice are
+// under way together; almost always they decide.
+__device__ __forceinline__ int64_t sorted_segment_start(const SgnsArgs& a, int64_t p, int lane, uint32_t back,
+                                                        uint32_t ahead, int64_t& first_row) {
+  const uint32_t* __restrict__ keys = a.term_key;
+  first_row = p;
+  if (p == 0 || p >= a.num_terms) return p;
+  const uint32_t key = uniform_u32(ahead);
+  const unsigned long long other_back = __builtin_amdgcn_ballot_w64(back != key);
+  if (other_back & 1ull) return p;                                   // a row starts at p
+  const unsigned long long other_ahead = __builtin_amdgcn_ballot_w64(ahead != key);
+  int64_t first;
+  if (other_back != 0ull) {
+    first = p - __builtin_ctzll(other_back);
+  } else {
+    int64_t lo = 0, hi = max((int64_t)0, p - 64);                     // (keys[hi] == key)
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (uniform_u32(keys[mid]) < key) lo = mid + 1; else hi = mid;
+    }
+    first = lo;
+  }
+  const int64_t segment = (int64_t)1 << a.seg_shift;
+  const int64_t next = first + ((p - first + segment - 1) & ~(segment - 1));      // the row's next segment, if it gets there
+  int64_t row_end = a.num_terms;                                     // first position behind the row, as far as it matters
+  if (other_ahead != 0ull) {
+    row_end = p + __builtin_ctzll(other_ahead);
+  } else {
+    for (int64_t x = p + 64; x < min(next, a.num_terms); x += 64) {
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(x + lane >= a.num_terms || keys[min(x + lane, a.num_terms - 1)] != key);
+      if (mask == 0ull) continue;
+      row_end = x + __builtin_ctzll(mask);
+      break;
+    }
+  }
+  if (next < row_end && next < a.num_terms) {
+    // (next may lie behind the last key looked at: the row's own segment only if it gets there)
+    if (uniform_u32(keys[next]) == key) {
+      first_row = first;
+      return next;
+    }
+  }
+  row_end = min(row_end, next < row_end ? next : row_end);
+  first_row = row_end;
+  return row_end;
+}
+
+template <typename T, int WPP, int PPL, int UB>
+__global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_update_kernel(SgnsArgs a) {
+  const uint32_t* __restrict__ keys = a.term_key;
+  const int lane = threadIdx.x & 63;
+  const int64_t wave = (int64_t)blockIdx.x * (kSgnsThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t p0 = wave * a.slice_terms;
+  if (p0 >= a.num_terms) return;
+  const int64_t p1 = min(p0 + a.slice_terms, a.num_terms);
+  auto key_at = [&](int64_t p) { return p >= 0 && p < a.num_terms ? keys[p] : kNoRow; };
+  const uint32_t back0 = key_at(p0 - 1 - lane), ahead0 = key_at(p0 + lane);
+  const uint32_t back1 = key_at(p1 - 1 - lane), ahead1 = key_at(p1 + lane);
+  int64_t first_row, unused;
+  const int64_t begin = sorted_segment_start(a, p0, lane, back0, ahead0, first_row);
+  const int64_t end = sorted_segment_start(a, p1, lane, back1, ahead1, unused);
+  update_range<T, WPP, PPL, UB, kPlain, false, true, true>(a, nullptr, begin, end, a.num_terms, lane, first_row);
+}
+
+// The long rows (more than one segment) of the sorted terms, 16 lanes per side-buffer slot: slot s
+// belongs to the row whose first term lies in positions [s * S, (s + 1) * S), if that row goes on for more
+// than S terms.  kZero: clears the slot; else table[row] = round(old + slot).
+template <typename T, bool kZero>
+__global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_long_kernel(SgnsArgs a) {
+  const uint32_t* __restrict__ keys = a.term_key;
+  const int l16 = threadIdx.x & (kGroupLanes - 1);
+  const int64_t s = ((int64_t)blockIdx.x * kSgnsThreads + threadIdx.x) / kGroupLanes;
+  const int64_t low = s << a.seg_shift, after = (s + 1) << a.seg_shift;
+  if (after >= a.num_terms) return;
+  const uint32_t key = keys[after];
+  if (keys[after - 1] != key) return;
+  int64_t lo = low, hi = after - 1;                      // first position of the row in the window
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (keys[mid] < key) lo = mid + 1; else hi = mid;
+  }
+  if (lo == low && lo > 0 && keys[lo - 1] == key) return;                  // started in an earlier window
+  const int64_t second = lo + ((int64_t)1 << a.seg_shift);
+  if (second >= a.num_terms || keys[second] != key) return;
+  unsigned long long* acc = reinterpret_cast<unsigned long long*>(a.long_acc) + s * (int64_t)a.dim;
+  if constexpr (kZero) {
+    for (int e = l16; e < a.dim; e += kGroupLanes) acc[e] = 0ull;
+  } else {
+    T* dst = static_cast<T*>(a.dst_out) + (int64_t)key * a.dim;
+    for (int e = l16; e < a.dim; e += kGroupLanes)
+      elem_store(dst, e, (float)((double)elem_load(dst, e) + fix_value(acc[e])));
+  }
 }
 
 // ---- small batches: the whole step in two launches -----------------------------------------
@@ -1628,6 +1772,11 @@ struct SgnsPlan {
   bool small = false;       // the two-launch step of a small batch, which keeps copies of the input rows
   void* snap = nullptr;
   int32_t* pair_slot = nullptr;
+  bool by_sort = false;     // the context-table terms as sorted records (large batches)
+  uint32_t* term_key[2] = {nullptr, nullptr};      // [0] holds the sorted ones
+  uint2* term_src[2] = {nullptr, nullptr};
+  void* sort_scratch = nullptr;
+  int64_t stage_base = 0, stage_long_base = 0;
   size_t bytes;
 };
 
@@ -1660,6 +1809,7 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
   p.cnt_last = (int64_t)(out_slots + in_slots);
   p.seg_shift = seg_shift_for((int64_t)b);
   p.long_slots = (int64_t)((terms + b) >> p.seg_shift) + 1;
+  p.stage_base = (int64_t)terms;
   p.loss_partials = cv.take<double>((size_t)forward_blocks_for((int64_t)b));
   p.g = cv.take<float>(terms);
   p.rank = cv.take<uint32_t>(terms);
@@ -1675,6 +1825,55 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
   p.bytes = cv.used;
   return p;
 }
+
+// Batches of at least this many terms take the sorted records.  Measured, counters against records: 2.4
+// million terms (300,007 pairs, 7 negatives, 200 fp16 columns on 778 k nodes) 775 / 786 us, 11 million (1 M
+// pairs, 10 negatives, 256 bf16 columns on 4 M nodes) 3000 / 2552, 12 million (2 M pairs, 5 negatives, 128 fp32
+// columns on 4 M nodes) 2606 / 2407, negatives and the rest of the step included.
+constexpr int64_t kSortedMinTerms = (int64_t)1 << 22;
+// Sorted terms per wave of the update (the ends of a slice cost four loads of keys: 256 against 128
+// terms, 2407 / 2425 us in the last case above).
+constexpr int kSortedSlice = 256;
+
+static int bits_for_rows(int64_t num_nodes) {
+  int b = 1;
+  while (((int64_t)1 << b) < num_nodes) ++b;
+  return b;
+}
+
+static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim) {
+  Carver cv(ws);
+  SgnsPlan p = {};
+  const size_t b = (size_t)num_pairs, terms = b * (size_t)(k + 1), nodes = (size_t)num_nodes;
+  p.by_sort = true;
+  // counters of the input-table keys alone, as in plan_sgns
+  int in_bits = 8;
+  while (((size_t)1 << in_bits) < 2 * b) ++in_bits;
+  p.in_bits = ((size_t)1 << in_bits) < nodes ? in_bits : 0;
+  p.cnt_last = (int64_t)(p.in_bits ? (size_t)1 << p.in_bits : nodes);
+  p.table_places = p.in_bits ? (int64_t)1 << p.in_bits : 0;
+  p.seg_shift = seg_shift_for(num_pairs);
+  p.stage_long_base = (int64_t)(terms >> p.seg_shift) + 1;
+  p.long_slots = (int64_t)(b >> p.seg_shift) + 1;            // of the input-table rows
+  p.loss_partials = cv.take<double>((size_t)forward_blocks_for(num_pairs));
+  for (int i = 0; i < 2; ++i) {
+    p.term_key[i] = cv.take<uint32_t>(terms);
+    p.term_src[i] = cv.take<uint2>(terms);
+  }
+  p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)terms));
+  p.cnt = cv.take<uint32_t>((size_t)p.cnt_last + 1 + 3);                   // cleared 16 bytes at a time
+  p.key_table = p.table_places > 0 ? cv.take<uint32_t>((size_t)p.table_places) : nullptr;
+  p.tile_sums = cv.take<uint32_t>((size_t)ceil_div(p.cnt_last + 1, kScanTile));
+  p.bad_ids = cv.take<uint32_t>(1);
+  p.sorted = cv.take<Term>(b);
+  p.long_acc = cv.take<long long>((size_t)(p.stage_long_base + p.long_slots) * (size_t)dim);
+  p.stage_center = cv.take<int32_t>(b);
+  p.stage_rank = cv.take<uint32_t>(b);
+  p.stage_delta = cv.take<float>(b * (size_t)dim);
+  p.bytes = cv.used;
+  return p;
+}
+static bool sorted_batch(int64_t num_pairs, int32_t k) { return num_pairs * (int64_t)(k + 1) >= kSortedMinTerms; }
 
 // Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every
 // workgroup of its update kernel reads all of them, so its time grows with the ids (about 0.8 us
@@ -1707,19 +1906,26 @@ static SgnsPlan plan_small(void* ws, int64_t num_pairs, int32_t k, int32_t dim, 
 }
 
 // The plan of a step in a workspace of ws_bytes, of which the call's own arrays take `extra` bytes
-// behind the plan: the two-launch step where the batch is small and the workspace holds it.
+// behind the plan: the two-launch step where the batch is small, the sorted records where it is
+// large, and the counters in between and in a workspace that holds no more than their plan.
 static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int64_t num_pairs, int64_t num_nodes,
                       int32_t k, int32_t dim, int32_t dtype, bool force_compact = false) {
   if (small_batch(num_pairs, k, dim, dtype)) {
     p = plan_small(ws, num_pairs, k, dim, dtype);
     if (p.bytes + extra <= ws_bytes) return true;
   }
+  if (sorted_batch(num_pairs, k)) {
+    p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
+    if (p.bytes + extra <= ws_bytes) return true;
+  }
   p = plan_sgns(ws, num_pairs, num_nodes, k, dim, force_compact);
   return p.bytes + extra <= ws_bytes;
 }
 static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
-  const size_t large = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  return small_batch(num_pairs, k, dim, dtype) ? max(large, plan_small(nullptr, num_pairs, k, dim, dtype).bytes) : large;
+  size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
+  if (small_batch(num_pairs, k, dim, dtype)) bytes = max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
+  if (sorted_batch(num_pairs, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  return bytes;
 }
 
 // the two update passes (context-table keys, then input-table keys) in the piece layout that
@@ -1743,7 +1949,7 @@ static int32_t launch_updates(const SgnsArgs& a, hipStream_t stream) {
 template <typename T, int VPL, int RB>
 static int32_t launch_small(const SgnsArgs& a, hipStream_t stream) {
   const size_t idx_lds = (size_t)(kSmallForwardThreads / kGroupLanes) * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
-  sgns_forward_kernel<T, VPL, RB, false, kSmallForwardThreads>
+  sgns_forward_kernel<T, VPL, RB, kInLds, kSmallForwardThreads>
       <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSmallForwardThreads, idx_lds, stream>>>(a);
   GS_LAUNCH_CHECK();
   const int row_bytes = a.dim * (int)sizeof(T);            // one block more adds up the loss
@@ -1776,24 +1982,20 @@ static int32_t launch_rows(const SgnsArgs& a, hipStream_t stream) {
   return GS_OK;
 }
 
-template <typename T, int VPL, int RB>
-static int32_t launch_sgns(const SgnsArgs& a, bool small, int opt, hipStream_t stream) {
-  if (small) {
-    // (row_bytes <= kSmallMaxRowBytes)
-    if constexpr (VPL * 64 * sizeof(T) <= (size_t)kSmallMaxRowBytes) return launch_small<T, VPL, RB>(a, stream);
-    return GS_EINVAL;
-  }
-  const int64_t keys1 = a.cnt_last + 1;
-  const int64_t tiles = ceil_div(keys1, kScanTile);
-  const int64_t keys4 = ceil_div(keys1, 4);
+// counters 0, key tables empty
+static int32_t launch_clear(const SgnsArgs& a, hipStream_t stream) {
+  const int64_t keys4 = ceil_div(a.cnt_last + 1, 4);
   const int64_t table4 = a.table_places / 4;   // (tables have at least 256 places each)
   sgns_clear_kernel<<<(unsigned)ceil_div(max(keys4, table4), 256), 256, 0, stream>>>(
       (uint4*)a.cnt, keys4, (uint4*)a.key_table, table4, a.bad_ids);
   GS_LAUNCH_CHECK();
-  const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
-  sgns_forward_kernel<T, VPL, RB, true, kSgnsThreads>
-      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds, stream>>>(a);
-  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+
+// counters to offsets
+static int32_t launch_scan(const SgnsArgs& a, hipStream_t stream) {
+  const int64_t keys1 = a.cnt_last + 1;
+  const int64_t tiles = ceil_div(keys1, kScanTile);
   if (keys1 <= kScanSmallMax) {
     scan_small_kernel<<<1, 1024, 0, stream>>>(a.cnt, keys1);
     GS_LAUNCH_CHECK();
@@ -1808,7 +2010,76 @@ static int32_t launch_sgns(const SgnsArgs& a, bool small, int opt, hipStream_t s
     scan_apply_kernel<<<(unsigned)tiles, kScanThreads, 0, stream>>>(a.cnt, keys1, a.tile_sums, raw_sums);
     GS_LAUNCH_CHECK();
   }
-  sgns_place_kernel<<<(unsigned)ceil_div(a.num_terms + a.num_pairs, 256), 256, 0, stream>>>(a);
+  return GS_OK;
+}
+
+// the passes over the input-table keys of a batch whose context-table terms are sorted records
+template <typename T, int WPP, int PPL, int UB>
+static int32_t launch_sorted_updates(const SgnsArgs& a, hipStream_t stream) {
+  constexpr int kWaves = kSgnsThreads / 64;
+  const unsigned out_blocks = (unsigned)ceil_div(ceil_div(a.num_terms, a.slice_terms), kWaves);
+  const unsigned in_blocks = (unsigned)min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
+  const unsigned long_blocks = (unsigned)ceil_div(a.stage_long_base, kGroupsPerBlock);
+  sgns_sorted_long_kernel<T, true><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_sorted_update_kernel<T, WPP, PPL, UB><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_sorted_long_kernel<T, false><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_update_kernel<T, WPP, PPL, UB, kPlain, true><<<in_blocks, kSgnsThreads, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+
+template <typename T, int VPL, int RB>
+static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStream_t stream) {
+  SgnsArgs a = unsorted;
+  const int bits = bits_for_rows(a.num_nodes);
+  const int made = radix_sort_passes(bits) & 1;              // the passes end in buffer 0
+  a.term_key = p.term_key[made];
+  a.term_src = p.term_src[made];
+  int32_t rc = launch_clear(a, stream);
+  if (rc != GS_OK) return rc;
+  const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
+  sgns_forward_kernel<T, VPL, RB, kBySort, kSgnsThreads>
+      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  rc = launch_scan(a, stream);
+  if (rc != GS_OK) return rc;
+  sgns_place_kernel<<<(unsigned)ceil_div(a.num_pairs, 256), 256, 0, stream>>>(a, a.num_terms);
+  GS_LAUNCH_CHECK();
+  rc = radix_sort(a.term_key, a.term_src, p.term_key[0], p.term_src[0], p.term_key[1], p.term_src[1], a.num_terms,
+                  ~0u, bits, p.sort_scratch, stream);
+  if (rc != GS_OK) return rc;
+  a.term_key = p.term_key[0];
+  a.term_src = p.term_src[0];
+  const int row_bytes = a.dim * (int)sizeof(T);
+  if (row_bytes <= 256) rc = launch_sorted_updates<T, 1, 1, 16>(a, stream);
+  else if (row_bytes <= 512) rc = launch_sorted_updates<T, 2, 1, 16>(a, stream);
+  else if (row_bytes <= 1024) rc = launch_sorted_updates<T, 4, 1, 8>(a, stream);
+  else if (row_bytes <= 2048) rc = launch_sorted_updates<T, 4, 2, 4>(a, stream);
+  else rc = launch_sorted_updates<T, 4, 4, 2>(a, stream);
+  if (rc != GS_OK) return rc;
+  // long rows of the input table; one more block sums the loss
+  sgns_finish_kernel<T, kPlain><<<(unsigned)ceil_div(a.long_slots, kGroupsPerBlock) + 1, kSgnsThreads, 0, stream>>>(a, 2);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+
+template <typename T, int VPL, int RB>
+static int32_t launch_sgns(const SgnsArgs& a, const SgnsPlan& p, int opt, hipStream_t stream) {
+  if (p.small) {
+    // (row_bytes <= kSmallMaxRowBytes)
+    if constexpr (VPL * 64 * sizeof(T) <= (size_t)kSmallMaxRowBytes) return launch_small<T, VPL, RB>(a, stream);
+    return GS_EINVAL;
+  }
+  if (p.by_sort) return launch_sorted<T, VPL, RB>(a, p, stream);
+  int32_t rc = launch_clear(a, stream);
+  if (rc != GS_OK) return rc;
+  const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
+  sgns_forward_kernel<T, VPL, RB, kByCounter, kSgnsThreads>
+      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  rc = launch_scan(a, stream);
+  if (rc != GS_OK) return rc;
+  sgns_place_kernel<<<(unsigned)ceil_div(a.num_terms + a.num_pairs, 256), 256, 0, stream>>>(a, 0);
   GS_LAUNCH_CHECK();
   if (opt == kMomentum) return launch_rows<T, kMomentum>(a, stream);
   if constexpr (std::is_same<T, float>::value)
@@ -2059,12 +2330,16 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   a.tile_sums = p.tile_sums;
   a.bad_ids = p.bad_ids;
   a.sorted = p.sorted;
+  a.stage_base = p.stage_base;
+  a.stage_long_base = p.stage_long_base;
+  a.term_key = nullptr;
+  a.term_src = nullptr;
   a.long_acc = p.long_acc;
   a.stage_center = p.stage_center;
   a.stage_rank = p.stage_rank;
   a.stage_delta = p.stage_delta;
   a.chunk_pairs = p.small ? kSmallChunkPairs : chunk_pairs_for(num_pairs);
-  a.slice_terms = slice_terms_for(num_pairs);
+  a.slice_terms = p.by_sort ? kSortedSlice : slice_terms_for(num_pairs);
   a.loss_partials = p.loss_partials;
   a.forward_blocks = p.small ? small_forward_blocks(num_pairs) : forward_blocks_for(num_pairs);
   a.forward_blocks_per_xcd = ceil_div(a.forward_blocks, 8);
@@ -2072,23 +2347,23 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   // float4 registers per lane for one row: 16 lanes x 4 floats = 64 elements each
   const int vpl = (dim + 63) / 64;
   if (dtype == GS_F32) {
-    if (vpl <= 1) return launch_sgns<float, 1, 6>(a, p.small, x.opt, stream);
-    if (vpl <= 2) return launch_sgns<float, 2, 6>(a, p.small, x.opt, stream);
-    if (vpl <= 4) return launch_sgns<float, 4, 3>(a, p.small, x.opt, stream);
-    if (vpl <= 8) return launch_sgns<float, 8, 2>(a, p.small, x.opt, stream);
-    return launch_sgns<float, 16, 1>(a, p.small, x.opt, stream);
+    if (vpl <= 1) return launch_sgns<float, 1, 6>(a, p, x.opt, stream);
+    if (vpl <= 2) return launch_sgns<float, 2, 6>(a, p, x.opt, stream);
+    if (vpl <= 4) return launch_sgns<float, 4, 3>(a, p, x.opt, stream);
+    if (vpl <= 8) return launch_sgns<float, 8, 2>(a, p, x.opt, stream);
+    return launch_sgns<float, 16, 1>(a, p, x.opt, stream);
   }
   // 16-bit rows: a 16-byte piece is 8 elements = two float4, so the register count is even
   if (dtype == GS_BF16) {
-    if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, p.small, x.opt, stream);
-    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, p.small, x.opt, stream);
-    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, p.small, x.opt, stream);
-    return launch_sgns<bf16_t, 16, 2>(a, p.small, x.opt, stream);
+    if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, p, x.opt, stream);
+    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, p, x.opt, stream);
+    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, p, x.opt, stream);
+    return launch_sgns<bf16_t, 16, 2>(a, p, x.opt, stream);
   }
-  if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, p.small, x.opt, stream);
-  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, p.small, x.opt, stream);
-  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, p.small, x.opt, stream);
-  return launch_sgns<f16_t, 16, 2>(a, p.small, x.opt, stream);
+  if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, p, x.opt, stream);
+  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, p, x.opt, stream);
+  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, p, x.opt, stream);
+  return launch_sgns<f16_t, 16, 2>(a, p, x.opt, stream);
 }
 
 }  // namespace gs
@@ -2279,8 +2554,9 @@ static size_t line1_slot_bytes(int64_t num_pairs) {
 extern "C" size_t gs_line1_step_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k,
                                                 int32_t dim, int32_t dtype) {
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
-  return plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes +
-         line1_snap_bytes(num_pairs, dim, dtype) + line1_slot_bytes(num_pairs);
+  size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
+  if (sorted_batch(num_pairs, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  return bytes + line1_snap_bytes(num_pairs, dim, dtype) + line1_slot_bytes(num_pairs);
 }
 
 extern "C" int32_t gs_line1_step(void* w, int64_t num_nodes, int32_t dim, int32_t dtype,
@@ -2291,9 +2567,11 @@ extern "C" int32_t gs_line1_step(void* w, int64_t num_nodes, int32_t dim, int32_
   const int32_t bad = check_sgns_args(w, w, num_nodes, dim, dtype, sources, targets, negs, num_pairs,
                                       k, loss_sum_out, ws, true);
   if (bad != GS_OK) return bad;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-  const size_t snap_bytes = line1_snap_bytes(num_pairs, dim, dtype);
-  if (ws_bytes < p.bytes + snap_bytes + line1_slot_bytes(num_pairs)) return GS_EWORKSPACE;
+  const size_t snap_bytes = line1_snap_bytes(num_pairs, dim, dtype), own_bytes = snap_bytes + line1_slot_bytes(num_pairs);
+  SgnsPlan p;
+  if (sorted_batch(num_pairs, k)) p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
+  if (!sorted_batch(num_pairs, k) || ws_bytes < p.bytes + own_bytes) p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
+  if (ws_bytes < p.bytes + own_bytes) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -2326,7 +2604,7 @@ extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, vo
   if (m_in == w_in || m_in == w_out || m_out == w_in || m_out == w_out || m_in == m_out)
     return GS_EINVAL;
   SgnsPlan p;
-  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
+  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;   // (the counters' plan fits too)
   const int64_t table_bytes = num_nodes * (int64_t)dim * (dtype == GS_F32 ? 4 : 2);
   if (num_pairs > 0 && !(p.small && table_bytes <= kSeparatePassBytes)) {
     p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
