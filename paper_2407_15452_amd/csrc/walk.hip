@@ -42,6 +42,10 @@ __device__ __forceinline__ int64_t alias_pick(const WalkArgs& a, int64_t at, int
   return (unit_float(word) < a.prob[at]) ? j : (int64_t)a.alias[at];
 }
 
+// slot in a row of n entries
+__device__ __forceinline__ int64_t row_slot(const Block4& b, int64_t n) { return (int64_t)slot_of(b, (uint64_t)n); }
+__device__ __forceinline__ int32_t row_slot(const Block4& b, int32_t n) { return (int32_t)slot_of32(b, (uint32_t)n); }
+
 // First-order walks: one lane per walk, one dependent pair of random reads per
 // step (row bounds, then the neighbour).  The 64 walks of a wave advance in
 // lock step, so their positions are staged in LDS in windows of kWin and the
@@ -75,7 +79,7 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs a) {
         const int64_t hi = (int64_t)offsets[(int64_t)cur + 1];
         if (hi > lo) {
           const Block4 b = philox_at(a.seed, id, (uint32_t)t, 0u);
-          int64_t j = (int64_t)slot_of(b, (uint64_t)(hi - lo));
+          int64_t j = row_slot(b, (OffT)(hi - lo));
           if (kWeighted) {
             j = alias_pick(a, lo + j, j, b.x2);
           }
@@ -121,6 +125,7 @@ struct __attribute__((packed, aligned(4))) Quad { int32_t v[4]; };   // four ent
 template <typename OffT, bool kWeighted>
 __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   __shared__ int32_t tile[kWalkThreads / 64][64][kWinPad];
+  using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t i = ((int64_t)blockIdx.x * (kWalkThreads / 64) + wave) * 64 + lane;
   if (i >= a.num_walks) return;
@@ -135,13 +140,14 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   enum : int { kRow, kNewDraw, kAlias, kDraw, kSearch, kDone };
   enum : int { kNone, kCommit, kReject };
   const uint2* __restrict__ packed = a.packed;
+  const Pos entries = (Pos)a.num_entries;
   const bool wide = a.num_entries >= 4;     // (a probe never reads past the array)
   // every read is part of 16 bytes of one array (an alias table that is not interleaved takes two)
   const bool one_read = wide && a.num_nodes >= 3 && (!kWeighted || packed != nullptr);
   int32_t cur = a.starts[i];
   if (cur < 0 || (int64_t)cur >= a.num_nodes) cur = -1;
   int32_t prev = -1;
-  int64_t prev_lo = 0, prev_hi = 0, lo = 0, hi = 0;
+  Pos prev_lo = 0, prev_hi = 0, lo = 0, hi = 0;
   int32_t t = 0;                            // position of cur
   uint32_t att = 0;
   int state = kRow;
@@ -151,16 +157,26 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   if (last == 0) { out[0] = cur; return; }
 
   // the attempt in flight
-  int64_t j = 0;                            // slot in the row of cur
+  Pos j = 0;                                // slot in the row of cur
   uint32_t word2 = 0;                       // alias uniform (weighted)
   float s = 0.f;                            // acceptance uniform * max_bias
   int32_t x = 0;                            // candidate
   // the membership search in flight: entries before L are < x, entries from H on are > x;
   // v_lo < x is the entry before L (or -1), v_hi > x the entry at H (or num_nodes)
-  int64_t L = 0, H = 0;
+  Pos L = 0, H = 0;
   int32_t v_lo = 0, v_hi = 0;
   int probes = 0;                           // probes made in this search
-  int64_t pos = 0;                          // what this iteration reads: nbrs[pos] (or the alias entry at pos)
+  Pos pos = 0;                              // what this iteration reads: nbrs[pos] (or the alias entry at pos)
+
+  // random numbers of the attempt after the one whose read is under way: the first of a step while
+  // its row bounds arrive, the next one while a candidate arrives (three of four are rejected at
+  // p = 0.5, q = 2); a membership search keeps those of its attempt's draw.  With 32-bit positions for
+  // 32-bit offsets, 1.49 -> 1.31 ms for the 47,000 walks below.
+  Block4 next_block = {0u, 0u, 0u, 0u};
+  auto draw_ahead = [&]() {
+    if (state == kRow || state == kDraw)
+      next_block = philox_at(a.seed, id, (uint32_t)t, state == kRow ? 0u : att + 1u);
+  };
 
   // position t + 1 of the walk is `node`: into the lane's window, and out when it is full
   auto put = [&](int32_t node) {
@@ -198,23 +214,23 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
 
     // ---- arithmetic ahead of the read -----------------------------------------------------
     if (state == kNewDraw) {
-      const Block4 b = philox_at(a.seed, id, (uint32_t)t, att);
-      j = (int64_t)slot_of(b, (uint64_t)(hi - lo));
-      word2 = b.x2;
-      s = unit_float(b.x3) * a.max_bias;
+      j = row_slot(next_block, (Pos)(hi - lo));
+      word2 = next_block.x2;
+      s = unit_float(next_block.x3) * a.max_bias;
       pos = lo + j;
       state = (kWeighted ? kAlias : kDraw);
     } else if (state == kSearch) {           // (the range [L, H) is never empty here)
-      int64_t p;
+      Pos p;
       if (probes % 3 == 2) {
         p = L + ((H - L) >> 1);
       } else {
-        const float part = (float)((int64_t)x - v_lo) / (float)((int64_t)v_hi - v_lo);
-        p = L + (int64_t)(part * (float)(H - L));
+        // (differences of ids and of -1 .. num_nodes, so below 2^32; a row that is not sorted may give anything)
+        const float part = fminf(fmaxf((float)((uint32_t)x - (uint32_t)v_lo) / (float)((uint32_t)v_hi - (uint32_t)v_lo), 0.f), 1.f);
+        p = L + (Pos)(part * (float)(H - L));
       }
       p = min(max(p, L), H - 1);
       // the four entries around p: an aligned group, or the array's last four
-      pos = wide ? min(p & ~(int64_t)3, a.num_entries - 4) : p;
+      pos = wide ? min((Pos)(p & ~(Pos)3), (Pos)(entries - 4)) : p;
     }
 
     // ---- the one read of this iteration ---------------------------------------------------
@@ -222,7 +238,7 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
     // row), it is part of 16 bytes of one array, so all lanes read through one instruction and a
     // trip waits once; reads in branches of their own waited one after the other (47,000 walks of 80
     // nodes on a 4 M-node graph, bound by the chain of reads: 1.78 -> 1.49 ms).
-    int64_t r0 = 0, r1 = 0;
+    Pos r0 = 0, r1 = 0;
     int32_t v = 0;
     Quad quad = {{0, 0, 0, 0}};
     uint32_t e_prob = 0, e_alias = 0;
@@ -238,38 +254,42 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
           from = reinterpret_cast<const char*>(offsets + at);
         }
       } else if (kWeighted && state == kAlias) {
-        const int64_t at = min(pos, a.num_entries - 2);
+        const Pos at = min(pos, (Pos)(entries - 2));
         skip = 2 * (int)(pos - at);
         from = reinterpret_cast<const char*>(packed + at);
       } else {                                // a probe's four entries; a neighbour among four that are aligned likewise
-        const int64_t at = state == kSearch ? pos : min(pos & ~(int64_t)3, a.num_entries - 4);
+        const Pos at = state == kSearch ? pos : min((Pos)(pos & ~(Pos)3), (Pos)(entries - 4));
         skip = (int)(pos - at);
         from = reinterpret_cast<const char*>(nbrs + at);
       }
       quad = *reinterpret_cast<const Quad*>(from);
+      draw_ahead();                           // (while the read is under way)
       const int32_t w0 = skip == 0 ? quad.v[0] : (skip == 1 ? quad.v[1] : (skip == 2 ? quad.v[2] : quad.v[3]));
       const int32_t w1 = skip == 0 ? quad.v[1] : (skip == 1 ? quad.v[2] : quad.v[3]);
       v = w0;
       e_prob = (uint32_t)w0;
       e_alias = (uint32_t)w1;
       if (sizeof(OffT) == 8) {
-        r0 = (int64_t)(((uint64_t)(uint32_t)quad.v[1] << 32) | (uint32_t)quad.v[0]);
-        r1 = (int64_t)(((uint64_t)(uint32_t)quad.v[3] << 32) | (uint32_t)quad.v[2]);
+        r0 = (Pos)(((uint64_t)(uint32_t)quad.v[1] << 32) | (uint32_t)quad.v[0]);
+        r1 = (Pos)(((uint64_t)(uint32_t)quad.v[3] << 32) | (uint32_t)quad.v[2]);
       } else {
         r0 = w0;
         r1 = w1;
       }
-    } else if (state == kSearch) {
-      if (wide) quad = *reinterpret_cast<const Quad*>(nbrs + pos);
-      else quad.v[0] = nbrs[pos];
-    } else if (state == kRow) {
-      r0 = (int64_t)offsets[cur];
-      r1 = (int64_t)offsets[(int64_t)cur + 1];
-    } else if (kWeighted && state == kAlias) {
-      if (packed != nullptr) { const uint2 e = packed[pos]; e_prob = e.x; e_alias = e.y; }
-      else { e_prob = __float_as_uint(a.prob[pos]); e_alias = (uint32_t)a.alias[pos]; }
     } else {
-      v = nbrs[pos];
+      draw_ahead();
+      if (state == kSearch) {
+        if (wide) quad = *reinterpret_cast<const Quad*>(nbrs + pos);
+        else quad.v[0] = nbrs[pos];
+      } else if (state == kRow) {
+        r0 = offsets[cur];
+        r1 = offsets[(int64_t)cur + 1];
+      } else if (kWeighted && state == kAlias) {
+        if (packed != nullptr) { const uint2 e = packed[pos]; e_prob = e.x; e_alias = e.y; }
+        else { e_prob = __float_as_uint(a.prob[pos]); e_alias = (uint32_t)a.alias[pos]; }
+      } else {
+        v = nbrs[pos];
+      }
     }
 
     // ---- consume it: new state, or a decision ----------------------------------------------
@@ -281,7 +301,7 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
         else { decision = kCommit; next = -1; }                    // dead end
         break;
       case kAlias:
-        if (!(unit_float(word2) < __uint_as_float(e_prob))) j = (int64_t)(int32_t)e_alias;
+        if (!(unit_float(word2) < __uint_as_float(e_prob))) j = (Pos)(int32_t)e_alias;
         pos = lo + j;
         state = kDraw;
         break;
@@ -306,7 +326,7 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
       case kSearch: {
         // entries pos + i0 .. pos + i1 of the probe lie in the remaining range [L, H)
         const int width = wide ? 4 : 1;
-        const int i0 = (int)(max(pos, L) - pos), i1 = (int)(min(pos + width, H) - 1 - pos);
+        const int i0 = (int)(max(pos, L) - pos), i1 = (int)(min((Pos)(pos + width), H) - 1 - pos);
         bool found = false;
         int32_t first_v = 0, last_v = 0;
 #pragma unroll
