@@ -18,12 +18,13 @@
 //    binade (at most one per doubling of the sum) are added one by one.
 //
 // Segments of up to kLaneSegment entries are built by one lane each, up to kWaveSegment by one wave
-// in LDS, longer ones (the noise table, the rows of hub nodes) by a workgroup of 1024 lanes.  All are
-// bound by latency, so the limits lie where the next larger team finishes the longest segment sooner.
-// Measured on a 1 M-node graph of 22 M weighted entries: row tables 2.65 ms (lanes 0.29, waves 0.20 +
-// 0.45, workgroups 1.70), against 9.5 ms with one lane per row up to 8191 entries; the noise table of
-// 1 M entries 5.8 ms, against 18.0 ms with the sum and the narrow stretches run by one lane from global
-// memory and 1024 iterations per trip.
+// in LDS, longer ones (the rows of hub nodes) by a workgroup of 1024 lanes; a very long one that is
+// alone in its call (the noise table) gets its sum, its lists and its first rounds from the whole chip.
+// All are bound by latency, so the limits lie where the next larger team finishes the longest segment
+// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 2.5 ms (lanes 0.29, waves
+// 0.20 + 0.45, workgroups 1.56), against 9.5 ms with one lane per row up to 8191 entries; the noise table
+// of 1 M entries 2.8 ms (sum 0.45, lists and 16 rounds 0.27, the rest 2.06 in one workgroup), against 18.0
+// ms in one workgroup whose lane 0 summed the weights and ran the narrow stretches from global memory.
 #include "common.h"
 
 namespace gs {
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __rest
 constexpr int kLongThreads = 1024, kLongWaves = kLongThreads / 64;
 constexpr int kLongItems = 4;                                  // iterations per lane and trip
 constexpr int kLongTrip = kLongThreads * kLongItems;
-constexpr int kSumItems = 8;                                   // consecutive weights per lane of the sum
+constexpr int kSumItems = 16;                                  // consecutive weights per lane of the sum
 constexpr int kSumChunk = 64 * kSumItems;                      // per wave
 constexpr int64_t kNarrow = 512;
 constexpr int kRing = 1024;                                    // list entries kept in LDS
@@ -223,71 +224,103 @@ __device__ __forceinline__ Runs then(const Runs& a, const Runs& b) {
   return r;
 }
 
-// index-order fp64 sum of w[0..n); every lane gets it
-__device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_s, uint32_t* bad_s, double* sum_s) {
+struct __attribute__((packed, aligned(4))) Weight4 { float v[4]; };
+
+// The run of the kSumChunk weights from `at` on (lane l: kSumItems of them), for sums in the binade of
+// exponent e; lane 0 gets it.  false: some weight is negative, not finite or beyond the binade.
+__device__ __forceinline__ bool run_of_chunk(const float* __restrict__ w, int64_t at, int64_t n, int e, Runs& run) {
 #pragma clang fp contract(off)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63;
+  const double per_unit = __longlong_as_double((long long)(uint64_t)(52 - e + 1023) << 52);
+  at += lane * kSumItems;
+  float v[kSumItems];
+  if (at + kSumItems <= n) {
+#pragma unroll
+    for (int q = 0; q < kSumItems / 4; ++q) {
+      const Weight4 x = *reinterpret_cast<const Weight4*>(w + at + 4 * q);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[4 * q + k] = x.v[k];
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kSumItems; ++k) v[k] = at + k < n ? w[at + k] : 0.f;
+  }
+  Runs r = {0, 0};
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < kSumItems; ++k) {
+    const double t = (double)v[k] * per_unit;                  // exact: a power of two
+    if (!(t >= 0.0 && t < 0x1p52)) { bad = true; continue; }
+    const double fl = floor(t), rest = t - fl;
+    const long long whole = (long long)fl;
+    const long long tie = rest == 0.5, up = rest > 0.5;
+    // N + whole + rest, rounded to the nearest whole number, ties to even
+    r.even += whole + (up | (tie & (r.even + whole)));
+    r.odd += whole + (up | (tie & (r.odd + 1 + whole)));
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {                            // lane l: the run of lanes l .. l + d - 1
+    Runs next;
+    next.even = __shfl_down(r.even, d, 64);
+    next.odd = __shfl_down(r.odd, d, 64);
+    r = then(r, next);
+  }
+  run = r;
+  return __ballot(bad) == 0ull;
+}
+
+// kSumChunk weights from `pos` on added to S one by one, by every wave alike
+__device__ __forceinline__ double add_one_by_one(double S, const float* __restrict__ w, int64_t pos, int64_t n) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63;
+  float v[kSumItems];
+#pragma unroll
+  for (int k = 0; k < kSumItems; ++k) v[k] = pos + k * 64 + lane < n ? w[pos + k * 64 + lane] : 0.f;
+#pragma unroll 1
+  for (int k = 0; k < kSumItems; ++k) {        // (+ 0.0 behind the end changes nothing)
+    const double x = (double)v[0];
+#pragma unroll 16
+    for (int l = 0; l < 64; ++l) S += lane_value(x, l);
+#pragma unroll
+    for (int q = 1; q < kSumItems; ++q) v[q - 1] = v[q];
+  }
+  return S;
+}
+
+__device__ __forceinline__ bool sums_by_runs(double S) { return S >= 0x1p-200 && S < 0x1p+200; }
+__device__ __forceinline__ int exponent_of(double S) {
+  return (int)(((uint64_t)__double_as_longlong(S) >> 52) & 2047u) - 1023;
+}
+// S after a run; false (S unchanged): the sum would leave its binade
+__device__ __forceinline__ bool add_run(double& S, const Runs& run) {
+  const int e = exponent_of(S);
+  const double per_unit = __longlong_as_double((long long)(uint64_t)(52 - e + 1023) << 52);
+  const double unit = __longlong_as_double((long long)(uint64_t)(e - 52 + 1023) << 52);
+  const long long N = (long long)(S * per_unit);                // in [2^52, 2^53)
+  const long long more = N + ((N & 1) ? run.odd : run.even);
+  if (more >= (1ll << 53)) return false;
+  S = (double)more * unit;
+  return true;
+}
+
+// index-order fp64 sum of w[0..n); every lane gets it
+__device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_s, uint32_t* bad_s) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double S = 0.0;
   int64_t pos = 0;
   while (pos < n) {
     int taken = 0;                             // waves whose chunk has been added
-    if (S >= 0x1p-200 && S < 0x1p+200) {
-      const int e = (int)(((uint64_t)__double_as_longlong(S) >> 52) & 2047u) - 1023;
-      const double per_unit = __longlong_as_double((long long)(uint64_t)(52 - e + 1023) << 52);
-      const double unit = __longlong_as_double((long long)(uint64_t)(e - 52 + 1023) << 52);
-      const int64_t at = pos + wave * kSumChunk + lane * kSumItems;
-      float v[kSumItems];
-#pragma unroll
-      for (int k = 0; k < kSumItems; ++k) v[k] = at + k < n ? w[at + k] : 0.f;
-      Runs r = {0, 0};
-      bool bad = false;
-#pragma unroll
-      for (int k = 0; k < kSumItems; ++k) {
-        const double t = (double)v[k] * per_unit;              // exact: a power of two
-        if (!(t >= 0.0 && t < 0x1p52)) { bad = true; continue; }
-        const double fl = floor(t), rest = t - fl;
-        const long long whole = (long long)fl;
-        const long long tie = rest == 0.5, up = rest > 0.5;
-        // N + whole + rest, rounded to the nearest whole number, ties to even
-        r.even += whole + (up | (tie & (r.even + whole)));
-        r.odd += whole + (up | (tie & (r.odd + 1 + whole)));
-      }
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {                        // lane l: the run of lanes l .. l + d - 1
-        Runs next;
-        next.even = __shfl_down(r.even, d, 64);
-        next.odd = __shfl_down(r.odd, d, 64);
-        r = then(r, next);
-      }
-      const uint64_t any_bad = __ballot(bad);
-      if (lane == 0) { run_s[wave] = r; bad_s[wave] = any_bad != 0ull; }
+    if (sums_by_runs(S)) {
+      Runs r;
+      const bool good = run_of_chunk(w, pos + wave * kSumChunk, n, exponent_of(S), r);
+      if (lane == 0) { run_s[wave] = r; bad_s[wave] = !good; }
       __syncthreads();
-      long long N = (long long)(S * per_unit);                  // in [2^52, 2^53)
-      for (; taken < kLongWaves; ++taken) {
-        if (bad_s[taken] != 0u) break;
-        const long long more = N + ((N & 1) ? run_s[taken].odd : run_s[taken].even);
-        if (more >= (1ll << 53)) break;
-        N = more;
-      }
-      S = (double)N * unit;
+      while (taken < kLongWaves && bad_s[taken] == 0u && add_run(S, run_s[taken])) ++taken;
       pos += (int64_t)taken * kSumChunk;
     }
-    if (taken < kLongWaves && pos < n) {       // the sum leaves its binade in this chunk (or starts): one by one
-      if (tid == 0) {
-        const int64_t end = min(n, pos + kSumChunk);
-        double run = S;
-        for (int64_t i = pos; i < end; i += 8) {
-          float v[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) v[k] = i + k < end ? w[i + k] : 0.f;
-#pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (i + k < end) run += (double)v[k];
-        }
-        *sum_s = run;
-      }
-      __syncthreads();
-      S = *sum_s;
+    if (taken < kLongWaves && pos < n) {       // the sum leaves its binade in this chunk (or starts)
+      S = add_one_by_one(S, w, pos, n);
       pos += kSumChunk;
     }
     __syncthreads();
@@ -327,6 +360,11 @@ __global__ void alias_find_long_kernel(const OffT* __restrict__ seg_offsets, int
 
 __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+  return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)x));
+}
+
 // The head of a list as one wave keeps it: entries [head, loaded) of the list in a ring in LDS.
 struct Window {
   int32_t* id;
@@ -358,7 +396,283 @@ __device__ __forceinline__ void append(Window& q, int32_t* list, bool mine, int3
   if (in_ring) q.loaded = q.tail;
 }
 
-// long_ids == null: the single segment 0.
+// ---- a single very long segment: its first rounds by the whole chip -------------------------
+// One workgroup moves about one cache line per cycle, which bounds the rounds of hundreds of
+// thousands of iterations a noise table starts with.  A segment that is alone in its call and long
+// enough therefore gets its sum, its lists and its first rounds from launches of many workgroups (a round is
+// two kernels: iterate, then append behind both lists), and the rest from the workgroup kernel.
+// A round that has become narrower than kWideRound is left to that one.
+struct ListState { int64_t sh, st, lh, lt; };
+constexpr int64_t kWideSegment = (int64_t)1 << 17;
+constexpr int64_t kWideRound = 8192;
+static int wide_rounds(int64_t n) { return n < ((int64_t)1 << 22) ? 16 : 48; }
+constexpr int kMostWideRounds = 48;
+
+// The sum in three steps: plain sums of the chunks, their prefix sums (which name the binade that the
+// running sum is in when it reaches a chunk, but for those next to a border), and the run of every
+// chunk for that binade; then one workgroup adds run after run, and one by one where the binade was not
+// the one or is left.
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_wide_chunks_kernel(const OffT* __restrict__ seg_offsets,
+                                                                         const float* __restrict__ weights,
+                                                                         double* __restrict__ chunk_sums) {
+  const int lane = threadIdx.x & 63;
+  const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
+  const int64_t waves = (int64_t)gridDim.x * kLongWaves;
+  for (int64_t c = (int64_t)blockIdx.x * kLongWaves + (threadIdx.x >> 6); c * kSumChunk < n; c += waves) {
+    double sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSumItems; ++k) {
+      const int64_t i = c * kSumChunk + k * 64 + lane;
+      sum += i < n ? (double)weights[begin + i] : 0.0;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) chunk_sums[c] = sum;
+  }
+}
+
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_wide_prefix_kernel(const OffT* __restrict__ seg_offsets,
+                                                                         double* __restrict__ chunk_sums) {
+  __shared__ double part[2][kLongWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t n = (int64_t)seg_offsets[1] - (int64_t)seg_offsets[0], chunks = (n + kSumChunk - 1) / kSumChunk;
+  double carry = 0.0;
+  int turn = 0;
+  for (int64_t base = 0; base < chunks; base += kLongThreads, turn ^= 1) {
+    const int64_t c = base + threadIdx.x;
+    const double own = c < chunks ? chunk_sums[c] : 0.0;
+    double incl = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const double up = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += up;
+    }
+    if (lane == 63) part[turn][wave] = incl;
+    __syncthreads();
+    double before = carry + incl - own;
+#pragma unroll
+    for (int w = 0; w < kLongWaves; ++w) {
+      if (w < wave) before += part[turn][w];
+      carry += part[turn][w];
+    }
+    if (c < chunks) chunk_sums[c] = before;
+  }
+}
+
+struct ChunkRun { Runs run; int e; int good; };
+template <typename OffT>
+__global__ __launch_bounds__(256) void alias_wide_runs_kernel(const OffT* __restrict__ seg_offsets,
+                                                              const float* __restrict__ weights,
+                                                              const double* __restrict__ chunk_sums,
+                                                              ChunkRun* __restrict__ runs) {
+  const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
+  const int64_t waves = (int64_t)gridDim.x * 4;
+  for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c * kSumChunk < n; c += waves) {
+    const double S = chunk_sums[c];
+    ChunkRun x = {{0, 0}, 0, 0};
+    if (sums_by_runs(S)) {
+      x.e = exponent_of(S);
+      x.good = run_of_chunk(weights + begin, c * kSumChunk, n, x.e, x.run) ? 1 : 0;
+    }
+    if ((threadIdx.x & 63) == 0) runs[c] = x;
+  }
+}
+
+template <typename OffT>
+__global__ __launch_bounds__(256) void alias_wide_sum_kernel(const OffT* __restrict__ seg_offsets,
+                                                             const float* __restrict__ weights,
+                                                             const ChunkRun* __restrict__ runs,
+                                                             double* __restrict__ sum_out) {
+  constexpr int kAtOnce = 512;
+  __shared__ ChunkRun run_s[kAtOnce];
+  const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
+  const int64_t chunks = (n + kSumChunk - 1) / kSumChunk;
+  double S = 0.0;
+  for (int64_t base = 0; base < chunks; base += kAtOnce) {
+    __syncthreads();
+    for (int64_t c = base + threadIdx.x; c < min(chunks, base + kAtOnce); c += 256) run_s[c - base] = runs[c];
+    __syncthreads();
+    const int here = (int)min((int64_t)kAtOnce, chunks - base);
+    for (int c = 0; c < here; ++c) {
+      const ChunkRun& x = run_s[c];
+      if (x.good != 0 && sums_by_runs(S) && exponent_of(S) == x.e && add_run(S, x.run)) continue;
+      S = add_one_by_one(S, weights + begin, (base + c) * kSumChunk, n);
+    }
+  }
+  if (threadIdx.x == 0) *sum_out = S;
+}
+
+// sum of counts[0 .. tile), by the whole workgroup
+__device__ __forceinline__ int64_t counts_before(const int32_t* __restrict__ counts, int64_t tile, int64_t* part) {
+  int64_t sum = 0;
+  for (int64_t i = threadIdx.x; i < tile; i += kLongThreads) sum += counts[i];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  sum = 0;
+#pragma unroll
+  for (int w = 0; w < kLongWaves; ++w) sum += part[w];
+  return sum;
+}
+
+// masses, and which entries start as smalls: a bit per entry and a count per tile
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_wide_masses_kernel(const OffT* __restrict__ seg_offsets,
+                                                                         const float* __restrict__ weights,
+                                                                         const double* __restrict__ sum, double* mass_ws,
+                                                                         uint64_t* __restrict__ flags,
+                                                                         int32_t* __restrict__ counts) {
+#pragma clang fp contract(off)
+  __shared__ int32_t tot[kLongWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
+  const double S = *sum, dn = (double)n;
+  for (int64_t tile = blockIdx.x; tile * kLongTrip < n; tile += gridDim.x) {
+    const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
+    int32_t count = 0;
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      const int64_t i = first + c * 64 + lane;
+      const double m = i < n ? (double)weights[begin + i] * dn : 0.0;
+      if (i < n) mass_ws[begin + i] = m;
+      const uint64_t smalls = __ballot(i < n && m < S);
+      if (lane == 0 && first + c * 64 < n) flags[(first >> 6) + c] = smalls;
+      count += __popcll(smalls);
+    }
+    if (lane == 0) tot[wave] = count;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int32_t all = 0;
+#pragma unroll
+      for (int w = 0; w < kLongWaves; ++w) all += tot[w];
+      counts[tile] = all;
+    }
+    __syncthreads();
+  }
+}
+
+// Appends entries 0 .. m - 1 (entry i is i itself, or large_q[lh + i]) behind the smalls or the larges, in
+// order, by their flags; the workgroup with the last tile writes the lists' next state.
+// initial: the lists are empty and the entries are the segment's.
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_wide_append_kernel(const OffT* __restrict__ seg_offsets,
+                                                                         int32_t* small_ws, int32_t* large_ws,
+                                                                         const uint64_t* __restrict__ flags,
+                                                                         const int32_t* __restrict__ counts,
+                                                                         ListState* __restrict__ states, int initial) {
+  __shared__ int64_t part[kLongWaves];
+  __shared__ int32_t tot[kLongWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
+  const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
+  int32_t* small_q = small_ws + begin;
+  int32_t* large_q = large_ws + 2 * begin;
+  ListState at = {0, 0, 0, 0};
+  if (!initial) at = states[0];
+  const int64_t m = initial ? n : min(at.st - at.sh, at.lt - at.lh);
+  if (!initial && m < kWideRound) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) states[1] = at;
+    return;
+  }
+  const int64_t tiles = (m + kLongTrip - 1) / kLongTrip;
+  if (tiles == 0 && blockIdx.x == 0 && threadIdx.x == 0) states[0] = at;     // (an empty segment)
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t before = counts_before(counts, tile, part);
+    const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
+    uint64_t down[kLongItems];
+    int32_t count = 0;
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      down[c] = first + c * 64 < m ? flags[(first >> 6) + c] : 0ull;
+      count += __popcll(down[c]);
+    }
+    if (lane == 0) tot[wave] = count;
+    __syncthreads();
+    int64_t rank = before;
+    int32_t all = 0;
+#pragma unroll
+    for (int w = 0; w < kLongWaves; ++w) {
+      if (w < wave) rank += tot[w];
+      all += tot[w];
+    }
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      const int64_t i = first + c * 64 + lane;
+      const int64_t d = rank + __popcll(down[c] & below);           // flagged entries before i
+      if (i < m) {
+        const int32_t b = initial ? (int32_t)i : large_q[at.lh + i];
+        if ((down[c] >> lane) & 1ull) small_q[at.st + d] = b;
+        else large_q[at.lt + (i - d)] = b;
+      }
+      rank += __popcll(down[c]);
+    }
+    if (tile == tiles - 1 && threadIdx.x == 0) {
+      const int64_t flagged = before + all;
+      ListState next = {at.sh + m, at.st + flagged, at.lh + m, at.lt + (m - flagged)};
+      if (initial) next = {0, flagged, 0, n - flagged};
+      states[initial ? 0 : 1] = next;
+    }
+    __syncthreads();
+  }
+}
+
+// one round: m iterations, which larges became smalls
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_wide_round_kernel(
+    const OffT* __restrict__ seg_offsets, const double* __restrict__ sum, float* __restrict__ prob_out,
+    int32_t* __restrict__ alias_out, double* mass_ws, const int32_t* __restrict__ small_ws,
+    const int32_t* __restrict__ large_ws, uint64_t* __restrict__ flags, int32_t* __restrict__ counts,
+    const ListState* __restrict__ states) {
+#pragma clang fp contract(off)
+  __shared__ int32_t tot[kLongWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t begin = (int64_t)seg_offsets[0];
+  const ListState at = states[0];
+  const int64_t m = min(at.st - at.sh, at.lt - at.lh);
+  if (m < kWideRound) return;
+  const double S = *sum;
+  const int32_t* small_q = small_ws + begin + at.sh;
+  const int32_t* large_q = large_ws + 2 * begin + at.lh;
+  float* prob = prob_out + begin;
+  int32_t* alias = alias_out + begin;
+  double* mass = mass_ws + begin;
+  for (int64_t tile = blockIdx.x; tile * kLongTrip < m; tile += gridDim.x) {
+    const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
+    int32_t count = 0;
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      const int64_t i = first + c * 64 + lane;
+      bool demoted = false;
+      if (i < m) {
+        const int32_t a = small_q[i], b = large_q[i];
+        const double ma = mass[a];
+        const double mb = (mass[b] + ma) - S;
+        prob[a] = (float)(ma / S);
+        alias[a] = b;
+        mass[b] = mb;
+        demoted = mb < S;
+      }
+      const uint64_t down = __ballot(demoted);
+      if (lane == 0 && first + c * 64 < m) flags[(first >> 6) + c] = down;
+      count += __popcll(down);
+    }
+    if (lane == 0) tot[wave] = count;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int32_t all = 0;
+#pragma unroll
+      for (int w = 0; w < kLongWaves; ++w) all += tot[w];
+      counts[tile] = all;
+    }
+    __syncthreads();
+  }
+}
+
+// long_ids == null: the single segment 0; resume != null: whose sum and lists exist already.
 // Scratch per entry of the segment, at the segment's own offsets: mass, the
 // small list (n entries), the large list (2n: appended without wrapping).
 template <typename OffT>
@@ -366,11 +680,10 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
     const OffT* __restrict__ seg_offsets, const int64_t* __restrict__ long_ids,
     const unsigned long long* __restrict__ long_count, const float* __restrict__ weights,
     float* __restrict__ prob_out, int32_t* __restrict__ alias_out, double* mass_ws,
-    int32_t* small_ws, int32_t* large_ws) {
+    int32_t* small_ws, int32_t* large_ws, const ListState* __restrict__ resume, const double* __restrict__ sum) {
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
   __shared__ Runs run_s[kLongWaves];
   __shared__ uint32_t bad_s[kLongWaves];
-  __shared__ double sum_s;
   __shared__ int tot[2][2][kLongWaves];        // (two sets, used in turn: one barrier per use)
   __shared__ int64_t q_s[4];                   // small head/tail, large head/tail after a narrow stretch
   __shared__ int32_t ring_id[2][kRing];
@@ -389,13 +702,16 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
   int32_t* small_q = small_ws + begin;
   int32_t* large_q = large_ws + 2 * begin;
 
-  const double S = ordered_sum(w, n, run_s, bad_s, &sum_s);
+  const double S = resume != nullptr ? *sum : ordered_sum(w, n, run_s, bad_s);
   const double dn = (double)n;
   int turn = 0;
 
   // initial lists, in index order (a wave takes 64 * kLongItems consecutive entries of a trip)
   int64_t sh = 0, st = 0, lh = 0, lt = 0;     // heads and tails, identical in every lane
-  for (int64_t base = 0; base < n; base += kLongTrip, turn ^= 1) {
+  if (resume != nullptr) {
+    sh = resume->sh; st = resume->st; lh = resume->lh; lt = resume->lt;
+  }
+  for (int64_t base = resume != nullptr ? n : 0; base < n; base += kLongTrip, turn ^= 1) {
     const int64_t first = base + wave * (64 * kLongItems) + lane;
     float v[kLongItems];
 #pragma unroll
@@ -431,8 +747,10 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
     const int64_t m = min(st - sh, lt - lh);
     if (m <= 0) break;
     if (m < kNarrow) {
+      const int64_t popped = sh;               // the smalls from here on are taken in this stretch
       if (wave == 0) {
-        Window s = {ring_id[0], ring_mass[0], sh, sh, st}, l = {ring_id[1], ring_mass[1], lh, lh, lt};
+        Window s = {ring_id[0], ring_mass[0], uniform64(sh), uniform64(sh), uniform64(st)};
+        Window l = {ring_id[1], ring_mass[1], uniform64(lh), uniform64(lh), uniform64(lt)};
         while (true) {
           const int64_t both = min(s.tail - s.head, l.tail - l.head);
           if (both <= 0 || both >= 2 * kNarrow) break;
@@ -442,12 +760,10 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
           int32_t b = 0;
           double mb = 0.0;
           if (lane < k) {
-            const int at_s = (int)((s.head + lane) & (kRing - 1)), at_l = (int)((l.head + lane) & (kRing - 1));
+            const int at_s = ((int)s.head + lane) & (kRing - 1), at_l = ((int)l.head + lane) & (kRing - 1);
             const int32_t a = s.id[at_s];
-            const double ma = s.mass[at_s];
             b = l.id[at_l];
-            mb = (l.mass[at_l] + ma) - S;
-            prob[a] = (float)(ma / S);
+            mb = (l.mass[at_l] + s.mass[at_s]) - S;
             alias[a] = b;
             mass[b] = mb;
           }
@@ -463,6 +779,11 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
       }
       __syncthreads();
       sh = q_s[0]; st = q_s[1]; lh = q_s[2]; lt = q_s[3];
+      // (a small's mass does not change once it is one: the divisions are left to all lanes)
+      for (int64_t i = popped + tid; i < sh; i += kLongThreads) {
+        const int32_t a = small_q[i];
+        prob[a] = (float)(mass[a] / S);
+      }
       continue;
     }
     int64_t add_s = 0, add_l = 0;
@@ -536,6 +857,14 @@ struct AliasPlan {
   unsigned long long* long_count;
   int64_t max_long;
   size_t bytes;
+  // a single very long segment only, behind the rest: null in a workspace without room for them
+  double* sum;
+  double* chunk_sums;
+  ChunkRun* runs;
+  ListState* states;
+  uint64_t* flags;
+  int32_t* counts;
+  size_t wide_bytes;
 };
 
 static AliasPlan plan_alias(void* ws, int64_t total_entries) {
@@ -549,16 +878,58 @@ static AliasPlan plan_alias(void* ws, int64_t total_entries) {
   p.long_ids = cv.take<int64_t>((size_t)p.max_long);
   p.long_count = cv.take<unsigned long long>(1);
   p.bytes = cv.used;
+  p.sum = cv.take<double>(1);
+  p.chunk_sums = cv.take<double>(t / kSumChunk + 1);
+  p.runs = cv.take<ChunkRun>(t / kSumChunk + 1);
+  p.states = cv.take<ListState>(kMostWideRounds + 1);
+  p.flags = cv.take<uint64_t>(t / 64 + 1);
+  p.counts = cv.take<int32_t>(t / kLongTrip + 1);
+  p.wide_bytes = cv.used;
   return p;
+}
+
+static bool wide_segment(int64_t num_segments, int64_t total_entries) {
+  return num_segments == 1 && total_entries >= kWideSegment;
+}
+
+template <typename OffT>
+static int32_t launch_alias_wide(const OffT* seg_offsets, int64_t n, const float* weights, float* prob_out,
+                                 int32_t* alias_out, const AliasPlan& p, hipStream_t stream) {
+  const unsigned tiles = (unsigned)min((int64_t)2048, ceil_div(n, kLongTrip));
+  const int64_t chunks = ceil_div(n, kSumChunk);
+  alias_wide_chunks_kernel<OffT><<<(unsigned)min((int64_t)1024, ceil_div(chunks, kLongWaves)), kLongThreads, 0, stream>>>(
+      seg_offsets, weights, p.chunk_sums);
+  alias_wide_prefix_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, p.chunk_sums);
+  alias_wide_runs_kernel<OffT><<<(unsigned)min((int64_t)8192, ceil_div(chunks, 4)), 256, 0, stream>>>(
+      seg_offsets, weights, p.chunk_sums, p.runs);
+  alias_wide_sum_kernel<OffT><<<1, 256, 0, stream>>>(seg_offsets, weights, p.runs, p.sum);
+  alias_wide_masses_kernel<OffT><<<tiles, kLongThreads, 0, stream>>>(seg_offsets, weights, p.sum, p.mass, p.flags, p.counts);
+  alias_wide_append_kernel<OffT><<<tiles, kLongThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags, p.counts,
+                                                                     p.states, 1);
+  GS_LAUNCH_CHECK();
+  const int rounds = wide_rounds(n);
+  const unsigned half = (unsigned)min((int64_t)2048, ceil_div(n / 2 + 1, kLongTrip));      // m is at most half of n
+  for (int r = 0; r < rounds; ++r) {
+    alias_wide_round_kernel<OffT><<<half, kLongThreads, 0, stream>>>(seg_offsets, p.sum, prob_out, alias_out, p.mass,
+                                                                     p.small_q, p.large_q, p.flags, p.counts, p.states + r);
+    alias_wide_append_kernel<OffT><<<half, kLongThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags,
+                                                                      p.counts, p.states + r, 0);
+    GS_LAUNCH_CHECK();
+  }
+  alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, nullptr, nullptr, weights, prob_out, alias_out,
+                                                                p.mass, p.small_q, p.large_q, p.states + rounds, p.sum);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
 }
 
 template <typename OffT>
 static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments, int64_t total_entries,
                                   const float* weights, float* prob_out, int32_t* alias_out,
                                   const AliasPlan& p, hipStream_t stream) {
+  if (p.sum != nullptr) return launch_alias_wide(seg_offsets, total_entries, weights, prob_out, alias_out, p, stream);
   if (num_segments == 1 && total_entries > kWaveSegment) {
     alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(
-        seg_offsets, nullptr, nullptr, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q);
+        seg_offsets, nullptr, nullptr, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q, nullptr, nullptr);
     GS_LAUNCH_CHECK();
     return GS_OK;
   }
@@ -589,7 +960,7 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
     GS_LAUNCH_CHECK();
     alias_build_long_kernel<OffT><<<(unsigned)max_long, kLongThreads, 0, stream>>>(
         seg_offsets, p.long_ids, p.long_count, weights, prob_out, alias_out, p.mass, p.small_q,
-        p.large_q);
+        p.large_q, nullptr, nullptr);
     GS_LAUNCH_CHECK();
   }
   return GS_OK;
@@ -600,9 +971,9 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
 using namespace gs;
 
 extern "C" size_t gs_alias_build_workspace_bytes(int64_t num_segments, int64_t total_entries) {
-  (void)num_segments;
   if (total_entries < 0) return 0;
-  return plan_alias(nullptr, total_entries).bytes;
+  const AliasPlan p = plan_alias(nullptr, total_entries);
+  return wide_segment(num_segments, total_entries) ? p.wide_bytes : p.bytes;
 }
 
 extern "C" int32_t gs_alias_build(const void* seg_offsets, int32_t offset_bits, int64_t num_segments,
@@ -615,6 +986,7 @@ extern "C" int32_t gs_alias_build(const void* seg_offsets, int32_t offset_bits, 
   if (!ws || !aligned(ws, 256)) return GS_EINVAL;
   AliasPlan p = plan_alias(ws, total_entries);
   if (ws_bytes < p.bytes) return GS_EWORKSPACE;
+  if (!wide_segment(num_segments, total_entries) || ws_bytes < p.wide_bytes) p.sum = nullptr;
   // alias[] holds 32-bit positions inside a segment; one segment over everything is the
   // one case the host can see
   if (num_segments == 1 && total_entries > (int64_t)INT32_MAX) return GS_EOVERFLOW;

@@ -1,5 +1,5 @@
 """Alias tables at the sizes where another kernel takes over (one lane up to 32 entries, one wave up
-to 256 and up to 2048, a workgroup beyond), and the index-order sum and the narrow stretches of long
+to 256 and up to 2048, a workgroup beyond, the whole chip for a single segment of 2^17), and the index-order sum and the narrow stretches of long
 segments on weights that make them hard; bit for bit against the sequential construction."""
 import numpy as np
 import pytest
@@ -36,7 +36,7 @@ def test_one_short_segment(oracle, n):
 
 
 @pytest.mark.parametrize("kind", ["ties", "wide", "tenths", "few_small", "two_hubs", "alternating"])
-@pytest.mark.parametrize("n", [2049, 4096, 70_001])
+@pytest.mark.parametrize("n", [2049, 4096, (1 << 17) - 1, 1 << 17, 500_001])
 def test_long_segments(oracle, kind, n):
     rng = np.random.default_rng(n)
     if kind == "ties":              # the running sum's unit is twice the last bit of every further weight
@@ -55,3 +55,19 @@ def test_long_segments(oracle, kind, n):
     else:                           # most iterations turn their large into a small
         w = np.where(np.arange(n) % 3 == 0, 1.5, 0.75).astype(np.float32)
     _check(oracle, np.array([0, n], dtype=np.int64), w)
+
+
+def test_long_segment_in_a_smaller_workspace(oracle):
+    """A workspace of the size that several segments need: the single segment is built by one workgroup."""
+    from paper_2407_15452_amd import binding as gs
+    import ctypes as C
+    n = 200_003
+    w = np.random.default_rng(4).lognormal(0, 1.5, n).astype(np.float32)
+    seg = np.array([0, n], dtype=np.int64)
+    prob, alias = oracle.alias_build(seg, w)
+    size = gs.lib().gs_alias_build_workspace_bytes(C.c_int64(2), C.c_int64(n))
+    assert size < gs.lib().gs_alias_build_workspace_bytes(C.c_int64(1), C.c_int64(n))
+    a = gs.gs_alias_build(torch.as_tensor(seg).to(DEV), torch.as_tensor(w).to(DEV),
+                          ws=torch.empty(size, dtype=torch.uint8, device=DEV))
+    np.testing.assert_array_equal(a.alias.cpu().numpy(), alias)
+    np.testing.assert_array_equal(a.prob.cpu().numpy(), prob)
