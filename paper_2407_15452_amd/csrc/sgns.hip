@@ -1358,7 +1358,7 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, i
 }
 
 // ---- large batches: the context-table terms as sorted records -------------------------------
-// With millions of terms the counters cost more than a sort: a random atomic per term in the forward
+// With many terms the counters cost more than a sort: a random atomic per term in the forward
 // kernel, and in the place kernel a random read and a random 16-byte write per term, all of them whole
 // cache lines.  The forward kernel writes each term as a record (row; source row, coefficient)
 // instead, three or four passes of the radix sort bring the records into row order in streams, and
@@ -1826,14 +1826,20 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
   return p;
 }
 
-// Batches of at least this many terms take the sorted records.  Measured, counters against records: 2.4
-// million terms (300,007 pairs, 7 negatives, 200 fp16 columns on 778 k nodes) 775 / 786 us, 11 million (1 M
-// pairs, 10 negatives, 256 bf16 columns on 4 M nodes) 3000 / 2552, 12 million (2 M pairs, 5 negatives, 128 fp32
-// columns on 4 M nodes) 2606 / 2407, negatives and the rest of the step included.
-constexpr int64_t kSortedMinTerms = (int64_t)1 << 22;
-// Sorted terms per wave of the update (the ends of a slice cost four loads of keys: 256 against 128
-// terms, 2407 / 2425 us in the last case above).
-constexpr int kSortedSlice = 256;
+// Batches of at least this many terms take the sorted records: fewer where two passes sort them (up to
+// 2^16 rows), because few rows also mean busy counters.  Measured, counters against records, 5 negatives
+// drawn with some skew: 60 k rows of 128 fp32 columns, 0.48 million terms 173 / 163 us, 3.6 million 693 /
+// 635; 30 k rows, 0.24 million 103 / 109, 0.48 million 144 / 142; 10 k rows of 64, 0.24 million 79 / 86, 0.48
+// million 122 / 106, 3.6 million 680 / 415; 100 k rows of 128 (three passes), 1.8 million 358 / 409, 3.6 million
+// 695 / 722; 1 M rows, 1.8 million 571 / 607, 3.6 million 929 / 921; 500 k rows of 256 bf16 columns, 3.3 million
+// 865 / 799; 4 M rows, negatives and the rest of the step included: 11 million (256 bf16 columns) 3000 / 2552, 12
+// million 2606 / 2407.
+constexpr int64_t kSortedMinTerms = (int64_t)1 << 22, kSortedMinTermsTwoPasses = (int64_t)1 << 19;
+// Sorted terms per wave of the update: the ends of a slice cost four loads of keys (256 against 128 terms:
+// 2407 / 2425 us in the last case above), and a short batch has to make enough waves.
+static int sorted_slice_for(int64_t num_terms) {
+  return num_terms >= ((int64_t)1 << 22) ? 256 : (num_terms >= ((int64_t)1 << 20) ? 128 : 32);
+}
 
 static int bits_for_rows(int64_t num_nodes) {
   int b = 1;
@@ -1873,7 +1879,10 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
   p.bytes = cv.used;
   return p;
 }
-static bool sorted_batch(int64_t num_pairs, int32_t k) { return num_pairs * (int64_t)(k + 1) >= kSortedMinTerms; }
+static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
+  const bool two_passes = radix_sort_passes(bits_for_rows(num_nodes)) <= 2;
+  return num_pairs * (int64_t)(k + 1) >= (two_passes ? kSortedMinTermsTwoPasses : kSortedMinTerms);
+}
 
 // Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every
 // workgroup of its update kernel reads all of them, so its time grows with the ids (about 0.8 us
@@ -1914,7 +1923,7 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
     p = plan_small(ws, num_pairs, k, dim, dtype);
     if (p.bytes + extra <= ws_bytes) return true;
   }
-  if (sorted_batch(num_pairs, k)) {
+  if (sorted_batch(num_pairs, num_nodes, k)) {
     p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
     if (p.bytes + extra <= ws_bytes) return true;
   }
@@ -1924,7 +1933,7 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
 static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
   if (small_batch(num_pairs, k, dim, dtype)) bytes = max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
-  if (sorted_batch(num_pairs, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  if (sorted_batch(num_pairs, num_nodes, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
   return bytes;
 }
 
@@ -2339,7 +2348,7 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   a.stage_rank = p.stage_rank;
   a.stage_delta = p.stage_delta;
   a.chunk_pairs = p.small ? kSmallChunkPairs : chunk_pairs_for(num_pairs);
-  a.slice_terms = p.by_sort ? kSortedSlice : slice_terms_for(num_pairs);
+  a.slice_terms = p.by_sort ? sorted_slice_for(a.num_terms) : slice_terms_for(num_pairs);
   a.loss_partials = p.loss_partials;
   a.forward_blocks = p.small ? small_forward_blocks(num_pairs) : forward_blocks_for(num_pairs);
   a.forward_blocks_per_xcd = ceil_div(a.forward_blocks, 8);
@@ -2555,7 +2564,7 @@ extern "C" size_t gs_line1_step_workspace_bytes(int64_t num_pairs, int64_t num_n
                                                 int32_t dim, int32_t dtype) {
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  if (sorted_batch(num_pairs, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  if (sorted_batch(num_pairs, num_nodes, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
   return bytes + line1_snap_bytes(num_pairs, dim, dtype) + line1_slot_bytes(num_pairs);
 }
 
@@ -2569,8 +2578,8 @@ extern "C" int32_t gs_line1_step(void* w, int64_t num_nodes, int32_t dim, int32_
   if (bad != GS_OK) return bad;
   const size_t snap_bytes = line1_snap_bytes(num_pairs, dim, dtype), own_bytes = snap_bytes + line1_slot_bytes(num_pairs);
   SgnsPlan p;
-  if (sorted_batch(num_pairs, k)) p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
-  if (!sorted_batch(num_pairs, k) || ws_bytes < p.bytes + own_bytes) p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
+  if (sorted_batch(num_pairs, num_nodes, k)) p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
+  if (!sorted_batch(num_pairs, num_nodes, k) || ws_bytes < p.bytes + own_bytes) p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
   if (ws_bytes < p.bytes + own_bytes) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
