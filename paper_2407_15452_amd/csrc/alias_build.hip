@@ -21,9 +21,9 @@
 // in LDS, longer ones (the rows of hub nodes) by a workgroup of 1024 lanes; a very long one that is
 // alone in its call (the noise table) gets its sum, its lists and its first rounds from the whole chip.
 // All are bound by latency, so the limits lie where the next larger team finishes the longest segment
-// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 2.5 ms (lanes 0.29, waves
-// 0.20 + 0.45, workgroups 1.56), against 9.5 ms with one lane per row up to 8191 entries; the noise table
-// of 1 M entries 2.8 ms (sum 0.45, lists and 16 rounds 0.27, the rest 2.06 in one workgroup), against 18.0
+// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 2.4 ms (lanes 0.29, waves
+// 0.20 + 0.45, workgroups 1.46), against 9.5 ms with one lane per row up to 8191 entries; the noise table
+// of 1 M entries 2.5 ms (sum 0.45, lists and 16 rounds 0.28, the rest 1.75 in one workgroup), against 18.0
 // ms in one workgroup whose lane 0 summed the weights and ran the narrow stretches from global memory.
 #include "common.h"
 
@@ -332,15 +332,19 @@ __device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_
 // are the wave's totals; returns the totals of the waves before, and all of them
 __device__ __forceinline__ void block_before(int c0, int c1, int (*tot)[kLongWaves], int& before0, int& before1,
                                              int& all0, int& all1) {
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if ((threadIdx.x & 63) == 0) { tot[0][wave] = c0; tot[1][wave] = c1; }
   __syncthreads();
+  int v0[kLongWaves], v1[kLongWaves];
+#pragma unroll
+  for (int v = 0; v < kLongWaves; ++v) { v0[v] = tot[0][v]; v1[v] = tot[1][v]; }
   before0 = before1 = all0 = all1 = 0;
 #pragma unroll
   for (int v = 0; v < kLongWaves; ++v) {
-    if (v < wave) { before0 += tot[0][v]; before1 += tot[1][v]; }
-    all0 += tot[0][v];
-    all1 += tot[1][v];
+    before0 += v < wave ? v0[v] : 0;
+    before1 += v < wave ? v1[v] : 0;
+    all0 += v0[v];
+    all1 += v1[v];
   }
 }
 
@@ -374,10 +378,19 @@ struct Window {
 __device__ __forceinline__ void refill(Window& q, const int32_t* list, const double* mass, int lane) {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");       // what this wave appended has to be there
   const int64_t end = min(q.tail, q.head + kRing);
-  for (int64_t i = q.loaded + lane; i < end; i += 64) {
-    const int32_t x = list[i];
-    q.id[i & (kRing - 1)] = x;
-    q.mass[i & (kRing - 1)] = mass[x];
+  int32_t x[kRing / 64];                       // (entries behind the end: the last one again, so that no read waits in a branch)
+  double m[kRing / 64];
+#pragma unroll
+  for (int c = 0; c < kRing / 64; ++c) x[c] = list[min(q.loaded + c * 64 + lane, end - 1)];
+#pragma unroll
+  for (int c = 0; c < kRing / 64; ++c) m[c] = mass[x[c]];
+#pragma unroll
+  for (int c = 0; c < kRing / 64; ++c) {
+    const int64_t i = q.loaded + c * 64 + lane;
+    if (i < end) {
+      q.id[i & (kRing - 1)] = x[c];
+      q.mass[i & (kRing - 1)] = m[c];
+    }
   }
   q.loaded = end;
   wave_fence();
@@ -643,20 +656,29 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_round_kernel(
   for (int64_t tile = blockIdx.x; tile * kLongTrip < m; tile += gridDim.x) {
     const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
     int32_t count = 0;
+    int32_t a[kLongItems], b[kLongItems];
+    double ma[kLongItems], mb[kLongItems];
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {                      // (behind the end: the last one again, read but not used)
+      const int64_t i = min(first + c * 64 + lane, m - 1);
+      a[c] = small_q[i];
+      b[c] = large_q[i];
+    }
 #pragma unroll
     for (int c = 0; c < kLongItems; ++c) {
-      const int64_t i = first + c * 64 + lane;
-      bool demoted = false;
-      if (i < m) {
-        const int32_t a = small_q[i], b = large_q[i];
-        const double ma = mass[a];
-        const double mb = (mass[b] + ma) - S;
-        prob[a] = (float)(ma / S);
-        alias[a] = b;
-        mass[b] = mb;
-        demoted = mb < S;
+      ma[c] = mass[a[c]];
+      mb[c] = mass[b[c]];
+    }
+#pragma unroll
+    for (int c = 0; c < kLongItems; ++c) {
+      const bool valid = first + c * 64 + lane < m;
+      mb[c] = (mb[c] + ma[c]) - S;
+      if (valid) {
+        prob[a[c]] = (float)(ma[c] / S);
+        alias[a[c]] = b[c];
+        mass[b[c]] = mb[c];
       }
-      const uint64_t down = __ballot(demoted);
+      const uint64_t down = __ballot(valid && mb[c] < S);
       if (lane == 0 && first + c * 64 < m) flags[(first >> 6) + c] = down;
       count += __popcll(down);
     }
@@ -792,16 +814,15 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
       int32_t a[kLongItems], b[kLongItems];
       double ma[kLongItems], mb[kLongItems];
 #pragma unroll
-      for (int c = 0; c < kLongItems; ++c) {
-        const bool valid = first + c * 64 < m;
-        a[c] = valid ? small_q[sh + first + c * 64] : 0;
-        b[c] = valid ? large_q[lh + first + c * 64] : 0;
+      for (int c = 0; c < kLongItems; ++c) {                   // (behind the end: the last one again, read but not used)
+        const int64_t i = min(first + c * 64, m - 1);
+        a[c] = small_q[sh + i];
+        b[c] = large_q[lh + i];
       }
 #pragma unroll
       for (int c = 0; c < kLongItems; ++c) {
-        const bool valid = first + c * 64 < m;
-        ma[c] = valid ? mass[a[c]] : 0.0;
-        mb[c] = valid ? mass[b[c]] : 0.0;
+        ma[c] = mass[a[c]];
+        mb[c] = mass[b[c]];
       }
       uint64_t down[kLongItems], stay[kLongItems];
       int cd = 0, cs = 0;
