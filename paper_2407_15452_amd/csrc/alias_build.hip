@@ -21,9 +21,9 @@
 // in LDS, longer ones (the rows of hub nodes) by a workgroup of 1024 lanes; a very long one that is
 // alone in its call (the noise table) gets its sum, its lists and its first rounds from the whole chip.
 // All are bound by latency, so the limits lie where the next larger team finishes the longest segment
-// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 2.4 ms (lanes 0.29, waves
-// 0.20 + 0.45, workgroups 1.46), against 9.5 ms with one lane per row up to 8191 entries; the noise table
-// of 1 M entries 2.5 ms (sum 0.45, lists and 16 rounds 0.28, the rest 1.75 in one workgroup), against 18.0
+// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 1.9 ms (lanes 0.29, waves
+// 0.20 + 0.45, workgroups 0.92), against 9.5 ms with one lane per row up to 8191 entries; the noise table
+// of 1 M entries 2.5 ms (sum 0.45, lists and 16 rounds 0.28, the rest 1.77 in one workgroup), against 18.0
 // ms in one workgroup whose lane 0 summed the weights and ran the narrow stretches from global memory.
 #include "common.h"
 
@@ -96,12 +96,6 @@ __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict_
     prob[i] = 1.0f;
     alias[i] = i;
   }
-}
-
-// LDS accesses of one wave complete in order; this keeps the compiler from moving them
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ double lane_value(double v, int lane) {
@@ -269,7 +263,7 @@ __device__ __forceinline__ bool run_of_chunk(const float* __restrict__ w, int64_
   return __ballot(bad) == 0ull;
 }
 
-// kSumChunk weights from `pos` on added to S one by one, by every wave alike
+// kSumChunk weights from `pos` on added to S one by one, by a wave
 __device__ __forceinline__ double add_one_by_one(double S, const float* __restrict__ w, int64_t pos, int64_t n) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
@@ -304,7 +298,7 @@ __device__ __forceinline__ bool add_run(double& S, const Runs& run) {
 }
 
 // index-order fp64 sum of w[0..n); every lane gets it
-__device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_s, uint32_t* bad_s) {
+__device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_s, uint32_t* bad_s, double* sum_s) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double S = 0.0;
@@ -320,7 +314,12 @@ __device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_
       pos += (int64_t)taken * kSumChunk;
     }
     if (taken < kLongWaves && pos < n) {       // the sum leaves its binade in this chunk (or starts)
-      S = add_one_by_one(S, w, pos, n);
+      if (wave == 0) {                         // (all waves at once would share the issue slots)
+        S = add_one_by_one(S, w, pos, n);
+        if (lane == 0) *sum_s = S;
+      }
+      __syncthreads();
+      S = *sum_s;
       pos += kSumChunk;
     }
     __syncthreads();
@@ -706,6 +705,7 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
   __shared__ Runs run_s[kLongWaves];
   __shared__ uint32_t bad_s[kLongWaves];
+  __shared__ double sum_s;
   __shared__ int tot[2][2][kLongWaves];        // (two sets, used in turn: one barrier per use)
   __shared__ int64_t q_s[4];                   // small head/tail, large head/tail after a narrow stretch
   __shared__ int32_t ring_id[2][kRing];
@@ -724,7 +724,7 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
   int32_t* small_q = small_ws + begin;
   int32_t* large_q = large_ws + 2 * begin;
 
-  const double S = resume != nullptr ? *sum : ordered_sum(w, n, run_s, bad_s);
+  const double S = resume != nullptr ? *sum : ordered_sum(w, n, run_s, bad_s, &sum_s);
   const double dn = (double)n;
   int turn = 0;
 

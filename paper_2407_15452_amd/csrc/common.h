@@ -119,6 +119,12 @@ __device__ __forceinline__ int64_t table_draw(const float* __restrict__ prob,
   return s;
 }
 
+// LDS accesses of one wave complete in order; this keeps the compiler from moving them
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // 16-bit storage formats of the embedding tables.  lo / hi widen the two halves of a
 // 32-bit word exactly; round() gives the 16 bits nearest to an fp32 value (ties to even).
 struct bf16_t {

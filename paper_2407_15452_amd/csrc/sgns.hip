@@ -1516,12 +1516,6 @@ __device__ __forceinline__ uint32_t small_home(uint32_t key) {
   return (small_hash(key) >> (32 - kSmallBlockBits - kSmallSlotBits)) & (uint32_t)(kSmallSlots - 1);
 }
 
-// LDS accesses of one wave complete in order; this keeps the compiler from moving them
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // The row of `key`, summed by the whole workgroup: every wave picks the key's entries out of its
 // share of the ids, 64 at a time, and adds their source rows; the waves' sums meet in row_acc.
 template <typename T, int WPP, int UB, bool kStage>
