@@ -231,10 +231,13 @@ int32_t gs_sample_edges(const gs_csr* g, const gs_alias* edge_alias, int64_t num
  *   reaches 16384 in magnitude (the exact accumulation of the row sums covers
  *   products below 32768).  The row sums are exact (64-bit fixed point, multiples
  *   of 2^-36), so the same call on the same inputs gives the same bits every
- *   time.  The workspace holds the per-term coefficients, the terms regrouped by
- *   destination row, a counter per key (two per node, or per key of the batch
- *   when the graph is much larger than the batch), a side buffer for rows with
- *   many terms and the staged centre-row gradients.
+ *   time.  The workspace holds the staged centre-row gradients and, by the size
+ *   of the batch: the per-term coefficients and copies of the centre rows (at
+ *   most 49,152 ids); or the coefficients, the terms regrouped by destination
+ *   row, a counter per key (two per node, or per key of the batch when the graph
+ *   is much larger than the batch) and a side buffer for rows with many terms; or
+ *   the terms as records in two sort buffers and the side buffer (2^22 terms and
+ *   more, 2^19 on at most 2^16 nodes).
  * ------------------------------------------------------------------------ */
 size_t gs_sgns_step_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim,
                                     int32_t dtype);
@@ -251,8 +254,8 @@ int32_t gs_sgns_step(void* w_in, void* w_out, int64_t num_nodes, int32_t dim, in
  * every GPU (held until the process ends); the call allocates and frees nothing.
  *   Same arguments (without ws, ws_bytes), results and errors as gs_sgns_step,
  *   for small batches: num_pairs <= 4096, num_pairs * (k+1) <= 65536, dim <=
- *   256; GS_EWORKSPACE beyond that.  The graph may have any size (the step
- *   counts over a table of the batch's keys).
+ *   256; GS_EWORKSPACE beyond that.  The graph may have any size (nothing in the
+ *   array has the size of the graph).
  *   All calls on one GPU share that GPU's array: calls that overlap in time on
  *   one GPU (two streams, two threads) race; one call at a time per GPU.  The
  *   first call on a device looks the array's address up (hipGetSymbolAddress)
@@ -273,8 +276,9 @@ int32_t gs_sgns_step_static(void* w_in, void* w_out, int64_t num_nodes, int32_t 
  *   gradient = gradient of the batch's summed loss at the pre-iteration model
  *   (the same terms gs_sgns_step applies).  m_in, m_out: momentum tables, same
  *   shape and dtype as w_in, w_out, distinct from them, updated in place.
- *   Unlike gs_sgns_step this streams over all four tables once or twice per
- *   call (two dense passes), as the paper's formulation does.
+ *   Unlike gs_sgns_step this streams over all four tables, as the paper's
+ *   formulation does (every row is read and written once; twice for momentum
+ *   rows where batch and tables are small).
  *   Workspace: gs_sgns_step_workspace_bytes().  Other arguments and errors as
  *   for gs_sgns_step.
  * ------------------------------------------------------------------------ */

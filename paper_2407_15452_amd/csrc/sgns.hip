@@ -57,6 +57,7 @@
 // draws the negatives in the forward kernel; the one-table step (first-order
 // LINE) reads the input rows in the update kernel from copies the forward kernel
 // kept, because that kernel then writes rows of the table it would read.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <type_traits>
@@ -1926,8 +1927,8 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
 }
 static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  if (small_batch(num_pairs, k, dim, dtype)) bytes = max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
-  if (sorted_batch(num_pairs, num_nodes, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  if (small_batch(num_pairs, k, dim, dtype)) bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
+  if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
   return bytes;
 }
 
@@ -2558,7 +2559,7 @@ extern "C" size_t gs_line1_step_workspace_bytes(int64_t num_pairs, int64_t num_n
                                                 int32_t dim, int32_t dtype) {
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  if (sorted_batch(num_pairs, num_nodes, k)) bytes = max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
   return bytes + line1_snap_bytes(num_pairs, dim, dtype) + line1_slot_bytes(num_pairs);
 }
 

@@ -101,3 +101,14 @@ def test_static_step_rejects_oversized_batches_on_the_host(lib):
     assert call(4097, 5, 128) == -2
     assert call(4096, 16, 128) == -2            # 4096 * 17 terms > 65536
     assert call(1024, 5, 260) == -2
+
+
+def test_workspace_sizes_beyond_two_gigabytes(lib):
+    """Sizes are size_t all the way: a batch whose staged rows alone take more than 2^31 bytes."""
+    for fn in (lib.gs_sgns_step_workspace_bytes, lib.gs_sgns_step_fused_workspace_bytes,
+               lib.gs_sgns_step_from_walks_workspace_bytes, lib.gs_line1_step_workspace_bytes):
+        for pairs, nodes, k, dim in ((2_000_000, 25_000_000, 10, 256), (4_000_000, 100_000_000, 5, 128),
+                                     (3_000_000, 50_000, 1, 256)):
+            staged = pairs * dim * 4
+            size = fn(C.c_int64(pairs), C.c_int64(nodes), C.c_int32(k), C.c_int32(dim), C.c_int32(1))
+            assert staged < size < 8 * staged
