@@ -256,15 +256,12 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
         if (sizeof(OffT) == 8) {
           from = reinterpret_cast<const char*>(offsets + cur);
         } else {                              // (the last rows' bounds are the tail of the last 16 bytes)
-          // Two neighbouring entries of four that lie in one cache line wherever the two do, likewise for alias
-          // entries: started at the entry itself one read in eight touches a second line, which costs launches
-          // that are bound by lines, not by latency (4 M walks on 140 M entries: 22.7 ms, 24.0 otherwise).
-          const int32_t at = min((cur & 3) == 3 ? cur - 1 : cur & ~3, (int32_t)(a.num_nodes - 3));
+          const int32_t at = min(cur, (int32_t)(a.num_nodes - 3));
           skip = cur - at;
           from = reinterpret_cast<const char*>(offsets + at);
         }
       } else if (kWeighted && state == kAlias) {
-        const Pos at = min((Pos)(pos & ~(Pos)1), (Pos)(entries - 2));
+        const Pos at = min(pos, (Pos)(entries - 2));
         skip = 2 * (int)(pos - at);
         from = reinterpret_cast<const char*>(packed + at);
       } else {                                // a probe's four entries; a neighbour among four that are aligned likewise
