@@ -338,9 +338,11 @@ static int32_t radix_pass(const K* keys, const V* vals, K* keys_out, V* vals_out
 constexpr int kSortItemsLarge = 16, kSortItemsSmall = 4;
 constexpr int64_t kSortLarge = (int64_t)1 << 21;
 
+// (never less than a shorter sort takes: a caller's workspace for its largest batch serves every batch)
 size_t radix_sort_scratch_bytes(int64_t n) {
-  const int64_t items = n >= kSortLarge ? kSortItemsLarge : kSortItemsSmall;
-  const size_t tiles = (size_t)ceil_div(n > 0 ? n : 1, kSortThreads * items);
+  const int64_t small = max((int64_t)1, min(n, kSortLarge - 1));
+  const size_t tiles = (size_t)max(ceil_div(small, kSortThreads * kSortItemsSmall),
+                                   n >= kSortLarge ? ceil_div(n, kSortThreads * kSortItemsLarge) : (int64_t)0);
   return align_up(tiles * kDigits * sizeof(uint32_t)) + align_up(kDigits * sizeof(uint32_t));
 }
 

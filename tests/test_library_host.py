@@ -112,3 +112,16 @@ def test_workspace_sizes_beyond_two_gigabytes(lib):
             staged = pairs * dim * 4
             size = fn(C.c_int64(pairs), C.c_int64(nodes), C.c_int32(k), C.c_int32(dim), C.c_int32(1))
             assert staged < size < 8 * staged
+
+
+def test_workspace_for_many_records_serves_fewer(lib):
+    """The sort takes larger tiles from 2^21 records on; what is asked for does not fall there."""
+    queries = [lambda n: lib.gs_sort_pairs_workspace_bytes(C.c_int64(n)),
+               lambda n: lib.gs_unique_ids_workspace_bytes(C.c_int64(n), C.c_int64(2_000_000_000)),
+               lambda n: lib.gs_csr_build_workspace_bytes(C.c_int64(n), C.c_int64(1000), C.c_uint32(0)),
+               lambda n: lib.gs_csr_build_workspace_bytes(C.c_int64(n // 2), C.c_int64(1000), C.c_uint32(1))]
+    sizes = sorted({max(1, (1 << 21) + d) for d in (-200_000, -4096, -2049, -2, -1, 0, 1, 2048, 8193, 1 << 21, 3 << 21)}
+                   | {1, 2047, 2048, 2049, 100_000, 1 << 28})
+    for query in queries:
+        got = [query(n) for n in sizes]
+        assert got == sorted(got) and got[0] > 0
