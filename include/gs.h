@@ -20,6 +20,10 @@
  *  - Calls that need scratch memory take (ws, ws_bytes); the matching
  *    *_workspace_bytes() function (host, O(1)) returns the size to provide.
  *    ws must be 256-byte aligned.  Its contents are undefined afterwards.
+ *    gs_alias_build and the training steps have more than one way of doing
+ *    their work and report what the largest takes; with less, down to what the
+ *    general way takes, they use that one (the same tables bit for bit, in
+ *    more time), and return GS_EWORKSPACE below it.
  *  - Return value: GS_OK or a negative gs_status.  Arguments are validated on
  *    the host only; nothing is enqueued when a call fails validation.  Node
  *    ids live in device memory and are checked by the kernels that use them as
@@ -48,7 +52,7 @@ extern "C" {
 typedef enum {
   GS_OK = 0,
   GS_EINVAL = -1,     /* null / negative / misaligned / unsupported argument      */
-  GS_EWORKSPACE = -2, /* ws_bytes smaller than *_workspace_bytes() reports        */
+  GS_EWORKSPACE = -2, /* ws_bytes too small: see *_workspace_bytes()              */
   GS_EOVERFLOW = -3,  /* a count does not fit the chosen index type               */
   GS_EHIP = -4        /* a HIP runtime call failed; see gs_last_hip_error()       */
 } gs_status;

@@ -1910,11 +1910,14 @@ static SgnsPlan plan_small(void* ws, int64_t num_pairs, int32_t k, int32_t dim, 
 }
 
 // The plan of a step in a workspace of ws_bytes, of which the call's own arrays take `extra` bytes
-// behind the plan: the two-launch step where the batch is small, the sorted records where it is
-// large, and the counters in between and in a workspace that holds no more than their plan.
+// behind the plan; false: too small.  Every call needs room for the counters' plan, whatever its
+// batch takes; with more room, the two-launch step where the batch is small (two_launches: the call can take
+// it) and the sorted records where it is large.
 static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int64_t num_pairs, int64_t num_nodes,
-                      int32_t k, int32_t dim, int32_t dtype, bool force_compact = false) {
-  if (small_batch(num_pairs, k, dim, dtype)) {
+                      int32_t k, int32_t dim, int32_t dtype, bool two_launches = true, bool force_compact = false) {
+  const SgnsPlan counters = plan_sgns(ws, num_pairs, num_nodes, k, dim, force_compact);
+  if (counters.bytes + extra > ws_bytes) return false;
+  if (two_launches && small_batch(num_pairs, k, dim, dtype)) {
     p = plan_small(ws, num_pairs, k, dim, dtype);
     if (p.bytes + extra <= ws_bytes) return true;
   }
@@ -1922,8 +1925,8 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
     p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
     if (p.bytes + extra <= ws_bytes) return true;
   }
-  p = plan_sgns(ws, num_pairs, num_nodes, k, dim, force_compact);
-  return p.bytes + extra <= ws_bytes;
+  p = counters;
+  return true;
 }
 static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
@@ -2443,7 +2446,7 @@ extern "C" int32_t gs_sgns_step_static(void* w_in, void* w_out, int64_t num_node
                                       num_pairs, k, loss_sum_out, ws);
   if (bad != GS_OK) return bad;
   SgnsPlan p;
-  if (!plan_step(p, ws, kStaticScratchBytes, 0, num_pairs, num_nodes, k, dim, dtype, true)) return GS_EWORKSPACE;
+  if (!plan_step(p, ws, kStaticScratchBytes, 0, num_pairs, num_nodes, k, dim, dtype, true, true)) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -2573,9 +2576,7 @@ extern "C" int32_t gs_line1_step(void* w, int64_t num_nodes, int32_t dim, int32_
   if (bad != GS_OK) return bad;
   const size_t snap_bytes = line1_snap_bytes(num_pairs, dim, dtype), own_bytes = snap_bytes + line1_slot_bytes(num_pairs);
   SgnsPlan p;
-  if (sorted_batch(num_pairs, num_nodes, k)) p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
-  if (!sorted_batch(num_pairs, num_nodes, k) || ws_bytes < p.bytes + own_bytes) p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-  if (ws_bytes < p.bytes + own_bytes) return GS_EWORKSPACE;
+  if (!plan_step(p, ws, ws_bytes, own_bytes, num_pairs, num_nodes, k, dim, dtype, false)) return GS_EWORKSPACE;
   if (num_pairs == 0) {
     zero_double_kernel<<<1, 1, 0, stream>>>(loss_sum_out);
     GS_LAUNCH_CHECK();
@@ -2608,11 +2609,10 @@ extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, vo
   if (m_in == w_in || m_in == w_out || m_out == w_in || m_out == w_out || m_in == m_out)
     return GS_EINVAL;
   SgnsPlan p;
-  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;   // (the counters' plan fits too)
+  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
   const int64_t table_bytes = num_nodes * (int64_t)dim * (dtype == GS_F32 ? 4 : 2);
   if (num_pairs > 0 && !(p.small && table_bytes <= kSeparatePassBytes)) {
-    p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-    if (p.bytes > ws_bytes) return GS_EWORKSPACE;
+    p = plan_sgns(ws, num_pairs, num_nodes, k, dim);       // (fits: every plan_step needs it to)
     SgnsExtras x;
     x.opt = kMomentum;
     x.rates.decay1 = mu;

@@ -125,3 +125,25 @@ def test_workspace_for_many_records_serves_fewer(lib):
     for query in queries:
         got = [query(n) for n in sizes]
         assert got == sorted(got) and got[0] > 0
+
+
+@pytest.mark.parametrize("pairs,nodes", [(1000, 1_000_000), (800_000, 3_000_000)])
+def test_workspace_below_the_counters_plan_is_refused(lib, pairs, nodes):
+    """Batches for which the counters' plan is the largest of those that the step may take (a small one, and one
+    whose terms are sorted): with less, no call starts, whatever else would fit.  Nothing is enqueued."""
+    k, dim, t = 5, 8, [C.c_void_p(256 * i) for i in range(1, 8)]
+    n, b, dims = C.c_int64(nodes), C.c_int64(pairs), (C.c_int32(k), C.c_int32(dim), C.c_int32(0))
+    lr, zero, null = C.c_float(0.1), C.c_uint64(0), None
+    size = lambda fn: C.c_size_t(fn(b, n, *dims) - 256)  # noqa: E731
+    table = (n, C.c_int32(dim), C.c_int32(0))
+    assert lib.gs_sgns_step(t[0], t[1], *table, t[2], t[3], t[4], b, dims[0], lr, t[5], t[6],
+                            size(lib.gs_sgns_step_workspace_bytes), null) == -2
+    assert lib.gs_sgns_momentum_step(t[0], t[1], t[2], t[3], *table, t[2], t[3], t[4], b, dims[0], lr, lr, t[5], t[6],
+                                     size(lib.gs_sgns_step_workspace_bytes), null) == -2
+    assert lib.gs_sgns_step_fused(t[0], t[1], *table, t[2], t[3], b, null, zero, zero, dims[0], lr, t[5], t[6],
+                                  size(lib.gs_sgns_step_fused_workspace_bytes), null) == -2
+    assert lib.gs_sgns_step_from_walks(t[0], t[1], *table, t[2], C.c_int64(10), C.c_int32(5), C.c_int32(2), t[3],
+                                       C.c_int64(0), b, null, zero, zero, dims[0], lr, t[5], t[6],
+                                       size(lib.gs_sgns_step_from_walks_workspace_bytes), null) == -2
+    assert lib.gs_line1_step(t[0], *table, t[2], t[3], t[4], b, dims[0], lr, t[5], t[6],
+                             size(lib.gs_line1_step_workspace_bytes), null) == -2
