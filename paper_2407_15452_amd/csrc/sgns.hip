@@ -1600,7 +1600,7 @@ template <typename T, int WPP, int UB>
 __global__ __launch_bounds__(kSmallThreads) void sgns_small_update_kernel(SgnsArgs a) {
   __shared__ uint32_t keys[kSmallSlots], cnt[kSmallSlots], off[kSmallSlots];
   __shared__ uint32_t long_keys[kSmallSlots];
-  __shared__ Term terms_s[kSmallTerms];
+  __shared__ __align__(16) Term terms_s[kSmallTerms];     // (the loss block keeps doubles here)
   __shared__ uint2 owned[kSmallTerms];                    // entry; slot and position among the terms of its key
   __shared__ unsigned long long row_acc[kSmallMaxDim];
   __shared__ uint32_t found[kSmallWaves][128];
