@@ -129,7 +129,8 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs a) {
 // Each lane stages its own last kWin positions in LDS and writes them out as one
 // 64-byte row segment when the window is full (or the walk is over).
 struct __attribute__((packed, aligned(4))) Quad { int32_t v[4]; };   // four entries, 4-byte aligned
-template <typename OffT, bool kWeighted>
+// kAhead: one read instruction per trip and random numbers drawn ahead, where that pays (reads_ahead()).
+template <typename OffT, bool kWeighted, bool kAhead>
 __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   __shared__ int32_t tile[kWalkThreads / 64][64][kWinPad];
   using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
@@ -149,8 +150,6 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   const uint2* __restrict__ packed = a.packed;
   const Pos entries = (Pos)a.num_entries;
   const bool wide = a.num_entries >= 4;     // (a probe never reads past the array)
-  // every read is part of 16 bytes of one array (an alias table that is not interleaved takes two)
-  const bool one_read = wide && a.num_nodes >= 3 && (!kWeighted || packed != nullptr);
   int32_t cur = a.starts[i];
   if (cur < 0 || (int64_t)cur >= a.num_nodes) cur = -1;
   int32_t prev = -1;
@@ -175,7 +174,7 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   int probes = 0;                           // probes made in this search
   Pos pos = 0;                              // what this iteration reads: nbrs[pos] (or the alias entry at pos)
 
-  // random numbers of the attempt after the one whose read is under way: the first of a step while
+  // kAhead: random numbers of the attempt after the one whose read is under way: the first of a step while
   // its row bounds arrive, the next one while a candidate arrives (three of four are rejected at
   // p = 0.5, q = 2); a membership search keeps those of its attempt's draw.  With 32-bit positions for
   // 32-bit offsets, 1.49 -> 1.31 ms for the 47,000 walks below.
@@ -221,6 +220,7 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
 
     // ---- arithmetic ahead of the read -----------------------------------------------------
     if (state == kNewDraw) {
+      if (!kAhead) next_block = philox_at(a.seed, id, (uint32_t)t, att);
       j = row_slot(next_block, (Pos)(hi - lo));
       word2 = next_block.x2;
       s = unit_float(next_block.x3) * a.max_bias;
@@ -242,14 +242,14 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
 
     // ---- the one read of this iteration ---------------------------------------------------
     // Whatever a lane needs next (two row bounds, an alias entry, a neighbour, four entries of prev's
-    // row), it is part of 16 bytes of one array, so all lanes read through one instruction and a
-    // trip waits once; reads in branches of their own waited one after the other (47,000 walks of 80
+    // row), it is part of 16 bytes of one array, so with kAhead all lanes read through one instruction
+    // and a trip waits once; reads in branches of their own wait one after the other (47,000 walks of 80
     // nodes on a 4 M-node graph, bound by the chain of reads: 1.78 -> 1.49 ms).
     Pos r0 = 0, r1 = 0;
     int32_t v = 0;
     Quad quad = {{0, 0, 0, 0}};
     uint32_t e_prob = 0, e_alias = 0;
-    if (one_read) {
+    if constexpr (kAhead) {
       const char* from;
       int skip = 0;                           // 32-bit words in front of what is wanted
       if (state == kRow) {
@@ -283,20 +283,17 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
         r0 = w0;
         r1 = w1;
       }
+    } else if (state == kSearch) {
+      if (wide) quad = *reinterpret_cast<const Quad*>(nbrs + pos);
+      else quad.v[0] = nbrs[pos];
+    } else if (state == kRow) {
+      r0 = offsets[cur];
+      r1 = offsets[(int64_t)cur + 1];
+    } else if (kWeighted && state == kAlias) {
+      if (packed != nullptr) { const uint2 e = packed[pos]; e_prob = e.x; e_alias = e.y; }
+      else { e_prob = __float_as_uint(a.prob[pos]); e_alias = (uint32_t)a.alias[pos]; }
     } else {
-      draw_ahead();
-      if (state == kSearch) {
-        if (wide) quad = *reinterpret_cast<const Quad*>(nbrs + pos);
-        else quad.v[0] = nbrs[pos];
-      } else if (state == kRow) {
-        r0 = offsets[cur];
-        r1 = offsets[(int64_t)cur + 1];
-      } else if (kWeighted && state == kAlias) {
-        if (packed != nullptr) { const uint2 e = packed[pos]; e_prob = e.x; e_alias = e.y; }
-        else { e_prob = __float_as_uint(a.prob[pos]); e_alias = (uint32_t)a.alias[pos]; }
-      } else {
-        v = nbrs[pos];
-      }
+      v = nbrs[pos];
     }
 
     // ---- consume it: new state, or a decision ----------------------------------------------
@@ -357,12 +354,30 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   }
 }
 
+// One read instruction for all states and an attempt drawn ahead cost instructions on every trip and pay
+// where a trip waits for memory: neighbours beyond the L2 caches, waves that are full but few (two per SIMD
+// are 2^17 walks), and attempts that are rejected.  Measured, reads in branches of their own against one
+// read ahead: 47,000 walks of 40 nodes at p = 0.5, q = 2 on 128 M entries 1.23 times as fast ahead, interleaved
+// alias tables 1.48 times, 64-bit offsets 1.07 and 1.17 times; on 3.2 M entries 1.13, on 0.4 M 0.97 times.
+// 200,000 walks 0.91, 10 walks 0.94.  p = q = 1 (every candidate is taken) 0.88 to 0.95; q = 1, p = 2: 1.18,
+// but 120,000 walks 0.95 and 64-bit offsets without weights 0.97.  64-bit offsets on rows of 8 entries (8 M
+// in all), p = 4, q = 0.25: 0.91, hence their higher limit.
+static bool reads_ahead(bool weighted, bool bits64, float p, float q, const WalkArgs& a) {
+  // (every read is part of 16 bytes of one array; an alias table that is not interleaved takes two)
+  if (a.num_entries < ((int64_t)1 << (bits64 ? 24 : 22)) || a.num_nodes < 3 || (weighted && a.packed == nullptr)) return false;
+  if (a.num_walks < 1024 || a.num_walks > ((int64_t)1 << 17)) return false;
+  if (q != 1.0f) return true;
+  return p != 1.0f && (weighted || !bits64) && a.num_walks <= ((int64_t)1 << 16);
+}
+
 template <typename OffT>
-static void launch_walk(bool weighted, bool second, const WalkArgs& a, hipStream_t stream) {
+static void launch_walk(bool weighted, bool second, float p, float q, const WalkArgs& a, hipStream_t stream) {
   const unsigned blocks = (unsigned)ceil_div(a.num_walks, kWalkThreads);
   if (second) {
-    if (weighted) node2vec_kernel<OffT, true><<<blocks, kWalkThreads, 0, stream>>>(a);
-    else node2vec_kernel<OffT, false><<<blocks, kWalkThreads, 0, stream>>>(a);
+    const bool ahead = reads_ahead(weighted, sizeof(OffT) == 8, p, q, a);
+    auto kernel = weighted ? (ahead ? node2vec_kernel<OffT, true, true> : node2vec_kernel<OffT, true, false>)
+                           : (ahead ? node2vec_kernel<OffT, false, true> : node2vec_kernel<OffT, false, false>);
+    kernel<<<blocks, kWalkThreads, 0, stream>>>(a);
   } else {
     if (weighted) walk_kernel<OffT, true><<<blocks, kWalkThreads, 0, stream>>>(a);
     else walk_kernel<OffT, false><<<blocks, kWalkThreads, 0, stream>>>(a);
@@ -399,8 +414,8 @@ static int32_t walk_common(const gs_csr* g, const gs_alias* al, const int32_t* s
   a.inv_p = 1.0f / p;
   a.inv_q = 1.0f / q;
   a.max_bias = fmaxf(a.inv_p, fmaxf(1.0f, a.inv_q));
-  if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, a, stream);
-  else launch_walk<int32_t>(weighted, second, a, stream);
+  if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, p, q, a, stream);
+  else launch_walk<int32_t>(weighted, second, p, q, a, stream);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }

@@ -1,0 +1,53 @@
+"""The node2vec walker that reads ahead (graphs of at least 2^22 entries, 2^24 with 64-bit offsets, and 1024 to 2^17 walks) and, just outside
+its range, the other, against the CPU reference, bit for bit: rows at both ends of the arrays, dead ends,
+32- and 64-bit offsets, uniform and weighted draws, walks of one wave's width more than a full block."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+ENTRIES = 1 << 22
+
+
+def _dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(DEV)
+
+
+def _graph(kind, n, entries):
+    rng = np.random.default_rng(n)
+    if kind == "dead-ends":               # half of the nodes have no row
+        return rng.integers(0, n // 2, entries).astype(np.int32) * 2, rng.integers(0, n, entries).astype(np.int32)
+    return rng.integers(0, n, entries).astype(np.int32), rng.integers(0, n, entries).astype(np.int32)
+
+
+@pytest.mark.parametrize("kind,n,entries,walks", [("even", 3, ENTRIES, 1024), ("even", 2, ENTRIES + 1, 1024),
+                                                  ("even", 5000, ENTRIES, 1087), ("even", 5000, ENTRIES - 1, 1087),
+                                                  ("even", 5000, ENTRIES + 3, 1023),
+                                                  ("dead-ends", 300_000, ENTRIES + 2, 131_072),
+                                                  ("dead-ends", 300_000, ENTRIES + 2, 131_073),
+                                                  ("rows", 4096, 1 << 24, 1087)])
+def test_same_walks(oracle, kind, n, entries, walks):
+    from paper_2407_15452_amd import binding as gs
+    w = np.random.default_rng(1).lognormal(0, 1, entries).astype(np.float32)
+    if kind == "rows":                    # rows of equal length, as they are
+        off = np.arange(n + 1, dtype=np.int32) * (entries // n)
+        nb, ww = np.sort(np.random.default_rng(2).integers(0, n, (n, entries // n)).astype(np.int32), axis=1).ravel(), w
+    else:
+        off, nb, ww = oracle.csr_build(*_graph(kind, n, entries), w, n, 0)
+    assert nb.size == entries
+    table = oracle.alias_build(off, ww)
+    starts = (n - 1 - np.arange(walks) % n).astype(np.int32)     # the last rows first
+    length = 9 if walks > 100_000 else 24
+    nbrs = _dev(nb)
+    prob, alias = _dev(table[0]), _dev(table[1])
+    packed = gs.gs_alias_pack(prob, alias)
+    for p, q in ((0.5, 2.0), (2.0, 1.0), (1.0, 1.0)):
+        for tab in (None, table):
+            want = oracle.node2vec_walk(off, nb, starts, length, p, q, 5, alias=tab, walk_id_base=7)
+            for dtype in (np.int32, np.int64):
+                g = gs.Csr(_dev(off.astype(dtype)), nbrs)
+                for a in ([None] if tab is None else [gs.Alias(prob, alias, packed), gs.Alias(prob, alias)]):
+                    got = gs.gs_node2vec_walk(g, a, _dev(starts), length, p, q, 5, walk_id_base=7)
+                    np.testing.assert_array_equal(got.cpu().numpy(), want)
