@@ -1886,9 +1886,20 @@ static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
 // 46, 12,000 (84 k) 89 / 105; 64 columns on 10 k nodes: 4096 (29 k) 50 / 38, 6000 53 / 46, 8192 (57 k)
 // 54 / 59; 10 negatives, 256 bf16 columns on 500 k nodes: 4096 (49 k) 123 / 64, 8192 (98 k) 117 / 125.
 constexpr int64_t kSmallMaxEntries = 3 << 14;
+// A row is summed by one workgroup (about 14 ns a term with 128 fp32 columns, in fp64 instructions), and one of
+// more than kSmallRow terms costs a look at all ids as well, so the step must not be taken by batches with long
+// rows.  The ids are on the device; of a skewed graph the most frequent one has a share of about one
+// in sqrt(num_nodes), which leaves such batches of at most sqrt(2^17 * num_nodes) ids.  Seven launches against
+// two, R-MAT graphs, walks, k = 5 and 128 columns: 10,000 nodes, 35 k ids 63 / 56 us, 42 k 63 / 74; 5000 nodes, 28 k 58
+// / 49, 35 k 59 / 63; 20,000 nodes, 49 k 75 / 70; and ids drawn with a density of 1 / sqrt(id): 3000 nodes, 14 k 52
+// / 42, 28 k 53 / 66; 1000 nodes, 7 k 51 / 30, 14 k 52 / 47, 28 k 53 / 61.  Where it still loses: a tenth of
+// all ids the same one (10,000 nodes, 14 k ids 62 / 66; 1 M nodes, 49 k ids 85 / 123).
+constexpr int kSmallShareShift = 17;
 
-static bool small_batch(int64_t num_pairs, int32_t k, int32_t dim, int32_t dtype) {
-  return num_pairs * (int64_t)(k + 2) <= kSmallMaxEntries && dim * (dtype == GS_F32 ? 4 : 2) <= kSmallMaxRowBytes;
+static bool small_batch(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
+  const int64_t ids = num_pairs * (int64_t)(k + 2);
+  return ids <= kSmallMaxEntries && ids * ids <= (num_nodes << kSmallShareShift) &&
+         dim * (dtype == GS_F32 ? 4 : 2) <= kSmallMaxRowBytes;
 }
 static int64_t small_forward_blocks(int64_t num_pairs) {
   return ceil_div(ceil_div(num_pairs, kSmallChunkPairs), kSmallForwardThreads / kGroupLanes);
@@ -1917,7 +1928,7 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
                       int32_t k, int32_t dim, int32_t dtype, bool two_launches = true, bool force_compact = false) {
   const SgnsPlan counters = plan_sgns(ws, num_pairs, num_nodes, k, dim, force_compact);
   if (counters.bytes + extra > ws_bytes) return false;
-  if (two_launches && small_batch(num_pairs, k, dim, dtype)) {
+  if (two_launches && small_batch(num_pairs, num_nodes, k, dim, dtype)) {
     p = plan_small(ws, num_pairs, k, dim, dtype);
     if (p.bytes + extra <= ws_bytes) return true;
   }
@@ -1930,7 +1941,7 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
 }
 static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  if (small_batch(num_pairs, k, dim, dtype)) bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
+  if (small_batch(num_pairs, num_nodes, k, dim, dtype)) bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
   if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
   return bytes;
 }

@@ -28,8 +28,17 @@ def _step(oracle, n, dim, c, o, neg, lr=0.05):
 @pytest.mark.parametrize("b,k,dim", [(1, 0, 4), (2, 1, 256), (7021, 5, 12), (7022, 5, 12), (24576, 0, 8),
                                      (24577, 0, 8), (792, 60, 16), (1000, 3, 260)])
 def test_sizes(oracle, b, k, dim):
+    _sizes(oracle, 20_000, b, k, dim)
+
+
+@pytest.mark.parametrize("n", [127, 128])
+def test_few_nodes(oracle, n):
+    """4096 ids: the square is 2^17 times 128."""
+    _sizes(oracle, n, 1024, 2, 16)
+
+
+def _sizes(oracle, n, b, k, dim):
     rng = np.random.default_rng(b + k)
-    n = 3000
     c = np.repeat(rng.integers(0, n, (b + 6) // 7), 7)[:b].astype(np.int32)
     o = rng.integers(0, n, b).astype(np.int32)
     neg = rng.integers(0, n, (b, k)).astype(np.int32)
