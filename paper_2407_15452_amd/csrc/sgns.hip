@@ -1822,14 +1822,17 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
 }
 
 // Batches of at least this many terms take the sorted records: fewer where two passes sort them (up to
-// 2^16 rows), because few rows also mean busy counters.  Measured, counters against records, 5 negatives
-// drawn with some skew: 60 k rows of 128 fp32 columns, 0.48 million terms 173 / 163 us, 3.6 million 693 /
-// 635; 30 k rows, 0.24 million 103 / 109, 0.48 million 144 / 142; 10 k rows of 64, 0.24 million 79 / 86, 0.48
-// million 122 / 106, 3.6 million 680 / 415; 100 k rows of 128 (three passes), 1.8 million 358 / 409, 3.6 million
-// 695 / 722; 1 M rows, 1.8 million 571 / 607, 3.6 million 929 / 921; 500 k rows of 256 bf16 columns, 3.3 million
-// 865 / 799; 4 M rows, negatives and the rest of the step included: 11 million (256 bf16 columns) 3000 / 2552, 12
-// million 2606 / 2407.
-constexpr int64_t kSortedMinTerms = (int64_t)1 << 22, kSortedMinTermsTwoPasses = (int64_t)1 << 19;
+// 2^16 rows), because few rows also mean busy counters.  Counters over records, 5 negatives, ids even and with
+// a density of 1 / sqrt(id).  Two passes: 65 k rows, 0.53 million terms 1.02 to 1.09 (16 to 256 columns); 30 k,
+// 0.65 million 0.96 to 1.03, 1.05 million 0.99 to 1.15; 10 k, 0.65 million 0.94 to 1.12, 1.05 million 1.09 to 1.24;
+// 3 k, 0.65 million 0.95 to 1.20, 1.05 million 1.11 to 1.54.  Three: 70 k to 100 k rows, 4.2 million 0.96 to 1.08,
+// 4.7 million 0.97 to 1.14; 300 k to 1 M, 4.2 million 1.01 to 1.11; 4 M, 4.2 million 0.97 to 1.09, 4.7 million
+// 0.99 to 1.10 (128 fp32 columns the least, 1.01 at 6 million and 1.04 to 1.07 from 12 million on).  Four passes
+// (over 2^24 rows): 17 M and 25 M rows, 4.7 million 1.02 to 1.12; 25 M of 256 bf16 columns, 22 million 8697 /
+// 7879 us; 100 M of 128 fp32 columns, 24 million 11866 / 10166 us.
+constexpr int64_t kSortedMinTerms = (int64_t)9 << 19;
+constexpr int64_t kSortedMinTermsTwoPasses = (int64_t)1 << 19, kSortedMinTermsFewRows = (int64_t)1 << 20;
+constexpr int64_t kSortedFewRows = (int64_t)1 << 15;
 // Sorted terms per wave of the update: the ends of a slice cost four loads of keys (256 against 128 terms:
 // 2407 / 2425 us in the last case above), and a short batch has to make enough waves.
 static int sorted_slice_for(int64_t num_terms) {
@@ -1876,7 +1879,9 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
 }
 static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
   const bool two_passes = radix_sort_passes(bits_for_rows(num_nodes)) <= 2;
-  return num_pairs * (int64_t)(k + 1) >= (two_passes ? kSortedMinTermsTwoPasses : kSortedMinTerms);
+  const int64_t terms = num_pairs * (int64_t)(k + 1);
+  if (!two_passes) return terms >= kSortedMinTerms;
+  return terms >= (num_nodes <= kSortedFewRows ? kSortedMinTermsFewRows : kSortedMinTermsTwoPasses);
 }
 
 // Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every
