@@ -1944,10 +1944,29 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
   p = counters;
   return true;
 }
-static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype) {
+// The largest plan that a batch of num_pairs may take.
+static size_t plan_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype, bool two_launches) {
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  if (small_batch(num_pairs, num_nodes, k, dim, dtype)) bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
+  if (two_launches && small_batch(num_pairs, num_nodes, k, dim, dtype))
+    bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
   if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  return bytes;
+}
+// The same over all batches of up to num_pairs: the workspace of a program's largest batch serves every
+// batch, on the way that it would take with a workspace of its own.  A plan grows with its batch but for a few
+// borders behind which a smaller one follows.
+static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, int32_t dtype, bool two_launches = true) {
+  size_t bytes = plan_bytes(num_pairs, num_nodes, k, dim, dtype, two_launches);
+  int64_t power = 1;                                      // the largest power of two below the nodes
+  while (2 * power < num_nodes) power *= 2;
+  const int64_t small_ids = std::min(kSmallMaxEntries, (int64_t)std::sqrt((double)(num_nodes << kSmallShareShift)));
+  const int64_t last[] = {(1 << 18) - 1, (1 << 20) - 1,   // before fewer, longer chunks and segments
+                          (int64_t)((2 * (size_t)std::max(num_nodes, (int64_t)1) - 1) / kCompactFactor) / (k + 2),
+                                                          // of those with counters for the batch's keys only
+                          power / 2,                      // of those with a table of the input keys
+                          small_ids / (k + 2)};           // of those with two launches
+  for (const int64_t pairs : last)
+    if (pairs > 0 && pairs < num_pairs) bytes = std::max(bytes, plan_bytes(pairs, num_nodes, k, dim, dtype, two_launches));
   return bytes;
 }
 
@@ -2577,9 +2596,8 @@ static size_t line1_slot_bytes(int64_t num_pairs) {
 extern "C" size_t gs_line1_step_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k,
                                                 int32_t dim, int32_t dtype) {
   if (num_pairs < 0 || num_nodes < 0 || k < 0 || dim < 1) return 0;
-  size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
-  if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
-  return bytes + line1_snap_bytes(num_pairs, dim, dtype) + line1_slot_bytes(num_pairs);
+  return step_bytes(num_pairs, num_nodes, k, dim, dtype, false) + line1_snap_bytes(num_pairs, dim, dtype) +
+         line1_slot_bytes(num_pairs);
 }
 
 extern "C" int32_t gs_line1_step(void* w, int64_t num_nodes, int32_t dim, int32_t dtype,

@@ -147,3 +147,20 @@ def test_workspace_below_the_counters_plan_is_refused(lib, pairs, nodes):
                                        size(lib.gs_sgns_step_from_walks_workspace_bytes), null) == -2
     assert lib.gs_line1_step(t[0], *table, t[2], t[3], t[4], b, dims[0], lr, t[5], t[6],
                              size(lib.gs_line1_step_workspace_bytes), null) == -2
+
+
+@pytest.mark.parametrize("nodes", [1, 5, 300, 10_000, 18_431, 131_072, 131_073, 300_000, 4_000_000, 100_000_000])
+def test_workspace_of_a_large_batch_serves_smaller_ones(lib, nodes):
+    """What the training steps ask for never falls as the batch grows: over the ends of the two-launch step, of
+    the table of the batch's keys and of the input keys, of short segments, and the start of the sorted records."""
+    queries = (lib.gs_sgns_step_workspace_bytes, lib.gs_sgns_step_fused_workspace_bytes,
+               lib.gs_sgns_step_from_walks_workspace_bytes, lib.gs_line1_step_workspace_bytes)
+    for k, dim, dtype in ((0, 256, 0), (5, 256, 0), (5, 8, 1), (60, 512, 2)):
+        ends = {1, 2, 1 << 18, 1 << 20, 49_152 // (k + 2), int((nodes << 17) ** 0.5) // (k + 2), nodes // 8 // (k + 2),
+                (1 << 19) // (k + 1), (1 << 20) // (k + 1), (9 << 19) // (k + 1), (1 << 21) // (k + 1), 3_000_000}
+        ends |= {1 << s for s in range(1, 22)}
+        sizes = sorted({e + d for e in ends for d in (-1, 0, 1, 2) if e + d > 0 and (e + d) * (k + 1) < 1 << 31})
+        for query in queries:
+            got = [query(C.c_int64(b), C.c_int64(nodes), C.c_int32(k), C.c_int32(dim), C.c_int32(dtype)) for b in sizes]
+            falls = [(b, x, y) for b, x, y in zip(sizes, got, got[1:]) if y < x]
+            assert not falls, (k, dim, dtype, falls)
