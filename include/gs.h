@@ -22,10 +22,10 @@
  *    ws must be 256-byte aligned.  Its contents are undefined afterwards.
  *    gs_alias_build and the training steps have more than one way of doing
  *    their work and report what the largest takes; with less, down to what the
- *    general way takes, they use that one (the same tables bit for bit, in
- *    more time), and return GS_EWORKSPACE below it.
- *    A workspace for one size of batch also serves every smaller one (other
- *    arguments alike), with the same results in the same time.
+ *    general way takes, they use that one (in more time, and a training step
+ *    with fp32 gradients of centre rows that may be added in another order), and
+ *    return GS_EWORKSPACE below it.  A workspace for one size of batch also
+ *    serves every smaller one that is not empty (other arguments alike).
  *  - Return value: GS_OK or a negative gs_status.  Arguments are validated on
  *    the host only; nothing is enqueued when a call fails validation.  Node
  *    ids live in device memory and are checked by the kernels that use them as

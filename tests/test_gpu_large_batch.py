@@ -72,8 +72,9 @@ def test_one_table(oracle):
     assert_emb_close(d.cpu().numpy(), h)
 
 
-def test_reports_bad_ids_and_takes_a_smaller_workspace():
-    """An id that is not a row turns the loss into NaN; the same batch twice gives the same bits."""
+def test_reports_bad_ids_and_repeats_the_bits():
+    """An id that is not a row turns the loss into NaN; the same batch twice gives the same bits.  (Workspaces
+    without room for the records: test_gpu_step_routes.py.)"""
     from paper_2407_15452_amd import binding as gs, inputs
     n, dim, k, b = 2_000, 8, 5, 699_051
     rng = np.random.default_rng(2)

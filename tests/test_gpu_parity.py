@@ -900,9 +900,10 @@ def test_sgns_step_same_bits_every_run(gs, fmt):
 @pytest.mark.parametrize("b,k", [(1, 5), (37, 0), (2_048, 5), (9_000, 2)])
 def test_sgns_step_small_batch_on_large_graph(gs, oracle, b, k, fmt):
     """The paper's own regime (Sec. 4: batches of 512 to 2048 source nodes on graphs of 10^8
-    vertices): the batch names a tiny part of the rows, so the step counts over a table of the
-    batch's keys instead of over all vertices.  Hub rows with thousands of terms, runs of equal
-    centres, centres that are also contexts; rows the batch does not name keep their bits."""
+    vertices): the batch names a tiny part of the rows, and nothing in the step has the size of
+    the graph (two launches for these sizes; counters over the keys of a larger batch are in
+    test_gpu_step_routes.py).  Hub rows with thousands of terms, runs of equal centres, centres
+    that are also contexts; rows the batch does not name keep their bits."""
     from paper_2407_15452_amd import inputs
     n, dim = 400_000, 64
     f_in, f_out = inputs.random_tables(n, dim, seed=b + k, scale=0.25)

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from tolerances import LOSS_RTOL, assert_emb_close
+from tolerances import LOSS_RTOL, assert_emb_close, assert_half_close
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,25 @@ def test_ids_that_share_a_hash(oracle, distinct, b):
     neg = pick[rng.integers(0, distinct, (b, 1))].astype(np.int32)
     c = rng.integers(0, n, b).astype(np.int32)
     _step(oracle, n, 4, c, o, neg)
+
+
+@pytest.mark.parametrize("dim,b,k", [(8, 3000, 3), (200, 1500, 5), (512, 700, 2)])
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+def test_sixteen_bit_tables(oracle, dim, b, k, fmt):
+    """Short rows and two long ones, in rows of up to 256, 512 and 1024 bytes."""
+    from paper_2407_15452_amd import binding as gs, inputs
+    n = 20_000
+    rng = np.random.default_rng(dim)
+    tabs = [t.to(torch.bfloat16 if fmt == "bf16" else torch.float16) for t in inputs.random_tables(n, dim, 5, 0.4)]
+    dev = [t.to(DEV) for t in tabs]
+    host = [t.view(torch.int16).numpy().view(np.uint16).copy() for t in tabs]
+    c = np.repeat(rng.integers(0, n, b // 4 + 1), 4)[:b].astype(np.int32)
+    c[:300:2] = 17
+    o = rng.integers(0, n, b).astype(np.int32)
+    o[:129] = 4
+    neg = rng.integers(0, n, (b, k)).astype(np.int32)
+    want = oracle.sgns_step(*host, c, o, neg, 0.02, dtype=oracle.BF16 if fmt == "bf16" else oracle.F16)
+    loss = gs.gs_sgns_step(*dev, *(torch.as_tensor(x).to(DEV) for x in (c, o, neg)), 0.02)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for d, h in zip(dev, host):
+        assert_half_close(d.view(torch.int16).cpu().numpy().view(np.uint16), h, fmt)

@@ -1,0 +1,162 @@
+"""The ways of one training step (two launches, counters per row or per key of the batch, sorted records)
+against the CPU reference where other files do not: every row width and storage type of the sorted records, the calls
+that draw their negatives or make their pairs on them, counters over the keys of a batch that is too
+large or too wide for two launches, and each way against the counters in a workspace that only holds those."""
+import numpy as np
+import pytest
+import torch
+
+from tolerances import LOSS_RTOL, assert_emb_close, assert_half_close
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TYPES = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+
+
+def _dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(DEV)
+
+
+def _host(t, fmt):
+    return t.cpu().numpy().copy() if fmt == "f32" else t.view(torch.int16).cpu().numpy().view(np.uint16).copy()
+
+
+def _code(oracle, fmt):
+    return {"f32": oracle.F32, "bf16": oracle.BF16, "f16": oracle.F16}[fmt]
+
+
+def _tables(n, dim, fmt, count=2):
+    from paper_2407_15452_amd import inputs
+    return [t.to(TYPES[fmt]) for s in range(0, count, 2) for t in inputs.random_tables(n, dim, 7 + s, 0.2)]
+
+
+def _close(dev, host, fmt, flip_fraction=None):
+    for d, h in zip(dev, host):
+        if fmt == "f32":
+            assert_emb_close(_host(d, fmt), h)
+        else:
+            assert_half_close(_host(d, fmt), h, fmt, flip_fraction=flip_fraction)
+
+
+def _batch(n, b, k, seed):
+    """Runs of equal centres; a few rows with hundreds of terms, in both tables."""
+    rng = np.random.default_rng(seed)
+    c = np.repeat(rng.integers(0, n, b // 3 + 1), 3)[:b].astype(np.int32)
+    c[:600:2] = 5
+    o = rng.integers(0, n, b).astype(np.int32)
+    o[:700] = n - 1
+    neg = rng.integers(0, n, (b, k)).astype(np.int32)
+    neg[:257, 0] = 3
+    return c, o, neg
+
+
+def _step(oracle, n, b, k, dim, fmt, flip_fraction=None):
+    from paper_2407_15452_amd import binding as gs
+    tabs = _tables(n, dim, fmt)
+    host, dev = [_host(t, fmt) for t in tabs], [t.to(DEV) for t in tabs]
+    c, o, neg = _batch(n, b, k, dim)
+    want = oracle.sgns_step(*host, c, o, neg, 0.01, dtype=_code(oracle, fmt))
+    loss = gs.gs_sgns_step(*dev, _dev(c), _dev(o), _dev(neg), 0.01)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    _close(dev, host, fmt, flip_fraction)
+
+
+@pytest.mark.parametrize("dim,fmt", [(132, "f32"), (260, "f32"), (516, "f32"), (1024, "f32"), (8, "f16"), (264, "f16"),
+                                     (264, "bf16"), (520, "bf16"), (1024, "bf16")])
+def test_sorted_records_of_every_width(oracle, dim, fmt):
+    """Rows of up to 512, 1024, 2048 and 4096 bytes; 2^19 terms and a few on 40,000 rows."""
+    _step(oracle, 40_000, 32_770, 15, dim, fmt)
+
+
+@pytest.mark.parametrize("n,b,k,dim,fmt", [(800_000, 9_000, 5, 64, "f32"), (800_000, 9_000, 5, 64, "bf16"),
+                                           (400_000, 9_000, 5, 20, "f32"), (150_000, 2_048, 5, 260, "f32"),
+                                           (150_000, 2_048, 5, 520, "f16")])
+def test_counters_over_the_keys_of_a_batch(oracle, n, b, k, dim, fmt):
+    """A graph much larger than the batch: all keys, or the input keys, through a table; more than 49,152 ids, or
+    rows of more than 1024 bytes.  (Few elements are touched: one that rounds the other way weighs more.)"""
+    _step(oracle, n, b, k, dim, fmt, None if fmt == "f32" else 2e-3)
+
+
+@pytest.mark.parametrize("call", ["fused", "from_walks"])
+def test_sorted_records_made_in_the_call(oracle, call):
+    from paper_2407_15452_amd import binding as gs
+    n, k, dim, length, window = 40_000, 5, 12, 20, 5
+    rng = np.random.default_rng(3)
+    walks = rng.integers(0, n, (1000, length)).astype(np.int32)
+    for i, end in enumerate(rng.integers(0, length + 20, 1000)):      # some end early
+        walks[i, end:] = -1
+    c, o = oracle.make_pairs(walks, window)
+    first, b = 1, (1 << 19) // (k + 1) + 3
+    assert c.size >= first + b
+    c, o = c[first:first + b], o[first:first + b]
+    seg, weights = np.array([0, n], dtype=np.int32), rng.random(n).astype(np.float32)
+    table = oracle.alias_build(seg, weights)
+    noise = gs.gs_alias_build(_dev(seg), _dev(weights))
+    tabs = _tables(n, dim, "f32")
+    host, dev = [_host(t, "f32") for t in tabs], [t.to(DEV) for t in tabs]
+    neg = oracle.sample_negatives(table, n, b, k, seed=9, pair_index_base=77)
+    want = oracle.sgns_step(*host, c, o, neg, 0.01)
+    if call == "fused":
+        loss = gs.gs_sgns_step_fused(*dev, _dev(c), _dev(o), noise, k, 9, 0.01, pair_index_base=77)
+    else:
+        d_walks = _dev(walks)
+        loss = gs.gs_sgns_step_from_walks(*dev, d_walks, window, gs.gs_pair_offsets(d_walks, window), first, b, noise,
+                                          k, 9, 0.01, pair_index_base=77)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    _close(dev, host, "f32")
+
+
+@pytest.mark.parametrize("call,n,b,k,dim", [(call, 20_000, 1_500, 5, 256) for call in ("step", "fused", "from_walks", "momentum")] +
+                         [(call, 30_000, 17_200, 60, 8) for call in ("step", "fused", "from_walks", "line1")])
+def test_smaller_workspace(call, n, b, k, dim):
+    """Two launches, and sorted records, against the counters that the least workspace leaves.  The row sums are
+    exact and a row is rounded at the same places, so the tables agree bit for bit, but for the centre rows of the
+    two launches: their gradients are summed in fp32 over two pairs of a run at a time instead of four."""
+    from paper_2407_15452_amd import binding as gs
+    length, window = 20, 5
+    c, o, neg = (_dev(x) for x in _batch(n, b, k, 1))
+    walks = _dev(np.random.default_rng(2).integers(0, n, (b // 150 + 1, length)).astype(np.int32))
+    offsets = gs.gs_pair_offsets(walks, window)
+    tabs = [t.to(DEV) for t in _tables(n, dim, "f32", 4)]
+    size = {"step": gs.gs_sgns_step_workspace_bytes, "momentum": gs.gs_sgns_step_workspace_bytes,
+            "fused": gs.gs_sgns_step_fused_workspace_bytes, "line1": gs.gs_line1_step_workspace_bytes,
+            "from_walks": gs.gs_sgns_step_from_walks_workspace_bytes}[call](b, n, k, dim)
+    ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+
+    def run(nbytes):
+        t = [x.clone() for x in tabs]
+        use = ws[:nbytes]
+        if call == "step":
+            loss = gs.gs_sgns_step(*t[:2], c, o, neg, 0.01, ws=use)
+        elif call == "fused":
+            loss = gs.gs_sgns_step_fused(*t[:2], c, o, None, k, 9, 0.01, ws=use)
+        elif call == "from_walks":
+            loss = gs.gs_sgns_step_from_walks(*t[:2], walks, window, offsets, 0, b, None, k, 9, 0.01, ws=use)
+        elif call == "line1":
+            loss = gs.gs_line1_step(t[0], c, o, neg, 0.01, ws=use)
+        else:
+            loss = gs.gs_sgns_momentum_step(*t, c, o, neg, 0.01, 0.9, ws=use)
+        return float(loss.item()), t
+
+    refused, taken = 0, size // 256                      # in steps of the alignment
+    while taken - refused > 1:
+        middle = (taken + refused) // 2
+        try:
+            run(middle * 256)
+            taken = middle
+        except gs.GsError as e:
+            assert e.status == gs.GS_EWORKSPACE
+            refused = middle
+    # the call's own arrays, and less than the step's other plan takes: what is taken here has no room for it
+    own = {"fused": 4 * b * k, "from_walks": 4 * b * k + 8 * b, "line1": 4 * b * (dim + 1)}.get(call, 0)
+    other = b * (8 * dim + 4 * (k + 1) + 8) if b < 2_000 else b * (24 * (k + 1) + 4 * dim + 24) + b * (k + 1) * (dim + 4) // 8
+    assert taken * 256 - own < other <= size - own
+    loss, t = run(taken * 256)
+    want_loss, want = run(size)
+    assert np.isfinite(want_loss) and abs(loss - want_loss) <= LOSS_RTOL * abs(want_loss)
+    for i, (x, y) in enumerate(zip(t, want)):
+        if b < 2_000 and i % 2 == 0:
+            assert_emb_close(_host(x, "f32"), _host(y, "f32"))
+        else:
+            assert torch.equal(x, y)
