@@ -416,8 +416,9 @@ __device__ __forceinline__ void append(Window& q, int32_t* list, bool mine, int3
 // A round that has become narrower than kWideRound is left to that one.  Measured in ms, degree^0.75 of a skewed
 // graph and lognormal weights: the whole chip against one workgroup, 2^15 entries 0.39 / 0.34 and 0.32 / 0.28, 2^16
 // 0.56 / 0.55 and 0.41 / 0.42 (2^17 equal weights 0.32 / 0.33, half of them zero 0.37 / 0.52; 2^18 0.40 / 0.52 and
-// 0.44 / 0.93).  16 rounds against 48: 1 M entries 1.99 / 2.07 and 1.31 / 1.41, 2 M 3.36 / 3.18 and 1.83 / 1.84, 4 M 4.83 / 3.93 and 3.03 / 2.68, 8 M 8.61 / 5.95 and 5.36 / 3.99 (so the line
-// between them could lie at 2 M).  kWideRound of 2048, 8192 and 32768: 1 M 1.99, 1.99, 2.37, 8 M 5.92, 5.96, 7.15.
+// 0.44 / 0.93).  16 rounds against 48: 1 M entries 1.99 / 2.07 and 1.31 / 1.41, 2 M 3.36 / 3.18 and 1.83 / 1.84, 4 M
+// 4.83 / 3.93 and 3.03 / 2.68, 8 M 8.61 / 5.95 and 5.36 / 3.99 (so the line between them could lie at 2 M).
+// kWideRound of 2048, 8192 and 32768: 1 M entries 1.99, 1.99, 2.37, 8 M 5.92, 5.96, 7.15.
 struct ListState { int64_t sh, st, lh, lt; };
 constexpr int64_t kWideSegment = (int64_t)1 << 17;
 constexpr int64_t kWideRound = 8192;
