@@ -178,10 +178,10 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   // its row bounds arrive, the next one while a candidate arrives (three of four are rejected at
   // p = 0.5, q = 2); a membership search keeps those of its attempt's draw.  With 32-bit positions for
   // 32-bit offsets, 1.49 -> 1.31 ms for the 47,000 walks below.
-  Block4 next_block = {0u, 0u, 0u, 0u};
+  Block4 ahead = {0u, 0u, 0u, 0u};
   auto draw_ahead = [&]() {
     if (state == kRow || state == kDraw)
-      next_block = philox_at(a.seed, id, (uint32_t)t, state == kRow ? 0u : att + 1u);
+      ahead = philox_at(a.seed, id, (uint32_t)t, state == kRow ? 0u : att + 1u);
   };
 
   // position t + 1 of the walk is `node`: into the lane's window, and out when it is full
@@ -220,10 +220,10 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
 
     // ---- arithmetic ahead of the read -----------------------------------------------------
     if (state == kNewDraw) {
-      if (!kAhead) next_block = philox_at(a.seed, id, (uint32_t)t, att);
-      j = row_slot(next_block, (Pos)(hi - lo));
-      word2 = next_block.x2;
-      s = unit_float(next_block.x3) * a.max_bias;
+      const Block4 b = kAhead ? ahead : philox_at(a.seed, id, (uint32_t)t, att);
+      j = row_slot(b, (Pos)(hi - lo));
+      word2 = b.x2;
+      s = unit_float(b.x3) * a.max_bias;
       pos = lo + j;
       state = (kWeighted ? kAlias : kDraw);
     } else if (state == kSearch) {           // (the range [L, H) is never empty here)
@@ -354,20 +354,30 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   }
 }
 
-// One read instruction for all states and an attempt drawn ahead cost instructions on every trip and pay
-// where a trip waits for memory: neighbours beyond the L2 caches, waves that are full but few (two per SIMD
-// are 2^17 walks), and attempts that are rejected.  Measured, reads in branches of their own against one
-// read ahead: 47,000 walks of 40 nodes at p = 0.5, q = 2 on 128 M entries 1.23 times as fast ahead, interleaved
-// alias tables 1.48 times, 64-bit offsets 1.07 and 1.17 times; on 3.2 M entries 1.13, on 0.4 M 0.97 times.
-// 200,000 walks 0.91, 10 walks 0.94.  p = q = 1 (every candidate is taken) 0.88 to 0.95; q = 1, p = 2: 1.18,
-// but 120,000 walks 0.95 and 64-bit offsets without weights 0.97.  64-bit offsets on rows of 8 entries (8 M
-// in all), p = 4, q = 0.25: 0.91, hence their higher limit.
+// One read instruction for all states and an attempt drawn ahead cost instructions on every trip and pay where a
+// trip waits for memory: waves that are full but few (two per SIMD are 2^17 walks), attempts that are rejected, rows
+// beyond the caches; sooner with alias tables (a read more per attempt), later with 64-bit offsets (more
+// arithmetic).  Times of reads in branches of their own over times of one read ahead, R-MAT graphs, walks of 20 to 80
+// nodes, p = 0.5, q = 2 unless stated:
+//   unweighted  47,000 walks: 128 M entries 1.26, 3.2 M 1.13, 1.6 M 1.08, 0.4 M 0.97; 1000 walks: 128 M 1.17, 6 M 0.97;
+//               200,000 walks 0.91; 10 walks 0.91
+//   64 bits     47,000 walks: 128 M 1.07, 8 M 1.04, 0.4 M 0.94; 10 walks 0.91
+//   alias       47,000 walks: 128 M 1.47, 8 M 1.34, 0.4 M 1.14; 40 walks 1.05; 200,000 walks 0.90
+//   both        47,000 walks: 128 M 1.17, 8 M 1.09, 0.8 M 1.07; 600 walks on 280 entries 0.96; 200 walks 0.98 to 1.07
+// p = q = 1 (every candidate is taken) 0.78 to 0.97.  q = 1, p = 2: 47,000 walks on 128 M entries 1.18, 64 bits 0.97, alias
+// table 1.50; 120,000 walks 0.95, alias table 1.15, on 280 entries 0.95.  q = 0.25, p = 4 on rows of 8 entries: 47,000
+// walks 0.95, 3000 walks 1.17, both 0.95.
 static bool reads_ahead(bool weighted, bool bits64, float p, float q, const WalkArgs& a) {
   // (every read is part of 16 bytes of one array; an alias table that is not interleaved takes two)
-  if (a.num_entries < ((int64_t)1 << (bits64 ? 24 : 22)) || a.num_nodes < 3 || (weighted && a.packed == nullptr)) return false;
-  if (a.num_walks < 1024 || a.num_walks > ((int64_t)1 << 17)) return false;
-  if (q != 1.0f) return true;
-  return p != 1.0f && (weighted || !bits64) && a.num_walks <= ((int64_t)1 << 16);
+  if (a.num_entries < 4 || a.num_nodes < 3 || (weighted && a.packed == nullptr)) return false;
+  if ((p == 1.0f && q == 1.0f) || a.num_walks > (int64_t)1 << 17) return false;
+  if (q == 1.0f && a.num_walks > (int64_t)3 << 15 && (bits64 || !weighted)) return false;
+  if (q < 1.0f && a.num_entries < 10 * a.num_nodes && (bits64 || a.num_walks > 4096)) return false;
+  if (weighted && !bits64) return a.num_walks >= 32 && a.num_entries >= 4096;
+  if (a.num_walks < 512) return false;
+  if (weighted) return a.num_entries >= (int64_t)3 << 18;
+  if (bits64) return q != 1.0f && a.num_entries >= (int64_t)1 << 23;
+  return a.num_entries >= (a.num_walks >= (1 << 14) ? (int64_t)3 << 19 : (int64_t)1 << 22);
 }
 
 template <typename OffT>

@@ -1,6 +1,6 @@
-"""The node2vec walker that reads ahead (graphs of at least 2^22 entries, 2^24 with 64-bit offsets, and 1024 to 2^17 walks) and, just outside
-its range, the other, against the CPU reference, bit for bit: rows at both ends of the arrays, dead ends,
-32- and 64-bit offsets, uniform and weighted draws, walks of one wave's width more than a full block."""
+"""The node2vec walker that reads ahead and, just outside its range, the other, against the CPU reference, bit for
+bit: around the limits in entries (2^22, 3 * 2^19 from 2^14 walks on, 2^23 with 64-bit offsets, 4096 and 3 * 2^18 with an alias
+table) and walks (32 with an alias table, 512, 2^17), rows at both ends of the arrays, dead ends, uniform and weighted draws."""
 import numpy as np
 import pytest
 import torch
@@ -22,12 +22,13 @@ def _graph(kind, n, entries):
     return rng.integers(0, n, entries).astype(np.int32), rng.integers(0, n, entries).astype(np.int32)
 
 
-@pytest.mark.parametrize("kind,n,entries,walks", [("even", 3, ENTRIES, 1024), ("even", 2, ENTRIES + 1, 1024),
-                                                  ("even", 5000, ENTRIES, 1087), ("even", 5000, ENTRIES - 1, 1087),
-                                                  ("even", 5000, ENTRIES + 3, 1023),
+@pytest.mark.parametrize("kind,n,entries,walks", [("even", 3, ENTRIES, 512), ("even", 2, ENTRIES + 1, 512),
+                                                  ("even", 60, 4096, 32), ("even", 60, 4095, 33), ("even", 60, 4097, 31),
+                                                  ("even", 5000, ENTRIES, 575), ("even", 5000, ENTRIES - 1, 575),
+                                                  ("even", 5000, ENTRIES + 3, 511), ("even", 5000, 3 << 19, 1 << 14), ("even", 5000, 3 << 18, 512),
                                                   ("dead-ends", 300_000, ENTRIES + 2, 131_072),
                                                   ("dead-ends", 300_000, ENTRIES + 2, 131_073),
-                                                  ("rows", 4096, 1 << 24, 1087)])
+                                                  ("dead-ends", 500_000, ENTRIES, 5_000), ("rows", 4096, 1 << 23, 575)])
 def test_same_walks(oracle, kind, n, entries, walks):
     from paper_2407_15452_amd import binding as gs
     w = np.random.default_rng(1).lognormal(0, 1, entries).astype(np.float32)
@@ -43,7 +44,7 @@ def test_same_walks(oracle, kind, n, entries, walks):
     nbrs = _dev(nb)
     prob, alias = _dev(table[0]), _dev(table[1])
     packed = gs.gs_alias_pack(prob, alias)
-    for p, q in ((0.5, 2.0), (2.0, 1.0), (1.0, 1.0)):
+    for p, q in ((0.5, 2.0), (2.0, 1.0), (4.0, 0.25), (1.0, 1.0)):
         for tab in (None, table):
             want = oracle.node2vec_walk(off, nb, starts, length, p, q, 5, alias=tab, walk_id_base=7)
             for dtype in (np.int32, np.int64):
