@@ -243,8 +243,8 @@ int32_t gs_sample_edges(const gs_csr* g, const gs_alias* edge_alias, int64_t num
  *   terms regrouped by destination row, a counter per key (two per node, or per
  *   key of the batch when the graph is much larger than the batch) and a side
  *   buffer for rows with many terms; or the terms as records in two sort buffers
- *   and the side buffer (large batches: from 4.7 million terms on, from 2^19 or
- *   2^20 on at most 2^16 nodes).
+ *   and the side buffer (large batches: from 4.7 million terms on, from 2^20 on at
+ *   most 2^16 nodes).
  * ------------------------------------------------------------------------ */
 size_t gs_sgns_step_workspace_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim,
                                     int32_t dtype);

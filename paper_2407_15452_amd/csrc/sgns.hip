@@ -1825,22 +1825,21 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
 }
 
 // Batches of at least this many terms take the sorted records: fewer where two passes sort them (up to
-// 2^16 rows), because few rows also mean busy counters.  Counters over records, 5 negatives, ids even and with
-// a density of 1 / sqrt(id).  Two passes: 65 k rows, 0.53 million terms 1.02 to 1.09 (16 to 256 columns); 30 k,
-// 0.65 million 0.96 to 1.03, 1.05 million 0.99 to 1.15; 10 k, 0.65 million 0.94 to 1.12, 1.05 million 1.09 to 1.24;
-// 3 k, 0.65 million 0.95 to 1.20, 1.05 million 1.11 to 1.54.  Three: 70 k to 100 k rows, 4.2 million 0.96 to 1.08,
-// 4.7 million 0.97 to 1.14; 300 k to 1 M, 4.2 million 1.01 to 1.11; 4 M, 4.2 million 0.97 to 1.09, 4.7 million
-// 0.99 to 1.10 (128 fp32 columns the least, 1.01 at 6 million and 1.04 to 1.07 from 12 million on).  Four passes
-// (over 2^24 rows): 17 M and 25 M rows, 4.7 million 1.02 to 1.12; 25 M of 256 bf16 columns, 22 million 8697 /
-// 7879 us; 100 M of 128 fp32 columns, 24 million 11866 / 10166 us.
-constexpr int64_t kSortedMinTerms = (int64_t)9 << 19;
-constexpr int64_t kSortedMinTermsTwoPasses = (int64_t)1 << 19, kSortedMinTermsFewRows = (int64_t)1 << 20;
-constexpr int64_t kSortedFewRows = (int64_t)1 << 15;
+// 2^16 rows), because few rows also mean busy counters.  Times of the counters over those of the records, batches of
+// walks and negatives on R-MAT graphs, 16 to 256 columns (least and most of them):
+//   two passes    0.65 M terms: 10 k rows, k = 1 0.85 to 0.94, k = 5 0.90 to 1.07
+//                 1.05 M terms: 5 k to 60 k rows, k = 1 0.96 to 1.05, 2 0.99 to 1.07, 5 1.04 to 1.12, 10 1.05 to 1.16
+//                 2.0 M terms: the same rows, k = 1 0.99 to 1.11, 5 1.05 to 1.23
+//   three passes  4.8 M terms: 100 k rows, k = 1 0.90 to 1.07, 5 0.99 to 1.06; 400 k 0.99 to 1.11; 1 M and 4 M 1.01 to 1.15
+//                 8 M terms: 100 k rows 1.02 to 1.21, 4 M 1.03 to 1.23
+//   four passes   4.8 M terms: 18 M rows 1.02 to 1.14, 16 M terms 1.06 to 1.16; 25 M rows of 256 bf16 columns, 22 M
+//                 terms 8697 / 7879 us; 100 M rows of 128 fp32 columns, 24 M terms 11866 / 10166 us
+// (Ids drawn one by one, evenly, on 4 M rows of 128 fp32 columns: 0.98 to 0.99 at 4.7 M to 6.6 M terms, 1.04 at 12 M.)
+constexpr int64_t kSortedMinTerms = (int64_t)9 << 19, kSortedMinTermsFewRows = (int64_t)3 << 21, kSortedFewRows = (int64_t)1 << 17;
+constexpr int64_t kSortedMinTermsTwoPasses = (int64_t)1 << 20;
 // Sorted terms per wave of the update: the ends of a slice cost four loads of keys (256 against 128 terms:
-// 2407 / 2425 us in the last case above), and a short batch has to make enough waves.
-static int sorted_slice_for(int64_t num_terms) {
-  return num_terms >= ((int64_t)1 << 22) ? 256 : (num_terms >= ((int64_t)1 << 20) ? 128 : 32);
-}
+// 2407 / 2425 us for 12 million terms on 4 M rows), and a short batch has to make enough waves.
+static int sorted_slice_for(int64_t num_terms) { return num_terms >= ((int64_t)1 << 22) ? 256 : 128; }
 
 static int bits_for_rows(int64_t num_nodes) {
   int b = 1;
@@ -1881,10 +1880,9 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
   return p;
 }
 static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
-  const bool two_passes = radix_sort_passes(bits_for_rows(num_nodes)) <= 2;
   const int64_t terms = num_pairs * (int64_t)(k + 1);
-  if (!two_passes) return terms >= kSortedMinTerms;
-  return terms >= (num_nodes <= kSortedFewRows ? kSortedMinTermsFewRows : kSortedMinTermsTwoPasses);
+  if (radix_sort_passes(bits_for_rows(num_nodes)) <= 2) return terms >= (k >= 2 ? kSortedMinTermsTwoPasses : 2 * kSortedMinTermsTwoPasses);
+  return terms >= (num_nodes <= kSortedFewRows ? kSortedMinTermsFewRows : kSortedMinTerms);
 }
 
 // Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every

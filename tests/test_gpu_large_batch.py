@@ -1,5 +1,5 @@
-"""The step on sorted records (batches of at least 9 * 2^19 terms, 2^19 on at most 2^16 rows, 2^20 on at most
-2^15) and just below, against the CPU reference: a handful of rows with everything in them, rows around the segment length (256 terms) and around slice borders,
+"""The step on sorted records (batches of at least 9 * 2^19 terms, 2^20 or, with at most one negative, 2^21 on at
+most 2^16 rows) and just below, against the CPU reference: a handful of rows with everything in them, rows around the segment length (256 terms) and around slice borders,
 rows of a few terms on a large table, both table types and the one-table step."""
 import numpy as np
 import pytest
@@ -27,8 +27,9 @@ def _ids(kind, n, count, rng):
 
 
 @pytest.mark.parametrize("kind,n,k,b", [("few", 7, 3, 1 << 18), ("few", 1, 3, 1 << 18),
-                                        ("even", 32_768, 3, (1 << 18) - 1), ("even", 32_769, 3, 1 << 17),
-                                        ("even", 65_536, 5, 87_382), ("even", 65_537, 5, 87_382),
+                                        ("even", 3_000, 1, (1 << 20) - 1), ("even", 3_000, 1, 1 << 20),
+                                        ("even", 65_536, 5, 174_762), ("even", 65_536, 5, 174_763),
+                                        ("even", 65_537, 5, 174_763),
                                         ("few", 7, 3, 1 << 20), ("segments", 18_000, 0, (1 << 22) + 1),
                                         ("even", 3_000, 5, 699_051), ("even", 700_000, 2, 1_572_864),
                                         ("even", 20_000_000, 6, 674_085)])

@@ -157,7 +157,7 @@ def test_workspace_of_a_large_batch_serves_smaller_ones(lib, nodes):
                lib.gs_sgns_step_from_walks_workspace_bytes, lib.gs_line1_step_workspace_bytes)
     for k, dim, dtype in ((0, 256, 0), (5, 256, 0), (5, 8, 1), (60, 512, 2)):
         ends = {1, 2, 1 << 18, 1 << 20, 49_152 // (k + 2), int((nodes << 17) ** 0.5) // (k + 2), nodes // 8 // (k + 2),
-                (1 << 19) // (k + 1), (1 << 20) // (k + 1), (9 << 19) // (k + 1), (1 << 21) // (k + 1), 3_000_000}
+                (1 << 20) // (k + 1), (1 << 21) // (k + 1), (9 << 19) // (k + 1), (3 << 21) // (k + 1), 3_000_000}
         ends |= {1 << s for s in range(1, 22)}
         sizes = sorted({e + d for e in ends for d in (-1, 0, 1, 2) if e + d > 0 and (e + d) * (k + 1) < 1 << 31})
         for query in queries:
