@@ -1,12 +1,15 @@
 // gs_random_walk / gs_node2vec_walk (GraphScale Sec. 2.2: DeepWalk-style walks
 // from every node and node2vec's biased second-order walk).
 //
-// One lane per walk.  Every transition is a chain of dependent random reads
+// Every transition is a chain of dependent random reads
 // (row bounds -> neighbour -> for node2vec, the previous node's row), each of
 // which costs a whole cache line from HBM, so throughput comes from many walks
-// in flight and from touching few lines per step.  Output rows are staged in LDS
+// in flight and from touching few lines per step; node2vec launches of few walks put several
+// lanes to one.  Output rows are staged in LDS
 // in windows of kWin positions and written out as 64-byte row segments instead
 // of one scattered 4-byte store per position.
+#include <type_traits>
+
 #include "common.h"
 
 namespace gs {
@@ -111,45 +114,83 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs a) {
   }
 }
 
-// Second-order walks as a per-lane state machine with ONE memory access
-// instruction per loop iteration.  A step of a walk is a chain of dependent random reads of
-// very different length (row bounds; one candidate per attempt, 3.5 attempts on
-// average at p=0.5, q=2; for a quarter of the attempts a search in the previous
-// node's row).  Written as nested loops, a wave waits in every inner loop for
-// its slowest lane and keeps about a third of its lanes busy.  Here every lane
-// carries its own state (which read it needs next), each iteration issues that
-// one read for all 64 lanes together, and the lane then moves to its next state;
-// lanes never wait for each other except at the one load per iteration.
-// The membership search in the previous node's row is an interpolation search (the ids of
-// a row are spread evenly over [0, num_nodes), so x is expected where a straight line
-// between the entries that bound the remaining range puts it; every third probe bisects
-// instead, which bounds the search on rows that are not spread evenly).  A probe reads four
-// neighbouring entries (one 16-byte access, the same cache line as a 4-byte one), and a
-// probe whose entries lie on both sides of x ends the search at once.
+typedef int32_t Quad __attribute__((ext_vector_type(4), aligned(4)));   // four entries, 4-byte aligned
+
+// Second-order walks, a step of which is a chain of dependent random reads of very different length: the row's
+// bounds, a candidate per attempt (3.7 attempts on average at p = 0.5, q = 2), for a quarter of the attempts a membership search
+// in the previous node's row, and an alias entry before every candidate of a weighted graph.  Two kernels:
+// a lane per walk where the walks fill the chip, a team of lanes per walk where they do not.
+//
+// The membership search is an interpolation search (the ids of a row are spread evenly over [0, num_nodes), so x
+// is expected where a straight line between the entries that bound the remaining range puts it; every
+// third probe bisects instead, which bounds the search on rows that are not spread evenly).  A probe reads
+// four neighbouring entries (one 16-byte access, the same cache line as a 4-byte one), and a probe whose
+// entries lie on both sides of x ends the search at once.  The state of a search: entries before L are < x, entries from
+// H on are > x; v_lo < x is the entry before L (or -1), v_hi > x the entry at H (or num_nodes).
+
+// the first of the four entries to read next; [L, H) is not empty, and the array has at least four
+template <typename Pos>
+__device__ __forceinline__ Pos probe_at(int32_t x, Pos L, Pos H, int32_t v_lo, int32_t v_hi, bool bisect, Pos entries) {
+  Pos p;
+  if (bisect) {
+    p = L + ((H - L) >> 1);
+  } else {
+    // (differences of ids and of -1 .. num_nodes, so below 2^32; a row that is not sorted may give anything.  Only a
+    // guess, so the approximate reciprocal will do)
+    const float part = (float)((uint32_t)x - (uint32_t)v_lo) * __builtin_amdgcn_rcpf((float)((uint32_t)v_hi - (uint32_t)v_lo));
+    p = L + (Pos)(fminf(fmaxf(part, 0.f), 1.f) * (float)(H - L));
+  }
+  p = min(max(p, L), H - 1);
+  return min((Pos)(p & ~(Pos)3), (Pos)(entries - 4));           // an aligned group, or the array's last four
+}
+// What the entries at pos say.  true: the search is over, and found says how
+template <typename Pos>
+__device__ __forceinline__ bool probe_says(int32_t x, Pos pos, Quad quad, Pos& L, Pos& H, int32_t& v_lo, int32_t& v_hi,
+                                           bool& found) {
+  // entries pos + i0 .. pos + i1 of the probe lie in the remaining range [L, H)
+  const int i0 = (int)(max(pos, L) - pos), i1 = (int)(min((Pos)(pos + 4), H) - 1 - pos);
+  int32_t first_v = 0, last_v = 0;
+  bool hit = false;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    hit = hit | ((q >= i0) & (q <= i1) & (quad[q] == x));
+    first_v = q == i0 ? quad[q] : first_v;
+    last_v = q == i1 ? quad[q] : last_v;
+  }
+  found = hit;
+  const bool left = x < first_v, right = x > last_v;            // (neither: x lies between two neighbouring entries)
+  if (left) { H = pos + i0; v_hi = first_v; }
+  else if (right) { L = pos + i1 + 1; v_lo = last_v; }
+  return hit || !(left || right) || L >= H;
+}
+
+// A lane per walk, as a state machine with ONE read instruction per trip through the loop.  Written as nested loops, a
+// wave waits in every inner loop for its slowest lane and keeps about a third of its lanes busy.  Here every
+// lane carries its own state (which read it needs next), each trip issues that one read for all 64 lanes
+// together, and the lane then moves to its next state; lanes never wait for each other except at the one read.
+// Whatever a lane needs (two row bounds, an alias entry, a neighbour, four entries of prev's row), it is part of 16
+// bytes of one array, so all lanes read through one instruction and a trip waits once; the random numbers of the attempt that
+// may come next are drawn while the read is under way.
 // Each lane stages its own last kWin positions in LDS and writes them out as one
 // 64-byte row segment when the window is full (or the walk is over).
-struct __attribute__((packed, aligned(4))) Quad { int32_t v[4]; };   // four entries, 4-byte aligned
-// kAhead: one read instruction per trip and random numbers drawn ahead, where that pays (reads_ahead()).
-template <typename OffT, bool kWeighted, bool kAhead>
+// Needs at least four entries and three nodes.
+template <typename OffT, bool kWeighted>
 __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
-  __shared__ int32_t tile[kWalkThreads / 64][64][kWinPad];
+  __shared__ int32_t tile[kWalkThreads][kWinPad];
   using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t i = ((int64_t)blockIdx.x * (kWalkThreads / 64) + wave) * 64 + lane;
+  const int64_t i = (int64_t)blockIdx.x * kWalkThreads + threadIdx.x;
   if (i >= a.num_walks) return;
   const uint64_t id = a.id_base + (uint64_t)i;
   const int32_t* __restrict__ nbrs = a.nbrs;
   const OffT* __restrict__ offsets = static_cast<const OffT*>(a.offsets);
+  const uint2* __restrict__ packed = a.packed;
   int32_t* __restrict__ out = a.walks + i * (int64_t)a.walk_len;
-  int32_t* mine = tile[wave][lane];
+  int32_t* mine = tile[threadIdx.x];
   const int32_t last = a.walk_len - 1;      // index of the last position
   const float bias_lo = fminf(1.0f, a.inv_q), bias_hi = fmaxf(1.0f, a.inv_q);
-
-  enum : int { kRow, kNewDraw, kAlias, kDraw, kSearch, kDone };
-  enum : int { kNone, kCommit, kReject };
-  const uint2* __restrict__ packed = a.packed;
   const Pos entries = (Pos)a.num_entries;
-  const bool wide = a.num_entries >= 4;     // (a probe never reads past the array)
+
+  enum : int { kRow, kAlias, kDraw, kSearch };
   int32_t cur = a.starts[i];
   if (cur < 0 || (int64_t)cur >= a.num_nodes) cur = -1;
   int32_t prev = -1;
@@ -157,32 +198,20 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   int32_t t = 0;                            // position of cur
   uint32_t att = 0;
   int state = kRow;
-  int decision = kNone;                     // what the last read decided: taken at the top of the loop
-  int32_t next = -1;                        // the node a commit moves to
+  bool fresh = false;                       // a new attempt begins
   mine[0] = cur;
   if (last == 0) { out[0] = cur; return; }
 
   // the attempt in flight
+  Block4 ahead = {0u, 0u, 0u, 0u};          // random numbers of the next one
   Pos j = 0;                                // slot in the row of cur
   uint32_t word2 = 0;                       // alias uniform (weighted)
   float s = 0.f;                            // acceptance uniform * max_bias
   int32_t x = 0;                            // candidate
-  // the membership search in flight: entries before L are < x, entries from H on are > x;
-  // v_lo < x is the entry before L (or -1), v_hi > x the entry at H (or num_nodes)
-  Pos L = 0, H = 0;
+  Pos L = 0, H = 0;                         // its membership search
   int32_t v_lo = 0, v_hi = 0;
-  int probes = 0;                           // probes made in this search
-  Pos pos = 0;                              // what this iteration reads: nbrs[pos] (or the alias entry at pos)
-
-  // kAhead: random numbers of the attempt after the one whose read is under way: the first of a step while
-  // its row bounds arrive, the next one while a candidate arrives (three of four are rejected at
-  // p = 0.5, q = 2); a membership search keeps those of its attempt's draw.  With 32-bit positions for
-  // 32-bit offsets, 1.49 -> 1.31 ms for the 47,000 walks below.
-  Block4 ahead = {0u, 0u, 0u, 0u};
-  auto draw_ahead = [&]() {
-    if (state == kRow || state == kDraw)
-      ahead = philox_at(a.seed, id, (uint32_t)t, state == kRow ? 0u : att + 1u);
-  };
+  int turn = 0;                             // every third probe bisects
+  Pos pos = 0;                              // what this trip reads: nbrs[pos] (or the alias entry at pos)
 
   // position t + 1 of the walk is `node`: into the lane's window, and out when it is full
   auto put = [&](int32_t node) {
@@ -195,199 +224,298 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
     }
   };
 
-  // Every stage below appears once, so a wave whose lanes are in different states runs each
-  // of them once per trip: the decision of the last read (a step taken, or an attempt
-  // rejected), the random numbers of a new attempt, the address of the next read, the read,
-  // and what the value read means for the lane's state.
   while (true) {
-    // ---- the decision of the last read ----------------------------------------------------
-    if (decision == kCommit) {
-      prev = cur; prev_lo = lo; prev_hi = hi;
-      cur = next;
-      att = 0;
-      put(cur);
-      state = (t == last) ? kDone : kRow;
-    } else if (decision == kReject) {
-      ++att;
-      state = kNewDraw;
+    if (state == kRow) {
+      if (cur < 0)                          // dead walk: -1 to the end
+        while (t < last) put(-1);
+      if (t == last) break;
     }
-    decision = kNone;
-    if (state == kRow && cur < 0) {          // dead walk: -1 to the end
-      while (t < last) put(-1);
-      state = kDone;
-    }
-    if (state == kDone) break;
-
-    // ---- arithmetic ahead of the read -----------------------------------------------------
-    if (state == kNewDraw) {
-      const Block4 b = kAhead ? ahead : philox_at(a.seed, id, (uint32_t)t, att);
-      j = row_slot(b, (Pos)(hi - lo));
-      word2 = b.x2;
-      s = unit_float(b.x3) * a.max_bias;
+    if (fresh) {
+      j = row_slot(ahead, (Pos)(hi - lo));
+      word2 = ahead.x2;
+      s = unit_float(ahead.x3) * a.max_bias;
       pos = lo + j;
       state = (kWeighted ? kAlias : kDraw);
-    } else if (state == kSearch) {           // (the range [L, H) is never empty here)
-      Pos p;
-      if (probes % 3 == 2) {
-        p = L + ((H - L) >> 1);
-      } else {
-        // (differences of ids and of -1 .. num_nodes, so below 2^32; a row that is not sorted may give anything)
-        const float part = fminf(fmaxf((float)((uint32_t)x - (uint32_t)v_lo) / (float)((uint32_t)v_hi - (uint32_t)v_lo), 0.f), 1.f);
-        p = L + (Pos)(part * (float)(H - L));
-      }
-      p = min(max(p, L), H - 1);
-      // the four entries around p: an aligned group, or the array's last four
-      pos = wide ? min((Pos)(p & ~(Pos)3), (Pos)(entries - 4)) : p;
+      fresh = false;
     }
 
-    // ---- the one read of this iteration ---------------------------------------------------
-    // Whatever a lane needs next (two row bounds, an alias entry, a neighbour, four entries of prev's
-    // row), it is part of 16 bytes of one array, so with kAhead all lanes read through one instruction
-    // and a trip waits once; reads in branches of their own wait one after the other (47,000 walks of 80
-    // nodes on a 4 M-node graph, bound by the chain of reads: 1.78 -> 1.49 ms).
-    Pos r0 = 0, r1 = 0;
-    int32_t v = 0;
-    Quad quad = {{0, 0, 0, 0}};
-    uint32_t e_prob = 0, e_alias = 0;
-    if constexpr (kAhead) {
-      const char* from;
-      int skip = 0;                           // 32-bit words in front of what is wanted
-      if (state == kRow) {
-        if (sizeof(OffT) == 8) {
-          from = reinterpret_cast<const char*>(offsets + cur);
-        } else {                              // (the last rows' bounds are the tail of the last 16 bytes)
-          const int32_t at = min(cur, (int32_t)(a.num_nodes - 3));
-          skip = cur - at;
-          from = reinterpret_cast<const char*>(offsets + at);
-        }
-      } else if (kWeighted && state == kAlias) {
-        const Pos at = min(pos, (Pos)(entries - 2));
-        skip = 2 * (int)(pos - at);
-        from = reinterpret_cast<const char*>(packed + at);
-      } else {                                // a probe's four entries; a neighbour among four that are aligned likewise
-        const Pos at = state == kSearch ? pos : min((Pos)(pos & ~(Pos)3), (Pos)(entries - 4));
-        skip = (int)(pos - at);
-        from = reinterpret_cast<const char*>(nbrs + at);
-      }
-      quad = *reinterpret_cast<const Quad*>(from);
-      draw_ahead();                           // (while the read is under way)
-      const int32_t w0 = skip == 0 ? quad.v[0] : (skip == 1 ? quad.v[1] : (skip == 2 ? quad.v[2] : quad.v[3]));
-      const int32_t w1 = skip == 0 ? quad.v[1] : (skip == 1 ? quad.v[2] : quad.v[3]);
-      v = w0;
-      e_prob = (uint32_t)w0;
-      e_alias = (uint32_t)w1;
+    // ---- the one read of this trip --------------------------------------------------------
+    const char* from;
+    int skip = 0;                           // 32-bit words in front of what is wanted
+    if (state == kRow) {
       if (sizeof(OffT) == 8) {
-        r0 = (Pos)(((uint64_t)(uint32_t)quad.v[1] << 32) | (uint32_t)quad.v[0]);
-        r1 = (Pos)(((uint64_t)(uint32_t)quad.v[3] << 32) | (uint32_t)quad.v[2]);
-      } else {
-        r0 = w0;
-        r1 = w1;
+        from = reinterpret_cast<const char*>(offsets + cur);
+      } else {                              // (the last rows' bounds are the tail of the last 16 bytes)
+        const int32_t at = min(cur, (int32_t)(a.num_nodes - 3));
+        skip = cur - at;
+        from = reinterpret_cast<const char*>(offsets + at);
       }
-    } else if (state == kSearch) {
-      if (wide) quad = *reinterpret_cast<const Quad*>(nbrs + pos);
-      else quad.v[0] = nbrs[pos];
-    } else if (state == kRow) {
-      r0 = offsets[cur];
-      r1 = offsets[(int64_t)cur + 1];
-    } else if (kWeighted && state == kAlias) {
-      if (packed != nullptr) { const uint2 e = packed[pos]; e_prob = e.x; e_alias = e.y; }
-      else { e_prob = __float_as_uint(a.prob[pos]); e_alias = (uint32_t)a.alias[pos]; }
-    } else {
-      v = nbrs[pos];
+    } else if (kWeighted && state == kAlias && packed != nullptr) {
+      const Pos at = min(pos, (Pos)(entries - 2));
+      skip = 2 * (int)(pos - at);
+      from = reinterpret_cast<const char*>(packed + at);
+    } else {                                // a probe's four entries; a neighbour among four that are aligned likewise
+      Pos at;
+      if (state == kSearch) at = pos = probe_at(x, L, H, v_lo, v_hi, turn == 2, entries);
+      else at = min((Pos)(pos & ~(Pos)3), (Pos)(entries - 4));
+      skip = (int)(pos - at);
+      from = reinterpret_cast<const char*>(nbrs + at);
+      if (kWeighted && state == kAlias) from = reinterpret_cast<const char*>(a.prob + at);
     }
+    const Quad quad = *reinterpret_cast<const Quad*>(from);
+    uint32_t other = 0;                     // (a table that is not interleaved takes a second read)
+    if (kWeighted && state == kAlias && packed == nullptr) other = (uint32_t)a.alias[pos];
+    // while it is under way: the first attempt of the next step, or the one after the one at hand
+    if (state == kRow || state == kDraw)
+      ahead = philox_at(a.seed, id, (uint32_t)t, state == kRow ? 0u : att + 1u);
+    const int32_t w0 = skip == 0 ? quad[0] : (skip == 1 ? quad[1] : (skip == 2 ? quad[2] : quad[3]));
+    const int32_t w1 = skip == 0 ? quad[1] : (skip == 1 ? quad[2] : quad[3]);
 
-    // ---- consume it: new state, or a decision ----------------------------------------------
-    bool known = false, member = false;      // membership of x in the row of prev has been settled
-    switch (state) {
-      case kRow:
-        lo = r0; hi = r1;
-        if (hi > lo) state = kNewDraw;
-        else { decision = kCommit; next = -1; }                    // dead end
-        break;
-      case kAlias:
-        if (!(unit_float(word2) < __uint_as_float(e_prob))) j = (Pos)(int32_t)e_alias;
-        pos = lo + j;
-        state = kDraw;
-        break;
-      case kDraw:
-        x = v;
-        next = x;
-        // a neighbour id that is not a node (a CSR not built by gs_csr_build) ends the walk
-        if ((uint32_t)x >= (uint32_t)a.num_nodes) { decision = kCommit; next = -1; break; }
-        if (t == 0 || att == kMaxAttempts - 1) { decision = kCommit; break; }   // unbiased first step; last attempt is taken
-        // accept iff s < bias(x).  For x != prev the bias is 1 or 1/q, so the
-        // membership search is only needed when s falls between the two.
-        if (x == prev) { decision = (s < a.inv_p) ? kCommit : kReject; break; }
-        if (s < bias_lo) { decision = kCommit; break; }
-        if (!(s < bias_hi)) { decision = kReject; break; }
-        L = prev_lo; H = prev_hi;
-        if (L >= H) { known = true; break; }                       // (prev has no row: cannot happen after a step)
-        v_lo = -1;
-        v_hi = (int32_t)a.num_nodes;
-        probes = 0;
-        state = kSearch;
-        break;
-      case kSearch: {
-        // entries pos + i0 .. pos + i1 of the probe lie in the remaining range [L, H)
-        const int width = wide ? 4 : 1;
-        const int i0 = (int)(max(pos, L) - pos), i1 = (int)(min((Pos)(pos + width), H) - 1 - pos);
-        bool found = false;
-        int32_t first_v = 0, last_v = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          found = found || (q >= i0 && q <= i1 && quad.v[q] == x);
-          if (q == i0) first_v = quad.v[q];
-          if (q == i1) last_v = quad.v[q];
-        }
-        ++probes;
-        if (found) { known = true; member = true; break; }
-        if (x < first_v) { H = pos + i0; v_hi = first_v; }
-        else if (x > last_v) { L = pos + i1 + 1; v_lo = last_v; }
-        else known = true;                  // x lies between two neighbouring entries
-        if (L >= H) known = true;
-        break;
+    // ---- what it means ----------------------------------------------------------------------
+    bool taken = false;                     // the walk moves to x
+    if (state == kRow) {
+      if (sizeof(OffT) == 8) {
+        lo = (Pos)(((uint64_t)(uint32_t)quad[1] << 32) | (uint32_t)quad[0]);
+        hi = (Pos)(((uint64_t)(uint32_t)quad[3] << 32) | (uint32_t)quad[2]);
+      } else {
+        lo = w0;
+        hi = w1;
       }
-      default:
-        break;
+      att = 0;
+      fresh = hi > lo;
+      taken = !fresh;                       // dead end
+      x = -1;
+    } else if (kWeighted && state == kAlias) {
+      if (!(unit_float(word2) < __uint_as_float((uint32_t)w0))) j = (Pos)(int32_t)(packed != nullptr ? (uint32_t)w1 : other);
+      pos = lo + j;
+      state = kDraw;
+    } else {
+      bool known = false, member = false;   // membership of x in the row of prev has been settled
+      bool decided = true;
+      if (state == kDraw) {
+        x = w0;
+        if ((uint32_t)x >= (uint32_t)a.num_nodes) {
+          x = -1;                           // not a node (a CSR not built by gs_csr_build): ends the walk
+          taken = true;
+        } else if (t == 0 || att == kMaxAttempts - 1) {
+          taken = true;                     // unbiased first step; the last attempt is taken
+        } else if (x == prev) {
+          taken = s < a.inv_p;
+        } else if (s < bias_lo) {           // for x != prev the bias is 1 or 1/q: the search is only
+          taken = true;                     // needed when s falls between the two
+        } else if (s < bias_hi) {
+          L = prev_lo; H = prev_hi;
+          v_lo = -1; v_hi = (int32_t)a.num_nodes;
+          known = L >= H;             // (prev has no row: cannot happen after a step)
+          decided = known;
+          state = kSearch;
+          turn = 0;
+        }
+      } else {
+        known = probe_says(x, pos, quad, L, H, v_lo, v_hi, member);
+        decided = known;
+        turn = turn == 2 ? 0 : turn + 1;
+      }
+      if (known) taken = s < (member ? 1.0f : a.inv_q);
+      if (decided && !taken) {
+        ++att;
+        fresh = true;
+      }
     }
-    if (known) decision = (s < (member ? 1.0f : a.inv_q)) ? kCommit : kReject;
+    if (taken) {
+      prev = cur; prev_lo = lo; prev_hi = hi;
+      cur = x;
+      put(cur);
+      state = kRow;
+    }
   }
 }
 
-// One read instruction for all states and an attempt drawn ahead cost instructions on every trip and pay where a
-// trip waits for memory: waves that are full but few (two per SIMD are 2^17 walks), attempts that are rejected, rows
-// beyond the caches; sooner with alias tables (a read more per attempt), later with 64-bit offsets (more
-// arithmetic).  Times of reads in branches of their own over times of one read ahead, R-MAT graphs, walks of 20 to 80
-// nodes, p = 0.5, q = 2 unless stated:
-//   unweighted  47,000 walks: 128 M entries 1.26, 3.2 M 1.13, 1.6 M 1.08, 0.4 M 0.97; 1000 walks: 128 M 1.17, 6 M 0.97;
-//               200,000 walks 0.91; 10 walks 0.91
-//   64 bits     47,000 walks: 128 M 1.07, 8 M 1.04, 0.4 M 0.94; 10 walks 0.91
-//   alias       47,000 walks: 128 M 1.47, 8 M 1.34, 0.4 M 1.14; 40 walks 1.05; 200,000 walks 0.90
-//   both        47,000 walks: 128 M 1.17, 8 M 1.09, 0.8 M 1.07; 600 walks on 280 entries 0.96; 200 walks 0.98 to 1.07
-// p = q = 1 (every candidate is taken) 0.78 to 0.97.  q = 1, p = 2: 47,000 walks on 128 M entries 1.18, 64 bits 0.97, alias
-// table 1.50; 120,000 walks 0.95, alias table 1.15, on 280 entries 0.95.  q = 0.25, p = 4 on rows of 8 entries: 47,000
-// walks 0.95, 3000 walks 1.17, both 0.95.
-static bool reads_ahead(bool weighted, bool bits64, float p, float q, const WalkArgs& a) {
-  // (every read is part of 16 bytes of one array; an alias table that is not interleaved takes two)
-  if (a.num_entries < 4 || a.num_nodes < 3 || (weighted && a.packed == nullptr)) return false;
-  if ((p == 1.0f && q == 1.0f) || a.num_walks > (int64_t)1 << 17) return false;
-  if (q == 1.0f && a.num_walks > (int64_t)3 << 15 && (bits64 || !weighted)) return false;
-  if (q < 1.0f && a.num_entries < 10 * a.num_nodes && (bits64 || a.num_walks > 4096)) return false;
-  if (weighted && !bits64) return a.num_walks >= 32 && a.num_entries >= 4096;
-  if (a.num_walks < 512) return false;
-  if (weighted) return a.num_entries >= (int64_t)3 << 18;
-  if (bits64) return q != 1.0f && a.num_entries >= (int64_t)1 << 23;
-  return a.num_entries >= (a.num_walks >= (1 << 14) ? (int64_t)3 << 19 : (int64_t)1 << 22);
+// A team of kTeam lanes per walk, for launches whose walks do not fill the chip and wait for their chains of reads.  The
+// random numbers of an attempt depend on nothing but its number, so lane l of a team makes attempt att + l: the
+// candidates of kTeam attempts are under way at once, and the walk takes the first of them, in order of their numbers, that
+// is accepted.  An attempt whose acceptance uniform is below every bias is accepted whatever its candidate is, so the
+// lanes behind the first such one read nothing: no more lines are fetched than one attempt after the other would.
+// Lanes whose candidate needs the membership search search side by side, as long as no attempt before theirs is accepted.
+// The walks of a wave advance in lock step (most steps take one round of attempts), which leaves few instructions
+// per step: row bounds, draw, one read of candidates, votes.
+template <int kTeam>
+__device__ __forceinline__ uint32_t first_in_team(bool vote, int base) {     // ~0u: none
+  const uint64_t votes = __ballot(vote);
+  if constexpr (kTeam == 64) return votes != 0ull ? (uint32_t)__builtin_ctzll(votes) : ~0u;
+  const uint32_t own = (uint32_t)(votes >> base) & (uint32_t)((1ull << (kTeam & 63)) - 1ull);
+  return (uint32_t)(__ffs((int)own) - 1);
+}
+// x of the team's lane `who` (anything if ~0u)
+template <int kTeam>
+__device__ __forceinline__ int32_t from_lane(int32_t x, uint32_t who, uint32_t sub, int base) {
+  if constexpr (kTeam > 16) return __shfl(x, base + (int)(who & 63u), 64);
+  uint32_t v = sub == who ? (uint32_t)x : 0u;
+  auto step = [&](auto ctrl) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF, 0xF, true);
+  };
+  if constexpr (kTeam >= 2) step(std::integral_constant<int, 0xB1>());     // quad_perm [1,0,3,2]
+  if constexpr (kTeam >= 4) step(std::integral_constant<int, 0x4E>());     // quad_perm [2,3,0,1]
+  if constexpr (kTeam >= 8) step(std::integral_constant<int, 0x141>());    // row_half_mirror
+  if constexpr (kTeam >= 16) step(std::integral_constant<int, 0x140>());   // row_mirror
+  return (int32_t)v;
+}
+
+template <typename OffT, bool kWeighted, int kTeam>
+__global__ __launch_bounds__(kWalkThreads) void node2vec_team_kernel(WalkArgs a) {
+  constexpr int kTeams = kWalkThreads / kTeam;
+  static_assert(kMaxAttempts % kTeam == 0, "the last attempt belongs to a team's last lane");
+  __shared__ int32_t tile[kTeams][kWinPad];
+  using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
+  const int lane = threadIdx.x & 63, base = lane & ~(kTeam - 1);
+  const uint32_t sub = lane & (kTeam - 1);
+  const int64_t i = (int64_t)blockIdx.x * kTeams + (int)threadIdx.x / kTeam;
+  const bool live = i < a.num_walks;
+  const uint64_t id = a.id_base + (uint64_t)i;
+  const int32_t* __restrict__ nbrs = a.nbrs;
+  const OffT* __restrict__ offsets = static_cast<const OffT*>(a.offsets);
+  int32_t* __restrict__ out = a.walks + i * (int64_t)a.walk_len;
+  int32_t* mine = tile[(int)threadIdx.x / kTeam];      // (every lane of the team writes all of it, the same values)
+  const int32_t last = a.walk_len - 1;      // index of the last position
+  const float bias_lo = fminf(1.0f, a.inv_q), bias_hi = fmaxf(1.0f, a.inv_q), bias_min = fminf(a.inv_p, bias_lo);
+  const Pos entries = (Pos)a.num_entries;
+  const bool wide = a.num_entries >= 4;     // (a probe reads four entries)
+
+  int32_t cur = -1, prev = -1;
+  if (live) {
+    cur = a.starts[i];
+    if (cur < 0 || (int64_t)cur >= a.num_nodes) cur = -1;
+  }
+  Pos prev_lo = 0, prev_hi = 0;
+  for (int32_t t = 0;; ++t) {
+    const int col = t & (kWin - 1);
+    mine[col] = cur;
+    if (col == kWin - 1 || t == last) {
+      const int32_t first = t - col;
+      if (live)
+        for (int c = (int)sub; c <= col; c += kTeam) out[first + c] = mine[c];
+    }
+    if (t == last) break;
+    Pos lo = 0, hi = 0;
+    if (cur >= 0) {
+      const OffsetPair<OffT> row = *reinterpret_cast<const OffsetPair<OffT>*>(offsets + cur);
+      lo = row.lo;
+      hi = row.hi;
+    }
+    Block4 b = philox_at(a.seed, id, (uint32_t)t, sub);         // (while the bounds are under way)
+    bool pending = hi > lo;                 // (the same in all lanes of a team)
+    int32_t next = -1;
+    for (uint32_t att = sub; __ballot(pending) != 0ull;) {
+      Pos j = row_slot(b, (Pos)(hi - lo));
+      const float s = unit_float(b.x3) * a.max_bias;
+      // unbiased first step; the last attempt is taken
+      const bool sure = pending && (t == 0 || s < bias_min || att == kMaxAttempts - 1);
+      const bool reads = pending && sub <= first_in_team<kTeam>(sure, base);
+      int32_t x = -1;
+      if (reads) {
+        if (kWeighted) j = (Pos)alias_pick(a, (int64_t)(lo + j), (int64_t)j, b.x2);
+        x = nbrs[lo + j];
+      }
+      bool accepted = false, open = false;
+      if ((uint32_t)x >= (uint32_t)a.num_nodes) { x = -1; accepted = reads; }   // not a node (a CSR not built by gs_csr_build): ends the walk
+      else if (sure) accepted = true;
+      else if (x == prev) accepted = s < a.inv_p;
+      else if (s < bias_lo) accepted = true;                    // for x != prev the bias is 1 or 1/q: the search is
+      else open = s < bias_hi;                                  // only needed when s falls between the two
+      uint32_t winner = first_in_team<kTeam>(accepted, base);
+      open = open && sub < winner;
+      if (__ballot(open) != 0ull) {
+        Pos L = prev_lo, H = prev_hi;
+        int32_t v_lo = -1, v_hi = (int32_t)a.num_nodes;
+        if (open && (L >= H || !wide)) {    // (prev has a row after a step)
+          bool member = false;
+          for (Pos e = L; e < H; ++e) member = member || nbrs[e] == x;
+          open = false;
+          accepted = s < (member ? 1.0f : a.inv_q);
+        }
+        for (int turn = 0;; turn = turn == 2 ? 0 : turn + 1) {                      // every third probe bisects
+          if (open) {
+            const Pos pos = probe_at(x, L, H, v_lo, v_hi, turn == 2, entries);
+            const Quad quad = *reinterpret_cast<const Quad*>(nbrs + pos);
+            bool member;
+            if (probe_says(x, pos, quad, L, H, v_lo, v_hi, member)) {
+              open = false;
+              accepted = s < (member ? 1.0f : a.inv_q);
+            }
+          }
+          winner = first_in_team<kTeam>(accepted, base);
+          open = open && sub < winner;
+          if (__ballot(open) == 0ull) break;
+        }
+      }
+      const int32_t moved = from_lane<kTeam>(x, winner, sub, base);
+      if (pending && winner != ~0u) { next = moved; pending = false; }
+      if (__ballot(pending) == 0ull) break;
+      att += kTeam;
+      b = philox_at(a.seed, id, (uint32_t)t, att);
+    }
+    prev = cur; prev_lo = lo; prev_hi = hi;
+    cur = next;
+  }
+}
+
+// Lanes per walk; 0: the state machine, a lane per walk.  Wide teams have the candidates of more attempts under way and
+// cost instructions and lines for attempts that do not matter, so they pay while few walks share the chip, and the
+// more attempts a step takes.  Most candidates are no neighbours of prev, so that is about max_bias * q of them: 4 at p =
+// 0.5, q = 2, 1 at p = 4, q = 0.25.  Microseconds of 40 nodes per walk, R-MAT graph of 4 M nodes and 140 M entries (alias tables: 1 M
+// nodes, 22 M entries); the kernel that was there before, a lane per walk with a read per state or one read per trip: 637
+// for 10 walks of 80 nodes at p = 0.5, q = 2, 1245 for 47,000, 1868 for 200,000, and these: 119, 552, 1578.
+//   p 0.5, q 2   1000 walks: teams of 64 66, 16 100, 8 140, a lane 475; 6000: 64 119, 32 118, 16 135; 10,000: 64 167, 32 136, 16 142, 8
+//                192; 20,000: 32 218, 16 170, 8 207; 47,000: 16 323, 8 273, 4 409, a lane 563; 150,000: 16 821, 8 669, 4 779, a lane 711;
+//                200,000: 8 862, a lane 789; 1 M: 4 3558, a lane 3091; alias tables, 300,000: 4 1184, a lane 1550, 1 M: 3539, 4451
+//   p 4, q 0.25  20,000 walks: 16 190, 8 194, 4 228; 60,000: 8 274, 4 302; 100,000: 8 451, 4 355, 2 451; 300,000: 4 933, 2 858, a lane
+//                1016; alias tables, 60,000: 8 401, 4 320; 300,000: 4 1108, 2 943, a lane 1606
+//   p 1, q 2     30,000 walks: 16 204, 8 180, 4 221; 150,000: 8 554, 4 490, a lane 528; 300,000: 4 768, 2 908, a lane 813
+// Where every candidate other than prev is accepted (the least bias of those is the greatest of all) rounds hardly
+// repeat: p = 2, q = 1, 10,000 walks: 4 45, 1 59; 30,000: 4 50, 1 68, a lane 100; 100,000: 4 121, 1 102, a lane 129; p = q = 1,
+// 1 M: 1 765, a lane 845.
+// (Offsets of 64 bits, 10,000-node graphs: the same order.)
+static int team_size(bool weighted, float q, const WalkArgs& a) {
+  const int64_t walks = a.num_walks;
+  if (a.max_bias <= fminf(1.0f, a.inv_q)) return walks <= (int64_t)3 << 14 ? 4 : 1;
+  const bool many_attempts = a.max_bias * q >= 3.0f;
+  if (walks <= (int64_t)1 << 12) return 64;
+  if (walks <= (int64_t)3 << 12) return 32;
+  if (walks <= (int64_t)3 << 13) return 16;
+  if (walks <= (many_attempts ? (int64_t)5 << 15 : (int64_t)3 << 14)) return 8;
+  if (!many_attempts && walks <= (int64_t)1 << 18) return 4;
+  if (weighted) return many_attempts ? 4 : 2;
+  return a.num_entries >= 4 && a.num_nodes >= 3 ? 0 : 1;         // (what one read of the state machine needs)
+}
+
+template <typename OffT, bool kWeighted, int kTeam>
+static void launch_team(const WalkArgs& a, hipStream_t stream) {
+  node2vec_team_kernel<OffT, kWeighted, kTeam>
+      <<<(unsigned)ceil_div(a.num_walks, kWalkThreads / kTeam), kWalkThreads, 0, stream>>>(a);
+}
+
+template <typename OffT, bool kWeighted>
+static void launch_node2vec(int team, const WalkArgs& a, hipStream_t stream) {
+  switch (team) {
+    case 1: return launch_team<OffT, kWeighted, 1>(a, stream);
+    case 2: return launch_team<OffT, kWeighted, 2>(a, stream);
+    case 4: return launch_team<OffT, kWeighted, 4>(a, stream);
+    case 8: return launch_team<OffT, kWeighted, 8>(a, stream);
+    case 16: return launch_team<OffT, kWeighted, 16>(a, stream);
+    case 32: return launch_team<OffT, kWeighted, 32>(a, stream);
+    case 64: return launch_team<OffT, kWeighted, 64>(a, stream);
+    default:
+      node2vec_kernel<OffT, kWeighted><<<(unsigned)ceil_div(a.num_walks, kWalkThreads), kWalkThreads, 0, stream>>>(a);
+  }
 }
 
 template <typename OffT>
-static void launch_walk(bool weighted, bool second, float p, float q, const WalkArgs& a, hipStream_t stream) {
+static void launch_walk(bool weighted, bool second, float q, const WalkArgs& a, hipStream_t stream) {
   const unsigned blocks = (unsigned)ceil_div(a.num_walks, kWalkThreads);
   if (second) {
-    const bool ahead = reads_ahead(weighted, sizeof(OffT) == 8, p, q, a);
-    auto kernel = weighted ? (ahead ? node2vec_kernel<OffT, true, true> : node2vec_kernel<OffT, true, false>)
-                           : (ahead ? node2vec_kernel<OffT, false, true> : node2vec_kernel<OffT, false, false>);
-    kernel<<<blocks, kWalkThreads, 0, stream>>>(a);
+    const int team = team_size(weighted, q, a);
+    if (weighted) launch_node2vec<OffT, true>(team, a, stream);
+    else launch_node2vec<OffT, false>(team, a, stream);
   } else {
     if (weighted) walk_kernel<OffT, true><<<blocks, kWalkThreads, 0, stream>>>(a);
     else walk_kernel<OffT, false><<<blocks, kWalkThreads, 0, stream>>>(a);
@@ -424,8 +552,8 @@ static int32_t walk_common(const gs_csr* g, const gs_alias* al, const int32_t* s
   a.inv_p = 1.0f / p;
   a.inv_q = 1.0f / q;
   a.max_bias = fmaxf(a.inv_p, fmaxf(1.0f, a.inv_q));
-  if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, p, q, a, stream);
-  else launch_walk<int32_t>(weighted, second, p, q, a, stream);
+  if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, q, a, stream);
+  else launch_walk<int32_t>(weighted, second, q, a, stream);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
