@@ -15,16 +15,21 @@
 //    round(w / u) to it, where only an exact tie depends on N, and only on whether N is even.  A run of
 //    weights is therefore the pair of whole numbers it adds to an even and to an odd N, and such
 //    pairs combine in any grouping that keeps their order.  Stretches in which the sum leaves its
-//    binade (at most one per doubling of the sum) are added one by one.
+//    binade (at most one per doubling of the sum) are added one by one.  Most weights do without: where
+//    every partial sum in any grouping is exact (any_order below), any order gives S.
+//  * While the larges are fewer than the smalls, whole runs of rounds are one chain of additions per large
+//    (rounds_of_few_larges below).
 //
 // Segments of up to kLaneSegment entries are built by one lane each, up to kWaveSegment by one wave
 // in LDS, longer ones (the rows of hub nodes) by a workgroup of 1024 lanes; a very long one that is
 // alone in its call (the noise table) gets its sum, its lists and its first rounds from the whole chip.
 // All are bound by latency, so the limits lie where the next larger team finishes the longest segment
-// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 1.9 ms (lanes 0.29, waves
-// 0.20 + 0.45, workgroups 0.92), against 9.5 ms with one lane per row up to 8191 entries; the noise table
-// of 1 M entries 2.5 ms (sum 0.45, lists and 16 rounds 0.28, the rest 1.77 in one workgroup), against 18.0
-// ms in one workgroup whose lane 0 summed the weights and ran the narrow stretches from global memory.
+// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 0.86 ms (lanes 0.12, waves
+// 0.11 + 0.19, workgroups 0.41), 1.9 ms (0.29, 0.20 + 0.45, 0.92) with lists in global memory for the lanes, sums in index order and
+// a look at all lists in every round; the noise table of 1 M entries 0.72 ms (sum 0.02, lists and 16 rounds of the chip 0.18, few
+// larges 0.47), 2.5 ms before; that of 4 M nodes 1.6 ms, 7.1 before.
+#include <type_traits>
+
 #include "common.h"
 
 namespace gs {
@@ -33,66 +38,67 @@ constexpr int64_t kLaneSegment = 32;
 constexpr int kWaveSegment = 2048;
 
 // ---- one lane per segment ------------------------------------------------------------------
+// Masses and both lists in LDS, entry i of lane l at [i][l].  (In global scratch every step of the loop below
+// is a chain of reads of cache lines of its own.)
 template <typename OffT>
 __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict__ seg_offsets,
                                                          int64_t num_segments,
                                                          const float* __restrict__ weights,
                                                          float* __restrict__ prob_out,
-                                                         int32_t* __restrict__ alias_out,
-                                                         double* __restrict__ mass_ws,
-                                                         int32_t* __restrict__ small_ws,
-                                                         int32_t* __restrict__ large_ws) {
+                                                         int32_t* __restrict__ alias_out) {
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int kMost = (int)kLaneSegment;
+  static_assert((kMost & (kMost - 1)) == 0, "the list of larges wraps by a mask");
+  __shared__ double mass[kMost][64];
+  __shared__ uint8_t small_q[kMost][64];       // every entry enters at most once: no wrap
+  __shared__ uint8_t large_q[kMost][64];
+  const int lane = threadIdx.x;
+  const int64_t s = (int64_t)blockIdx.x * 64 + lane;
   if (s >= num_segments) return;
   const int64_t begin = (int64_t)seg_offsets[s];
-  const int64_t n = (int64_t)seg_offsets[s + 1] - begin;
-  if (n <= 0 || n > kLaneSegment) return;
+  const int64_t size = (int64_t)seg_offsets[s + 1] - begin;
+  if (size <= 0 || size > kLaneSegment) return;
+  const int n = (int)size;
   const float* w = weights + begin;
   float* prob = prob_out + begin;
   int32_t* alias = alias_out + begin;
-  double* mass = mass_ws + begin;
-  int32_t* small_q = small_ws + begin;   // every entry enters at most once: no wrap
-  int32_t* large_q = large_ws + begin;   // ring of capacity n
 
   double S = 0.0;
-  for (int64_t i = 0; i < n; ++i) S += (double)w[i];
-  int64_t small_head = 0, small_tail = 0;
-  int64_t large_head = 0, large_count = 0;
   const double dn = (double)n;
-  for (int64_t i = 0; i < n; ++i) {
-    const double m = (double)w[i] * dn;
-    mass[i] = m;
-    if (m < S) small_q[small_tail++] = (int32_t)i;
-    else large_q[large_count++] = (int32_t)i;
-  }
-  while (small_head < small_tail && large_count > 0) {
-    const int32_t a = small_q[small_head++];
-    const int32_t b = large_q[large_head];
-    large_head = (large_head + 1 == n) ? 0 : large_head + 1;
-    --large_count;
-    const double ma = mass[a];
-    prob[a] = (float)(ma / S);
-    alias[a] = b;
-    const double mb = (mass[b] + ma) - S;
-    mass[b] = mb;
-    if (mb < S) {
-      small_q[small_tail++] = b;
-    } else {
-      int64_t at = large_head + large_count;
-      if (at >= n) at -= n;
-      large_q[at] = b;
-      ++large_count;
+  for (int i0 = 0; i0 < n; i0 += 4) {          // (four reads under way at a time)
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = w[min(i0 + k, n - 1)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i0 + k >= n) break;
+      S += (double)v[k];
+      mass[i0 + k][lane] = (double)v[k] * dn;
     }
   }
+  int small_head = 0, small_tail = 0, large_head = 0, large_tail = 0;
+  for (int i = 0; i < n; ++i) {
+    if (mass[i][lane] < S) small_q[small_tail++][lane] = (uint8_t)i;
+    else large_q[large_tail++][lane] = (uint8_t)i;
+  }
+  while (small_head < small_tail && large_head < large_tail) {
+    const int a = small_q[small_head++][lane];
+    const int b = large_q[large_head++ & (kMost - 1)][lane];
+    const double ma = mass[a][lane];
+    prob[a] = (float)(ma / S);
+    alias[a] = b;
+    const double mb = (mass[b][lane] + ma) - S;
+    mass[b][lane] = mb;
+    if (mb < S) small_q[small_tail++][lane] = (uint8_t)b;
+    else large_q[large_tail++ & (kMost - 1)][lane] = (uint8_t)b;
+  }
   for (; small_head < small_tail; ++small_head) {
-    const int32_t i = small_q[small_head];
+    const int i = small_q[small_head][lane];
     prob[i] = 1.0f;
     alias[i] = i;
   }
-  for (; large_count > 0; --large_count) {
-    const int32_t i = large_q[large_head];
-    large_head = (large_head + 1 == n) ? 0 : large_head + 1;
+  for (; large_head < large_tail; ++large_head) {
+    const int i = large_q[large_head & (kMost - 1)][lane];
     prob[i] = 1.0f;
     alias[i] = i;
   }
@@ -103,6 +109,23 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sums that no order changes.  Every weight is a whole multiple of u = 2^(least exponent - 23); while the sum of the
+// weights stays below 2^53 u, every partial sum in every grouping is a whole number of units below 2^53,
+// which fp64 holds exactly, so any order gives the index-order sum.  (The check is sound on the computed
+// sum: rounding is monotonic, so a partial sum that reached 2^53 u would leave the result there.)  Weights of 1 and more with
+// a sum below 2^30 pass, as do lognormal weights of a few million entries.
+// The exponent field of a weight; of zeros (multiples of anything) the largest; 0 only for weights below zero
+__device__ __forceinline__ int weight_exponent(float v) {
+  const uint32_t bits = __float_as_uint(v);
+  if ((bits & 0x7fffffffu) == 0u) return 255;
+  if (bits >> 31) return 0;
+  return max(1, (int)(bits >> 23));
+}
+__device__ __forceinline__ bool any_order(double sum, int least_exponent) {      // (false for infinities and NaN)
+  return least_exponent > 0 &&
+         sum < __longlong_as_double((long long)(uint64_t)(least_exponent - 127 - 23 + 53 + 1023) << 52);
 }
 
 // ---- one wave per segment --------------------------------------------------------------------
@@ -139,11 +162,25 @@ __global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __rest
     int32_t* alias = alias_out + begin;
     const double dn = (double)n;
     double S = 0.0;
-    for (int base = 0; base < n; base += 64) {
-      const double v = base + lane < n ? (double)w[base + lane] : 0.0;
+    int least = 255;
+    for (int base = lane; base < n; base += 64) {
+      const float v = w[base];
+      mass[base] = (double)v * dn;
+      S += (double)v;
+      least = min(least, weight_exponent(v));
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+      S += __shfl_xor(S, d, 64);
+      least = min(least, __shfl_xor(least, d, 64));
+    }
+    if (!any_order(S, least)) {
+      S = 0.0;
+      for (int base = 0; base < n; base += 64) {
+        const double v = base + lane < n ? (double)w[base + lane] : 0.0;
 #pragma unroll 16
-      for (int k = 0; k < 64; ++k) S += lane_value(v, k);       // (+ 0.0 behind the end changes nothing)
-      if (base + lane < n) mass[base + lane] = v * dn;
+        for (int k = 0; k < 64; ++k) S += lane_value(v, k);       // (+ 0.0 behind the end changes nothing)
+      }
     }
     int sh = 0, st = 0, lh = 0, lt = 0;        // heads and tails of the lists, the same in every lane
     wave_fence();
@@ -164,10 +201,8 @@ __global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __rest
       if (lane < m) {
         const int a = small_q[sh + lane];
         b = large_q[(lh + lane) & (MAX_N - 1)];
-        const double ma = mass[a];
-        prob[a] = (float)(ma / S);
         alias[a] = b;
-        const double mb = (mass[b] + ma) - S;
+        const double mb = (mass[b] + mass[a]) - S;
         mass[b] = mb;
         demoted = mb < S;
       }
@@ -182,6 +217,11 @@ __global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __rest
       st += __popcll(down);
       lt += __popcll(stay);
       wave_fence();
+    }
+    // (a small's mass does not change once it is one: the divisions are left to all lanes)
+    for (int i = lane; i < sh; i += 64) {
+      const int a = small_q[i];
+      prob[a] = (float)(mass[a] / S);
     }
     for (int i = sh + lane; i < st; i += 64) {
       const int x = small_q[i];
@@ -302,6 +342,33 @@ __device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double S = 0.0;
+  int least = 255;
+  for (int64_t base = threadIdx.x; base < n; base += 4 * kLongThreads) {
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = base + k * kLongThreads < n ? w[base + k * kLongThreads] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      S += (double)v[k];
+      least = min(least, weight_exponent(v[k]));
+    }
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    S += __shfl_xor(S, d, 64);
+    least = min(least, __shfl_xor(least, d, 64));
+  }
+  if (lane == 0) { run_s[wave].even = __double_as_longlong(S); run_s[wave].odd = least; }
+  __syncthreads();
+  S = 0.0;
+#pragma unroll
+  for (int v = 0; v < kLongWaves; ++v) {
+    S += __longlong_as_double(run_s[v].even);
+    least = min(least, (int)run_s[v].odd);
+  }
+  __syncthreads();
+  if (any_order(S, least)) return S;
+  S = 0.0;
   int64_t pos = 0;
   while (pos < n) {
     int taken = 0;                             // waves whose chunk has been added
@@ -327,13 +394,20 @@ __device__ double ordered_sum(const float* __restrict__ w, int64_t n, Runs* run_
   return S;
 }
 
+// A barrier for what the waves exchange through LDS alone: it does not wait for stores to global memory.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // places of the wave's votes in the workgroup's order, for two kinds of votes at once: c0 and c1
 // are the wave's totals; returns the totals of the waves before, and all of them
 __device__ __forceinline__ void block_before(int c0, int c1, int (*tot)[kLongWaves], int& before0, int& before1,
                                              int& all0, int& all1) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if ((threadIdx.x & 63) == 0) { tot[0][wave] = c0; tot[1][wave] = c1; }
-  __syncthreads();
+  lds_barrier();
   int v0[kLongWaves], v1[kLongWaves];
 #pragma unroll
   for (int v = 0; v < kLongWaves; ++v) { v0[v] = tot[0][v]; v1[v] = tot[1][v]; }
@@ -412,54 +486,74 @@ __device__ __forceinline__ void append(Window& q, int32_t* list, bool mine, int3
 // One workgroup moves about one cache line per cycle, which bounds the rounds of hundreds of
 // thousands of iterations a noise table starts with.  A segment that is alone in its call and long
 // enough therefore gets its sum, its lists and its first rounds from launches of many workgroups (a round is
-// two kernels: iterate, then append behind both lists), and the rest from the workgroup kernel.
-// A round that has become narrower than kWideRound is left to that one.  Measured in ms, degree^0.75 of a skewed
-// graph and lognormal weights: the whole chip against one workgroup, 2^15 entries 0.39 / 0.34 and 0.32 / 0.28, 2^16
-// 0.56 / 0.55 and 0.41 / 0.42 (2^17 equal weights 0.32 / 0.33, half of them zero 0.37 / 0.52; 2^18 0.40 / 0.52 and
-// 0.44 / 0.93).  16 rounds against 48: 1 M entries 1.99 / 2.07 and 1.31 / 1.41, 2 M 3.36 / 3.18 and 1.83 / 1.84, 4 M
-// 4.83 / 3.93 and 3.03 / 2.68, 8 M 8.61 / 5.95 and 5.36 / 3.99 (so the line between them could lie at 2 M).
-// kWideRound of 2048, 8192 and 32768: 1 M entries 1.99, 1.99, 2.37, 8 M 5.92, 5.96, 7.15.
+// two kernels: iterate, then append behind both lists), and the rest from one workgroup.
+// Rounds narrower than kWideRound are left to that one: what it keeps in registers.  Measured in ms, degree^0.75 of a skewed graph and
+// lognormal weights: the whole chip against one workgroup, 2^15 entries 0.25 / 0.17 and 0.22 / 0.16, 2^16 0.29 / 0.26 and
+// 0.26 / 0.25, 2^17 0.35 / 0.43 and 0.30 / 0.41, 2^18 0.41 / 0.85 and 0.36 / 0.82.  Of the launches, those behind the last wide
+// round cost 3 to 4 us a round, and a wide round that is left to one workgroup 30 and more: 16, 32 and 96 rounds 1 M entries
+// 0.67, 0.72, 0.93 and 0.51, 0.56, 0.78; 2 M 2.32, 0.94, 1.16 and 1.06, 0.68, 0.89; 4 M 4.67, 3.61, 1.62 and 2.87, 1.87, 2.09; 8 M
+// 9.23, 7.44, 5.32 (256 rounds 4.00) and 5.32, 3.91, 3.60 (4.42).
 struct ListState { int64_t sh, st, lh, lt; };
 constexpr int64_t kWideSegment = (int64_t)1 << 17;
+// Workgroups of the chip-wide kernels: small ones, so that the scattered accesses of a round spread over all compute
+// units, while every workgroup can still add up the counts of the tiles before its own.
+constexpr int kWideThreads = 256, kWideTile = kWideThreads * kLongItems;
+constexpr int64_t kWideSmallTiles = (int64_t)1 << 22;          // entries
 constexpr int64_t kWideRound = 8192;
-static int wide_rounds(int64_t n) { return n < ((int64_t)1 << 22) ? 16 : 48; }
-constexpr int kMostWideRounds = 48;
+static int wide_rounds(int64_t n) {
+  return n < (int64_t)3 << 19 ? 16 : (n < (int64_t)3 << 20 ? 32 : (n < (int64_t)3 << 21 ? 96 : 128));
+}
+constexpr int kMostWideRounds = 128;
 
-// The sum in three steps: plain sums of the chunks, their prefix sums (which name the binade that the
+struct ChunkRun { Runs run; int e; int good; };
+// The sum: plain sums of the chunks and their prefix sums, which end in the total.  Where the order of the additions
+// does not matter (any_order) that is the sum, and the next two kernels return at once.  Else in three steps: plain sums of the chunks, their prefix sums (which name the binade that the
 // running sum is in when it reaches a chunk, but for those next to a border), and the run of every
 // chunk for that binade; then one workgroup adds run after run, and one by one where the binade was not
 // the one or is left.
 template <typename OffT>
 __global__ __launch_bounds__(kLongThreads) void alias_wide_chunks_kernel(const OffT* __restrict__ seg_offsets,
                                                                          const float* __restrict__ weights,
-                                                                         double* __restrict__ chunk_sums) {
+                                                                         double* __restrict__ chunk_sums,
+                                                                         ChunkRun* __restrict__ runs) {
   const int lane = threadIdx.x & 63;
   const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
   const int64_t waves = (int64_t)gridDim.x * kLongWaves;
   for (int64_t c = (int64_t)blockIdx.x * kLongWaves + (threadIdx.x >> 6); c * kSumChunk < n; c += waves) {
     double sum = 0.0;
+    int least = 255;
 #pragma unroll
     for (int k = 0; k < kSumItems; ++k) {
       const int64_t i = c * kSumChunk + k * 64 + lane;
-      sum += i < n ? (double)weights[begin + i] : 0.0;
+      const float v = i < n ? weights[begin + i] : 0.f;
+      sum += (double)v;
+      least = min(least, weight_exponent(v));
     }
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
-    if (lane == 0) chunk_sums[c] = sum;
+    for (int d = 32; d > 0; d >>= 1) {
+      sum += __shfl_xor(sum, d, 64);
+      least = min(least, __shfl_xor(least, d, 64));
+    }
+    if (lane == 0) { chunk_sums[c] = sum; runs[c].e = least; }
   }
 }
 
 template <typename OffT>
 __global__ __launch_bounds__(kLongThreads) void alias_wide_prefix_kernel(const OffT* __restrict__ seg_offsets,
-                                                                         double* __restrict__ chunk_sums) {
+                                                                         double* __restrict__ chunk_sums,
+                                                                         const ChunkRun* __restrict__ runs,
+                                                                         double* __restrict__ sum_out,
+                                                                         int32_t* __restrict__ summed) {
   __shared__ double part[2][kLongWaves];
+  __shared__ int least_s[kLongWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t n = (int64_t)seg_offsets[1] - (int64_t)seg_offsets[0], chunks = (n + kSumChunk - 1) / kSumChunk;
   double carry = 0.0;
-  int turn = 0;
+  int turn = 0, least = 255;
   for (int64_t base = 0; base < chunks; base += kLongThreads, turn ^= 1) {
     const int64_t c = base + threadIdx.x;
     const double own = c < chunks ? chunk_sums[c] : 0.0;
+    if (c < chunks) least = min(least, runs[c].e);
     double incl = own;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -476,14 +570,25 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_prefix_kernel(const O
     }
     if (c < chunks) chunk_sums[c] = before;
   }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) least = min(least, __shfl_xor(least, d, 64));
+  if (lane == 0) least_s[wave] = least;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 0; w < kLongWaves; ++w) least = min(least, least_s[w]);
+    const bool done = any_order(carry, least);
+    if (done) *sum_out = carry;
+    *summed = done ? 1 : 0;
+  }
 }
 
-struct ChunkRun { Runs run; int e; int good; };
 template <typename OffT>
 __global__ __launch_bounds__(256) void alias_wide_runs_kernel(const OffT* __restrict__ seg_offsets,
                                                               const float* __restrict__ weights,
                                                               const double* __restrict__ chunk_sums,
-                                                              ChunkRun* __restrict__ runs) {
+                                                              ChunkRun* __restrict__ runs,
+                                                              const int32_t* __restrict__ summed) {
+  if (*summed != 0) return;
   const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
   const int64_t waves = (int64_t)gridDim.x * 4;
   for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c * kSumChunk < n; c += waves) {
@@ -501,7 +606,9 @@ template <typename OffT>
 __global__ __launch_bounds__(256) void alias_wide_sum_kernel(const OffT* __restrict__ seg_offsets,
                                                              const float* __restrict__ weights,
                                                              const ChunkRun* __restrict__ runs,
-                                                             double* __restrict__ sum_out) {
+                                                             double* __restrict__ sum_out,
+                                                             const int32_t* __restrict__ summed) {
+  if (*summed != 0) return;
   constexpr int kAtOnce = 512;
   __shared__ ChunkRun run_s[kAtOnce];
   const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
@@ -522,9 +629,10 @@ __global__ __launch_bounds__(256) void alias_wide_sum_kernel(const OffT* __restr
 }
 
 // sum of counts[0 .. tile), by the whole workgroup
+template <int kThreads>
 __device__ __forceinline__ int64_t counts_before(const int32_t* __restrict__ counts, int64_t tile, int64_t* part) {
   int64_t sum = 0;
-  for (int64_t i = threadIdx.x; i < tile; i += kLongThreads) sum += counts[i];
+  for (int64_t i = threadIdx.x; i < tile; i += kThreads) sum += counts[i];
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
   __syncthreads();
@@ -532,24 +640,24 @@ __device__ __forceinline__ int64_t counts_before(const int32_t* __restrict__ cou
   __syncthreads();
   sum = 0;
 #pragma unroll
-  for (int w = 0; w < kLongWaves; ++w) sum += part[w];
+  for (int w = 0; w < kThreads / 64; ++w) sum += part[w];
   return sum;
 }
 
 // masses, and which entries start as smalls: a bit per entry and a count per tile
-template <typename OffT>
-__global__ __launch_bounds__(kLongThreads) void alias_wide_masses_kernel(const OffT* __restrict__ seg_offsets,
+template <typename OffT, int kThreads>
+__global__ __launch_bounds__(kThreads) void alias_wide_masses_kernel(const OffT* __restrict__ seg_offsets,
                                                                          const float* __restrict__ weights,
                                                                          const double* __restrict__ sum, double* mass_ws,
                                                                          uint64_t* __restrict__ flags,
                                                                          int32_t* __restrict__ counts) {
 #pragma clang fp contract(off)
-  __shared__ int32_t tot[kLongWaves];
+  __shared__ int32_t tot[kThreads / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
   const double S = *sum, dn = (double)n;
-  for (int64_t tile = blockIdx.x; tile * kLongTrip < n; tile += gridDim.x) {
-    const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
+  for (int64_t tile = blockIdx.x; tile * kThreads * kLongItems < n; tile += gridDim.x) {
+    const int64_t first = tile * kThreads * kLongItems + wave * (64 * kLongItems);
     int32_t count = 0;
 #pragma unroll
     for (int c = 0; c < kLongItems; ++c) {
@@ -565,7 +673,7 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_masses_kernel(const O
     if (threadIdx.x == 0) {
       int32_t all = 0;
 #pragma unroll
-      for (int w = 0; w < kLongWaves; ++w) all += tot[w];
+      for (int w = 0; w < kThreads / 64; ++w) all += tot[w];
       counts[tile] = all;
     }
     __syncthreads();
@@ -575,14 +683,14 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_masses_kernel(const O
 // Appends entries 0 .. m - 1 (entry i is i itself, or large_q[lh + i]) behind the smalls or the larges, in
 // order, by their flags; the workgroup with the last tile writes the lists' next state.
 // initial: the lists are empty and the entries are the segment's.
-template <typename OffT>
-__global__ __launch_bounds__(kLongThreads) void alias_wide_append_kernel(const OffT* __restrict__ seg_offsets,
+template <typename OffT, int kThreads>
+__global__ __launch_bounds__(kThreads) void alias_wide_append_kernel(const OffT* __restrict__ seg_offsets,
                                                                          int32_t* small_ws, int32_t* large_ws,
                                                                          const uint64_t* __restrict__ flags,
                                                                          const int32_t* __restrict__ counts,
                                                                          ListState* __restrict__ states, int initial) {
-  __shared__ int64_t part[kLongWaves];
-  __shared__ int32_t tot[kLongWaves];
+  __shared__ int64_t part[kThreads / 64];
+  __shared__ int32_t tot[kThreads / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t below = (1ull << lane) - 1ull;
   const int64_t begin = (int64_t)seg_offsets[0], n = (int64_t)seg_offsets[1] - begin;
@@ -595,11 +703,11 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_append_kernel(const O
     if (blockIdx.x == 0 && threadIdx.x == 0) states[1] = at;
     return;
   }
-  const int64_t tiles = (m + kLongTrip - 1) / kLongTrip;
+  const int64_t tiles = (m + kThreads * kLongItems - 1) / (kThreads * kLongItems);
   if (tiles == 0 && blockIdx.x == 0 && threadIdx.x == 0) states[0] = at;     // (an empty segment)
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t before = counts_before(counts, tile, part);
-    const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
+    const int64_t before = counts_before<kThreads>(counts, tile, part);
+    const int64_t first = tile * kThreads * kLongItems + wave * (64 * kLongItems);
     uint64_t down[kLongItems];
     int32_t count = 0;
 #pragma unroll
@@ -612,7 +720,7 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_append_kernel(const O
     int64_t rank = before;
     int32_t all = 0;
 #pragma unroll
-    for (int w = 0; w < kLongWaves; ++w) {
+    for (int w = 0; w < kThreads / 64; ++w) {
       if (w < wave) rank += tot[w];
       all += tot[w];
     }
@@ -638,14 +746,14 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_append_kernel(const O
 }
 
 // one round: m iterations, which larges became smalls
-template <typename OffT>
-__global__ __launch_bounds__(kLongThreads) void alias_wide_round_kernel(
+template <typename OffT, int kThreads>
+__global__ __launch_bounds__(kThreads) void alias_wide_round_kernel(
     const OffT* __restrict__ seg_offsets, const double* __restrict__ sum, float* __restrict__ prob_out,
     int32_t* __restrict__ alias_out, double* mass_ws, const int32_t* __restrict__ small_ws,
     const int32_t* __restrict__ large_ws, uint64_t* __restrict__ flags, int32_t* __restrict__ counts,
     const ListState* __restrict__ states) {
 #pragma clang fp contract(off)
-  __shared__ int32_t tot[kLongWaves];
+  __shared__ int32_t tot[kThreads / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t begin = (int64_t)seg_offsets[0];
   const ListState at = states[0];
@@ -657,8 +765,8 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_round_kernel(
   float* prob = prob_out + begin;
   int32_t* alias = alias_out + begin;
   double* mass = mass_ws + begin;
-  for (int64_t tile = blockIdx.x; tile * kLongTrip < m; tile += gridDim.x) {
-    const int64_t first = tile * kLongTrip + wave * (64 * kLongItems);
+  for (int64_t tile = blockIdx.x; tile * kThreads * kLongItems < m; tile += gridDim.x) {
+    const int64_t first = tile * kThreads * kLongItems + wave * (64 * kLongItems);
     int32_t count = 0;
     int32_t a[kLongItems], b[kLongItems];
     double ma[kLongItems], mb[kLongItems];
@@ -691,10 +799,386 @@ __global__ __launch_bounds__(kLongThreads) void alias_wide_round_kernel(
     if (threadIdx.x == 0) {
       int32_t all = 0;
 #pragma unroll
-      for (int w = 0; w < kLongWaves; ++w) all += tot[w];
+      for (int w = 0; w < kThreads / 64; ++w) all += tot[w];
       counts[tile] = all;
     }
     __syncthreads();
+  }
+}
+
+// ---- rounds of few larges -------------------------------------------------------------------
+// While there are no more larges than smalls, a round gives every large the next small: large i of l takes the smalls i, i + l,
+// i + 2l, ... of the list, until one of the larges has become a small.  So the workgroup keeps the larges in
+// registers and the head of the smalls in LDS, and every large runs down its own smalls, a chain of two
+// additions per round, with nothing to agree on but the first round in which any of them drops below S.
+// After that round the larges that are left close up, in order.  Up to 64 larges are one wave's, which needs no barriers.
+// A noise table of 1 M entries (degree^0.75 of a skewed graph) has 1486 rounds of fewer than 8192 larges, all but
+// 120 of them without a large that drops out: 1.77 ms with a look at both lists in every round, 0.47 ms like this, bound
+// by the instructions of one compute unit (23 rounds of more than 2048 larges 0.10 ms, 232 of more than 64 0.23, the rest 0.11).
+//
+// A compute unit moves about one cache line per cycle, so for a segment alone in its call (kAlone) the scattered
+// accesses of these rounds, a mass in and a probability and an alias out per small, are left to the whole chip: before,
+// the masses of the smalls are brought into the order of the list (mass_seq), after, what each small was paired with
+// (alias_seq) becomes the table.
+constexpr int kBigItems = 2, kBigItemsAlone = 8;               // larges per lane
+constexpr int kBig = kLongThreads * kBigItems, kBigAlone = kLongThreads * kBigItemsAlone;
+constexpr int kBigRounds = 8;                                  // rounds between two looks at the others
+constexpr int kBigRoundsOneWave = 16;
+// smalls in LDS: two workgroups per compute unit, or most of its LDS for a segment alone
+constexpr int kWindow = 3072, kWindowAlone = 12288;
+static_assert(kWindow >= kBig && kWindow % kLongThreads == 0 && kWindowAlone % kLongThreads == 0, "a round fits the window");
+static_assert(kWindowAlone * sizeof(double) >= kBigAlone * (sizeof(double) + sizeof(int32_t)), "or the larges of the wider rounds");
+static_assert(kBigAlone >= kWideRound, "what the chip leaves");
+struct RowWindow {
+  int32_t id[kWindow];                         // the smalls
+  int32_t alias[kWindow];                      // the large that takes each of them
+};
+struct NoRowWindow {};
+template <bool kAlone>
+struct BigRounds {
+  double mass[kAlone ? kWindowAlone : kWindow];          // of the smalls
+  double big_mass[kBig];                       // the larges, where they close up
+  int32_t big_id[kBig];
+  std::conditional_t<kAlone, NoRowWindow, RowWindow> row;
+  int first_event[4];                          // (four, used in turn: a slot is reset two turns ahead of its use)
+  int state[4];                                // one wave's rounds: smalls taken, larges left, smalls appended
+};
+
+// The larges of all lanes after a round: those below S to the smalls, the others closed up in big_id / big_mass.  Lane's
+// larges: mine, mine + 64, ...  Returns larges left and (in demoted) smalls appended.
+template <bool kAlone, int ITEMS>
+__device__ __forceinline__ int close_up(int32_t* big_id, double* big_mass, const double S, int l, int mine,
+                                        const int32_t (&id)[ITEMS], const double (&m)[ITEMS], int64_t st, int32_t* small_q,
+                                        double* mass, double* mass_seq, int (*tot)[kLongWaves], int& demoted) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t below = (1ull << lane) - 1ull;
+  const bool busy = __builtin_amdgcn_readfirstlane(mine - lane) < l;
+  uint64_t down[ITEMS], stay[ITEMS];
+  int cd = 0, cs = 0;
+  if (busy) {
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) {
+      const bool valid = mine + c * 64 < l;
+      down[c] = __ballot(valid && m[c] < S);
+      stay[c] = __ballot(valid && !(m[c] < S));
+      cd += __popcll(down[c]);
+      cs += __popcll(stay[c]);
+    }
+  }
+  int bd, bs, left;
+  block_before(cd, cs, tot, bd, bs, demoted, left);
+  if (!busy) return left;
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    if ((down[c] >> lane) & 1ull) {
+      const int64_t to = st + bd + __popcll(down[c] & below);
+      small_q[to] = id[c];
+      mass[id[c]] = m[c];
+      if (kAlone) mass_seq[to] = m[c];
+    } else if ((stay[c] >> lane) & 1ull) {
+      const int to = bs + __popcll(stay[c] & below);
+      big_id[to] = id[c];
+      big_mass[to] = m[c];
+    }
+    bd += __popcll(down[c]);
+    bs += __popcll(stay[c]);
+  }
+  return left;
+}
+
+template <bool kAlone>
+__device__ void rounds_of_few_larges(BigRounds<kAlone>& b, const double S, float* prob, int32_t* alias, double* mass,
+                                     double* mass_seq, int32_t* alias_seq, int32_t* small_q, int32_t* large_q, int64_t& sh,
+                                     int64_t& st, int64_t& lh, int64_t& lt, int (*tot)[2][kLongWaves]) {
+#pragma clang fp contract(off)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t below = (1ull << lane) - 1ull;
+  int l = (int)(lt - lh);
+  int turn = 0, votes_turn = 0;
+  bool closed_up = false;                                      // the larges are in wide_id / wide_mass, not in the list
+  double* wide_mass = b.mass;                                  // (the window's place)
+  int32_t* wide_id = kAlone ? reinterpret_cast<int32_t*>(b.mass + kBigAlone) : nullptr;
+  if constexpr (kAlone) {
+    // more larges than two per lane: round by round, the smalls straight from memory
+    if (l > kBig && st - sh >= l) {
+      const int mine = wave * (64 * kBigItemsAlone) + lane;
+      if (tid < 4) b.first_event[tid] = 0;
+      __syncthreads();
+      int32_t id[kBigItemsAlone];
+      double m[kBigItemsAlone];
+#pragma unroll
+      for (int c = 0; c < kBigItemsAlone; ++c) id[c] = large_q[lh + min(mine + c * 64, l - 1)];
+#pragma unroll
+      for (int c = 0; c < kBigItemsAlone; ++c) m[c] = mass[id[c]];
+      int64_t written = st;                                    // the smalls up to here are there for all lanes
+      while (l > kBig && st - sh >= l) {
+        double v[kBigItemsAlone];
+        bool event = false;
+        if (sh + l > written) {
+          __syncthreads();
+          written = st;
+        }
+        if (wave * (64 * kBigItemsAlone) < l) {                // (waves without larges leave the issue slots to the others)
+#pragma unroll
+          for (int c = 0; c < kBigItemsAlone; ++c) v[c] = mass_seq[sh + min(mine + c * 64, l - 1)];
+#pragma unroll
+          for (int c = 0; c < kBigItemsAlone; ++c) {
+            m[c] = (m[c] + v[c]) - S;
+            if (mine + c * 64 < l) {
+              alias_seq[sh + mine + c * 64] = id[c];
+              event = event || m[c] < S;
+            }
+          }
+        }
+        sh += l;
+        if (__ballot(event) != 0ull && lane == 0) b.first_event[turn & 3] = 1;
+        if (tid == 0) b.first_event[(turn + 2) & 3] = 0;
+        lds_barrier();
+        const bool any = b.first_event[turn & 3] != 0;
+        ++turn;
+        if (!any) continue;
+        int demoted;
+        l = close_up<kAlone, kBigItemsAlone>(wide_id, wide_mass, S, l, mine, id, m, st, small_q, mass, mass_seq, tot[votes_turn], demoted);
+        votes_turn ^= 1;
+        st += demoted;
+        closed_up = true;
+        lds_barrier();
+        if (wave * (64 * kBigItemsAlone) < l) {
+#pragma unroll
+          for (int c = 0; c < kBigItemsAlone; ++c) {
+            const int at = min(mine + c * 64, l - 1);
+            id[c] = wide_id[at];
+            m[c] = wide_mass[at];
+          }
+        }
+        lds_barrier();
+      }
+      if (l > kBig) {                                          // (too few smalls)
+#pragma unroll
+        for (int c = 0; c < kBigItemsAlone; ++c)
+          if (mine + c * 64 < l) {
+            large_q[lt + mine + c * 64] = id[c];
+            mass[id[c]] = m[c];
+          }
+        lh = lt;
+        lt += l;
+        return;
+      }
+    }
+  }
+  const int mine = wave * (64 * kBigItems) + lane;             // this lane's larges: mine, mine + 64
+  int32_t id[kBigItems];
+  double m[kBigItems];
+#pragma unroll
+  for (int c = 0; c < kBigItems; ++c) {
+    const bool valid = mine + c * 64 < l;
+    id[c] = !valid ? 0 : (closed_up ? wide_id[mine + c * 64] : large_q[lh + mine + c * 64]);
+    m[c] = !valid ? 0.0 : (closed_up ? wide_mass[mine + c * 64] : mass[id[c]]);
+  }
+  constexpr int kSmalls = kAlone ? kWindowAlone : kWindow;
+  if (kAlone) __syncthreads();                                 // (the flags' last use above)
+  if (tid < 4) b.first_event[tid] = kBigRounds;
+  while (l > 0 && st - sh >= l) {
+    const int count = (int)min((int64_t)kSmalls, st - sh);
+    __syncthreads();                                           // (what was appended is there)
+    if constexpr (kAlone) {
+#pragma unroll
+      for (int c = 0; c < kSmalls / kLongThreads; ++c)         // (behind the end: the last one again, not used)
+        b.mass[c * kLongThreads + tid] = mass_seq[sh + min(c * kLongThreads + tid, count - 1)];
+    } else {
+      int32_t a[kWindow / kLongThreads];
+#pragma unroll
+      for (int c = 0; c < kWindow / kLongThreads; ++c) a[c] = small_q[sh + min(c * kLongThreads + tid, count - 1)];
+#pragma unroll
+      for (int c = 0; c < kWindow / kLongThreads; ++c) {
+        b.row.id[c * kLongThreads + tid] = a[c];
+        b.mass[c * kLongThreads + tid] = mass[a[c]];
+      }
+    }
+    __syncthreads();
+    int at = 0;                                                // smalls of the window that have been taken
+    // (of rounds behind an event: written again)
+    auto pair = [&](int small, int32_t large) {
+      if constexpr (kAlone) alias_seq[sh + small] = large;
+      else b.row.alias[small] = large;
+    };
+    while (l > 64 && count - at >= l) {
+      const int rounds = min(kBigRounds, (count - at) / l);
+      double v[kBigRounds][kBigItems], x[kBigItems];
+      int event = kBigRounds;
+#pragma unroll
+      for (int c = 0; c < kBigItems; ++c) x[c] = m[c];
+      const bool busy = wave * (64 * kBigItems) < l;           // (waves without larges leave the issue slots to the others)
+      if (busy) {
+#pragma unroll
+        for (int j = 0; j < kBigRounds; ++j)
+#pragma unroll
+          for (int c = 0; c < kBigItems; ++c)
+            v[j][c] = b.mass[min(at + j * l + mine + c * 64, kSmalls - 1)];
+#pragma unroll
+        for (int j = 0; j < kBigRounds; ++j) {
+          if (j >= rounds) break;
+#pragma unroll
+          for (int c = 0; c < kBigItems; ++c) {
+            x[c] = (x[c] + v[j][c]) - S;
+            if (mine + c * 64 < l) {
+              if (x[c] < S) event = min(event, j);
+              pair(at + j * l + mine + c * 64, id[c]);
+            }
+          }
+        }
+      }
+      if (event < kBigRounds) atomicMin(&b.first_event[turn & 3], event);
+      if (tid == 0) b.first_event[(turn + 2) & 3] = kBigRounds;
+      lds_barrier();
+      event = __builtin_amdgcn_readfirstlane(b.first_event[turn & 3]);
+      ++turn;
+      if (event == kBigRounds) {
+#pragma unroll
+        for (int c = 0; c < kBigItems; ++c) m[c] = x[c];
+        at += rounds * l;
+        continue;
+      }
+      // up to and with the round of the event once more; the larges that are left close up
+      if (busy) {
+#pragma unroll
+        for (int j = 0; j < kBigRounds; ++j) {
+          if (j > event) break;
+#pragma unroll
+          for (int c = 0; c < kBigItems; ++c) m[c] = (m[c] + v[j][c]) - S;
+        }
+      }
+      at += (event + 1) * l;
+      int demoted;
+      l = close_up<kAlone, kBigItems>(b.big_id, b.big_mass, S, l, mine, id, m, st, small_q, mass, mass_seq, tot[votes_turn], demoted);
+      votes_turn ^= 1;
+      st += demoted;
+      lds_barrier();
+#pragma unroll
+      for (int c = 0; c < kBigItems; ++c)
+        if (mine + c * 64 < l) { id[c] = b.big_id[mine + c * 64]; m[c] = b.big_mass[mine + c * 64]; }
+    }
+    if (l > 0 && l <= 64 && count - at >= l) {
+      if (wave == 0) {
+        int appended = 0;
+        int32_t own = id[0];
+        double x = m[0];
+        while (l > 0 && count - at >= l) {
+          const int rounds = min(kBigRoundsOneWave, (count - at) / l);
+          double v[kBigRoundsOneWave];
+#pragma unroll
+          for (int j = 0; j < kBigRoundsOneWave; ++j) v[j] = b.mass[min(at + j * l + lane, kSmalls - 1)];
+          // the chain first, then the votes on all of its rounds, which do not wait for one another
+          double y[kBigRoundsOneWave];
+          uint32_t events = 0u;
+#pragma unroll
+          for (int j = 0; j < kBigRoundsOneWave; ++j) y[j] = x = (x + v[j]) - S;
+#pragma unroll
+          for (int j = 0; j < kBigRoundsOneWave; ++j) events |= __ballot(lane < l && y[j] < S) != 0ull ? 1u << j : 0u;
+          const int event = min(rounds, events != 0u ? __builtin_ctz(events) : kBigRoundsOneWave);
+          const int taken = min(rounds, event + 1);
+#pragma unroll
+          for (int j = 0; j < kBigRoundsOneWave; ++j) {
+            if (j >= taken) break;
+            x = y[j];
+            if (lane < l) pair(at + j * l + lane, own);
+          }
+          at += taken * l;
+          if (event == rounds) continue;
+          const uint64_t down = __ballot(lane < l && x < S);
+          const uint64_t stay = __ballot(lane < l && !(x < S));
+          if ((down >> lane) & 1ull) {
+            const int64_t to = st + appended + __popcll(down & below);
+            small_q[to] = own;
+            mass[own] = x;
+            if (kAlone) mass_seq[to] = x;
+          } else if ((stay >> lane) & 1ull) {
+            const int to = __popcll(stay & below);
+            b.big_id[to] = own;
+            b.big_mass[to] = x;
+          }
+          appended += __popcll(down);
+          l = __popcll(stay);
+          wave_fence();
+          if (lane < l) { own = b.big_id[lane]; x = b.big_mass[lane]; }
+          wave_fence();
+        }
+        id[0] = own;
+        m[0] = x;
+        if (lane == 0) { b.state[0] = at; b.state[1] = l; b.state[2] = appended; }
+      }
+      __syncthreads();
+      at = __builtin_amdgcn_readfirstlane(b.state[0]);
+      l = __builtin_amdgcn_readfirstlane(b.state[1]);
+      st += __builtin_amdgcn_readfirstlane(b.state[2]);
+    }
+    if constexpr (!kAlone) {
+      __syncthreads();
+      for (int k = tid; k < at; k += kLongThreads) {
+        const int32_t a = b.row.id[k];
+        prob[a] = (float)(b.mass[k] / S);
+        alias[a] = b.row.alias[k];
+      }
+    }
+    sh += at;
+  }
+#pragma unroll
+  for (int c = 0; c < kBigItems; ++c)
+    if (mine + c * 64 < l) {
+      large_q[lt + mine + c * 64] = id[c];
+      mass[id[c]] = m[c];
+    }
+  lh = lt;
+  lt += l;
+}
+
+// Between the chip-wide rounds and the workgroup kernel, which does what these leave.  All for segment 0.
+__device__ __forceinline__ bool few_larges(const ListState& at) {
+  return at.lt > at.lh && at.lt - at.lh <= (int64_t)kBigAlone && at.lt - at.lh <= at.st - at.sh;
+}
+template <typename OffT>
+__global__ __launch_bounds__(256) void alias_wide_gather_kernel(const OffT* __restrict__ seg_offsets,
+                                                                const double* __restrict__ mass_ws,
+                                                                const int32_t* __restrict__ small_ws,
+                                                                const ListState* __restrict__ states,
+                                                                double* __restrict__ mass_seq) {
+  const ListState at = states[0];
+  if (!few_larges(at)) return;
+  const int64_t begin = (int64_t)seg_offsets[0];
+  for (int64_t k = at.sh + (int64_t)blockIdx.x * 256 + threadIdx.x; k < at.st; k += (int64_t)gridDim.x * 256)
+    mass_seq[k] = mass_ws[begin + small_ws[begin + k]];
+}
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_wide_tail_kernel(const OffT* __restrict__ seg_offsets,
+                                                                       const double* __restrict__ sum, double* mass_ws,
+                                                                       int32_t* small_ws, int32_t* large_ws, double* mass_seq,
+                                                                       int32_t* alias_seq, ListState* states) {
+  __shared__ BigRounds<true> big;
+  __shared__ int tot[2][2][kLongWaves];
+  ListState at = states[0];
+  if (few_larges(at)) {
+    const int64_t begin = (int64_t)seg_offsets[0];
+    rounds_of_few_larges<true>(big, *sum, nullptr, nullptr, mass_ws + begin, mass_seq, alias_seq, small_ws + begin,
+                               large_ws + 2 * begin, at.sh, at.st, at.lh, at.lt, tot);
+  }
+  if (threadIdx.x == 0) states[1] = at;
+}
+// the smalls that the tail took: positions states[0].sh .. states[1].sh of the list
+template <typename OffT>
+__global__ __launch_bounds__(256) void alias_wide_table_kernel(const OffT* __restrict__ seg_offsets,
+                                                               const double* __restrict__ sum,
+                                                               const int32_t* __restrict__ small_ws,
+                                                               const double* __restrict__ mass_seq,
+                                                               const int32_t* __restrict__ alias_seq,
+                                                               const ListState* __restrict__ states,
+                                                               float* __restrict__ prob_out, int32_t* __restrict__ alias_out) {
+#pragma clang fp contract(off)
+  const int64_t begin = (int64_t)seg_offsets[0], last = states[1].sh;
+  const double S = *sum;
+  for (int64_t k = states[0].sh + (int64_t)blockIdx.x * 256 + threadIdx.x; k < last; k += (int64_t)gridDim.x * 256) {
+    const int32_t a = small_ws[begin + k];
+    prob_out[begin + a] = (float)(mass_seq[k] / S);
+    alias_out[begin + a] = alias_seq[k];
   }
 }
 
@@ -713,8 +1197,8 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
   __shared__ double sum_s;
   __shared__ int tot[2][2][kLongWaves];        // (two sets, used in turn: one barrier per use)
   __shared__ int64_t q_s[4];                   // small head/tail, large head/tail after a narrow stretch
-  __shared__ int32_t ring_id[2][kRing];
-  __shared__ double ring_mass[2][kRing];
+  __shared__ BigRounds<false> big;
+  static_assert(kWindow >= 2 * kRing, "the rings lie in the window");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = (1ull << lane) - 1ull;
   if (long_ids != nullptr && (unsigned long long)blockIdx.x >= *long_count) return;
@@ -773,11 +1257,15 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
     __syncthreads();
     const int64_t m = min(st - sh, lt - lh);
     if (m <= 0) break;
+    if (lt - lh <= (int64_t)kBig && lt - lh <= st - sh) {
+      rounds_of_few_larges<false>(big, S, prob, alias, mass, nullptr, nullptr, small_q, large_q, sh, st, lh, lt, tot);
+      continue;
+    }
     if (m < kNarrow) {
       const int64_t popped = sh;               // the smalls from here on are taken in this stretch
       if (wave == 0) {
-        Window s = {ring_id[0], ring_mass[0], uniform64(sh), uniform64(sh), uniform64(st)};
-        Window l = {ring_id[1], ring_mass[1], uniform64(lh), uniform64(lh), uniform64(lt)};
+        Window s = {big.row.id, big.mass, uniform64(sh), uniform64(sh), uniform64(st)};
+        Window l = {big.row.id + kRing, big.mass + kRing, uniform64(lh), uniform64(lh), uniform64(lt)};
         while (true) {
           const int64_t both = min(s.tail - s.head, l.tail - l.head);
           if (both <= 0 || both >= 2 * kNarrow) break;
@@ -890,6 +1378,8 @@ struct AliasPlan {
   ListState* states;
   uint64_t* flags;
   int32_t* counts;
+  double* mass_seq;
+  int32_t* alias_seq;
   size_t wide_bytes;
 };
 
@@ -907,9 +1397,11 @@ static AliasPlan plan_alias(void* ws, int64_t total_entries) {
   p.sum = cv.take<double>(1);
   p.chunk_sums = cv.take<double>(t / kSumChunk + 1);
   p.runs = cv.take<ChunkRun>(t / kSumChunk + 1);
-  p.states = cv.take<ListState>(kMostWideRounds + 1);
+  p.states = cv.take<ListState>(kMostWideRounds + 2);
   p.flags = cv.take<uint64_t>(t / 64 + 1);
-  p.counts = cv.take<int32_t>(t / kLongTrip + 1);
+  p.counts = cv.take<int32_t>(t / kWideTile + 1);
+  p.mass_seq = cv.take<double>(t);
+  p.alias_seq = cv.take<int32_t>(t);
   p.wide_bytes = cv.used;
   return p;
 }
@@ -918,32 +1410,51 @@ static bool wide_segment(int64_t num_segments, int64_t total_entries) {
   return num_segments == 1 && total_entries >= kWideSegment;
 }
 
+template <typename OffT, int kThreads>
+static int32_t launch_wide_rounds(const OffT* seg_offsets, int64_t n, const float* weights, float* prob_out,
+                                  int32_t* alias_out, const AliasPlan& p, hipStream_t stream) {
+  const unsigned tiles = (unsigned)min((int64_t)4096, ceil_div(n, kThreads * kLongItems));
+  alias_wide_masses_kernel<OffT, kThreads><<<tiles, kThreads, 0, stream>>>(seg_offsets, weights, p.sum, p.mass, p.flags, p.counts);
+  alias_wide_append_kernel<OffT, kThreads><<<tiles, kThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags, p.counts,
+                                                                           p.states, 1);
+  GS_LAUNCH_CHECK();
+  const int rounds = wide_rounds(n);
+  const unsigned half = (unsigned)min((int64_t)2048, ceil_div(n / 2 + 1, kThreads * kLongItems));      // m is at most half of n
+  for (int r = 0; r < rounds; ++r) {
+    alias_wide_round_kernel<OffT, kThreads><<<half, kThreads, 0, stream>>>(
+        seg_offsets, p.sum, prob_out, alias_out, p.mass, p.small_q, p.large_q, p.flags, p.counts, p.states + r);
+    alias_wide_append_kernel<OffT, kThreads><<<half, kThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags,
+                                                                            p.counts, p.states + r, 0);
+    GS_LAUNCH_CHECK();
+  }
+  return GS_OK;
+}
+
 template <typename OffT>
 static int32_t launch_alias_wide(const OffT* seg_offsets, int64_t n, const float* weights, float* prob_out,
                                  int32_t* alias_out, const AliasPlan& p, hipStream_t stream) {
-  const unsigned tiles = (unsigned)min((int64_t)2048, ceil_div(n, kLongTrip));
   const int64_t chunks = ceil_div(n, kSumChunk);
   alias_wide_chunks_kernel<OffT><<<(unsigned)min((int64_t)1024, ceil_div(chunks, kLongWaves)), kLongThreads, 0, stream>>>(
-      seg_offsets, weights, p.chunk_sums);
-  alias_wide_prefix_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, p.chunk_sums);
-  alias_wide_runs_kernel<OffT><<<(unsigned)min((int64_t)8192, ceil_div(chunks, 4)), 256, 0, stream>>>(
       seg_offsets, weights, p.chunk_sums, p.runs);
-  alias_wide_sum_kernel<OffT><<<1, 256, 0, stream>>>(seg_offsets, weights, p.runs, p.sum);
-  alias_wide_masses_kernel<OffT><<<tiles, kLongThreads, 0, stream>>>(seg_offsets, weights, p.sum, p.mass, p.flags, p.counts);
-  alias_wide_append_kernel<OffT><<<tiles, kLongThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags, p.counts,
-                                                                     p.states, 1);
+  int32_t* summed = p.counts;                  // (the counts come later)
+  alias_wide_prefix_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, p.chunk_sums, p.runs, p.sum, summed);
+  alias_wide_runs_kernel<OffT><<<(unsigned)min((int64_t)8192, ceil_div(chunks, 4)), 256, 0, stream>>>(
+      seg_offsets, weights, p.chunk_sums, p.runs, summed);
+  alias_wide_sum_kernel<OffT><<<1, 256, 0, stream>>>(seg_offsets, weights, p.runs, p.sum, summed);
   GS_LAUNCH_CHECK();
-  const int rounds = wide_rounds(n);
-  const unsigned half = (unsigned)min((int64_t)2048, ceil_div(n / 2 + 1, kLongTrip));      // m is at most half of n
-  for (int r = 0; r < rounds; ++r) {
-    alias_wide_round_kernel<OffT><<<half, kLongThreads, 0, stream>>>(seg_offsets, p.sum, prob_out, alias_out, p.mass,
-                                                                     p.small_q, p.large_q, p.flags, p.counts, p.states + r);
-    alias_wide_append_kernel<OffT><<<half, kLongThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags,
-                                                                      p.counts, p.states + r, 0);
-    GS_LAUNCH_CHECK();
-  }
+  const int32_t rc = n <= kWideSmallTiles
+      ? launch_wide_rounds<OffT, kWideThreads>(seg_offsets, n, weights, prob_out, alias_out, p, stream)
+      : launch_wide_rounds<OffT, kLongThreads>(seg_offsets, n, weights, prob_out, alias_out, p, stream);
+  if (rc != GS_OK) return rc;
+  ListState* left = p.states + wide_rounds(n);
+  const unsigned blocks = (unsigned)min((int64_t)4096, ceil_div(n, 256));
+  alias_wide_gather_kernel<OffT><<<blocks, 256, 0, stream>>>(seg_offsets, p.mass, p.small_q, left, p.mass_seq);
+  alias_wide_tail_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, p.sum, p.mass, p.small_q, p.large_q, p.mass_seq,
+                                                               p.alias_seq, left);
+  alias_wide_table_kernel<OffT><<<blocks, 256, 0, stream>>>(seg_offsets, p.sum, p.small_q, p.mass_seq, p.alias_seq, left,
+                                                            prob_out, alias_out);
   alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, nullptr, nullptr, weights, prob_out, alias_out,
-                                                                p.mass, p.small_q, p.large_q, p.states + rounds, p.sum);
+                                                                p.mass, p.small_q, p.large_q, left + 1, p.sum);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
@@ -961,7 +1472,7 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
   }
   const int threads = 64;
   alias_build_kernel<OffT><<<(unsigned)ceil_div(num_segments, threads), threads, 0, stream>>>(
-      seg_offsets, num_segments, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q);
+      seg_offsets, num_segments, weights, prob_out, alias_out);
   GS_LAUNCH_CHECK();
   // few segments: a wave each; many: up to 64 per wave, so that the short ones cost one look
   const int per_wave = (int)max((int64_t)1, min((int64_t)64, num_segments / 16384));
@@ -971,8 +1482,14 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
         seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
     GS_LAUNCH_CHECK();
   }
+  // (the LDS of a wave bounds how many there are at a time: 257 .. 2048 entries in one kernel 267 us on the 1 M-node graph)
   if (total_entries > 256) {
-    alias_build_wave_kernel<OffT, 257, kWaveSegment><<<waves, 64, 0, stream>>>(
+    alias_build_wave_kernel<OffT, 257, 1024><<<waves, 64, 0, stream>>>(
+        seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
+    GS_LAUNCH_CHECK();
+  }
+  if (total_entries > 1024) {
+    alias_build_wave_kernel<OffT, 1025, kWaveSegment><<<waves, 64, 0, stream>>>(
         seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
     GS_LAUNCH_CHECK();
   }
