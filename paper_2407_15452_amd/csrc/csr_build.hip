@@ -194,16 +194,18 @@ extern "C" int32_t gs_csr_build(const int32_t* src, const int32_t* dst, const fl
   const int64_t tiles = ceil_div(cap, kCompactTile);
   const int nb = bits_for(num_nodes);
   if (cap > 0) {
-    // ids take nb bits, and the key has one bit more than two ids, so dropped records sort last.
+    // ids take nb bits; dropped records, all of whose bits are set, sort last: their source id is no node's unless
+    // the nodes fill the nb bits, and then the key has one bit more.
     // The passes go back and forth between two buffers and end in (keys, vals).
-    const bool odd = radix_sort_passes(2 * nb + 1) & 1;
+    const int key_bits = 2 * nb + (num_nodes < ((int64_t)1 << nb) ? 0 : 1);
+    const bool odd = radix_sort_passes(key_bits) & 1;
     uint64_t* made = odd ? p.keys_alt : p.keys;
     uint32_t* made_vals = w == nullptr ? nullptr : (odd ? p.vals_alt : p.vals);
     csr_keygen_kernel<<<(unsigned)ceil_div(cap, threads), threads, 0, stream>>>(src, dst, w, cap, num_nodes, flags, nb,
                                                                                made, made_vals);
     GS_LAUNCH_CHECK();
     const int32_t rc = radix_sort<uint64_t>(made, made_vals, p.keys, p.vals, p.keys_alt, p.vals_alt, cap, kDroppedKey,
-                                            2 * nb + 1, p.sort_scratch, stream);
+                                            key_bits, p.sort_scratch, stream);
     if (rc != GS_OK) return rc;
     csr_count_kernel<<<(unsigned)tiles, kCompactThreads, 0, stream>>>(p.keys, cap, flags, p.tile_first);
     GS_LAUNCH_CHECK();
