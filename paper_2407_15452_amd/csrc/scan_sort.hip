@@ -10,16 +10,46 @@ void set_last_hip_error(hipError_t e) { g_last_error = e; }
 extern "C" int32_t gs_last_hip_error(void) { return (int32_t)g_last_error; }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan: tiles of 1024 values, tile totals scanned recursively.
+// Exclusive scan: tiles of 1024 values.  The tiles' sums first; then every tile is scanned from the sum of the
+// tiles before it, which its workgroup adds up itself while there are few (a launch costs more).  Beyond that the
+// tile sums are scanned the same way in between.
 // ---------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int64_t kScanFewTiles = 4096;
 
-__global__ __launch_bounds__(kScanThreads) void scan_tiles_kernel(int64_t* __restrict__ data,
-                                                                  int64_t n,
-                                                                  int64_t* __restrict__ tile_sums) {
+// sum over the workgroup; every lane gets it
+__device__ __forceinline__ int64_t block_sum_i64(int64_t v, int64_t* wave_sums) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  if ((threadIdx.x & 63) == 0) wave_sums[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = 0;
+#pragma unroll
+  for (int w = 0; w < kScanThreads / 64; ++w) v += wave_sums[w];
+  return v;
+}
+
+__global__ __launch_bounds__(kScanThreads) void scan_sums_i64_kernel(const int64_t* __restrict__ data, int64_t n,
+                                                                     int64_t* __restrict__ tile_sums) {
   __shared__ int64_t wave_sums[kScanThreads / 64];
+  int64_t local = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    const int64_t i = (int64_t)blockIdx.x * kScanTile + k * kScanThreads + threadIdx.x;
+    local += (i < n) ? data[i] : 0;
+  }
+  local = block_sum_i64(local, wave_sums);
+  if (threadIdx.x == 0) tile_sums[blockIdx.x] = local;
+}
+
+// tile_sums: sums of the tiles (scanned == 0) or their exclusive prefix sums
+__global__ __launch_bounds__(kScanThreads) void scan_apply_i64_kernel(int64_t* __restrict__ data, int64_t n,
+                                                                      const int64_t* __restrict__ tile_sums, int scanned,
+                                                                      int64_t* __restrict__ total_out) {
+  __shared__ int64_t wave_sums[2][kScanThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   int64_t v[kScanItems];
   int64_t local = 0;
@@ -28,40 +58,34 @@ __global__ __launch_bounds__(kScanThreads) void scan_tiles_kernel(int64_t* __res
     v[k] = (base + k < n) ? data[base + k] : 0;
     local += v[k];
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t before = 0;
+  if (scanned) {
+    before = tile_sums[blockIdx.x];
+  } else if (blockIdx.x > 0) {
+    for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kScanThreads) before += tile_sums[t];
+    before = block_sum_i64(before, wave_sums[1]);
+  }
   int64_t incl = local;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    int64_t up = __shfl_up(incl, d, 64);
+    const int64_t up = __shfl_up(incl, d, 64);
     if (lane >= d) incl += up;
   }
-  if (lane == 63) wave_sums[wave] = incl;
+  if (lane == 63) wave_sums[0][wave] = incl;
   __syncthreads();
-  int64_t wave_base = 0, total = 0;
+  int64_t run = before + incl - local;
 #pragma unroll
-  for (int w = 0; w < kScanThreads / 64; ++w) {
-    if (w < wave) wave_base += wave_sums[w];
-    total += wave_sums[w];
-  }
-  int64_t run = wave_base + incl - local;
+  for (int w = 0; w < kScanThreads / 64; ++w)
+    if (w < wave) run += wave_sums[0][w];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     if (base + k < n) data[base + k] = run;
     run += v[k];
   }
-  if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
+  if (total_out != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) *total_out = run;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_add_kernel(int64_t* __restrict__ data, int64_t n,
-                                                                const int64_t* __restrict__ tile_offsets) {
-  const int64_t add = tile_offsets[blockIdx.x];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k)
-    if (base + k < n) data[base + k] += add;
-}
-
-__global__ void copy_one_i64_kernel(const int64_t* src, int64_t* dst) { *dst = src ? *src : 0; }
+__global__ void zero_one_i64_kernel(int64_t* dst) { *dst = 0; }
 
 size_t scan_scratch_elems(int64_t n) {
   size_t total = 1;
@@ -77,39 +101,22 @@ int32_t exclusive_scan_i64(int64_t* data, int64_t n, int64_t* scratch, int64_t* 
                            hipStream_t stream) {
   if (n <= 0) {
     if (total_out) {
-      copy_one_i64_kernel<<<1, 1, 0, stream>>>(nullptr, total_out);
+      zero_one_i64_kernel<<<1, 1, 0, stream>>>(total_out);
       GS_LAUNCH_CHECK();
     }
     return GS_OK;
   }
-  constexpr int kMaxLevels = 8;
-  int64_t* ptr[kMaxLevels + 1];
-  int64_t size[kMaxLevels + 1];
-  ptr[0] = data;
-  size[0] = n;
-  int levels = 0;
-  size_t used = 0;
-  while (true) {
-    const int64_t tiles = ceil_div(size[levels], kScanTile);
-    ptr[levels + 1] = scratch + used;
-    size[levels + 1] = tiles;
-    used += (size_t)tiles;
-    scan_tiles_kernel<<<dim3((unsigned)tiles), kScanThreads, 0, stream>>>(ptr[levels], size[levels],
-                                                                           ptr[levels + 1]);
+  const int64_t tiles = ceil_div(n, kScanTile);
+  if (tiles > 1) {
+    scan_sums_i64_kernel<<<(unsigned)tiles, kScanThreads, 0, stream>>>(data, n, scratch);
     GS_LAUNCH_CHECK();
-    ++levels;
-    if (tiles == 1 || levels == kMaxLevels) break;
+    if (tiles > kScanFewTiles) {
+      const int32_t rc = exclusive_scan_i64(scratch, tiles, scratch + tiles, nullptr, stream);
+      if (rc != GS_OK) return rc;
+    }
   }
-  // ptr[levels][0] is the grand total (single tile at the top level)
-  if (total_out) {
-    copy_one_i64_kernel<<<1, 1, 0, stream>>>(ptr[levels], total_out);
-    GS_LAUNCH_CHECK();
-  }
-  for (int l = levels - 2; l >= 0; --l) {
-    scan_add_kernel<<<dim3((unsigned)size[l + 1]), kScanThreads, 0, stream>>>(ptr[l], size[l],
-                                                                               ptr[l + 1]);
-    GS_LAUNCH_CHECK();
-  }
+  scan_apply_i64_kernel<<<(unsigned)tiles, kScanThreads, 0, stream>>>(data, n, scratch, tiles > kScanFewTiles ? 1 : 0, total_out);
+  GS_LAUNCH_CHECK();
   return GS_OK;
 }
 
