@@ -584,21 +584,33 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
   } else if (l16 < count) {
     cen_s[l16] = row_of(a.centers[first + l16]);
   }
-  for (int t = l16; t < count * K1; t += kGroupLanes) {
-    const int p = t / K1, j = t - p * K1;
-    int32_t row;
-    if (j == 0) {
-      if (a.walks != nullptr) continue;     // set above
-      row = row_of(a.contexts[first + p]);
-    } else if (a.draw_negs) {
-      const Block4 b = philox_at(a.neg_seed, a.neg_pair_base + (uint64_t)(first + p), (uint32_t)(j - 1),
-                                 0x80000000u);
-      row = (int32_t)table_draw(a.noise_prob, a.noise_alias, a.noise_packed, (uint64_t)a.num_nodes, b);
-      a.negs_draw[(first + p) * (int64_t)K + (j - 1)] = row;
-    } else {
-      row = row_of(a.negs[(first + p) * (int64_t)K + (j - 1)]);
+  const int terms = count * K1;
+  constexpr int kIds = 4;                   // ids in flight per lane
+  for (int t0 = l16; t0 < terms; t0 += kIds * kGroupLanes) {
+    int32_t id[kIds];
+#pragma unroll
+    for (int c = 0; c < kIds; ++c) {
+      const int t = t0 + c * kGroupLanes;
+      const int p = t / K1, j = t - p * K1;
+      id[c] = 0;
+      if (t >= terms) continue;
+      if (j == 0) {
+        if (a.walks == nullptr) id[c] = a.contexts[first + p];
+      } else if (a.draw_negs) {
+        const Block4 b = philox_at(a.neg_seed, a.neg_pair_base + (uint64_t)(first + p), (uint32_t)(j - 1),
+                                   0x80000000u);
+        id[c] = (int32_t)table_draw(a.noise_prob, a.noise_alias, a.noise_packed, (uint64_t)a.num_nodes, b);
+        a.negs_draw[(first + p) * (int64_t)K + (j - 1)] = id[c];
+      } else {
+        id[c] = a.negs[(first + p) * (int64_t)K + (j - 1)];
+      }
     }
-    rows_s[t] = row;
+#pragma unroll
+    for (int c = 0; c < kIds; ++c) {
+      const int t = t0 + c * kGroupLanes;
+      if (t >= terms || (a.walks != nullptr && t % K1 == 0)) continue;      // (a walk's pairs: set above)
+      rows_s[t] = row_of(id[c]);
+    }
   }
   __syncthreads();
 
@@ -617,6 +629,10 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
     const int32_t c = cen_s[p];
     if (c != cur_c) {
       if (cur_c >= 0) {
+  // The rank of the lane's last term, and the place of that term's id, which it takes one block of terms later: reads and
+  // atomics return in order, so a rank is asked for behind the rows of its block and not waited for before the next.
+  uint32_t held = 0u;
+  int held_at = -1;
         peak = fmaxf(peak, row_peak<VPL>(du));
         stage_flush<T, VPL, kGroup>(a, first + flushes++, cur_c, l16, du);
       }
@@ -637,14 +653,6 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
       // lane b of the group owns term j0 + b of this block of RB terms
       const int my_j = j0 + l16;
       const bool mine = l16 < RB && my_j <= K;
-      uint32_t rk = 0;
-      if (kGroup == kByCounter && mine) {
-        const int32_t row = prow[my_j];
-        const uint32_t h = ((uint32_t)row * 2654435761u) >> (32 - kHotBits);
-        const int32_t seen = atomicCAS(&hot_key[h], -1, row);
-        if (seen == -1 || seen == row) rk = kRankPending | (atomicAdd(&hot_cnt[h], 1u) << kHotBits) | h;
-        else rk = atomicAdd(a.cnt + claim_slot(a, (uint32_t)row), 1u);
-      }
       RawRow<T, VPL> vv[RB];
 #pragma unroll
       for (int b = 0; b < RB; ++b)
@@ -654,6 +662,18 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
       for (int b = 0; b < RB; ++b) {
         if (j0 + b <= K) {
           const float x = row_sum16(dot_partial<VPL>(u, vv[b]));
+      if constexpr (kGroup == kByCounter) {
+        if (held_at >= 0) rows_s[held_at] = (int32_t)held;
+        held_at = -1;
+        if (mine) {
+          const int32_t row = prow[my_j];
+          const uint32_t h = ((uint32_t)row * 2654435761u) >> (32 - kHotBits);
+          const int32_t seen = atomicCAS(&hot_key[h], -1, row);
+          if (seen == -1 || seen == row) held = kRankPending | (atomicAdd(&hot_cnt[h], 1u) << kHotBits) | h;
+          else held = atomicAdd(a.cnt + claim_slot(a, (uint32_t)row), 1u);
+          held_at = p * K1 + my_j;
+        }
+      }
           if (l16 == b) x_mine = x;
         }
       }
@@ -673,7 +693,6 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
         } else {
           a.g[e0 + my_j] = g_mine;
         }
-        if constexpr (kGroup == kByCounter) a.rank[e0 + my_j] = rk;
       }
     }
   }
@@ -692,13 +711,12 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
     // one global update per locally counted row, then complete the pending ranks
     for (int h = threadIdx.x; h < kHotSlots; h += kThreads)
       if (hot_key[h] >= 0) hot_base[h] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)hot_key[h]), hot_cnt[h]);
+  if (kGroup == kByCounter && held_at >= 0) rows_s[held_at] = (int32_t)held;
     __syncthreads();
-    for (int t = l16; t < count * K1; t += kGroupLanes) {
-      const int64_t e = first * (int64_t)K1 + t;
-      // written above by another lane of this group: read it back past the L1
-      const uint32_t rk = __hip_atomic_load(a.rank + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (rk & kRankPending)
-        a.rank[e] = hot_base[rk & (kHotSlots - 1)] + ((rk & ~kRankPending) >> kHotBits);
+    for (int t = l16; t < terms; t += kGroupLanes) {
+      const uint32_t rk = (uint32_t)rows_s[t];
+      a.rank[first * (int64_t)K1 + t] =
+          (rk & kRankPending) ? hot_base[rk & (kHotSlots - 1)] + ((rk & ~kRankPending) >> kHotBits) : rk;
     }
   }
   if (threadIdx.x == 0 && block_live) {
@@ -1282,8 +1300,16 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_update_kernel(SgnsArgs a) {
     const int64_t slice_begin = pos_lo + wave * slice;
     if (slice_begin >= pos_hi) break;
     const int64_t slice_end = min(slice_begin + slice, pos_hi);
-    const int64_t begin = next_segment_start(sorted, slice_begin, pos_hi, lane, seg_mask);   // what lies before is an earlier wave's
-    const int64_t end = next_segment_start(sorted, slice_end, pos_hi, lane, seg_mask);       // finish the segment we started
+    // what lies before `begin` is an earlier wave's; up to `end`: finish the segment we started (the 64 positions
+    // behind either end, which almost always decide, are read together)
+    const uint32_t behind_begin = slice_begin + lane < pos_hi ? sorted[slice_begin + lane].pos & seg_mask : 0u;
+    const uint32_t behind_end = slice_end + lane < pos_hi ? sorted[slice_end + lane].pos & seg_mask : 0u;
+    auto segment_start = [&](int64_t p, uint32_t behind) {
+      const unsigned long long starts = __builtin_amdgcn_ballot_w64(behind == 0u);
+      return starts != 0ull ? min(pos_hi, p + (int64_t)__builtin_ctzll(starts)) : next_segment_start(sorted, p + 64, pos_hi, lane, seg_mask);
+    };
+    const int64_t begin = segment_start(slice_begin, behind_begin);
+    const int64_t end = segment_start(slice_end, behind_end);
     update_range<T, WPP, PPL, UB, kOpt, kStage, true>(a, sorted, begin, end, pos_hi, lane);
   }
 }
