@@ -624,15 +624,15 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
   // coef is -lr * g with |g| <= 1 times an element of an input row, or -lr times an element
   // of a staged gradient.  Both kinds of rows pass through this kernel, which checks them.
   float peak = 0.f;
+  // The rank of the lane's last term, and the place of that term's id, which it takes one block of terms later: reads and
+  // atomics return in order, so a rank is asked for behind the rows of its block and not waited for before the next.
+  uint32_t held = 0u;
+  int held_at = -1;
 
   for (int p = 0; p < count; ++p) {
     const int32_t c = cen_s[p];
     if (c != cur_c) {
       if (cur_c >= 0) {
-  // The rank of the lane's last term, and the place of that term's id, which it takes one block of terms later: reads and
-  // atomics return in order, so a rank is asked for behind the rows of its block and not waited for before the next.
-  uint32_t held = 0u;
-  int held_at = -1;
         peak = fmaxf(peak, row_peak<VPL>(du));
         stage_flush<T, VPL, kGroup>(a, first + flushes++, cur_c, l16, du);
       }
@@ -657,11 +657,6 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
 #pragma unroll
       for (int b = 0; b < RB; ++b)
         if (j0 + b <= K) load_raw<VPL>(w_out, prow[j0 + b], a.dim, l16, vv[b]);
-      float x_mine = 0.f;
-#pragma unroll
-      for (int b = 0; b < RB; ++b) {
-        if (j0 + b <= K) {
-          const float x = row_sum16(dot_partial<VPL>(u, vv[b]));
       if constexpr (kGroup == kByCounter) {
         if (held_at >= 0) rows_s[held_at] = (int32_t)held;
         held_at = -1;
@@ -674,6 +669,11 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
           held_at = p * K1 + my_j;
         }
       }
+      float x_mine = 0.f;
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        if (j0 + b <= K) {
+          const float x = row_sum16(dot_partial<VPL>(u, vv[b]));
           if (l16 == b) x_mine = x;
         }
       }
@@ -706,12 +706,12 @@ __global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
 
   loss = row_sum16(loss);
   if (l16 == 0) loss_s[group_in_block] = loss;
+  if (kGroup == kByCounter && held_at >= 0) rows_s[held_at] = (int32_t)held;
   __syncthreads();
   if constexpr (kGroup == kByCounter) {
     // one global update per locally counted row, then complete the pending ranks
     for (int h = threadIdx.x; h < kHotSlots; h += kThreads)
       if (hot_key[h] >= 0) hot_base[h] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)hot_key[h]), hot_cnt[h]);
-  if (kGroup == kByCounter && held_at >= 0) rows_s[held_at] = (int32_t)held;
     __syncthreads();
     for (int t = l16; t < terms; t += kGroupLanes) {
       const uint32_t rk = (uint32_t)rows_s[t];
@@ -2294,6 +2294,11 @@ __global__ __launch_bounds__(256) void dense_rest_kernel(SgnsArgs a, int pieces,
       }
       store_once(v_t + at, make_uint4(__float_as_uint(ve[0]), __float_as_uint(ve[1]), __float_as_uint(ve[2]), __float_as_uint(ve[3])));
     }
+    uint32_t mo[4], wo[4];
+    pack_piece<T, 4>(me, mo);
+    pack_piece<T, 4>(we, wo);
+    store_once(m_t + at, make_uint4(mo[0], mo[1], mo[2], mo[3]));
+    store_once(w_t + at, make_uint4(wo[0], wo[1], wo[2], wo[3]));
   }
 }
 
@@ -2325,11 +2330,6 @@ static int32_t check_sgns_args(const void* w_in, const void* w_out, int64_t num_
 }
 
 // What the variants of the step add to the plain one.
-    uint32_t mo[4], wo[4];
-    pack_piece<T, 4>(me, mo);
-    pack_piece<T, 4>(we, wo);
-    store_once(m_t + at, make_uint4(mo[0], mo[1], mo[2], mo[3]));
-    store_once(w_t + at, make_uint4(wo[0], wo[1], wo[2], wo[3]));
 struct SgnsExtras {
   int opt = kPlain;                // the optimizer behind the update, its rates
   OptRates rates = {};
