@@ -513,8 +513,16 @@ __device__ __forceinline__ float row_peak(const float4 (&r)[VPL]) {
 //   kInLds      the step of a small batch, whose update kernel groups the terms itself: nothing is
 //               counted, and a bad id or an out-of-range product turns the block's loss partial into
 //               NaN (there is no flag that an earlier kernel would have cleared)
+// Waves per SIMD that the registers have to leave room for (0: no say), where a few registers less make one more: the
+// kernel waits for rows, and waves are what covers that.  Steps of 60,000 pairs, 256 fp32 columns 190 -> 179 us (131 registers
+// before), 100,000 pairs, 400 bf16 columns 450 -> 393 us (175), 300,000, 200 fp16 columns 650 -> 630; 384 and 512 fp32 columns with
+// 3 instead of 2 waves 248 -> 263 and 277 -> 289, up to 128 with 5 instead of 4 208 -> 217, so not there.
+template <typename T, int VPL>
+constexpr int forward_waves() {
+  return VPL == 4 ? 4 : (VPL == 8 && sizeof(T) == 2 ? 3 : 0);
+}
 template <typename T, int VPL, int RB, int kGroup, int kThreads>
-__global__ __launch_bounds__(kThreads) void sgns_forward_kernel(SgnsArgs a) {
+__global__ __launch_bounds__(kThreads, (forward_waves<T, VPL>())) void sgns_forward_kernel(SgnsArgs a) {
   constexpr int kGroups = kThreads / kGroupLanes;
   extern __shared__ int32_t idx_s[];              // per group: centres[chunk], rows[chunk][K+1]
   __shared__ float loss_s[kGroups];
