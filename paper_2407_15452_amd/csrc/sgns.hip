@@ -506,23 +506,15 @@ __device__ __forceinline__ float row_peak(const float4 (&r)[VPL]) {
   return m;
 }
 
-//
 // kGroup: how the terms of a row come together afterwards.
 //   kByCounter  every term takes a rank from its row's counter (for the place kernel)
 //   kBySort     every term is written as a record for the sort; only staging slots are counted
 //   kInLds      the step of a small batch, whose update kernel groups the terms itself: nothing is
 //               counted, and a bad id or an out-of-range product turns the block's loss partial into
 //               NaN (there is no flag that an earlier kernel would have cleared)
-// Waves per SIMD that the registers have to leave room for (0: no say), where a few registers less make one more: the
-// kernel waits for rows, and waves are what covers that.  Steps of 60,000 pairs, 256 fp32 columns 190 -> 179 us (131 registers
-// before), 100,000 pairs, 400 bf16 columns 450 -> 393 us (175), 300,000, 200 fp16 columns 650 -> 630; 384 and 512 fp32 columns with
-// 3 instead of 2 waves 248 -> 263 and 277 -> 289, up to 128 with 5 instead of 4 208 -> 217, so not there.
-template <typename T, int VPL>
-constexpr int forward_waves() {
-  return VPL == 4 ? 4 : (VPL == 8 && sizeof(T) == 2 ? 3 : 0);
-}
-template <typename T, int VPL, int RB, int kGroup, int kThreads>
-__global__ __launch_bounds__(kThreads, (forward_waves<T, VPL>())) void sgns_forward_kernel(SgnsArgs a) {
+// kWaves: waves per SIMD that the registers have to leave room for (0: no say); see launch_forward.
+template <typename T, int VPL, int RB, int kGroup, int kThreads, int kWaves = 0>
+__global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs a) {
   constexpr int kGroups = kThreads / kGroupLanes;
   extern __shared__ int32_t idx_s[];              // per group: centres[chunk], rows[chunk][K+1]
   __shared__ float loss_s[kGroups];
@@ -594,14 +586,15 @@ __global__ __launch_bounds__(kThreads, (forward_waves<T, VPL>())) void sgns_forw
   }
   const int terms = count * K1;
   constexpr int kIds = 4;                   // ids in flight per lane
+  const uint32_t per_k1 = (65535u + (uint32_t)K1) / (uint32_t)K1;       // t / K1 = t * per_k1 >> 16 for t < 16 * 61
   for (int t0 = l16; t0 < terms; t0 += kIds * kGroupLanes) {
     int32_t id[kIds];
 #pragma unroll
     for (int c = 0; c < kIds; ++c) {
       const int t = t0 + c * kGroupLanes;
-      const int p = t / K1, j = t - p * K1;
       id[c] = 0;
       if (t >= terms) continue;
+      const int p = (int)((uint32_t)t * per_k1 >> 16), j = t - p * K1;
       if (j == 0) {
         if (a.walks == nullptr) id[c] = a.contexts[first + p];
       } else if (a.draw_negs) {
@@ -2106,6 +2099,23 @@ static int32_t launch_sorted_updates(const SgnsArgs& a, hipStream_t stream) {
   return GS_OK;
 }
 
+// The kernel waits for rows, and waves are what covers that: where a few registers less make one more wave per SIMD, batches that
+// fill the chip take them.  Steps of 60,000 pairs, 256 fp32 columns 190 -> 179 us (131 registers before), 100,000 pairs, 400 bf16
+// columns 450 -> 393 us (175), 300,000, 200 fp16 columns 650 -> 630, 1 M, 256 bf16 columns 2559 -> 2440; 7712 pairs, 196 fp32 columns
+// (482 waves) 101 -> 103.5, so not there; 384 and 512 fp32 columns with 3 instead of 2 waves 248 -> 263 and 277 -> 289, up to 128
+// with 5 instead of 4 208 -> 217, so neither there.
+template <typename T, int VPL, int RB, int kGroup>
+static void launch_forward(const SgnsArgs& a, hipStream_t stream) {
+  constexpr int kMore = VPL == 4 ? 4 : (VPL == 8 && sizeof(T) == 2 ? 3 : 0);
+  const unsigned blocks = (unsigned)(a.forward_blocks_per_xcd * 8);
+  const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
+  constexpr int64_t kSimds = 1024;
+  if (kMore != 0 && a.forward_blocks * (kSgnsThreads / 64) > (kMore - 1) * kSimds)
+    sgns_forward_kernel<T, VPL, RB, kGroup, kSgnsThreads, kMore><<<blocks, kSgnsThreads, idx_lds, stream>>>(a);
+  else
+    sgns_forward_kernel<T, VPL, RB, kGroup, kSgnsThreads><<<blocks, kSgnsThreads, idx_lds, stream>>>(a);
+}
+
 template <typename T, int VPL, int RB>
 static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStream_t stream) {
   SgnsArgs a = unsorted;
@@ -2115,9 +2125,7 @@ static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStr
   a.term_src = p.term_src[made];
   int32_t rc = launch_clear(a, stream);
   if (rc != GS_OK) return rc;
-  const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
-  sgns_forward_kernel<T, VPL, RB, kBySort, kSgnsThreads>
-      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds, stream>>>(a);
+  launch_forward<T, VPL, RB, kBySort>(a, stream);
   GS_LAUNCH_CHECK();
   rc = launch_scan(a, stream);
   if (rc != GS_OK) return rc;
@@ -2151,9 +2159,7 @@ static int32_t launch_sgns(const SgnsArgs& a, const SgnsPlan& p, int opt, hipStr
   if (p.by_sort) return launch_sorted<T, VPL, RB>(a, p, stream);
   int32_t rc = launch_clear(a, stream);
   if (rc != GS_OK) return rc;
-  const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
-  sgns_forward_kernel<T, VPL, RB, kByCounter, kSgnsThreads>
-      <<<(unsigned)(a.forward_blocks_per_xcd * 8), kSgnsThreads, idx_lds, stream>>>(a);
+  launch_forward<T, VPL, RB, kByCounter>(a, stream);
   GS_LAUNCH_CHECK();
   rc = launch_scan(a, stream);
   if (rc != GS_OK) return rc;
