@@ -2248,6 +2248,7 @@ __device__ __forceinline__ bool row_named(const SgnsArgs& a, uint32_t key) {
 // them: 0.65 and 1.00 ms with four rows, a loop over the rest of the table and accesses that go through the caches
 // (plain against uncached accesses, no rows left out: 5.5 and 6.1 TB/s).
 constexpr int kDenseRows = 2;
+constexpr int kDenseBlocks = 1 << 23;          // workgroups in one dimension of the launch
 // accesses to memory that no cache will be asked for again
 typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_once(const uint4* p) {
@@ -2266,7 +2267,8 @@ __global__ __launch_bounds__(256) void dense_rest_kernel(SgnsArgs a, int pieces,
   uint4* __restrict__ m_t = static_cast<uint4*>(input_table ? a.dst_in : a.dst_out);
   uint4* __restrict__ w_t = static_cast<uint4*>(input_table ? a.w_in : a.w_out);
   uint4* __restrict__ v_t = reinterpret_cast<uint4*>(input_table ? a.sq_in : a.sq_out);
-  const int64_t first = (int64_t)blockIdx.x * (rows_at_once * kDenseRows) + in_iter;
+  const int64_t block = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+  const int64_t first = block * (rows_at_once * kDenseRows) + in_iter;
   bool mine[kDenseRows];
 #pragma unroll
   for (int u = 0; u < kDenseRows; ++u) {
@@ -2320,7 +2322,10 @@ template <typename T, int kOpt>
 static int32_t launch_dense_rest(const SgnsArgs& a, bool any_named, hipStream_t stream) {
   const int pieces = a.dim * (int)sizeof(T) / 16;
   const int64_t per_block = (int64_t)(256 / pieces) * kDenseRows;
-  const dim3 grid((unsigned)ceil_div(a.num_nodes, per_block), 2);
+  // (a dimension of a launch is below 2^32 lanes, which 2 rows of 129 pieces per workgroup leave within this card's memory)
+  const int64_t blocks = ceil_div(a.num_nodes, per_block);
+  const int64_t layers = max((int64_t)1, ceil_div(blocks, (int64_t)kDenseBlocks));
+  const dim3 grid((unsigned)ceil_div(blocks, layers), 2, (unsigned)layers);
   dense_rest_kernel<T, kOpt><<<grid, 256, 0, stream>>>(a, pieces, any_named);
   GS_LAUNCH_CHECK();
   return GS_OK;

@@ -69,3 +69,30 @@ def test_unique_ids_by_sorting(gs, n, num_nodes):
     got = inv.cpu().numpy()
     np.testing.assert_array_equal(got[ids >= 0], inverse)
     assert (got[ids < 0] == -1).all()
+
+
+@pytest.mark.parametrize("num_nodes", [1, 2, 3, 255, 256, 257, 65_535, 65_536])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_csr_with_nodes_that_fill_their_bits(gs, oracle, num_nodes, weighted):
+    """Dropped records (ids that are no nodes, self loops) next to the largest entry a graph can have."""
+    m = 5000
+    rng = np.random.default_rng(num_nodes)
+    src, dst = (rng.integers(-1, num_nodes + 1, m).astype(np.int32) for _ in range(2))
+    src[:3], dst[:3] = num_nodes - 1, [num_nodes - 1, max(0, num_nodes - 2), num_nodes - 1]
+    w = rng.random(m).astype(np.float32) if weighted else None
+    for flags in (0, gs.GS_SYMMETRIZE | gs.GS_DROP_SELF_LOOPS | gs.GS_DEDUPE):
+        off, nb, wo = oracle.csr_build(src, dst, w, num_nodes, flags, 32)
+        g = gs.gs_csr_build(_t(src), _t(dst), _t(w) if weighted else None, num_nodes, flags)
+        np.testing.assert_array_equal(g.offsets.cpu().numpy(), off)
+        np.testing.assert_array_equal(g.nbrs.cpu().numpy(), nb)
+        if weighted:
+            np.testing.assert_array_equal(g.weights.cpu().numpy(), wo)
+
+
+@pytest.mark.parametrize("walks", [1, 1023, 1024, 1025, 70_001, (4096 << 10) - 1, (4096 << 10) + 1])
+def test_offsets_of_pairs(gs, walks):
+    """The 64-bit scan: one tile, tiles whose sums every workgroup adds up, and more tiles than that."""
+    length = np.random.default_rng(walks).integers(1, 4, walks)
+    w = np.where(np.arange(3)[None, :] < length[:, None], 7, -1).astype(np.int32)
+    want = np.concatenate([[0], np.cumsum(2 * (length - 1))])            # window 1: both directions of every step
+    np.testing.assert_array_equal(gs.gs_pair_offsets(_t(w), 1).cpu().numpy(), want)

@@ -160,3 +160,12 @@ def test_smaller_workspace(call, n, b, k, dim):
             assert_emb_close(_host(x, "f32"), _host(y, "f32"))
         else:
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("b,k,dim,fmt", [(49_152, 5, 256, "f32"), (49_153, 5, 196, "f32"), (49_217, 2, 256, "bf16"),
+                                         (49_217, 1, 200, "f16"), (32_768, 3, 400, "bf16"), (32_769, 3, 264, "f16"),
+                                         (32_833, 60, 512, "bf16")])
+def test_wide_rows_on_both_sides_of_a_full_chip(oracle, b, k, dim, fmt):
+    """The forward kernel with room for one more wave per SIMD (3072 waves and more of four pieces per lane, 2048 of eight)
+    and without; one negative to the most there are."""
+    _step(oracle, 15_000, b, k, dim, fmt)
