@@ -49,6 +49,24 @@ def test_unique_ids(gs, oracle, n, num_nodes, bad):
     np.testing.assert_array_equal(u2[:k].cpu().numpy(), want_u)
 
 
+@pytest.mark.parametrize("n,num_nodes", [(1, 1), (1, 16), (1, 17), (3, 31), (3, 32), (3, 33), (1023, 16_000), (1024, 16_384),
+                                         (1025, 16_401), (5000, 8_191), (5000, 80_001), (600_000, 40)])
+def test_unique_ids_by_bytes_and_by_bits(gs, oracle, n, num_nodes):
+    """Both ways of marking: up to 16 nodes per id with a byte per node where the workspace has room for them, else bits."""
+    rng = np.random.default_rng(n + num_nodes)
+    ids = rng.integers(-2, num_nodes + 2, n).astype(np.int32)
+    ids[0] = num_nodes - 1
+    want_u, want_inv = oracle.unique_ids(ids, num_nodes)
+    full = gs.gs_unique_ids_workspace_bytes(n, num_nodes)
+    bits = gs.gs_unique_ids_workspace_bytes((num_nodes + 255) // 256, num_nodes)   # what the bits take
+    for size in {full, min(full, bits)}:
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
+        u, count, inv = gs.gs_unique_ids(_t(ids), num_nodes, ws=ws)
+        assert int(count.item()) == want_u.size
+        np.testing.assert_array_equal(u[:want_u.size].cpu().numpy(), want_u)
+        np.testing.assert_array_equal(inv.cpu().numpy(), want_inv)
+
+
 @pytest.mark.parametrize("dtype,dim", [("f32", 128), ("f32", 4), ("f32", 100), ("bf16", 256),
                                        ("bf16", 8), ("bf16", 72), ("f32", 1024), ("f16", 128),
                                        ("f16", 8)])
