@@ -24,8 +24,8 @@
 // in LDS, longer ones (the rows of hub nodes) by a workgroup of 1024 lanes; a very long one that is
 // alone in its call (the noise table) gets its sum, its lists and its first rounds from the whole chip.
 // All are bound by latency, so the limits lie where the next larger team finishes the longest segment
-// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 0.86 ms (lanes 0.12, waves
-// 0.11 + 0.19, workgroups 0.41), 1.9 ms (0.29, 0.20 + 0.45, 0.92) with lists in global memory for the lanes, sums in index order and
+// sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 0.76 ms (lanes 0.12, the
+// rest, whose longest row takes 0.41, 0.62), 1.9 ms (lanes 0.29, waves 0.20 + 0.45, workgroups 0.92) with a launch per size, lists in global memory for the lanes, sums in index order and
 // a look at all lists in every round; the noise table of 1 M entries 0.72 ms (sum 0.02, lists and 16 rounds of the chip 0.18, few
 // larges 0.47), 2.5 ms before; that of 4 M nodes 1.6 ms, 7.1 before.
 #include <type_traits>
@@ -129,21 +129,109 @@ __device__ __forceinline__ bool any_order(double sum, int least_exponent) {     
 }
 
 // ---- one wave per segment --------------------------------------------------------------------
-// Segments of MIN_N .. MAX_N entries: masses and both lists in LDS, up to 64 iterations at a time.  A
-// wave looks at `per_wave` consecutive segments and takes those of its size.
+// A segment of n <= MAX_N entries: masses and both lists in LDS, up to 64 iterations at a time.
+template <int MAX_N>
+struct WaveLists {
+  double mass[MAX_N];
+  uint16_t small_q[MAX_N];                     // every entry enters at most once: no wrap
+  uint16_t large_q[MAX_N];
+};
+template <int MAX_N>
+__device__ __forceinline__ void wave_segment(WaveLists<MAX_N>& lists, int lane, int n, const float* __restrict__ w,
+                                             float* __restrict__ prob, int32_t* __restrict__ alias) {
+#pragma clang fp contract(off)  // every fp64 operation below must round on its own
+  static_assert((MAX_N & (MAX_N - 1)) == 0, "the list of larges wraps by a mask");
+  double* mass = lists.mass;
+  uint16_t *small_q = lists.small_q, *large_q = lists.large_q;
+  const uint64_t below = (1ull << lane) - 1ull;
+  const double dn = (double)n;
+  double S = 0.0;
+  int least = 255;
+  for (int base = lane; base < n; base += 64) {
+    const float v = w[base];
+    mass[base] = (double)v * dn;
+    S += (double)v;
+    least = min(least, weight_exponent(v));
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    S += __shfl_xor(S, d, 64);
+    least = min(least, __shfl_xor(least, d, 64));
+  }
+  if (!any_order(S, least)) {
+    S = 0.0;
+    for (int base = 0; base < n; base += 64) {
+      const double v = base + lane < n ? (double)w[base + lane] : 0.0;
+#pragma unroll 16
+      for (int k = 0; k < 64; ++k) S += lane_value(v, k);       // (+ 0.0 behind the end changes nothing)
+    }
+  }
+  int sh = 0, st = 0, lh = 0, lt = 0;        // heads and tails of the lists, the same in every lane
+  wave_fence();
+  for (int base = 0; base < n; base += 64) {
+    const bool valid = base + lane < n;
+    const bool is_small = valid && mass[base + lane] < S;
+    const uint64_t smalls = __ballot(is_small), larges = __ballot(valid && !is_small);
+    if (is_small) small_q[st + __popcll(smalls & below)] = (uint16_t)(base + lane);
+    else if (valid) large_q[lt + __popcll(larges & below)] = (uint16_t)(base + lane);
+    st += __popcll(smalls);
+    lt += __popcll(larges);
+  }
+  wave_fence();
+  while (sh < st && lh < lt) {
+    const int m = min(64, min(st - sh, lt - lh));
+    int b = 0;
+    bool demoted = false;
+    if (lane < m) {
+      const int a = small_q[sh + lane];
+      b = large_q[(lh + lane) & (MAX_N - 1)];
+      alias[a] = b;
+      const double mb = (mass[b] + mass[a]) - S;
+      mass[b] = mb;
+      demoted = mb < S;
+    }
+    const uint64_t down = __ballot(lane < m && demoted), stay = __ballot(lane < m && !demoted);
+    sh += m;
+    lh += m;
+    wave_fence();
+    if (lane < m) {
+      if (demoted) small_q[st + __popcll(down & below)] = (uint16_t)b;
+      else large_q[(lt + __popcll(stay & below)) & (MAX_N - 1)] = (uint16_t)b;
+    }
+    st += __popcll(down);
+    lt += __popcll(stay);
+    wave_fence();
+  }
+  // (a small's mass does not change once it is one: the divisions are left to all lanes)
+  for (int i = lane; i < sh; i += 64) {
+    const int a = small_q[i];
+    prob[a] = (float)(mass[a] / S);
+  }
+  for (int i = sh + lane; i < st; i += 64) {
+    const int x = small_q[i];
+    prob[x] = 1.0f;
+    alias[x] = x;
+  }
+  for (int i = lh + lane; i < lt; i += 64) {
+    const int x = large_q[i & (MAX_N - 1)];
+    prob[x] = 1.0f;
+    alias[x] = x;
+  }
+  wave_fence();
+}
+
+// Segments of MIN_N .. MAX_N entries; a wave looks at `per_wave` consecutive segments and takes those of its size.
+// unless: nothing is done where this holds a number other than 0.
 template <typename OffT, int MIN_N, int MAX_N>
 __global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __restrict__ seg_offsets,
                                                               int64_t num_segments, int per_wave,
+                                                              const unsigned long long* __restrict__ unless,
                                                               const float* __restrict__ weights,
                                                               float* __restrict__ prob_out,
                                                               int32_t* __restrict__ alias_out) {
-#pragma clang fp contract(off)  // every fp64 operation below must round on its own
-  static_assert((MAX_N & (MAX_N - 1)) == 0, "the list of larges wraps by a mask");
-  __shared__ double mass[MAX_N];
-  __shared__ uint16_t small_q[MAX_N];          // every entry enters at most once: no wrap
-  __shared__ uint16_t large_q[MAX_N];
+  if (unless != nullptr && *unless != 0ull) return;
+  __shared__ WaveLists<MAX_N> lists;
   const int lane = threadIdx.x;
-  const uint64_t below = (1ull << lane) - 1ull;
   const int64_t first = (int64_t)blockIdx.x * per_wave;
   int64_t my_begin = 0, my_n = 0;
   if (lane < per_wave && first + lane < num_segments) {
@@ -157,83 +245,7 @@ __global__ __launch_bounds__(64) void alias_build_wave_kernel(const OffT* __rest
     const int n = __builtin_amdgcn_readlane((int)my_n, who);
     const int64_t begin = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(my_begin >> 32), who) << 32) |
                                     (uint32_t)__builtin_amdgcn_readlane((int)my_begin, who));
-    const float* w = weights + begin;
-    float* prob = prob_out + begin;
-    int32_t* alias = alias_out + begin;
-    const double dn = (double)n;
-    double S = 0.0;
-    int least = 255;
-    for (int base = lane; base < n; base += 64) {
-      const float v = w[base];
-      mass[base] = (double)v * dn;
-      S += (double)v;
-      least = min(least, weight_exponent(v));
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-      S += __shfl_xor(S, d, 64);
-      least = min(least, __shfl_xor(least, d, 64));
-    }
-    if (!any_order(S, least)) {
-      S = 0.0;
-      for (int base = 0; base < n; base += 64) {
-        const double v = base + lane < n ? (double)w[base + lane] : 0.0;
-#pragma unroll 16
-        for (int k = 0; k < 64; ++k) S += lane_value(v, k);       // (+ 0.0 behind the end changes nothing)
-      }
-    }
-    int sh = 0, st = 0, lh = 0, lt = 0;        // heads and tails of the lists, the same in every lane
-    wave_fence();
-    for (int base = 0; base < n; base += 64) {
-      const bool valid = base + lane < n;
-      const bool is_small = valid && mass[base + lane] < S;
-      const uint64_t smalls = __ballot(is_small), larges = __ballot(valid && !is_small);
-      if (is_small) small_q[st + __popcll(smalls & below)] = (uint16_t)(base + lane);
-      else if (valid) large_q[lt + __popcll(larges & below)] = (uint16_t)(base + lane);
-      st += __popcll(smalls);
-      lt += __popcll(larges);
-    }
-    wave_fence();
-    while (sh < st && lh < lt) {
-      const int m = min(64, min(st - sh, lt - lh));
-      int b = 0;
-      bool demoted = false;
-      if (lane < m) {
-        const int a = small_q[sh + lane];
-        b = large_q[(lh + lane) & (MAX_N - 1)];
-        alias[a] = b;
-        const double mb = (mass[b] + mass[a]) - S;
-        mass[b] = mb;
-        demoted = mb < S;
-      }
-      const uint64_t down = __ballot(lane < m && demoted), stay = __ballot(lane < m && !demoted);
-      sh += m;
-      lh += m;
-      wave_fence();
-      if (lane < m) {
-        if (demoted) small_q[st + __popcll(down & below)] = (uint16_t)b;
-        else large_q[(lt + __popcll(stay & below)) & (MAX_N - 1)] = (uint16_t)b;
-      }
-      st += __popcll(down);
-      lt += __popcll(stay);
-      wave_fence();
-    }
-    // (a small's mass does not change once it is one: the divisions are left to all lanes)
-    for (int i = lane; i < sh; i += 64) {
-      const int a = small_q[i];
-      prob[a] = (float)(mass[a] / S);
-    }
-    for (int i = sh + lane; i < st; i += 64) {
-      const int x = small_q[i];
-      prob[x] = 1.0f;
-      alias[x] = x;
-    }
-    for (int i = lh + lane; i < lt; i += 64) {
-      const int x = large_q[i & (MAX_N - 1)];
-      prob[x] = 1.0f;
-      alias[x] = x;
-    }
-    wave_fence();
+    wave_segment<MAX_N>(lists, lane, n, weights + begin, prob_out + begin, alias_out + begin);
   }
 }
 
@@ -1182,27 +1194,33 @@ __global__ __launch_bounds__(256) void alias_wide_table_kernel(const OffT* __res
   }
 }
 
-// long_ids == null: the single segment 0; resume != null: whose sum and lists exist already.
+struct LongShared {
+  Runs run_s[kLongWaves];
+  uint32_t bad_s[kLongWaves];
+  double sum_s;
+  int tot[2][2][kLongWaves];                   // (two sets, used in turn: one barrier per use)
+  int64_t q_s[4];                              // small head/tail, large head/tail after a narrow stretch
+  BigRounds<false> big;
+};
+// One segment by the workgroup.  resume != null: its sum and lists exist already.
 // Scratch per entry of the segment, at the segment's own offsets: mass, the
 // small list (n entries), the large list (2n: appended without wrapping).
 template <typename OffT>
-__global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
-    const OffT* __restrict__ seg_offsets, const int64_t* __restrict__ long_ids,
-    const unsigned long long* __restrict__ long_count, const float* __restrict__ weights,
-    float* __restrict__ prob_out, int32_t* __restrict__ alias_out, double* mass_ws,
-    int32_t* small_ws, int32_t* large_ws, const ListState* __restrict__ resume, const double* __restrict__ sum) {
+__device__ __forceinline__ void long_segment(LongShared& shared, const OffT* __restrict__ seg_offsets, int64_t seg,
+                                             const float* __restrict__ weights, float* __restrict__ prob_out,
+                                             int32_t* __restrict__ alias_out, double* mass_ws, int32_t* small_ws,
+                                             int32_t* large_ws, const ListState* __restrict__ resume,
+                                             const double* __restrict__ sum) {
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
-  __shared__ Runs run_s[kLongWaves];
-  __shared__ uint32_t bad_s[kLongWaves];
-  __shared__ double sum_s;
-  __shared__ int tot[2][2][kLongWaves];        // (two sets, used in turn: one barrier per use)
-  __shared__ int64_t q_s[4];                   // small head/tail, large head/tail after a narrow stretch
-  __shared__ BigRounds<false> big;
+  auto& run_s = shared.run_s;
+  auto& bad_s = shared.bad_s;
+  auto& sum_s = shared.sum_s;
+  auto& tot = shared.tot;
+  auto& q_s = shared.q_s;
+  auto& big = shared.big;
   static_assert(kWindow >= 2 * kRing, "the rings lie in the window");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = (1ull << lane) - 1ull;
-  if (long_ids != nullptr && (unsigned long long)blockIdx.x >= *long_count) return;
-  const int64_t seg = long_ids != nullptr ? long_ids[blockIdx.x] : 0;
   const int64_t begin = (int64_t)seg_offsets[seg];
   const int64_t n = (int64_t)seg_offsets[seg + 1] - begin;
   if (n <= 0) return;
@@ -1358,6 +1376,90 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(
   }
 }
 
+// the single segment 0
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(const OffT* __restrict__ seg_offsets,
+                                                                        const float* __restrict__ weights,
+                                                                        float* __restrict__ prob_out,
+                                                                        int32_t* __restrict__ alias_out, double* mass_ws,
+                                                                        int32_t* small_ws, int32_t* large_ws,
+                                                                        const ListState* __restrict__ resume,
+                                                                        const double* __restrict__ sum) {
+  __shared__ LongShared shared;
+  long_segment<OffT>(shared, seg_offsets, 0, weights, prob_out, alias_out, mass_ws, small_ws, large_ws, resume, sum);
+}
+
+// All segments of 33 to 1024 entries and the long ones: the first `long_blocks` workgroups take the long ones, each of the
+// others the segments of its size among `per_block` consecutive ones, a wave per segment, whichever wave is free.
+// One launch, because the longest row of a skewed graph keeps one compute unit busy while the others wait for work.  R-MAT graphs,
+// whole calls, one launch per size against this: 10,000 nodes 145 / 109 us, 100,000 257 / 195, 300,000 (4 M edges) 396 / 296, 1 M
+// (10 M edges) 967 / 847.  But a compute unit holds 16 of these waves, and 32 that take 33 to 256 entries alone: without a long
+// row (200,000 rows of 100 entries 386 us, 453 from here) the segments are left to launches of their own.  The number of
+// long rows is known to the device alone, so both are launched, and the waves of the one that is not to be return.
+constexpr int kRowsMiddle = 256, kRowsMost = 1024;
+constexpr int kRowsWideWaves = 11;             // waves whose lists hold kRowsMost entries; the others' hold kRowsMiddle
+constexpr int kRowsPerBlock = 512;
+constexpr int64_t kRowsLongBlocks = 1024;
+struct RowsShared {
+  WaveLists<kRowsMost> wide[kRowsWideWaves];
+  WaveLists<kRowsMiddle> narrow[kLongWaves - kRowsWideWaves];
+  uint16_t wide_seg[kRowsPerBlock], narrow_seg[kRowsPerBlock];
+  int wide_count, narrow_count, wide_next, narrow_next;
+};
+static_assert(sizeof(RowsShared) <= 160 * 1024 && sizeof(RowsShared) >= sizeof(LongShared), "LDS of a compute unit");
+template <typename OffT>
+__global__ __launch_bounds__(kLongThreads) void alias_build_rows_kernel(
+    const OffT* __restrict__ seg_offsets, int64_t num_segments, int per_block, const int64_t* __restrict__ long_ids,
+    const unsigned long long* __restrict__ long_count, int64_t max_long, int long_blocks, const float* __restrict__ weights,
+    float* __restrict__ prob_out, int32_t* __restrict__ alias_out, double* mass_ws, int32_t* small_ws, int32_t* large_ws) {
+  __shared__ __attribute__((aligned(16))) char lds[sizeof(RowsShared)];
+  if ((int)blockIdx.x < long_blocks) {
+    LongShared& shared = *reinterpret_cast<LongShared*>(lds);
+    const int64_t count = (int64_t)min(*long_count, (unsigned long long)max_long);
+    for (int64_t b = blockIdx.x; b < count; b += long_blocks) {
+      long_segment<OffT>(shared, seg_offsets, long_ids[b], weights, prob_out, alias_out, mass_ws, small_ws, large_ws, nullptr,
+                         nullptr);
+      __syncthreads();
+    }
+    return;
+  }
+  if (*long_count == 0ull) return;
+  RowsShared& shared = *reinterpret_cast<RowsShared*>(lds);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  for (int64_t first = (int64_t)((int)blockIdx.x - long_blocks) * per_block; first < num_segments;
+       first += (int64_t)((int)gridDim.x - long_blocks) * per_block) {
+    __syncthreads();                           // (the last turn's segments have been taken)
+    if (threadIdx.x == 0) shared.wide_count = shared.narrow_count = shared.wide_next = shared.narrow_next = 0;
+    __syncthreads();
+    if ((int)threadIdx.x < per_block && first + threadIdx.x < num_segments) {
+      const int64_t n = (int64_t)seg_offsets[first + threadIdx.x + 1] - (int64_t)seg_offsets[first + threadIdx.x];
+      if (n > kRowsMiddle && n <= kRowsMost) shared.wide_seg[atomicAdd(&shared.wide_count, 1)] = (uint16_t)threadIdx.x;
+      else if (n > kLaneSegment && n <= kRowsMiddle) shared.narrow_seg[atomicAdd(&shared.narrow_count, 1)] = (uint16_t)threadIdx.x;
+    }
+    __syncthreads();
+    int64_t begin;
+    int n;
+    auto take = [&](int* next, int count, const uint16_t* segs) {
+      int at = 0;
+      if (lane == 0) at = atomicAdd(next, 1);
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (at >= count) return false;
+      const int64_t seg = first + __builtin_amdgcn_readfirstlane((int)segs[at]);
+      begin = (int64_t)seg_offsets[seg];
+      n = __builtin_amdgcn_readfirstlane((int)((int64_t)seg_offsets[seg + 1] - begin));
+      return true;
+    };
+    if (wave < kRowsWideWaves)
+      while (take(&shared.wide_next, shared.wide_count, shared.wide_seg))
+        wave_segment<kRowsMost>(shared.wide[wave], lane, n, weights + begin, prob_out + begin, alias_out + begin);
+    // (the lists of a wide wave are its own, and idle by now)
+    WaveLists<kRowsMiddle>& lists = wave < kRowsWideWaves ? *reinterpret_cast<WaveLists<kRowsMiddle>*>(&shared.wide[wave])
+                                                          : shared.narrow[wave - kRowsWideWaves];
+    while (take(&shared.narrow_next, shared.narrow_count, shared.narrow_seg))
+      wave_segment<kRowsMiddle>(lists, lane, n, weights + begin, prob_out + begin, alias_out + begin);
+  }
+}
+
 __global__ void alias_pack_kernel(const float* __restrict__ prob, const int32_t* __restrict__ alias,
                                   int64_t n, uint64_t* __restrict__ packed) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1453,8 +1555,8 @@ static int32_t launch_alias_wide(const OffT* seg_offsets, int64_t n, const float
                                                                p.alias_seq, left);
   alias_wide_table_kernel<OffT><<<blocks, 256, 0, stream>>>(seg_offsets, p.sum, p.small_q, p.mass_seq, p.alias_seq, left,
                                                             prob_out, alias_out);
-  alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, nullptr, nullptr, weights, prob_out, alias_out,
-                                                                p.mass, p.small_q, p.large_q, left + 1, p.sum);
+  alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, weights, prob_out, alias_out, p.mass, p.small_q,
+                                                                p.large_q, left + 1, p.sum);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
@@ -1465,8 +1567,8 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
                                   const AliasPlan& p, hipStream_t stream) {
   if (p.sum != nullptr) return launch_alias_wide(seg_offsets, total_entries, weights, prob_out, alias_out, p, stream);
   if (num_segments == 1 && total_entries > kWaveSegment) {
-    alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(
-        seg_offsets, nullptr, nullptr, weights, prob_out, alias_out, p.mass, p.small_q, p.large_q, nullptr, nullptr);
+    alias_build_long_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, weights, prob_out, alias_out, p.mass,
+                                                                  p.small_q, p.large_q, nullptr, nullptr);
     GS_LAUNCH_CHECK();
     return GS_OK;
   }
@@ -1474,36 +1576,44 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
   alias_build_kernel<OffT><<<(unsigned)ceil_div(num_segments, threads), threads, 0, stream>>>(
       seg_offsets, num_segments, weights, prob_out, alias_out);
   GS_LAUNCH_CHECK();
-  // few segments: a wave each; many: up to 64 per wave, so that the short ones cost one look
-  const int per_wave = (int)max((int64_t)1, min((int64_t)64, num_segments / 16384));
-  const unsigned waves = (unsigned)ceil_div(num_segments, per_wave);
-  if (total_entries > kLaneSegment) {
-    alias_build_wave_kernel<OffT, (int)kLaneSegment + 1, 256><<<waves, 64, 0, stream>>>(
-        seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
-    GS_LAUNCH_CHECK();
-  }
-  // (the LDS of a wave bounds how many there are at a time: 257 .. 2048 entries in one kernel 267 us on the 1 M-node graph)
-  if (total_entries > 256) {
-    alias_build_wave_kernel<OffT, 257, 1024><<<waves, 64, 0, stream>>>(
-        seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
-    GS_LAUNCH_CHECK();
-  }
-  if (total_entries > 1024) {
-    alias_build_wave_kernel<OffT, 1025, kWaveSegment><<<waves, 64, 0, stream>>>(
-        seg_offsets, num_segments, per_wave, weights, prob_out, alias_out);
-    GS_LAUNCH_CHECK();
-  }
-  // at most this many segments can be longer
+  // at most this many segments are longer than a wave's
   const int64_t max_long = min(num_segments, total_entries / (kWaveSegment + 1));
+  const unsigned long long* any_long = nullptr;
   if (max_long > 0) {
     zero_u64_kernel<<<1, 1, 0, stream>>>(p.long_count);
     GS_LAUNCH_CHECK();
     alias_find_long_kernel<OffT><<<(unsigned)ceil_div(num_segments, 256), 256, 0, stream>>>(
         seg_offsets, num_segments, p.long_ids, max_long, p.long_count);
     GS_LAUNCH_CHECK();
-    alias_build_long_kernel<OffT><<<(unsigned)max_long, kLongThreads, 0, stream>>>(
-        seg_offsets, p.long_ids, p.long_count, weights, prob_out, alias_out, p.mass, p.small_q,
-        p.large_q, nullptr, nullptr);
+    any_long = p.long_count;
+  }
+  // few segments: a wave each; many: up to 64 per wave, so that the short ones cost one look
+  const int per_wave = (int)max((int64_t)1, min((int64_t)64, num_segments / 16384));
+  const unsigned waves = (unsigned)ceil_div(num_segments, per_wave);
+  if (total_entries > kLaneSegment) {
+    alias_build_wave_kernel<OffT, (int)kLaneSegment + 1, kRowsMiddle><<<waves, 64, 0, stream>>>(
+        seg_offsets, num_segments, per_wave, any_long, weights, prob_out, alias_out);
+    GS_LAUNCH_CHECK();
+  }
+  // (the LDS of a wave bounds how many there are at a time: 257 .. 2048 entries in one kernel 267 us on the 1 M-node graph)
+  if (total_entries > kRowsMiddle) {
+    alias_build_wave_kernel<OffT, kRowsMiddle + 1, kRowsMost><<<waves, 64, 0, stream>>>(
+        seg_offsets, num_segments, per_wave, any_long, weights, prob_out, alias_out);
+    GS_LAUNCH_CHECK();
+  }
+  if (total_entries > kRowsMost) {
+    alias_build_wave_kernel<OffT, kRowsMost + 1, kWaveSegment><<<waves, 64, 0, stream>>>(
+        seg_offsets, num_segments, per_wave, nullptr, weights, prob_out, alias_out);
+    GS_LAUNCH_CHECK();
+  }
+  if (max_long > 0) {
+    const int long_blocks = (int)min(kRowsLongBlocks, max_long);
+    // few segments: 16 per workgroup, whose waves then take one or two each
+    const int per_block = (int)max((int64_t)16, min((int64_t)kRowsPerBlock, ceil_div(num_segments, 1024)));
+    const int64_t row_blocks = min((int64_t)1 << 20, ceil_div(num_segments, per_block));
+    alias_build_rows_kernel<OffT><<<(unsigned)(long_blocks + row_blocks), kLongThreads, 0, stream>>>(
+        seg_offsets, num_segments, per_block, p.long_ids, p.long_count, max_long, long_blocks, weights, prob_out, alias_out,
+        p.mass, p.small_q, p.large_q);
     GS_LAUNCH_CHECK();
   }
   return GS_OK;

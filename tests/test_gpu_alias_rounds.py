@@ -70,3 +70,19 @@ def test_order_of_the_sum_matters(oracle):
     w[::7] = np.float32(1e-42)
     w[5] = 1.0
     _check(oracle, np.array([0, 3000], dtype=np.int64), w)
+
+
+@pytest.mark.parametrize("segments", [1, 15, 16, 17, 1025, 16_385, 600_001])
+def test_rows_of_all_sizes_side_by_side(oracle, segments):
+    """The launch that takes rows by waves and by workgroups: 16 to 512 segments per workgroup, sizes at its edges, many long
+    rows next to each other, and none."""
+    rng = np.random.default_rng(segments)
+    edges = [32, 33, 255, 256, 257, 1023, 1024, 1025, 2047, 2048, 2049, 0, 1]
+    lens = rng.integers(0, 12, segments)
+    some = rng.random(segments) < min(1.0, 2000 / segments)
+    lens[some] = rng.choice(edges, int(some.sum()))
+    for long_rows in (True, False):
+        use = lens if long_rows else np.minimum(lens, 300 if segments > 1 else 1024)
+        seg = np.concatenate([[0], np.cumsum(use)]).astype(np.int32)
+        if seg[-1] > 0:
+            _check(oracle, seg, _weights("steep" if long_rows else "lognormal", int(seg[-1]), rng))
