@@ -25,8 +25,8 @@
 // alone in its call (the noise table) gets its sum, its lists and its first rounds from the whole chip.
 // All are bound by latency, so the limits lie where the next larger team finishes the longest segment
 // sooner.  Measured on a 1 M-node graph of 22 M weighted entries: row tables 0.76 ms (lanes 0.12, the
-// rest, whose longest row takes 0.41, 0.62), 1.9 ms (lanes 0.29, waves 0.20 + 0.45, workgroups 0.92) with a launch per size, lists in global memory for the lanes, sums in index order and
-// a look at all lists in every round; the noise table of 1 M entries 0.72 ms (sum 0.02, lists and 16 rounds of the chip 0.18, few
+// rest, whose longest row takes 0.41, 0.62), 1.9 ms (lanes 0.29, waves 0.20 + 0.45, workgroups 0.92) with a launch per size, lists
+// in global memory for the lanes, sums in index order and a look at all lists in every round; the noise table of 1 M entries 0.72 ms (sum 0.02, lists and 16 rounds of the chip 0.18, few
 // larges 0.47), 2.5 ms before; that of 4 M nodes 1.6 ms, 7.1 before.
 #include <type_traits>
 
