@@ -8,6 +8,7 @@
 // lanes to one.  Output rows are staged in LDS
 // in windows of kWin positions and written out as 64-byte row segments instead
 // of one scattered 4-byte store per position.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -510,10 +511,9 @@ static void launch_node2vec(int team, const WalkArgs& a, hipStream_t stream) {
 }
 
 template <typename OffT>
-static void launch_walk(bool weighted, bool second, float q, const WalkArgs& a, hipStream_t stream) {
+static void launch_walk(bool weighted, bool second, int team, const WalkArgs& a, hipStream_t stream) {
   const unsigned blocks = (unsigned)ceil_div(a.num_walks, kWalkThreads);
   if (second) {
-    const int team = team_size(weighted, q, a);
     if (weighted) launch_node2vec<OffT, true>(team, a, stream);
     else launch_node2vec<OffT, false>(team, a, stream);
   } else {
@@ -521,6 +521,9 @@ static void launch_walk(bool weighted, bool second, float q, const WalkArgs& a, 
     else walk_kernel<OffT, false><<<blocks, kWalkThreads, 0, stream>>>(a);
   }
 }
+
+// Walks in one launch, whose lanes (at most four to a walk where there are so many) have to stay below 2^32.
+constexpr int64_t kLaunchWalks = (int64_t)1 << 28;
 
 static int32_t walk_common(const gs_csr* g, const gs_alias* al, const int32_t* starts,
                            int64_t num_walks, uint64_t id_base, int32_t walk_len, bool second,
@@ -541,20 +544,24 @@ static int32_t walk_common(const gs_csr* g, const gs_alias* al, const int32_t* s
   a.prob = weighted ? al->prob : nullptr;
   a.alias = weighted ? al->alias : nullptr;
   a.packed = weighted ? reinterpret_cast<const uint2*>(al->packed) : nullptr;
-  a.starts = starts;
-  a.walks = walks_out;
   a.num_nodes = g->num_nodes;
   a.num_entries = g->num_entries;
   a.num_walks = num_walks;
-  a.id_base = id_base;
   a.seed = seed;
   a.walk_len = walk_len;
   a.inv_p = 1.0f / p;
   a.inv_q = 1.0f / q;
   a.max_bias = fmaxf(a.inv_p, fmaxf(1.0f, a.inv_q));
-  if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, q, a, stream);
-  else launch_walk<int32_t>(weighted, second, q, a, stream);
-  GS_LAUNCH_CHECK();
+  const int team = second ? team_size(weighted, q, a) : 1;
+  for (int64_t first = 0; first < num_walks; first += kLaunchWalks) {
+    a.starts = starts + first;
+    a.walks = walks_out + first * walk_len;
+    a.id_base = id_base + (uint64_t)first;
+    a.num_walks = std::min(kLaunchWalks, num_walks - first);          // (the runtime's own min takes ints on the host)
+    if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, team, a, stream);
+    else launch_walk<int32_t>(weighted, second, team, a, stream);
+    GS_LAUNCH_CHECK();
+  }
   return GS_OK;
 }
 

@@ -1,0 +1,107 @@
+"""What the library launches for calls of sizes that no test runs, on the CPU: a recorder takes the place of the HIP runtime's
+launch functions, refuses what no launch takes (2^32 lanes in one dimension), and writes down the rest.  Pointers are never followed."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+RECORDER = r"""
+#include <stddef.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <string.h>
+typedef struct { uint32_t x, y, z; } Dim;
+static struct { const void* f; const char* name; } known[4096];
+static int count, error;
+static Dim grid, block;
+static void* handle;
+int __hipPushCallConfiguration(Dim g, Dim b, size_t lds, void* s) { (void)lds; (void)s; grid = g; block = b; return 0; }
+int __hipPopCallConfiguration(Dim* g, Dim* b, size_t* lds, void** s) { *g = grid; *b = block; *lds = 0; *s = NULL; return 0; }
+void** __hipRegisterFatBinary(const void* d) { (void)d; return &handle; }
+void __hipUnregisterFatBinary(void** h) { (void)h; }
+void __hipRegisterVar(void** h, void* v, char* a, char* b, int e, size_t s, int c, int g) {
+  (void)h; (void)v; (void)a; (void)b; (void)e; (void)s; (void)c; (void)g;
+}
+void __hipRegisterFunction(void** h, const void* f, char* d, const char* name, unsigned t, void* a, void* b, void* c, void* e, int* w) {
+  (void)h; (void)d; (void)t; (void)a; (void)b; (void)c; (void)e; (void)w;
+  if (count < 4096) { known[count].f = f; known[count++].name = name; }
+}
+int hipGetLastError(void) { int e = error; error = 0; return e; }
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = (void*)256; return 0; }
+int hipLaunchKernel(const void* f, Dim g, Dim b, void** args, size_t lds, void* s) {
+  const char* name = "?";
+  int i;
+  (void)lds; (void)s;
+  for (i = 0; i < count; ++i) if (known[i].f == f) name = known[i].name;
+  if ((uint64_t)g.x * b.x >> 32 || (uint64_t)g.y * b.y >> 32 || (uint64_t)g.z * b.z >> 32 || !g.x || !g.y || !g.z) {
+    error = 9;
+    return 9;
+  }
+  printf("[\"%s\", %u, %u, %u, %u", name, g.x, g.y, g.z, b.x);
+  if (strstr(name, "WalkArgs"))                /* its first 13 words: pointers, sizes, first id, seed, length */
+    for (i = 0; i < 13; ++i) printf(", %llu", ((unsigned long long*)args[0])[i]);
+  printf("]\n");
+  fflush(stdout);
+  return 0;
+}
+"""
+
+CALLS = """
+import ctypes as C, json, sys
+C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)        # its symbols come before those of the HIP runtime
+lib = C.CDLL(sys.argv[2])
+class Csr(C.Structure):
+    _fields_ = [("num_nodes", C.c_int64), ("num_entries", C.c_int64), ("offsets", C.c_void_p), ("offset_bits", C.c_int32),
+                ("nbrs", C.c_void_p), ("weights", C.c_void_p)]
+class Alias(C.Structure):
+    _fields_ = [("prob", C.c_void_p), ("alias", C.c_void_p), ("packed", C.c_void_p)]
+"""
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """launches(code): runs `code` behind the recorder; returns the recorded launches and what it printed as "rc"."""
+    from paper_2407_15452_amd import binding, build
+    if not os.path.exists(binding.LIB_PATH):
+        build.build_lib()
+    where = tmp_path_factory.mktemp("recorder")
+    (where / "recorder.c").write_text(RECORDER)
+    shim = str(where / "recorder.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", shim, str(where / "recorder.c")], check=True)
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-c", CALLS + code, shim, binding.LIB_PATH], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
+        lines = [json.loads(line) for line in r.stdout.splitlines()]
+        return [x for x in lines if isinstance(x, list)], [x["rc"] for x in lines if isinstance(x, dict)]
+
+    return run
+
+
+@pytest.mark.parametrize("walks", [(1 << 28) - 1, (1 << 28) + 1, 1 << 30, (1 << 32) + 5])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_walks_beyond_one_launch(launches, walks, weighted):
+    """Every number of walks that is accepted is launched, each walk once, whatever the lanes per walk: 2^30 walks at 4 lanes
+    are 2^32 lanes, which one launch does not take."""
+    length, first_id, starts, out = 10, 77, 1 << 40, 1 << 44
+    for bits in (32, 64):
+        for p, q in ((None, None), (0.5, 2.0), (1.0, 2.0), (1.0, 0.5), (1.0, 1.0)):
+            call = ("gs_node2vec_walk(C.byref(g), a, C.c_void_p(%d), C.c_int64(%d), C.c_uint64(%d), C.c_int32(%d), C.c_float(%r), "
+                    "C.c_float(%r), C.c_uint64(5), C.c_void_p(%d), None)" % (starts, walks, first_id, length, p, q, out) if p else
+                    "gs_random_walk(C.byref(g), a, C.c_void_p(%d), C.c_int64(%d), C.c_uint64(%d), C.c_int32(%d), C.c_uint64(5), "
+                    "C.c_void_p(%d), None)" % (starts, walks, first_id, length, out))
+            got, rc = launches("g = Csr(1000, 9000, 256, %d, 512, None)\na = %s\nprint(json.dumps({'rc': lib.%s}))\n" % (
+                bits, "C.byref(Alias(768, 1024, 1280))" if weighted else "None", call))
+            assert rc == [0], (bits, p, q)
+            done = 0
+            for name, gx, gy, gz, threads, *args in got:
+                part = args[9]
+                assert args[5] == starts + 4 * done and args[6] == out + 4 * done * length and args[10] == first_id + done
+                assert gy == gz == 1 and gx * threads >= part > 0
+                done += part
+            assert done == walks
