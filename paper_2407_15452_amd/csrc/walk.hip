@@ -119,8 +119,9 @@ typedef int32_t Quad __attribute__((ext_vector_type(4), aligned(4)));   // four 
 
 // Second-order walks, a step of which is a chain of dependent random reads of very different length: the row's
 // bounds, a candidate per attempt (3.7 attempts on average at p = 0.5, q = 2), for a quarter of the attempts a membership search
-// in the previous node's row, and an alias entry before every candidate of a weighted graph.  Two kernels:
-// a lane per walk where the walks fill the chip, a team of lanes per walk where they do not.
+// in the previous node's row, and an alias entry before every candidate of a weighted graph.  Two kernels: a state machine with
+// a lane per walk, for unweighted launches that fill the chip with walks of many attempts, and a team of lanes per walk; which
+// and how many lanes: team_size() below.
 //
 // The membership search is an interpolation search (the ids of a row are spread evenly over [0, num_nodes), so x
 // is expected where a straight line between the entries that bound the remaining range puts it; every
@@ -165,17 +166,17 @@ __device__ __forceinline__ bool probe_says(int32_t x, Pos pos, Quad quad, Pos& L
   return hit || !(left || right) || L >= H;
 }
 
-// A lane per walk, as a state machine with ONE read instruction per trip through the loop.  Written as nested loops, a
-// wave waits in every inner loop for its slowest lane and keeps about a third of its lanes busy.  Here every
-// lane carries its own state (which read it needs next), each trip issues that one read for all 64 lanes
+// A lane per walk (no alias tables), as a state machine with ONE read instruction per trip through the loop.  Written as
+// nested loops, a wave waits in every inner loop for its slowest lane and keeps about a third of its lanes busy.  Here
+// every lane carries its own state (which read it needs next), each trip issues that one read for all 64 lanes
 // together, and the lane then moves to its next state; lanes never wait for each other except at the one read.
-// Whatever a lane needs (two row bounds, an alias entry, a neighbour, four entries of prev's row), it is part of 16
-// bytes of one array, so all lanes read through one instruction and a trip waits once; the random numbers of the attempt that
-// may come next are drawn while the read is under way.
+// Whatever a lane needs (two row bounds, a neighbour, four entries of prev's row), it is part of 16 bytes of one array, so
+// all lanes read through one instruction and a trip waits once; the random numbers of the attempt that may come next are
+// drawn while the read is under way.
 // Each lane stages its own last kWin positions in LDS and writes them out as one
 // 64-byte row segment when the window is full (or the walk is over).
 // Needs at least four entries and three nodes.
-template <typename OffT, bool kWeighted>
+template <typename OffT>
 __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   __shared__ int32_t tile[kWalkThreads][kWinPad];
   using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
@@ -184,14 +185,13 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   const uint64_t id = a.id_base + (uint64_t)i;
   const int32_t* __restrict__ nbrs = a.nbrs;
   const OffT* __restrict__ offsets = static_cast<const OffT*>(a.offsets);
-  const uint2* __restrict__ packed = a.packed;
   int32_t* __restrict__ out = a.walks + i * (int64_t)a.walk_len;
   int32_t* mine = tile[threadIdx.x];
   const int32_t last = a.walk_len - 1;      // index of the last position
   const float bias_lo = fminf(1.0f, a.inv_q), bias_hi = fmaxf(1.0f, a.inv_q);
   const Pos entries = (Pos)a.num_entries;
 
-  enum : int { kRow, kAlias, kDraw, kSearch };
+  enum : int { kRow, kDraw, kSearch };
   int32_t cur = a.starts[i];
   if (cur < 0 || (int64_t)cur >= a.num_nodes) cur = -1;
   int32_t prev = -1;
@@ -205,14 +205,12 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
 
   // the attempt in flight
   Block4 ahead = {0u, 0u, 0u, 0u};          // random numbers of the next one
-  Pos j = 0;                                // slot in the row of cur
-  uint32_t word2 = 0;                       // alias uniform (weighted)
   float s = 0.f;                            // acceptance uniform * max_bias
   int32_t x = 0;                            // candidate
   Pos L = 0, H = 0;                         // its membership search
   int32_t v_lo = 0, v_hi = 0;
   int turn = 0;                             // every third probe bisects
-  Pos pos = 0;                              // what this trip reads: nbrs[pos] (or the alias entry at pos)
+  Pos pos = 0;                              // what this trip reads: nbrs[pos]
 
   // position t + 1 of the walk is `node`: into the lane's window, and out when it is full
   auto put = [&](int32_t node) {
@@ -232,11 +230,9 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
       if (t == last) break;
     }
     if (fresh) {
-      j = row_slot(ahead, (Pos)(hi - lo));
-      word2 = ahead.x2;
       s = unit_float(ahead.x3) * a.max_bias;
-      pos = lo + j;
-      state = (kWeighted ? kAlias : kDraw);
+      pos = lo + row_slot(ahead, (Pos)(hi - lo));
+      state = kDraw;
       fresh = false;
     }
 
@@ -251,21 +247,14 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
         skip = cur - at;
         from = reinterpret_cast<const char*>(offsets + at);
       }
-    } else if (kWeighted && state == kAlias && packed != nullptr) {
-      const Pos at = min(pos, (Pos)(entries - 2));
-      skip = 2 * (int)(pos - at);
-      from = reinterpret_cast<const char*>(packed + at);
     } else {                                // a probe's four entries; a neighbour among four that are aligned likewise
       Pos at;
       if (state == kSearch) at = pos = probe_at(x, L, H, v_lo, v_hi, turn == 2, entries);
       else at = min((Pos)(pos & ~(Pos)3), (Pos)(entries - 4));
       skip = (int)(pos - at);
       from = reinterpret_cast<const char*>(nbrs + at);
-      if (kWeighted && state == kAlias) from = reinterpret_cast<const char*>(a.prob + at);
     }
     const Quad quad = *reinterpret_cast<const Quad*>(from);
-    uint32_t other = 0;                     // (a table that is not interleaved takes a second read)
-    if (kWeighted && state == kAlias && packed == nullptr) other = (uint32_t)a.alias[pos];
     // while it is under way: the first attempt of the next step, or the one after the one at hand
     if (state == kRow || state == kDraw)
       ahead = philox_at(a.seed, id, (uint32_t)t, state == kRow ? 0u : att + 1u);
@@ -286,10 +275,6 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
       fresh = hi > lo;
       taken = !fresh;                       // dead end
       x = -1;
-    } else if (kWeighted && state == kAlias) {
-      if (!(unit_float(word2) < __uint_as_float((uint32_t)w0))) j = (Pos)(int32_t)(packed != nullptr ? (uint32_t)w1 : other);
-      pos = lo + j;
-      state = kDraw;
     } else {
       bool known = false, member = false;   // membership of x in the row of prev has been settled
       bool decided = true;
@@ -460,7 +445,7 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_team_kernel(WalkArgs a)
   }
 }
 
-// Lanes per walk; 0: the state machine, a lane per walk.  Wide teams have the candidates of more attempts under way and
+// Lanes per walk; 0: the state machine (unweighted only).  Wide teams have the candidates of more attempts under way and
 // cost instructions and lines for attempts that do not matter, so they pay while few walks share the chip, and the
 // more attempts a step takes.  Most candidates are no neighbours of prev, so that is about max_bias * q of them: 4 at p =
 // 0.5, q = 2, 1 at p = 4, q = 0.25.  Microseconds of 40 nodes per walk, R-MAT graph of 4 M nodes and 140 M entries (alias tables: 1 M
@@ -506,7 +491,8 @@ static void launch_node2vec(int team, const WalkArgs& a, hipStream_t stream) {
     case 32: return launch_team<OffT, kWeighted, 32>(a, stream);
     case 64: return launch_team<OffT, kWeighted, 64>(a, stream);
     default:
-      node2vec_kernel<OffT, kWeighted><<<(unsigned)ceil_div(a.num_walks, kWalkThreads), kWalkThreads, 0, stream>>>(a);
+      if constexpr (!kWeighted)
+        node2vec_kernel<OffT><<<(unsigned)ceil_div(a.num_walks, kWalkThreads), kWalkThreads, 0, stream>>>(a);
   }
 }
 

@@ -1,6 +1,8 @@
-"""The node2vec walker that reads ahead and, just outside its range, the other, against the CPU reference, bit for
-bit: around the limits in entries (2^22, 3 * 2^19 from 2^14 walks on, 2^23 with 64-bit offsets, 4096 and 3 * 2^18 with an alias
-table) and walks (32 with an alias table, 512, 2^17), rows at both ends of the arrays, dead ends, uniform and weighted draws."""
+"""The node2vec walker against the CPU reference, bit for bit, on graphs that put its reads at both ends of the arrays: 4095 to 2^23
+entries, two and three nodes, dead ends, rows of equal length, 31 to 131,073 walks from the last rows on, uniform and weighted draws
+(all of them launches of teams of lanes); and its state machine, a lane per walk, which takes more than 163,840 unweighted walks of many
+attempts: walks that end inside a window of 16 positions and behind several, rows whose bounds are the last 16 bytes, dead
+ends before and after a window has been written out."""
 import numpy as np
 import pytest
 import torch
@@ -52,3 +54,28 @@ def test_same_walks(oracle, kind, n, entries, walks):
                 for a in ([None] if tab is None else [gs.Alias(prob, alias, packed), gs.Alias(prob, alias)]):
                     got = gs.gs_node2vec_walk(g, a, _dev(starts), length, p, q, 5, walk_id_base=7)
                     np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("kind,n,entries,length", [("even", 3, 40_000, 33), ("dead-ends", 40_000, 300_000, 17),
+                                                   ("dead-ends", 40_000, 300_000, 40), ("few-dead", 5000, 60_000, 40),
+                                                   ("few-dead", 5000, 60_000, 33)])
+def test_lane_per_walk(oracle, kind, n, entries, length):
+    from paper_2407_15452_amd import binding as gs
+    walks = 163_841
+    if kind == "few-dead":                # one node in 40 has no row: most walks end behind their first window
+        rng = np.random.default_rng(n)
+        src = rng.integers(0, n, entries).astype(np.int32)
+        dst = rng.integers(0, n, entries).astype(np.int32)
+        src = np.where(src % 40 == 7, src - 1, src).astype(np.int32)
+    else:
+        src, dst = _graph(kind, n, entries)
+    off, nb, _ = oracle.csr_build(src, dst, None, n, 0)
+    starts = (n - 1 - np.arange(walks) % (n + 1)).astype(np.int32)       # the last rows first; -1, no node, among them
+    want = oracle.node2vec_walk(off, nb, starts, length, 0.5, 2.0, 5, walk_id_base=7)
+    if kind == "few-dead":                # walks that end in every window
+        ends = (want >= 0).sum(1)
+        assert all(((ends > lo) & (ends <= lo + 16) & (ends < length)).any() for lo in range(0, length - 1, 16))
+    for dtype in (np.int32, np.int64):
+        got = gs.gs_node2vec_walk(gs.Csr(_dev(off.astype(dtype)), _dev(nb)), None, _dev(starts), length, 0.5, 2.0, 5,
+                                  walk_id_base=7)
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
