@@ -321,7 +321,9 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
 // random numbers of an attempt depend on nothing but its number, so lane l of a team makes attempt att + l: the
 // candidates of kTeam attempts are under way at once, and the walk takes the first of them, in order of their numbers, that
 // is accepted.  An attempt whose acceptance uniform is below every bias is accepted whatever its candidate is, so the
-// lanes behind the first such one read nothing: no more lines are fetched than one attempt after the other would.
+// lanes behind the first such one read nothing.  Candidates behind one that turns out accepted are read in vain: few where
+// most accepted attempts are of that kind (p = 0.5, q = 2: all but those of prev and its neighbours), most of a team's where
+// few are (p = 4, q = 0.25: one attempt in 16), so the widths go by the attempts a step takes (team_size() below).
 // Lanes whose candidate needs the membership search search side by side, as long as no attempt before theirs is accepted.
 // The walks of a wave advance in lock step (most steps take one round of attempts), which leaves few instructions
 // per step: row bounds, draw, one read of candidates, votes.
@@ -448,30 +450,56 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_team_kernel(WalkArgs a)
 // Lanes per walk; 0: the state machine (unweighted only).  Wide teams have the candidates of more attempts under way and
 // cost instructions and lines for attempts that do not matter, so they pay while few walks share the chip, and the
 // more attempts a step takes.  Most candidates are no neighbours of prev, so that is about max_bias * q of them: 4 at p =
-// 0.5, q = 2, 1 at p = 4, q = 0.25.  Microseconds of 40 nodes per walk, R-MAT graph of 4 M nodes and 140 M entries (alias tables: 1 M
-// nodes, 22 M entries); the kernel that was there before, a lane per walk with a read per state or one read per trip: 637
-// for 10 walks of 80 nodes at p = 0.5, q = 2, 1245 for 47,000, 1868 for 200,000, and these: 119, 552, 1578.
+// 0.5, q = 2, 2 at p = 1, q = 2, 1 at p = 1, q = 0.5 and p = 4, q = 0.25 (more where candidates are prev or its neighbours).
+// Microseconds of 40 nodes per walk (20 from 700,000 walks on), R-MAT graph of 4 M nodes and 126 M entries (alias tables: 1 M nodes,
+// 18 M entries); "before" is the better of two kernels that are gone, a lane per walk with a read per state or one read per trip.
 //   p 0.5, q 2   1000 walks: teams of 64 66, 16 100, 8 140, a lane 475; 6000: 64 119, 32 118, 16 135; 10,000: 64 167, 32 136, 16 142, 8
 //                192; 20,000: 32 218, 16 170, 8 207; 47,000: 16 323, 8 273, 4 409, a lane 563; 150,000: 16 821, 8 669, 4 779, a lane 711;
-//                200,000: 8 862, a lane 789; 1 M: 4 3558, a lane 3091; alias tables, 300,000: 4 1184, a lane 1550, 1 M: 3539, 4451
-//   p 4, q 0.25  20,000 walks: 16 190, 8 194, 4 228; 60,000: 8 274, 4 302; 100,000: 8 451, 4 355, 2 451; 300,000: 4 933, 2 858, a lane
-//                1016; alias tables, 60,000: 8 401, 4 320; 300,000: 4 1108, 2 943, a lane 1606
-//   p 1, q 2     30,000 walks: 16 204, 8 180, 4 221; 150,000: 8 554, 4 490, a lane 528; 300,000: 4 768, 2 908, a lane 813
+//                200,000: 8 862, a lane 813, before 1013; 400,000: 4 1575, a lane 1508, before 1496; 1 M: 1706, 1555, 1679; 4 M: 6481,
+//                5250, 5374; 64-bit offsets, 1 M nodes, 4 M: a lane 4700, before 4629
+//      alias     200,000: 8 826, 4 851, 2 993, before 1449; 400,000: 4 1544, 2 1733, 2018; 4 M: 6551, 6797, 7478
+//   p 1, q 2     4096 walks: 64 97, 32 112, 16 127, before 475; 12,000: 64 181, 32 145, 16 149, 8 154, 485; 30,000: 16 210, 8 178, 4 222;
+//                100,000: 8 398, 4 313, 2 462, 538; 260,000: 4 651, 2 657, a lane 687, 799; 400,000: 990, 1022, 1129, 1145; 4 M:
+//                4091, 3850, 3902, 4031
+//      alias     100,000: 4 299, 2 434, 660; 260,000: 687, 828, 1020; 1 M: 1086, 1091, 1528; 4 M: 4183, 4045, 4919
+//   p 1, q 0.5   4096 walks: 64 95, 32 101, 16 117, before 273; 12,000: 64 170, 32 131, 16 131, 8 143, 275; 20,000: 32 200, 16 152, 8
+//                148, 4 157, 270; 47,000: 8 203, 4 192, 2 213, 284; 100,000: 4 251, 2 243, 1 335, 314; 160,000: 403, 280, 363, 428;
+//                400,000: 2 643, 1 528, a lane 687, 682; 1 M: 711, 605, 738, 763; 4 M: 2691, 2242, 2599, 2549
+//      alias     100,000: 4 238, 2 234, 1 319, before 375; 200,000: 446, 392, 374, 577; 260,000: 595, 589, 411, 598; 4 M: 2 3391, 1
+//                2746, 3015
+//   p 4, q 0.25  4096 walks: 64 112, 32 121, before 482; 12,000: 32 167, 16 163, 726; 47,000: 8 261, 4 301, 759; 100,000: 4 361, 2 436, 754;
+//                160,000: 593, 490, 822; 400,000: 2 984, 1 932, a lane 1139, 1125; 4 M: 3656, 2748, 3139, 3227
+// Where reads are quick (an XCD's cache holds the rows of 2^20 entries) what repeats costs more, and where biases are uneven more
+// repeats than the attempts say; 10,000 nodes, 180,000 entries, before / then:
+//   p 1, q 0.5   400,000 walks: 2 409, 1 444, before 470; 4 M: 2 1534, 1 1383, a lane 1539, before 1612; p 1, q 0.25: 2072, 2057, 1975, 2057
+//   p 4, q 0.25  160,000: 4 345, 2 424, before 688; 400,000: 4 692, 2 720, 1 960, a lane 917, before 908; 4 M: 2 2510, 1 2785, a lane 2443, 2493
+//      alias     160,000: 4 388, 2 492, 1 820, before 1261; 400,000: 803, 844, 1140, 1624; 4 M: 2 3101, 1 3511, 4013
+//   (300,000 nodes, 5.6 M entries, p 4, q 0.25, 160,000 walks: 4 428, 2 461, before 839; 4 M: 2 2393, 1 2473, a lane 2526, 2659)
 // Where every candidate other than prev is accepted (the least bias of those is the greatest of all) rounds hardly
 // repeat: p = 2, q = 1, 10,000 walks: 4 45, 1 59; 30,000: 4 50, 1 68, a lane 100; 100,000: 4 121, 1 102, a lane 129; p = q = 1,
 // 1 M: 1 765, a lane 845.
-// (Offsets of 64 bits, 10,000-node graphs: the same order.)
 static int team_size(bool weighted, float q, const WalkArgs& a) {
   const int64_t walks = a.num_walks;
   if (a.max_bias <= fminf(1.0f, a.inv_q)) return walks <= (int64_t)3 << 14 ? 4 : 1;
-  const bool many_attempts = a.max_bias * q >= 3.0f;
+  const float attempts = a.max_bias * q;
   if (walks <= (int64_t)1 << 12) return 64;
   if (walks <= (int64_t)3 << 12) return 32;
   if (walks <= (int64_t)3 << 13) return 16;
-  if (walks <= (many_attempts ? (int64_t)5 << 15 : (int64_t)3 << 14)) return 8;
-  if (!many_attempts && walks <= (int64_t)1 << 18) return 4;
-  if (weighted) return many_attempts ? 4 : 2;
-  return a.num_entries >= 4 && a.num_nodes >= 3 ? 0 : 1;         // (what one read of the state machine needs)
+  if (walks <= (attempts >= 3.0f ? (int64_t)5 << 15 : (int64_t)3 << 14)) return 8;
+  const int lane = a.num_entries >= 4 && a.num_nodes >= 3 ? 0 : 1;         // (what one read of the state machine needs)
+  if (attempts >= 3.0f) return weighted ? 4 : lane;
+  if (attempts >= 1.5f) return walks <= (int64_t)1 << 18 ? 4 : (weighted ? 2 : lane);
+  // about one attempt: 4 lanes, 2, then 1
+  const int64_t entries = a.num_entries;
+  const bool uneven = a.max_bias >= 8.0f * fminf(a.inv_p, fminf(1.0f, a.inv_q)), quick = entries <= (int64_t)1 << 20;
+  int64_t four = (int64_t)7 << 14, two = quick ? (int64_t)1 << 20 : (weighted ? (int64_t)7 << 15 : (int64_t)1 << 19);
+  if (uneven) {
+    if (entries <= (int64_t)1 << 23) four = quick ? (int64_t)1 << 19 : (int64_t)1 << 18;
+    two = (int64_t)1 << 20;
+  }
+  if (walks <= four) return 4;
+  if (walks <= two || (weighted && uneven && entries <= (int64_t)1 << 21)) return 2;
+  return !weighted && (quick || (uneven && entries <= (int64_t)1 << 21)) ? lane : 1;
 }
 
 template <typename OffT, bool kWeighted, int kTeam>

@@ -51,6 +51,16 @@ def test_many_walks(oracle, walks, settings):
     _check(oracle, 5000, *_graph(5000, 40_000, True), walks, 6, settings)
 
 
+@pytest.mark.parametrize("walks", [114_688, 114_689, (1 << 18) + 1, 1 << 19, (1 << 19) + 1, 1 << 20, (1 << 20) + 1])
+def test_many_walks_of_few_attempts(oracle, walks):
+    _check(oracle, 5000, *_graph(5000, 40_000, True), walks, 5, ((1.0, 0.5), FEW))
+
+
+@pytest.mark.parametrize("walks", [229_376, 229_377, (1 << 19) + 1, (1 << 20) + 1])
+def test_few_attempts_on_more_entries(oracle, walks):
+    _check(oracle, 5000, *_graph(5000, (1 << 21) + 5, True), walks, 3, ((1.0, 0.5), FEW))
+
+
 @pytest.mark.parametrize("n,edges", [(1, [(0, 0)]), (2, [(0, 1), (1, 0)]), (2, [(0, 0), (0, 1), (1, 0)]),
                                      (3, [(0, 1), (1, 0), (1, 2)]), (2, [(0, 0), (0, 1), (1, 0), (1, 1)])])
 @pytest.mark.parametrize("walks", [3, 200_000])

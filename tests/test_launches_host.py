@@ -105,3 +105,21 @@ def test_walks_beyond_one_launch(launches, walks, weighted):
                 assert gy == gz == 1 and gx * threads >= part > 0
                 done += part
             assert done == walks
+
+
+@pytest.mark.parametrize("weighted,entries,walks,p,q,lanes", [
+    (True, 9 << 20, 114_688, 1.0, 0.5, 4), (True, 9 << 20, 114_689, 1.0, 0.5, 2), (True, 9 << 20, 229_377, 1.0, 0.5, 1),
+    (True, 9 << 20, 114_689, 4.0, 0.25, 2), (True, 1 << 23, 262_144, 4.0, 0.25, 4), (True, 1 << 20, 524_288, 4.0, 0.25, 4),
+    (True, 9 << 20, 4_000_000, 1.0, 0.5, 1), (True, 1 << 20, 4_000_000, 1.0, 0.5, 1), (True, 1 << 21, 4_000_000, 4.0, 0.25, 2),
+    (True, 9 << 20, 1_048_577, 4.0, 0.25, 1), (False, 9 << 20, 260_000, 1.0, 0.5, 2), (False, 9 << 20, 524_289, 1.0, 0.5, 1),
+    (False, 9 << 20, 1_048_576, 4.0, 0.25, 2), (False, 9 << 20, 1_048_577, 4.0, 0.25, 1), (False, 1 << 20, 1_048_577, 1.0, 0.5, 0),
+    (False, 1 << 21, 1_048_577, 4.0, 0.25, 0), (False, 1 << 21, 1_048_577, 1.0, 0.5, 1), (False, 3, 1_048_577, 4.0, 0.25, 1),
+    (True, 9 << 20, 262_144, 1.0, 2.0, 4), (True, 9 << 20, 262_145, 1.0, 2.0, 2), (False, 9 << 20, 262_145, 1.0, 2.0, 0),
+    (True, 9 << 20, 4_000_000, 0.5, 2.0, 4), (False, 9 << 20, 163_841, 0.5, 2.0, 0)])
+def test_lanes_per_walk(launches, weighted, entries, walks, p, q, lanes):
+    """Launches of many walks that take few attempts a step take narrower teams than those that take many (0: the state machine)."""
+    got, rc = launches("g = Csr(100000, %d, 256, 32, 512, None)\na = %s\nprint(json.dumps({'rc': lib.gs_node2vec_walk(C.byref(g), a, "
+                       "C.c_void_p(256), C.c_int64(%d), C.c_uint64(0), C.c_int32(10), C.c_float(%r), C.c_float(%r), C.c_uint64(5), "
+                       "C.c_void_p(512), None)}))\n" % (entries, "C.byref(Alias(768, 1024, 1280))" if weighted else "None", walks, p, q))
+    assert rc == [0] and len(got) == 1
+    assert ("node2vec_team_kernelIiLb%dELi%dE" % (weighted, lanes) if lanes else "node2vec_kernelIi") in got[0][0]
