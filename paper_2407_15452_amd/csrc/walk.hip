@@ -176,10 +176,9 @@ __device__ __forceinline__ bool probe_says(int32_t x, Pos pos, Quad quad, Pos& L
 // Each lane stages its own last kWin positions in LDS and writes them out as one
 // 64-byte row segment when the window is full (or the walk is over).
 // Needs at least four entries and three nodes.
-template <typename OffT>
+template <typename OffT, typename Pos>
 __global__ __launch_bounds__(kWalkThreads) void node2vec_kernel(WalkArgs a) {
   __shared__ int32_t tile[kWalkThreads][kWinPad];
-  using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
   const int64_t i = (int64_t)blockIdx.x * kWalkThreads + threadIdx.x;
   if (i >= a.num_walks) return;
   const uint64_t id = a.id_base + (uint64_t)i;
@@ -349,12 +348,11 @@ __device__ __forceinline__ int32_t from_lane(int32_t x, uint32_t who, uint32_t s
   return (int32_t)v;
 }
 
-template <typename OffT, bool kWeighted, int kTeam>
+template <typename OffT, typename Pos, bool kWeighted, int kTeam>
 __global__ __launch_bounds__(kWalkThreads) void node2vec_team_kernel(WalkArgs a) {
   constexpr int kTeams = kWalkThreads / kTeam;
   static_assert(kMaxAttempts % kTeam == 0, "the last attempt belongs to a team's last lane");
   __shared__ int32_t tile[kTeams][kWinPad];
-  using Pos = OffT;                         // positions in nbrs: below num_entries, which the offsets hold
   const int lane = threadIdx.x & 63, base = lane & ~(kTeam - 1);
   const uint32_t sub = lane & (kTeam - 1);
   const int64_t i = (int64_t)blockIdx.x * kTeams + (int)threadIdx.x / kTeam;
@@ -384,13 +382,12 @@ __global__ __launch_bounds__(kWalkThreads) void node2vec_team_kernel(WalkArgs a)
         for (int c = (int)sub; c <= col; c += kTeam) out[first + c] = mine[c];
     }
     if (t == last) break;
-    Pos lo = 0, hi = 0;
-    if (cur >= 0) {
-      const OffsetPair<OffT> row = *reinterpret_cast<const OffsetPair<OffT>*>(offsets + cur);
-      lo = row.lo;
-      hi = row.hi;
-    }
+    OffsetPair<OffT> row = {0, 0};
+    if (cur >= 0) row = *reinterpret_cast<const OffsetPair<OffT>*>(offsets + cur);
     Block4 b = philox_at(a.seed, id, (uint32_t)t, sub);         // (while the bounds are under way)
+    // (registers of upper halves that nobody asks for are given out again at once, and whoever gets one waits for the read)
+    if constexpr (sizeof(OffT) > sizeof(Pos)) asm volatile("" : : "v"(row.lo), "v"(row.hi), "v"(b.x0), "v"(b.x3));
+    const Pos lo = (Pos)row.lo, hi = (Pos)row.hi;
     bool pending = hi > lo;                 // (the same in all lanes of a team)
     int32_t next = -1;
     for (uint32_t att = sub; __ballot(pending) != 0ull;) {
@@ -502,34 +499,35 @@ static int team_size(bool weighted, float q, const WalkArgs& a) {
   return !weighted && (quick || (uneven && entries <= (int64_t)1 << 21)) ? lane : 1;
 }
 
-template <typename OffT, bool kWeighted, int kTeam>
+template <typename OffT, typename Pos, bool kWeighted, int kTeam>
 static void launch_team(const WalkArgs& a, hipStream_t stream) {
-  node2vec_team_kernel<OffT, kWeighted, kTeam>
+  node2vec_team_kernel<OffT, Pos, kWeighted, kTeam>
       <<<(unsigned)ceil_div(a.num_walks, kWalkThreads / kTeam), kWalkThreads, 0, stream>>>(a);
 }
 
-template <typename OffT, bool kWeighted>
+template <typename OffT, typename Pos, bool kWeighted>
 static void launch_node2vec(int team, const WalkArgs& a, hipStream_t stream) {
   switch (team) {
-    case 1: return launch_team<OffT, kWeighted, 1>(a, stream);
-    case 2: return launch_team<OffT, kWeighted, 2>(a, stream);
-    case 4: return launch_team<OffT, kWeighted, 4>(a, stream);
-    case 8: return launch_team<OffT, kWeighted, 8>(a, stream);
-    case 16: return launch_team<OffT, kWeighted, 16>(a, stream);
-    case 32: return launch_team<OffT, kWeighted, 32>(a, stream);
-    case 64: return launch_team<OffT, kWeighted, 64>(a, stream);
+    case 1: return launch_team<OffT, Pos, kWeighted, 1>(a, stream);
+    case 2: return launch_team<OffT, Pos, kWeighted, 2>(a, stream);
+    case 4: return launch_team<OffT, Pos, kWeighted, 4>(a, stream);
+    case 8: return launch_team<OffT, Pos, kWeighted, 8>(a, stream);
+    case 16: return launch_team<OffT, Pos, kWeighted, 16>(a, stream);
+    case 32: return launch_team<OffT, Pos, kWeighted, 32>(a, stream);
+    case 64: return launch_team<OffT, Pos, kWeighted, 64>(a, stream);
     default:
       if constexpr (!kWeighted)
-        node2vec_kernel<OffT><<<(unsigned)ceil_div(a.num_walks, kWalkThreads), kWalkThreads, 0, stream>>>(a);
+        node2vec_kernel<OffT, Pos><<<(unsigned)ceil_div(a.num_walks, kWalkThreads), kWalkThreads, 0, stream>>>(a);
   }
 }
 
-template <typename OffT>
+// Pos holds the node2vec walker's positions in nbrs, 64 bits only where there are so many entries, whatever the offsets.
+template <typename OffT, typename Pos>
 static void launch_walk(bool weighted, bool second, int team, const WalkArgs& a, hipStream_t stream) {
   const unsigned blocks = (unsigned)ceil_div(a.num_walks, kWalkThreads);
   if (second) {
-    if (weighted) launch_node2vec<OffT, true>(team, a, stream);
-    else launch_node2vec<OffT, false>(team, a, stream);
+    if (weighted) launch_node2vec<OffT, Pos, true>(team, a, stream);
+    else launch_node2vec<OffT, Pos, false>(team, a, stream);
   } else {
     if (weighted) walk_kernel<OffT, true><<<blocks, kWalkThreads, 0, stream>>>(a);
     else walk_kernel<OffT, false><<<blocks, kWalkThreads, 0, stream>>>(a);
@@ -572,8 +570,9 @@ static int32_t walk_common(const gs_csr* g, const gs_alias* al, const int32_t* s
     a.walks = walks_out + first * walk_len;
     a.id_base = id_base + (uint64_t)first;
     a.num_walks = std::min(kLaunchWalks, num_walks - first);          // (the runtime's own min takes ints on the host)
-    if (g->offset_bits == 64) launch_walk<int64_t>(weighted, second, team, a, stream);
-    else launch_walk<int32_t>(weighted, second, team, a, stream);
+    if (g->offset_bits == 32) launch_walk<int32_t, int32_t>(weighted, second, team, a, stream);
+    else if (g->num_entries <= (int64_t)INT32_MAX) launch_walk<int64_t, int32_t>(weighted, second, team, a, stream);
+    else launch_walk<int64_t, int64_t>(weighted, second, team, a, stream);
     GS_LAUNCH_CHECK();
   }
   return GS_OK;

@@ -67,3 +67,30 @@ def test_few_attempts_on_more_entries(oracle, walks):
 def test_tiny_graphs(oracle, n, edges, walks):
     src, dst = (np.array(c, dtype=np.int32) for c in zip(*edges))
     _check(oracle, n, src, dst, walks, 20 if walks < 100 else 4, (MANY, FEW, (1.0, 1.0)))
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_positions_beyond_31_bits(oracle, weighted):
+    """Node 0, to which no edge leads, has 2^31 entries; the rows of the other nodes lie behind them."""
+    from paper_2407_15452_amd import binding as gs
+    n, first = 700, 1 << 31
+    rng = np.random.default_rng(5)
+    src, dst = (rng.integers(1, n, 9000).astype(np.int32) for _ in range(2))
+    w = rng.lognormal(0, 1, src.size).astype(np.float32)
+    off, nb, ww = oracle.csr_build(src, dst, w, n, 0)
+    table = oracle.alias_build(off, ww)
+    shifted = off.astype(np.int64) + first
+    shifted[0] = 0
+
+    def behind(a):
+        out = torch.zeros(first + a.size, dtype=torch.as_tensor(a).dtype, device=DEV)
+        out[first:] = _dev(a)
+        return out
+
+    g = gs.Csr(_dev(shifted), behind(nb))
+    a = gs.Alias(behind(table[0]), behind(table[1])) if weighted else None
+    for walks, p, q in ((1000, 0.5, 2.0), (20_000, 1.0, 0.5), (170_000, 0.5, 2.0), (170_000, 2.0, 1.0)):
+        starts = (np.arange(walks) % (n - 1) + 1).astype(np.int32)
+        want = oracle.node2vec_walk(off, nb, starts, 6, p, q, 11, alias=table if weighted else None)
+        got = gs.gs_node2vec_walk(g, a, _dev(starts), 6, p, q, 11)
+        np.testing.assert_array_equal(got.cpu().numpy(), want)

@@ -122,4 +122,14 @@ def test_lanes_per_walk(launches, weighted, entries, walks, p, q, lanes):
                        "C.c_void_p(256), C.c_int64(%d), C.c_uint64(0), C.c_int32(10), C.c_float(%r), C.c_float(%r), C.c_uint64(5), "
                        "C.c_void_p(512), None)}))\n" % (entries, "C.byref(Alias(768, 1024, 1280))" if weighted else "None", walks, p, q))
     assert rc == [0] and len(got) == 1
-    assert ("node2vec_team_kernelIiLb%dELi%dE" % (weighted, lanes) if lanes else "node2vec_kernelIi") in got[0][0]
+    assert ("node2vec_team_kernelIiiLb%dELi%dE" % (weighted, lanes) if lanes else "node2vec_kernelIii") in got[0][0]
+
+
+@pytest.mark.parametrize("walks", [100, 200_000])
+def test_width_of_positions(launches, walks):
+    """64-bit arithmetic only for graphs of 2^31 entries and more, not for all with 64-bit offsets."""
+    for bits, entries, types in ((32, (1 << 31) - 1, "ii"), (64, (1 << 31) - 1, "li"), (64, 1 << 31, "ll")):
+        got, rc = launches("g = Csr(100000, %d, 256, %d, 512, None)\nprint(json.dumps({'rc': lib.gs_node2vec_walk(C.byref(g), None, "
+                           "C.c_void_p(256), C.c_int64(%d), C.c_uint64(0), C.c_int32(10), C.c_float(0.5), C.c_float(2.0), "
+                           "C.c_uint64(5), C.c_void_p(512), None)}))\n" % (entries, bits, walks))
+        assert rc == [0] and len(got) == 1 and ("kernelI" + types) in got[0][0], got
