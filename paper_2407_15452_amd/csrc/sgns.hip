@@ -171,6 +171,7 @@ struct SgnsArgs {
   int32_t chunk_pairs;      // consecutive pairs per 16-lane group in forward (<= 16)
   int32_t slice_terms;      // sorted terms per 16-lane group in update
   int32_t k;
+  uint32_t per_k1;          // t / (k + 1) = t * per_k1 >> 16 for t < 16 * 61 (k is at most 60)
   int32_t dim;
   float lr;
   float* g;                 // [num_terms]
@@ -585,32 +586,50 @@ __global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs
     cen_s[l16] = row_of(a.centers[first + l16]);
   }
   const int terms = count * K1;
-  constexpr int kIds = 4;                   // ids in flight per lane
-  const uint32_t per_k1 = (65535u + (uint32_t)K1) / (uint32_t)K1;       // t / K1 = t * per_k1 >> 16 for t < 16 * 61
-  for (int t0 = l16; t0 < terms; t0 += kIds * kGroupLanes) {
-    int32_t id[kIds];
-#pragma unroll
-    for (int c = 0; c < kIds; ++c) {
-      const int t = t0 + c * kGroupLanes;
-      id[c] = 0;
-      if (t >= terms) continue;
-      const int p = (int)((uint32_t)t * per_k1 >> 16), j = t - p * K1;
+  if constexpr (kGroup == kInLds) {         // (two pairs per group, so most lanes have one term: 256 to 4096 pairs are 0.5 % slower with the loop below)
+    for (int t = l16; t < terms; t += kGroupLanes) {
+      const int p = t / K1, j = t - p * K1;
+      int32_t row;
       if (j == 0) {
-        if (a.walks == nullptr) id[c] = a.contexts[first + p];
+        if (a.walks != nullptr) continue;   // set above
+        row = row_of(a.contexts[first + p]);
       } else if (a.draw_negs) {
         const Block4 b = philox_at(a.neg_seed, a.neg_pair_base + (uint64_t)(first + p), (uint32_t)(j - 1),
                                    0x80000000u);
-        id[c] = (int32_t)table_draw(a.noise_prob, a.noise_alias, a.noise_packed, (uint64_t)a.num_nodes, b);
-        a.negs_draw[(first + p) * (int64_t)K + (j - 1)] = id[c];
+        row = (int32_t)table_draw(a.noise_prob, a.noise_alias, a.noise_packed, (uint64_t)a.num_nodes, b);
+        a.negs_draw[(first + p) * (int64_t)K + (j - 1)] = row;
       } else {
-        id[c] = a.negs[(first + p) * (int64_t)K + (j - 1)];
+        row = row_of(a.negs[(first + p) * (int64_t)K + (j - 1)]);
       }
+      rows_s[t] = row;
     }
+  } else {
+    constexpr int kIds = 4;                 // ids in flight per lane
+    for (int t0 = l16; t0 < terms; t0 += kIds * kGroupLanes) {
+      int32_t id[kIds];
 #pragma unroll
-    for (int c = 0; c < kIds; ++c) {
-      const int t = t0 + c * kGroupLanes;
-      if (t >= terms || (a.walks != nullptr && t % K1 == 0)) continue;      // (a walk's pairs: set above)
-      rows_s[t] = row_of(id[c]);
+      for (int c = 0; c < kIds; ++c) {
+        const int t = t0 + c * kGroupLanes;
+        id[c] = 0;
+        if (t >= terms) continue;
+        const int p = (int)((uint32_t)t * a.per_k1 >> 16), j = t - p * K1;
+        if (j == 0) {
+          if (a.walks == nullptr) id[c] = a.contexts[first + p];
+        } else if (a.draw_negs) {
+          const Block4 b = philox_at(a.neg_seed, a.neg_pair_base + (uint64_t)(first + p), (uint32_t)(j - 1),
+                                     0x80000000u);
+          id[c] = (int32_t)table_draw(a.noise_prob, a.noise_alias, a.noise_packed, (uint64_t)a.num_nodes, b);
+          a.negs_draw[(first + p) * (int64_t)K + (j - 1)] = id[c];
+        } else {
+          id[c] = a.negs[(first + p) * (int64_t)K + (j - 1)];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < kIds; ++c) {
+        const int t = t0 + c * kGroupLanes;
+        if (t >= terms || (a.walks != nullptr && t % K1 == 0)) continue;    // (a walk's pairs: set above)
+        rows_s[t] = row_of(id[c]);
+      }
     }
   }
   __syncthreads();
@@ -2414,6 +2433,7 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   a.long_slots = p.long_slots;
   a.seg_shift = p.seg_shift;
   a.k = k;
+  a.per_k1 = (65535u + (uint32_t)(k + 1)) / (uint32_t)(k + 1);
   a.dim = dim;
   a.lr = lr;
   a.g = p.g;
