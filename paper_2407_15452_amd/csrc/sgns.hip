@@ -2122,14 +2122,21 @@ static int32_t launch_sorted_updates(const SgnsArgs& a, hipStream_t stream) {
 // fill the chip take them.  Steps of 60,000 pairs, 256 fp32 columns 190 -> 179 us (131 registers before), 100,000 pairs, 400 bf16
 // columns 450 -> 393 us (175), 300,000, 200 fp16 columns 650 -> 630, 1 M, 256 bf16 columns 2559 -> 2440; 7712 pairs, 196 fp32 columns
 // (482 waves) 101 -> 103.5, so not there; 384 and 512 fp32 columns with 3 instead of 2 waves 248 -> 263 and 277 -> 289, up to 128
-// with 5 instead of 4 208 -> 217, so neither there.
+// with 5 instead of 4 208 -> 217, so neither there.  With 16-bit tables that holds for every batch from there on; with fp32 tables,
+// where the kernel with fewer registers is 2 to 5 % slower by itself, where the waves are up to twice the chip's and come in fewer turns: 256
+// columns, 1 M nodes, 52,000 pairs (1 turn instead of 2) 192 -> 183 us, 100,000 (2 instead of 3) 315 -> 308, but 72,000 (2 and 2)
+// 238 -> 251, 200,000 (4 instead of 5) 548 -> 557; 10,000 nodes 152 -> 144, 230 -> 224, 178 -> 188, 352 -> 357.
 template <typename T, int VPL, int RB, int kGroup>
 static void launch_forward(const SgnsArgs& a, hipStream_t stream) {
   constexpr int kMore = VPL == 4 ? 4 : (VPL == 8 && sizeof(T) == 2 ? 3 : 0);
   const unsigned blocks = (unsigned)(a.forward_blocks_per_xcd * 8);
   const size_t idx_lds = (size_t)kGroupsPerBlock * a.chunk_pairs * (a.k + 2) * sizeof(int32_t);
   constexpr int64_t kSimds = 1024;
-  if (kMore != 0 && a.forward_blocks * (kSgnsThreads / 64) > (kMore - 1) * kSimds)
+  const int64_t waves = a.forward_blocks * (kSgnsThreads / 64);
+  bool more = kMore != 0 && waves > (kMore - 1) * kSimds;
+  if constexpr (kMore != 0 && sizeof(T) == 4)
+    more = waves <= 2 * kMore * kSimds && ceil_div(waves, kMore * kSimds) < ceil_div(waves, (kMore - 1) * kSimds);
+  if (more)
     sgns_forward_kernel<T, VPL, RB, kGroup, kSgnsThreads, kMore><<<blocks, kSgnsThreads, idx_lds, stream>>>(a);
   else
     sgns_forward_kernel<T, VPL, RB, kGroup, kSgnsThreads><<<blocks, kSgnsThreads, idx_lds, stream>>>(a);

@@ -133,3 +133,27 @@ def test_width_of_positions(launches, walks):
                            "C.c_void_p(256), C.c_int64(%d), C.c_uint64(0), C.c_int32(10), C.c_float(0.5), C.c_float(2.0), "
                            "C.c_uint64(5), C.c_void_p(512), None)}))\n" % (entries, bits, walks))
         assert rc == [0] and len(got) == 1 and ("kernelI" + types) in got[0][0], got
+
+
+STEP = """
+def step(call, pairs, nodes, dim, dtype=0, k=5):
+    p = [C.c_void_p(1 << (20 + i)) for i in range(12)]
+    head = p[:{'gs_sgns_step': 2, 'gs_sgns_momentum_step': 4, 'gs_sgns_adam_step': 6}[call]]
+    rates = {'gs_sgns_step': [0.1], 'gs_sgns_momentum_step': [0.1, 0.9], 'gs_sgns_adam_step': [0.1, 0.9, 0.999, 1e-8]}[call]
+    tail = [C.c_int64(3)] if call == 'gs_sgns_adam_step' else []
+    form = [C.c_int32(dtype)] if call != 'gs_sgns_adam_step' else []
+    return getattr(lib, call)(*head, C.c_int64(nodes), C.c_int32(dim), *form, *p[6:9], C.c_int64(pairs), C.c_int32(k),
+                              *[C.c_float(r) for r in rates], *tail, p[9], p[10], C.c_size_t(1 << 50), None)
+"""
+
+
+@pytest.mark.parametrize("dtype,dim,pairs,more", [
+    (0, 256, 49_152, False), (0, 256, 49_153, True), (0, 256, 65_536, True), (0, 256, 65_537, False), (0, 256, 98_304, False),
+    (0, 256, 98_305, True), (0, 256, 131_072, True), (0, 256, 131_073, False), (0, 256, 600_000, False), (0, 128, 65_536, False),
+    (1, 256, 49_152, False), (1, 256, 49_153, True), (1, 256, 72_000, True), (1, 256, 200_000, True), (2, 400, 32_769, True)])
+def test_forward_waves(launches, dtype, dim, pairs, more):
+    """The forward kernel for one more wave per SIMD: with fp32 tables where its waves come in fewer turns."""
+    got, rc = launches(STEP + "print(json.dumps({'rc': step('gs_sgns_step', %d, 100000, %d, %d)}))\n" % (pairs, dim, dtype))
+    assert rc == [0]
+    forward = [x[0] for x in got if "sgns_forward_kernel" in x[0]]
+    assert len(forward) == 1 and ("Li256ELi%dEEEv" % (0 if not more else (4 if dim <= 256 else 3))) in forward[0], forward
