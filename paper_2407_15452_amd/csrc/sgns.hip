@@ -2273,18 +2273,29 @@ __device__ __forceinline__ bool row_named(const SgnsArgs& a, uint32_t key) {
 // the batch.  A row takes `pieces` lanes of 16 bytes; a lane has kDenseRows rows in flight, and a workgroup ends with
 // them: 0.65 and 1.00 ms with four rows, a loop over the rest of the table and accesses that go through the caches
 // (plain against uncached accesses, no rows left out: 5.5 and 6.1 TB/s).
+// Tables that the 256 MB of cache in front of the memory hold together are still there when the next step reads them, so
+// they go through the caches.  Where a workgroup's rows end inside its lanes (its first and last lines are then shared), that
+// is better up to a quarter more.  Whole steps, us, with the former kernel / past the caches / through them: momentum, 20,000 pairs,
+// 64 columns, 200 MB of tables 126 / 131 / 123, 290 MB 174 / 167 / 165, 310 MB 181 / 165 / 170, 400 MB 225 / 196 / 217; 16 columns, 200 MB 133 / 142 / 129;
+// 100 columns, 240 MB 158 / 169 / 154, 290 MB 186 / 183 / 180, 340 MB 216 / 201 / 206; Adam, 1000 pairs, 128 columns, 60 MB 90 / 85 / 87, 200 MB 141
+// / 141 / 136, 290 MB 184 / 172 / 175, 400 MB 242 / 214 / 235; 100 columns, 240 MB 159 / 180 / 154, 310 MB 203 / 207 / 196, 400 MB 248 / 242 / 240.
 constexpr int kDenseRows = 2;
+constexpr int64_t kDenseCached = (int64_t)256 << 20;          // bytes
 constexpr int kDenseBlocks = 1 << 23;          // workgroups in one dimension of the launch
-// accesses to memory that no cache will be asked for again
+// kOnce: accesses to memory that no cache will be asked for again
 typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 load_once(const uint4* p) {
+template <bool kOnce>
+__device__ __forceinline__ uint4 dense_load(const uint4* p) {
+  if constexpr (!kOnce) return *p;
   const Vec4 v = __builtin_nontemporal_load(reinterpret_cast<const Vec4*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void store_once(uint4* p, const uint4& v) {
-  __builtin_nontemporal_store(Vec4{v.x, v.y, v.z, v.w}, reinterpret_cast<Vec4*>(p));
+template <bool kOnce>
+__device__ __forceinline__ void dense_store(uint4* p, const uint4& v) {
+  if constexpr (kOnce) __builtin_nontemporal_store(Vec4{v.x, v.y, v.z, v.w}, reinterpret_cast<Vec4*>(p));
+  else *p = v;
 }
-template <typename T, int kOpt>
+template <typename T, int kOpt, bool kOnce>
 __global__ __launch_bounds__(256) void dense_rest_kernel(SgnsArgs a, int pieces, bool any_named) {
   const int rows_at_once = 256 / pieces;
   const int in_iter = (int)threadIdx.x / pieces, piece = (int)threadIdx.x - in_iter * pieces;
@@ -2307,9 +2318,9 @@ __global__ __launch_bounds__(256) void dense_rest_kernel(SgnsArgs a, int pieces,
   for (int u = 0; u < kDenseRows; ++u) {
     if (!mine[u]) continue;
     const int64_t at = (first + (int64_t)u * rows_at_once) * pieces + piece;
-    m[u] = load_once(m_t + at);
-    w[u] = load_once(w_t + at);
-    if constexpr (kOpt == kAdam) v[u] = load_once(v_t + at);
+    m[u] = dense_load<kOnce>(m_t + at);
+    w[u] = dense_load<kOnce>(w_t + at);
+    if constexpr (kOpt == kAdam) v[u] = dense_load<kOnce>(v_t + at);
   }
 #pragma unroll
   for (int u = 0; u < kDenseRows; ++u) {
@@ -2334,13 +2345,13 @@ __global__ __launch_bounds__(256) void dense_rest_kernel(SgnsArgs a, int pieces,
         ve[i] *= a.opt.decay2;
         we[i] -= adam_move(me[i], ve[i], a.opt.lr, a.opt.root_c2, a.opt.eps);
       }
-      store_once(v_t + at, make_uint4(__float_as_uint(ve[0]), __float_as_uint(ve[1]), __float_as_uint(ve[2]), __float_as_uint(ve[3])));
+      dense_store<kOnce>(v_t + at, make_uint4(__float_as_uint(ve[0]), __float_as_uint(ve[1]), __float_as_uint(ve[2]), __float_as_uint(ve[3])));
     }
     uint32_t mo[4], wo[4];
     pack_piece<T, 4>(me, mo);
     pack_piece<T, 4>(we, wo);
-    store_once(m_t + at, make_uint4(mo[0], mo[1], mo[2], mo[3]));
-    store_once(w_t + at, make_uint4(wo[0], wo[1], wo[2], wo[3]));
+    dense_store<kOnce>(m_t + at, make_uint4(mo[0], mo[1], mo[2], mo[3]));
+    dense_store<kOnce>(w_t + at, make_uint4(wo[0], wo[1], wo[2], wo[3]));
   }
 }
 
@@ -2352,7 +2363,9 @@ static int32_t launch_dense_rest(const SgnsArgs& a, bool any_named, hipStream_t 
   const int64_t blocks = ceil_div(a.num_nodes, per_block);
   const int64_t layers = max((int64_t)1, ceil_div(blocks, (int64_t)kDenseBlocks));
   const dim3 grid((unsigned)ceil_div(blocks, layers), 2, (unsigned)layers);
-  dense_rest_kernel<T, kOpt><<<grid, 256, 0, stream>>>(a, pieces, any_named);
+  const int64_t bytes = 2 * a.num_nodes * a.dim * (int64_t)sizeof(T) * (kOpt == kAdam ? 3 : 2);
+  if (bytes <= (256 % pieces == 0 ? kDenseCached : kDenseCached / 4 * 5)) dense_rest_kernel<T, kOpt, false><<<grid, 256, 0, stream>>>(a, pieces, any_named);
+  else dense_rest_kernel<T, kOpt, true><<<grid, 256, 0, stream>>>(a, pieces, any_named);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }

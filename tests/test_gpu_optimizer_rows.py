@@ -10,8 +10,9 @@ from tolerances import EMB_ATOL, LOSS_RTOL, assert_emb_close, assert_half_close
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
-# (nodes, pairs, negatives, columns): per-vertex counters; input keys in a table; all keys in a table
-SHAPES = [(3_000, 9_000, 5, 20), (400_000, 9_000, 5, 8), (800_000, 9_000, 5, 8)]
+# (nodes, pairs, negatives, columns): per-vertex counters; input keys in a table; all keys in a table; tables that no cache
+# holds (more than 256 MB in bf16 too), rows that fill a workgroup's lanes and rows that do not
+SHAPES = [(3_000, 9_000, 5, 20), (400_000, 9_000, 5, 8), (800_000, 9_000, 5, 8), (280_000, 9_000, 3, 128), (430_000, 9_000, 3, 104)]
 
 
 def _batch(n, b, k, seed):

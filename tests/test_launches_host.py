@@ -157,3 +157,31 @@ def test_forward_waves(launches, dtype, dim, pairs, more):
     assert rc == [0]
     forward = [x[0] for x in got if "sgns_forward_kernel" in x[0]]
     assert len(forward) == 1 and ("Li256ELi%dEEEv" % (0 if not more else (4 if dim <= 256 else 3))) in forward[0], forward
+
+
+@pytest.mark.parametrize("call,nodes,dim,dtype,once", [
+    ("gs_sgns_momentum_step", 131_072, 128, 0, 0), ("gs_sgns_momentum_step", 131_073, 128, 0, 1),
+    ("gs_sgns_momentum_step", 262_144, 128, 1, 0), ("gs_sgns_momentum_step", 262_145, 128, 2, 1),
+    ("gs_sgns_adam_step", 87_381, 128, 0, 0), ("gs_sgns_adam_step", 87_382, 128, 0, 1),
+    ("gs_sgns_adam_step", 139_810, 100, 0, 0), ("gs_sgns_adam_step", 139_811, 100, 0, 1)])
+def test_dense_pass_past_the_caches(launches, call, nodes, dim, dtype, once):
+    """Tables of more than 256 MB in all (320 MB where a workgroup's lanes are not whole rows), and no others, are read and
+    written past the caches."""
+    got, rc = launches(STEP + "print(json.dumps({'rc': step('%s', 50000, %d, %d, %d)}))\n" % (call, nodes, dim, dtype))
+    assert rc == [0]
+    dense = [x[0] for x in got if "dense_rest_kernel" in x[0]]
+    assert len(dense) == 1 and ("ELb%dEEEv" % once) in dense[0], dense
+
+
+@pytest.mark.parametrize("call", ["gs_sgns_momentum_step", "gs_sgns_adam_step"])
+@pytest.mark.parametrize("dim,nodes", [(512, 33_554_432), (516, 33_554_432), (516, 33_554_433), (680, 50_331_651), (4, 2_000_000_000),
+                                       (1024, 100_000_000)])
+def test_dense_pass_reaches_every_row(launches, call, dim, nodes):
+    """Launches in one layer and in several: as many workgroups as cover the rows (two per row's worth of lanes), at most one
+    layer's remainder more, all within what a launch takes."""
+    got, rc = launches(STEP + "print(json.dumps({'rc': step('%s', 50000, %d, %d)}))\n" % (call, nodes, dim))
+    assert rc == [0]
+    (name, gx, gy, gz, threads), = [x for x in got if "dense_rest_kernel" in x[0]]
+    rows = 256 // (dim // 4) * 2
+    assert gy == 2 and threads == 256 and 0 <= gx * gz * rows - nodes < rows * (gz + 1)
+    assert gz == -(-(-(-nodes // rows)) // (1 << 23))
