@@ -39,13 +39,16 @@ constexpr int kWaveSegment = 2048;
 
 // ---- one lane per segment ------------------------------------------------------------------
 // Masses and both lists in LDS, entry i of lane l at [i][l].  (In global scratch every step of the loop below
-// is a chain of reads of cache lines of its own.)
+// is a chain of reads of cache lines of its own.)  long_ids: where the segments of more than kWaveSegment entries are
+// written to (a launch of its own for that: 10,000 rows of 10 entries 20.6 us, 19.1 like this).
 template <typename OffT>
 __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict__ seg_offsets,
                                                          int64_t num_segments,
                                                          const float* __restrict__ weights,
                                                          float* __restrict__ prob_out,
-                                                         int32_t* __restrict__ alias_out) {
+                                                         int32_t* __restrict__ alias_out,
+                                                         int64_t* __restrict__ long_ids, int64_t max_long,
+                                                         unsigned long long* __restrict__ long_count) {
 #pragma clang fp contract(off)  // every fp64 operation below must round on its own
   constexpr int kMost = (int)kLaneSegment;
   static_assert((kMost & (kMost - 1)) == 0, "the list of larges wraps by a mask");
@@ -57,6 +60,12 @@ __global__ __launch_bounds__(64) void alias_build_kernel(const OffT* __restrict_
   if (s >= num_segments) return;
   const int64_t begin = (int64_t)seg_offsets[s];
   const int64_t size = (int64_t)seg_offsets[s + 1] - begin;
+  if (size > kWaveSegment && long_ids != nullptr) {
+    // max_long bounds the count when the offsets add up to total_entries; an inconsistent pair of arguments must still
+    // not write out of bounds
+    const unsigned long long at = atomicAdd(long_count, 1ull);
+    if (at < (unsigned long long)max_long) long_ids[at] = s;
+  }
   if (size <= 0 || size > kLaneSegment) return;
   const int n = (int)size;
   const float* w = weights + begin;
@@ -430,20 +439,6 @@ __device__ __forceinline__ void block_before(int c0, int c1, int (*tot)[kLongWav
     before1 += v < wave ? v1[v] : 0;
     all0 += v0[v];
     all1 += v1[v];
-  }
-}
-
-template <typename OffT>
-__global__ void alias_find_long_kernel(const OffT* __restrict__ seg_offsets, int64_t num_segments,
-                                       int64_t* __restrict__ long_ids, int64_t capacity,
-                                       unsigned long long* __restrict__ long_count) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= num_segments) return;
-  if ((int64_t)seg_offsets[s + 1] - (int64_t)seg_offsets[s] > kWaveSegment) {
-    // capacity = total_entries / (kWaveSegment + 1) bounds the count when the offsets add up to
-    // total_entries; an inconsistent pair of arguments must still not write out of bounds
-    const unsigned long long at = atomicAdd(long_count, 1ull);
-    if (at < (unsigned long long)capacity) long_ids[at] = s;
   }
 }
 
@@ -836,7 +831,9 @@ constexpr int kBigItems = 2, kBigItemsAlone = 8;               // larges per lan
 constexpr int kBig = kLongThreads * kBigItems, kBigAlone = kLongThreads * kBigItemsAlone;
 constexpr int kBigRounds = 8;                                  // rounds between two looks at the others
 constexpr int kBigRoundsOneWave = 16;
-// smalls in LDS: two workgroups per compute unit, or most of its LDS for a segment alone
+// smalls in LDS: 74 KB for a workgroup that does one row of several (in the launch that has the shorter rows' lists too, 152 KB,
+// one workgroup per compute unit: 256 rows of 3000 entries 76 us, 300 123; 200 and 268 with a look at both lists in every round
+// and two workgroups per compute unit), or most of a compute unit's for a segment alone
 constexpr int kWindow = 3072, kWindowAlone = 12288;
 static_assert(kWindow >= kBig && kWindow % kLongThreads == 0 && kWindowAlone % kLongThreads == 0, "a round fits the window");
 static_assert(kWindowAlone * sizeof(double) >= kBigAlone * (sizeof(double) + sizeof(int32_t)), "or the larges of the wider rounds");
@@ -1572,21 +1569,18 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
     GS_LAUNCH_CHECK();
     return GS_OK;
   }
-  const int threads = 64;
-  alias_build_kernel<OffT><<<(unsigned)ceil_div(num_segments, threads), threads, 0, stream>>>(
-      seg_offsets, num_segments, weights, prob_out, alias_out);
-  GS_LAUNCH_CHECK();
   // at most this many segments are longer than a wave's
   const int64_t max_long = min(num_segments, total_entries / (kWaveSegment + 1));
   const unsigned long long* any_long = nullptr;
   if (max_long > 0) {
     zero_u64_kernel<<<1, 1, 0, stream>>>(p.long_count);
     GS_LAUNCH_CHECK();
-    alias_find_long_kernel<OffT><<<(unsigned)ceil_div(num_segments, 256), 256, 0, stream>>>(
-        seg_offsets, num_segments, p.long_ids, max_long, p.long_count);
-    GS_LAUNCH_CHECK();
     any_long = p.long_count;
   }
+  const int threads = 64;
+  alias_build_kernel<OffT><<<(unsigned)ceil_div(num_segments, threads), threads, 0, stream>>>(
+      seg_offsets, num_segments, weights, prob_out, alias_out, max_long > 0 ? p.long_ids : nullptr, max_long, p.long_count);
+  GS_LAUNCH_CHECK();
   // few segments: a wave each; many: up to 64 per wave, so that the short ones cost one look
   const int per_wave = (int)max((int64_t)1, min((int64_t)64, num_segments / 16384));
   const unsigned waves = (unsigned)ceil_div(num_segments, per_wave);

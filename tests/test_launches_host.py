@@ -185,3 +185,12 @@ def test_dense_pass_reaches_every_row(launches, call, dim, nodes):
     rows = 256 // (dim // 4) * 2
     assert gy == 2 and threads == 256 and 0 <= gx * gz * rows - nodes < rows * (gz + 1)
     assert gz == -(-(-(-nodes // rows)) // (1 << 23))
+
+
+def test_launches_of_alias_tables(launches):
+    """Short segments pay for the launches that other sizes would need; none of them only looks for long ones."""
+    got, rc = launches("p = [C.c_void_p(1 << (20 + i)) for i in range(6)]\nprint(json.dumps({'rc': lib.gs_alias_build(p[0], C.c_int32(32), "
+                       "C.c_int64(10000), C.c_int64(100000), *p[1:5], C.c_size_t(1 << 40), None)}))\n")
+    assert rc == [0]
+    names = [x[0].split("kernel")[0].split("gs")[1].lstrip("0123456789") for x in got]
+    assert names == ["zero_u64_", "alias_build_", "alias_build_wave_", "alias_build_wave_", "alias_build_wave_", "alias_build_rows_"]
