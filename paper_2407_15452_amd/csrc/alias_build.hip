@@ -503,9 +503,11 @@ __device__ __forceinline__ void append(Window& q, int32_t* list, bool mine, int3
 struct ListState { int64_t sh, st, lh, lt; };
 constexpr int64_t kWideSegment = (int64_t)1 << 17;
 // Workgroups of the chip-wide kernels: small ones, so that the scattered accesses of a round spread over all compute
-// units, while every workgroup can still add up the counts of the tiles before its own.
+// units, while every workgroup can still add up the counts of the tiles before its own.  Milliseconds, 256 against 1024
+// threads, lognormal weights and degree^0.75: 0.3 M entries 0.35 / 0.39 and 1.18 / 1.20, 2 M 0.66 / 0.84 and 2.15 / 2.30, 8 M 3.31 / 3.81
+// and 3.85 / 4.38, 32 M 9.74 / 10.9 and 25.9 / 27.5, 64 M 18.7 / 19.7 and 51.7 / 52.4, 128 M 37.5 / 37.2 and 106.3 / 106.1.
 constexpr int kWideThreads = 256, kWideTile = kWideThreads * kLongItems;
-constexpr int64_t kWideSmallTiles = (int64_t)1 << 22;          // entries
+constexpr int64_t kWideSmallTiles = (int64_t)1 << 26;          // entries
 constexpr int64_t kWideRound = 8192;
 static int wide_rounds(int64_t n) {
   return n < (int64_t)3 << 19 ? 16 : (n < (int64_t)3 << 20 ? 32 : (n < (int64_t)3 << 21 ? 96 : 128));
@@ -1394,7 +1396,9 @@ __global__ __launch_bounds__(kLongThreads) void alias_build_long_kernel(const Of
 // row (200,000 rows of 100 entries 386 us, 453 from here) the segments are left to launches of their own.  The number of
 // long rows is known to the device alone, so both are launched, and the waves of the one that is not to be return.
 constexpr int kRowsMiddle = 256, kRowsMost = 1024;
-constexpr int kRowsWideWaves = 11;             // waves whose lists hold kRowsMost entries; the others' hold kRowsMiddle
+// waves whose lists hold kRowsMost entries; the others' hold kRowsMiddle (7, 11 and 12 of them: 20,000 rows of 500 beside 5 of 3000 268,
+// 210, 208 us, 2000 of 1000 beside those 88, 75, 73, R-MAT of 1 M nodes 787, 755, 756; 12 fill the LDS)
+constexpr int kRowsWideWaves = 12;
 constexpr int kRowsPerBlock = 512;
 constexpr int64_t kRowsLongBlocks = 1024;
 struct RowsShared {

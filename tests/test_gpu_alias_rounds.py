@@ -37,6 +37,11 @@ def test_alone(oracle, kind, n):
     _check(oracle, np.array([0, n], dtype=np.int64), w)
 
 
+@pytest.mark.parametrize("n", [(1 << 22) + 5, 1 << 26, (1 << 26) + 1])       # 256 threads a workgroup up to 2^26 entries
+def test_alone_and_very_long(oracle, n):
+    _check(oracle, np.array([0, n], dtype=np.int64), _weights("lognormal", n, np.random.default_rng(n)))
+
+
 @pytest.mark.parametrize("larges", [1, 63, 64, 65, 2047, 2048, 2049, 8191, 8192])
 def test_alone_with_so_many_larges(oracle, larges):
     """Equal larges that last for 20 rounds and more of 300,000 smalls."""
