@@ -12,7 +12,8 @@ extern "C" int32_t gs_last_hip_error(void) { return (int32_t)g_last_error; }
 // ---------------------------------------------------------------------------
 // Exclusive scan: tiles of 1024 values.  The tiles' sums first; then every tile is scanned from the sum of the
 // tiles before it, which its workgroup adds up itself while there are few (a launch costs more).  Beyond that the
-// tile sums are scanned the same way in between.
+// tile sums are scanned the same way in between.  Offsets of walks, us, up to 1024, 4096 and 16,384 tiles without that: 1.1 M
+// walks 21.2, 17.3, 17.3, 4 M 44.3, 41.3, 41.5, 4.2 M 45.9, 45.9, 44.2, 8 M 76.5, 76.3, 78.8, 16 M 146, 146, 181.
 // ---------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4;
