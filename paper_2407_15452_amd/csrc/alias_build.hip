@@ -1516,13 +1516,13 @@ static bool wide_segment(int64_t num_segments, int64_t total_entries) {
 template <typename OffT, int kThreads>
 static int32_t launch_wide_rounds(const OffT* seg_offsets, int64_t n, const float* weights, float* prob_out,
                                   int32_t* alias_out, const AliasPlan& p, hipStream_t stream) {
-  const unsigned tiles = (unsigned)min((int64_t)4096, ceil_div(n, kThreads * kLongItems));
+  const unsigned tiles = (unsigned)std::min((int64_t)4096, ceil_div(n, kThreads * kLongItems));
   alias_wide_masses_kernel<OffT, kThreads><<<tiles, kThreads, 0, stream>>>(seg_offsets, weights, p.sum, p.mass, p.flags, p.counts);
   alias_wide_append_kernel<OffT, kThreads><<<tiles, kThreads, 0, stream>>>(seg_offsets, p.small_q, p.large_q, p.flags, p.counts,
                                                                            p.states, 1);
   GS_LAUNCH_CHECK();
   const int rounds = wide_rounds(n);
-  const unsigned half = (unsigned)min((int64_t)2048, ceil_div(n / 2 + 1, kThreads * kLongItems));      // m is at most half of n
+  const unsigned half = (unsigned)std::min((int64_t)2048, ceil_div(n / 2 + 1, kThreads * kLongItems));      // m is at most half of n
   for (int r = 0; r < rounds; ++r) {
     alias_wide_round_kernel<OffT, kThreads><<<half, kThreads, 0, stream>>>(
         seg_offsets, p.sum, prob_out, alias_out, p.mass, p.small_q, p.large_q, p.flags, p.counts, p.states + r);
@@ -1537,11 +1537,11 @@ template <typename OffT>
 static int32_t launch_alias_wide(const OffT* seg_offsets, int64_t n, const float* weights, float* prob_out,
                                  int32_t* alias_out, const AliasPlan& p, hipStream_t stream) {
   const int64_t chunks = ceil_div(n, kSumChunk);
-  alias_wide_chunks_kernel<OffT><<<(unsigned)min((int64_t)1024, ceil_div(chunks, kLongWaves)), kLongThreads, 0, stream>>>(
+  alias_wide_chunks_kernel<OffT><<<(unsigned)std::min((int64_t)1024, ceil_div(chunks, kLongWaves)), kLongThreads, 0, stream>>>(
       seg_offsets, weights, p.chunk_sums, p.runs);
   int32_t* summed = p.counts;                  // (the counts come later)
   alias_wide_prefix_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, p.chunk_sums, p.runs, p.sum, summed);
-  alias_wide_runs_kernel<OffT><<<(unsigned)min((int64_t)8192, ceil_div(chunks, 4)), 256, 0, stream>>>(
+  alias_wide_runs_kernel<OffT><<<(unsigned)std::min((int64_t)8192, ceil_div(chunks, 4)), 256, 0, stream>>>(
       seg_offsets, weights, p.chunk_sums, p.runs, summed);
   alias_wide_sum_kernel<OffT><<<1, 256, 0, stream>>>(seg_offsets, weights, p.runs, p.sum, summed);
   GS_LAUNCH_CHECK();
@@ -1550,7 +1550,7 @@ static int32_t launch_alias_wide(const OffT* seg_offsets, int64_t n, const float
       : launch_wide_rounds<OffT, kLongThreads>(seg_offsets, n, weights, prob_out, alias_out, p, stream);
   if (rc != GS_OK) return rc;
   ListState* left = p.states + wide_rounds(n);
-  const unsigned blocks = (unsigned)min((int64_t)4096, ceil_div(n, 256));
+  const unsigned blocks = (unsigned)std::min((int64_t)4096, ceil_div(n, 256));
   alias_wide_gather_kernel<OffT><<<blocks, 256, 0, stream>>>(seg_offsets, p.mass, p.small_q, left, p.mass_seq);
   alias_wide_tail_kernel<OffT><<<1, kLongThreads, 0, stream>>>(seg_offsets, p.sum, p.mass, p.small_q, p.large_q, p.mass_seq,
                                                                p.alias_seq, left);
@@ -1574,7 +1574,7 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
     return GS_OK;
   }
   // at most this many segments are longer than a wave's
-  const int64_t max_long = min(num_segments, total_entries / (kWaveSegment + 1));
+  const int64_t max_long = std::min(num_segments, total_entries / (kWaveSegment + 1));
   const unsigned long long* any_long = nullptr;
   if (max_long > 0) {
     zero_u64_kernel<<<1, 1, 0, stream>>>(p.long_count);
@@ -1586,7 +1586,7 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
       seg_offsets, num_segments, weights, prob_out, alias_out, max_long > 0 ? p.long_ids : nullptr, max_long, p.long_count);
   GS_LAUNCH_CHECK();
   // few segments: a wave each; many: up to 64 per wave, so that the short ones cost one look
-  const int per_wave = (int)max((int64_t)1, min((int64_t)64, num_segments / 16384));
+  const int per_wave = (int)std::max((int64_t)1, std::min((int64_t)64, num_segments / 16384));
   const unsigned waves = (unsigned)ceil_div(num_segments, per_wave);
   if (total_entries > kLaneSegment) {
     alias_build_wave_kernel<OffT, (int)kLaneSegment + 1, kRowsMiddle><<<waves, 64, 0, stream>>>(
@@ -1605,10 +1605,10 @@ static int32_t launch_alias_build(const OffT* seg_offsets, int64_t num_segments,
     GS_LAUNCH_CHECK();
   }
   if (max_long > 0) {
-    const int long_blocks = (int)min(kRowsLongBlocks, max_long);
+    const int long_blocks = (int)std::min(kRowsLongBlocks, max_long);
     // few segments: 16 per workgroup, whose waves then take one or two each
-    const int per_block = (int)max((int64_t)16, min((int64_t)kRowsPerBlock, ceil_div(num_segments, 1024)));
-    const int64_t row_blocks = min((int64_t)1 << 20, ceil_div(num_segments, per_block));
+    const int per_block = (int)std::max((int64_t)16, std::min((int64_t)kRowsPerBlock, ceil_div(num_segments, 1024)));
+    const int64_t row_blocks = std::min((int64_t)1 << 20, ceil_div(num_segments, per_block));
     alias_build_rows_kernel<OffT><<<(unsigned)(long_blocks + row_blocks), kLongThreads, 0, stream>>>(
         seg_offsets, num_segments, per_block, p.long_ids, p.long_count, max_long, long_blocks, weights, prob_out, alias_out,
         p.mass, p.small_q, p.large_q);

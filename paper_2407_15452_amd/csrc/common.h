@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>      // std::min and std::max on the host, where the runtime's own take ints
+
 #include "../../include/gs.h"
 
 namespace gs {

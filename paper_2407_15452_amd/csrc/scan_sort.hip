@@ -348,8 +348,8 @@ constexpr int64_t kSortLarge = (int64_t)1 << 21;
 
 // (never less than a shorter sort takes: a caller's workspace for its largest batch serves every batch)
 size_t radix_sort_scratch_bytes(int64_t n) {
-  const int64_t small = max((int64_t)1, min(n, kSortLarge - 1));
-  const size_t tiles = (size_t)max(ceil_div(small, kSortThreads * kSortItemsSmall),
+  const int64_t small = std::max((int64_t)1, std::min(n, kSortLarge - 1));
+  const size_t tiles = (size_t)std::max(ceil_div(small, kSortThreads * kSortItemsSmall),
                                    n >= kSortLarge ? ceil_div(n, kSortThreads * kSortItemsLarge) : (int64_t)0);
   return align_up(tiles * kDigits * sizeof(uint32_t)) + align_up(kDigits * sizeof(uint32_t));
 }
@@ -376,7 +376,7 @@ int32_t radix_sort(const K* keys_in, const V* vals_in, K* keys_out, V* vals_out,
     const bool to_alt = (passes - 1 - p) & 1;              // the last pass ends in the output
     K* k_to = to_alt ? keys_alt : keys_out;
     V* v_to = to_alt ? vals_alt : vals_out;
-    const int32_t rc = pass(k_from, v_from, k_to, v_to, n, limit, p * width, min(width, nbits - p * width), counts,
+    const int32_t rc = pass(k_from, v_from, k_to, v_to, n, limit, p * width, std::min(width, nbits - p * width), counts,
                             totals, stream);
     if (rc != GS_OK) return rc;
     k_from = k_to;

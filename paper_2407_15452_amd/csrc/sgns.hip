@@ -2024,7 +2024,7 @@ static int32_t launch_updates(const SgnsArgs& a, hipStream_t stream) {
   constexpr int kWaves = kSgnsThreads / 64;
   // context-table keys: exactly num_terms positions; input-table keys: at most one per pair
   const unsigned out_blocks = (unsigned)ceil_div(ceil_div(a.num_terms, a.slice_terms), kWaves);
-  const unsigned in_blocks = (unsigned)min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
+  const unsigned in_blocks = (unsigned)std::min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
   const size_t lds = 0;
   const unsigned finish_blocks = (unsigned)ceil_div(a.long_slots, kGroupsPerBlock) + 1;
   sgns_update_kernel<T, WPP, PPL, UB, kOpt, false><<<out_blocks, kSgnsThreads, lds, stream>>>(a);
@@ -2075,7 +2075,7 @@ static int32_t launch_rows(const SgnsArgs& a, hipStream_t stream) {
 static int32_t launch_clear(const SgnsArgs& a, hipStream_t stream) {
   const int64_t keys4 = ceil_div(a.cnt_last + 1, 4);
   const int64_t table4 = a.table_places / 4;   // (tables have at least 256 places each)
-  sgns_clear_kernel<<<(unsigned)ceil_div(max(keys4, table4), 256), 256, 0, stream>>>(
+  sgns_clear_kernel<<<(unsigned)ceil_div(std::max(keys4, table4), 256), 256, 0, stream>>>(
       (uint4*)a.cnt, keys4, (uint4*)a.key_table, table4, a.bad_ids);
   GS_LAUNCH_CHECK();
   return GS_OK;
@@ -2108,7 +2108,7 @@ template <typename T, int WPP, int PPL, int UB>
 static int32_t launch_sorted_updates(const SgnsArgs& a, hipStream_t stream) {
   constexpr int kWaves = kSgnsThreads / 64;
   const unsigned out_blocks = (unsigned)ceil_div(ceil_div(a.num_terms, a.slice_terms), kWaves);
-  const unsigned in_blocks = (unsigned)min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
+  const unsigned in_blocks = (unsigned)std::min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
   const unsigned long_blocks = (unsigned)ceil_div(a.stage_long_base, kGroupsPerBlock);
   sgns_sorted_long_kernel<T, true><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
   sgns_sorted_update_kernel<T, WPP, PPL, UB><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
@@ -2361,7 +2361,7 @@ static int32_t launch_dense_rest(const SgnsArgs& a, bool any_named, hipStream_t 
   const int64_t per_block = (int64_t)(256 / pieces) * kDenseRows;
   // (a dimension of a launch is below 2^32 lanes, which 2 rows of 129 pieces per workgroup leave within this card's memory)
   const int64_t blocks = ceil_div(a.num_nodes, per_block);
-  const int64_t layers = max((int64_t)1, ceil_div(blocks, (int64_t)kDenseBlocks));
+  const int64_t layers = std::max((int64_t)1, ceil_div(blocks, (int64_t)kDenseBlocks));
   const dim3 grid((unsigned)ceil_div(blocks, layers), 2, (unsigned)layers);
   const int64_t bytes = 2 * a.num_nodes * a.dim * (int64_t)sizeof(T) * (kOpt == kAdam ? 3 : 2);
   if (bytes <= (256 % pieces == 0 ? kDenseCached : kDenseCached / 4 * 5)) dense_rest_kernel<T, kOpt, false><<<grid, 256, 0, stream>>>(a, pieces, any_named);
@@ -2752,7 +2752,7 @@ extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, vo
   }
   const int per16 = (dtype == GS_F32) ? 4 : 8;
   const int64_t pieces = num_nodes * (int64_t)dim / per16;
-  const unsigned blocks = (unsigned)min((int64_t)(256 * 64), ceil_div(pieces, 256));
+  const unsigned blocks = (unsigned)std::min((int64_t)(256 * 64), ceil_div(pieces, 256));
   // mult: momentum <- mu * momentum, every row
   if (dtype == GS_F32) {
     table_scale_kernel<<<blocks, 256, 0, stream>>>((float4*)m_in, pieces, mu);

@@ -495,7 +495,7 @@ extern "C" int32_t gs_table_mult(void* table, int64_t num_nodes, int32_t dim, in
   const int32_t rc = check_table_args(table, num_nodes, dim, dtype);
   if (rc != GS_OK) return rc;
   const int64_t pieces = num_nodes * (int64_t)dim / (dtype == GS_F32 ? 4 : 8);
-  const unsigned blocks = (unsigned)min((int64_t)(256 * 64), ceil_div(pieces, 256));
+  const unsigned blocks = (unsigned)std::min((int64_t)(256 * 64), ceil_div(pieces, 256));
   if (dtype == GS_F32)
     table_mult_f32_kernel<<<blocks, 256, 0, stream>>>(static_cast<float4*>(table), pieces, factor);
   else if (dtype == GS_BF16)
@@ -515,7 +515,7 @@ extern "C" int32_t gs_table_mult_add(void* dst, const void* src, int64_t num_nod
   if (rc != GS_OK) return rc;
   if (dst == src) return GS_EINVAL;
   const int64_t pieces = num_nodes * (int64_t)dim / (dtype == GS_F32 ? 4 : 8);
-  const unsigned blocks = (unsigned)min((int64_t)(256 * 64), ceil_div(pieces, 256));
+  const unsigned blocks = (unsigned)std::min((int64_t)(256 * 64), ceil_div(pieces, 256));
   if (dtype == GS_F32)
     table_mult_add_f32_kernel<<<blocks, 256, 0, stream>>>(static_cast<float4*>(dst),
                                                           static_cast<const float4*>(src), pieces, factor);

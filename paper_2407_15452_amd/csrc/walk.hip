@@ -8,7 +8,6 @@
 // lanes to one.  Output rows are staged in LDS
 // in windows of kWin positions and written out as 64-byte row segments instead
 // of one scattered 4-byte store per position.
-#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -569,7 +568,7 @@ static int32_t walk_common(const gs_csr* g, const gs_alias* al, const int32_t* s
     a.starts = starts + first;
     a.walks = walks_out + first * walk_len;
     a.id_base = id_base + (uint64_t)first;
-    a.num_walks = std::min(kLaunchWalks, num_walks - first);          // (the runtime's own min takes ints on the host)
+    a.num_walks = std::min(kLaunchWalks, num_walks - first);
     if (g->offset_bits == 32) launch_walk<int32_t, int32_t>(weighted, second, team, a, stream);
     else if (g->num_entries <= (int64_t)INT32_MAX) launch_walk<int64_t, int32_t>(weighted, second, team, a, stream);
     else launch_walk<int64_t, int64_t>(weighted, second, team, a, stream);

@@ -194,3 +194,11 @@ def test_launches_of_alias_tables(launches):
     assert rc == [0]
     names = [x[0].split("kernel")[0].split("gs")[1].lstrip("0123456789") for x in got]
     assert names == ["zero_u64_", "alias_build_", "alias_build_wave_", "alias_build_wave_", "alias_build_wave_", "alias_build_rows_"]
+
+
+@pytest.mark.parametrize("segments", [(1 << 31) - 1, 1 << 31, (1 << 31) + 8])
+def test_long_segments_among_very_many(launches, segments):
+    """Sizes on the host are 64 bits wide: segments of more than 2048 entries are looked for however many segments there are."""
+    got, rc = launches("p = [C.c_void_p(1 << (20 + i)) for i in range(6)]\nprint(json.dumps({'rc': lib.gs_alias_build(p[0], C.c_int32(64), "
+                       "C.c_int64(%d), C.c_int64(1 << 33), *p[1:5], C.c_size_t(1 << 45), None)}))\n" % segments)
+    assert rc == [0] and "alias_build_rows_kernel" in got[-1][0]
