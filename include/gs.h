@@ -20,11 +20,12 @@
  *  - Calls that need scratch memory take (ws, ws_bytes); the matching
  *    *_workspace_bytes() function (host, O(1)) returns the size to provide.
  *    ws must be 256-byte aligned.  Its contents are undefined afterwards.
- *    gs_alias_build and the training steps have more than one way of doing
- *    their work and report what the largest takes; with less, down to what the
- *    general way takes, they use that one (in more time, and a training step
- *    with fp32 gradients of centre rows that may be added in another order), and
- *    return GS_EWORKSPACE below it.  A workspace for one size of batch also
+ *    gs_alias_build (one segment of 2^17 entries and more), gs_unique_ids and the
+ *    training steps have more than one way of doing their work and report what
+ *    the largest takes; with less, down to what the general way takes, they use
+ *    that one (in more time, without a word, and a training step with fp32
+ *    gradients of centre rows that may be added in another order), and return
+ *    GS_EWORKSPACE below it; so ask again for the size with every new library.  A workspace for one size of batch also
  *    serves every smaller one that is not empty (other arguments alike).
  *  - Return value: GS_OK or a negative gs_status.  Arguments are validated on
  *    the host only; nothing is enqueued when a call fails validation.  Node
@@ -401,8 +402,11 @@ int32_t gs_sgns_adam_step(float* w_in, float* w_out, float* m_in, float* m_out, 
  *   entries are written), num_unique_out int64[1] on the device, inverse_out
  *   int32[n] or NULL: position of ids[i] in unique_out.  Ids outside
  *   [0, num_nodes) are left out of unique_out and get inverse -1.
- *   Workspace: gs_unique_ids_workspace_bytes(n, num_nodes) (a bitmap of the node
- *   ids, or sort buffers for the batch when the graph is far larger).
+ *   Workspace: gs_unique_ids_workspace_bytes(n, num_nodes): a bitmap of the node
+ *   ids and its counts (3 bytes per 8 nodes), up to 16 nodes per id a byte per
+ *   node as well, or, when the graph is more than 256 times larger than the batch,
+ *   sort buffers for the ids.  Without room for the bytes the bitmap is written
+ *   with atomics, which takes up to 20 times as long on small graphs.
  *
  * gs_get_rows -- out[i] = table[ids[i]] for i < n, as fp32 (bf16 rows widened
  *   exactly); a zero row for an id outside [0, num_nodes).  out float[n][dim].
