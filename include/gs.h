@@ -20,8 +20,8 @@
  *  - Calls that need scratch memory take (ws, ws_bytes); the matching
  *    *_workspace_bytes() function (host, O(1)) returns the size to provide.
  *    ws must be 256-byte aligned.  Its contents are undefined afterwards.
- *    gs_alias_build (one segment of 2^17 entries and more), gs_unique_ids and the
- *    training steps have more than one way of doing their work and report what
+ *    gs_alias_build (one segment of 2^17 entries and more), gs_unique_ids, gs_sort_pairs
+ *    and the training steps have more than one way of doing their work and report what
  *    the largest takes; with less, down to what the general way takes, they use
  *    that one (in more time, without a word, and a training step with fp32
  *    gradients of centre rows that may be added in another order), and return

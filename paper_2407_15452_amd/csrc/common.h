@@ -56,12 +56,13 @@ int32_t exclusive_scan_i64(int64_t* data, int64_t n, int64_t* scratch, int64_t* 
 // alternate buffers and end in the output.  keys_in / vals_in are not written unless they are the
 // buffer of a later pass: they may be the alternate buffers when the number of passes is odd, the
 // output when it is even.  n < 2^32.
-size_t radix_sort_scratch_bytes(int64_t n);
-int radix_sort_passes(int nbits);
+struct SortPlan { int passes, width, items; };   // digits of `width` bits, records per lane
+size_t radix_sort_scratch_bytes(int64_t n, bool wide);                 // wide: for the fewest passes; else the least that will do
+SortPlan radix_sort_plan(int64_t n, int nbits, size_t scratch_bytes);
 // Records: (uint32_t, uint32_t), (uint32_t, uint2), (uint64_t, uint32_t).
 template <typename K, typename V>
-int32_t radix_sort(const K* keys_in, const V* vals_in, K* keys_out, V* vals_out, K* keys_alt, V* vals_alt, int64_t n,
-                   K limit, int nbits, void* scratch, hipStream_t stream);
+int32_t radix_sort(const SortPlan& plan, const K* keys_in, const V* vals_in, K* keys_out, V* vals_out, K* keys_alt, V* vals_alt,
+                   int64_t n, K limit, int nbits, void* scratch, hipStream_t stream);
 
 // ---- device side -----------------------------------------------------------
 #if defined(__HIPCC__)

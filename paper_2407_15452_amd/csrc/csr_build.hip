@@ -139,7 +139,8 @@ struct CsrPlan {
   uint32_t *vals, *vals_alt;     // weighted graphs only use them
   int64_t *tile_first, *scan_scratch;
   int32_t* row_of;
-  void* sort_scratch;
+  void* sort_scratch;            // (in the place of row_of, which is written when the records are sorted)
+  size_t sort_bytes;
   size_t bytes;
 };
 
@@ -154,8 +155,9 @@ static CsrPlan plan_csr(void* ws, int64_t cap) {
   p.vals_alt = cv.take<uint32_t>(c);
   p.tile_first = cv.take<int64_t>((size_t)tiles);
   p.scan_scratch = cv.take<int64_t>(scan_scratch_elems(tiles));
-  p.row_of = cv.take<int32_t>(c);
-  p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)c));
+  p.sort_bytes = std::max(c * sizeof(int32_t), radix_sort_scratch_bytes((int64_t)c, true));
+  p.sort_scratch = cv.take<char>(p.sort_bytes);
+  p.row_of = static_cast<int32_t*>(p.sort_scratch);
   p.bytes = cv.used;
   return p;
 }
@@ -198,13 +200,14 @@ extern "C" int32_t gs_csr_build(const int32_t* src, const int32_t* dst, const fl
     // the nodes fill the nb bits, and then the key has one bit more.
     // The passes go back and forth between two buffers and end in (keys, vals).
     const int key_bits = 2 * nb + (num_nodes < ((int64_t)1 << nb) ? 0 : 1);
-    const bool odd = radix_sort_passes(key_bits) & 1;
+    const SortPlan sort = radix_sort_plan(cap, key_bits, p.sort_bytes);
+    const bool odd = sort.passes & 1;
     uint64_t* made = odd ? p.keys_alt : p.keys;
     uint32_t* made_vals = w == nullptr ? nullptr : (odd ? p.vals_alt : p.vals);
     csr_keygen_kernel<<<(unsigned)ceil_div(cap, threads), threads, 0, stream>>>(src, dst, w, cap, num_nodes, flags, nb,
                                                                                made, made_vals);
     GS_LAUNCH_CHECK();
-    const int32_t rc = radix_sort<uint64_t>(made, made_vals, p.keys, p.vals, p.keys_alt, p.vals_alt, cap, kDroppedKey,
+    const int32_t rc = radix_sort<uint64_t>(sort, made, made_vals, p.keys, p.vals, p.keys_alt, p.vals_alt, cap, kDroppedKey,
                                             key_bits, p.sort_scratch, stream);
     if (rc != GS_OK) return rc;
     csr_count_kernel<<<(unsigned)tiles, kCompactThreads, 0, stream>>>(p.keys, cap, flags, p.tile_first);

@@ -124,23 +124,22 @@ int32_t exclusive_scan_i64(int64_t* data, int64_t n, int64_t* scratch, int64_t* 
 // ---------------------------------------------------------------------------
 // Stable least-significant-digit radix sort of (key, value) records.
 //
-// One pass over a digit: count (per tile and digit), a prefix sum per digit over the tiles, and
+// One pass over a digit: count (per tile and digit), prefix sums per digit over the tiles, and
 // the scatter.  A tile is kSortThreads * ITEMS consecutive records.  The scatter ranks a tile's
 // records stably (a wave takes its records 64 at a time in index order: the lanes of equal digit
 // find each other by ballots, the first of them advances the wave's counter of that digit),
 // brings the tile into digit order in LDS and writes it out from there, so that the records of a
 // digit leave as one contiguous run instead of one scattered record per lane.
 //
-// Bound by memory: a pass reads the keys twice and the values once and writes both once.  Measured
-// on 23 million records of 8 + 4 bytes: 200 us per pass (count 63, prefix sums 5, scatter 133; 3.7
-// TB/s of the 32 bytes per record), against 640 us with one wave per tile and every lane storing its
-// own record (445 us the scatter, 110 us its 64-bit prefix sums); 300,007 records of 4 + 4 bytes: 16
-// us per pass against 58.
+// Bound by memory: a pass reads the keys twice and the values once and writes both once, so fewer passes over wider digits
+// win as long as the runs of a digit still fill their cache lines.  23 million records of 8 + 4 bytes: 40 bits in four passes
+// of 10 (count 42, prefix sums 14, scatter 121 us: 710 us in all) against five of 8 (47, 5 and 130: 908); 20 bits of 11 million
+// records of 4 + 8 bytes 218 against 273.  Digits of 11 bits gain nothing: 22 bits of 12 million records in two passes 297 us (scatter 113),
+// in three of 8 296 (76).  Counts lie by tile, so that a tile's are written, and read, as one run (by digit: count 58 us
+// of 23 million records).  The values are read when the keys have left: 782 against 918 us for the same sort in five passes.
 // ---------------------------------------------------------------------------
 constexpr int kSortThreads = 512;
 constexpr int kSortWaves = kSortThreads / 64;
-constexpr int kDigitBits = 8;
-constexpr int kDigits = 1 << kDigitBits;
 
 // keys at or above `limit` sort as `limit` (and keep their value)
 template <typename K>
@@ -148,15 +147,21 @@ __device__ __forceinline__ uint32_t digit_of(K key, K limit, int shift, uint32_t
   return (uint32_t)(min(key, limit) >> shift) & mask;
 }
 
-template <typename K, int ITEMS>
+// The tile of a workgroup: each XCD (workgroups go to the 8 of them in turn) takes one contiguous eighth, so that the runs of a
+// digit that share a cache line meet in one L2.
+__device__ __forceinline__ int64_t sort_tile(int64_t tiles_per_xcd) {
+  return (int64_t)(blockIdx.x & 7u) * tiles_per_xcd + (blockIdx.x >> 3);
+}
+
+template <typename K, int ITEMS, int BITS>
 __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(const K* __restrict__ keys, int64_t n, K limit,
-                                                                   int shift, uint32_t mask, int64_t num_tiles,
+                                                                   int shift, uint32_t mask,
                                                                    uint32_t* __restrict__ counts) {
-  __shared__ uint32_t hist[kSortWaves / 2][kDigits];      // (two waves share a copy)
+  constexpr int kD = 1 << BITS;
+  constexpr int kCopies = BITS <= 8 ? 4 : 2;              // (the waves share them)
+  __shared__ uint32_t hist[kCopies][kD];
   uint32_t* flat = &hist[0][0];
-  for (int i = threadIdx.x; i < kSortWaves / 2 * kDigits; i += kSortThreads) flat[i] = 0u;
-  __syncthreads();
-  uint32_t* mine = hist[threadIdx.x >> 7];
+  for (int i = threadIdx.x; i < kCopies * kD; i += kSortThreads) flat[i] = 0u;
   const int64_t base = (int64_t)blockIdx.x * (kSortThreads * ITEMS);
   K key[ITEMS];
 #pragma unroll
@@ -164,15 +169,18 @@ __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(const K* __re
     const int64_t i = base + c * kSortThreads + threadIdx.x;
     key[c] = (i < n) ? keys[i] : (K)0;
   }
+  __syncthreads();
+  uint32_t* mine = hist[(threadIdx.x >> 6) % kCopies];
 #pragma unroll
   for (int c = 0; c < ITEMS; ++c)
     if (base + c * kSortThreads + threadIdx.x < n) atomicAdd(&mine[digit_of(key[c], limit, shift, mask)], 1u);
   __syncthreads();
+  uint32_t* row = counts + (int64_t)blockIdx.x * (mask + 1u);
   for (uint32_t d = threadIdx.x; d <= mask; d += kSortThreads) {
     uint32_t sum = 0;
 #pragma unroll
-    for (int w = 0; w < kSortWaves / 2; ++w) sum += hist[w][d];
-    counts[(int64_t)d * num_tiles + blockIdx.x] = sum;
+    for (int w = 0; w < kCopies; ++w) sum += hist[w][d];
+    row[d] = sum;
   }
 }
 
@@ -186,56 +194,74 @@ __device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, int lane) {
   return v;
 }
 
-// block d: exclusive prefix sums of the counts of digit d over the tiles, and their total
-__global__ __launch_bounds__(256) void radix_scan_kernel(uint32_t* __restrict__ counts, int64_t num_tiles,
-                                                         uint32_t* __restrict__ totals) {
-  __shared__ uint32_t wave_sum[2][4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t* row = counts + (int64_t)blockIdx.x * num_tiles;
-  uint32_t carry = 0;
-  int turn = 0;
-  for (int64_t base = 0; base < num_tiles; base += 1024, turn ^= 1) {
-    const int64_t at = base + (int64_t)threadIdx.x * 4;
-    uint32_t v[4];
+// Exclusive prefix sums of the counts of a digit over the tiles, and their total: a workgroup takes kScanDigits digits, a
+// lane one digit of a stretch of tiles.
+constexpr int kScanDigits = 16, kScanStretches = 1024 / kScanDigits;
+__global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__ counts, int64_t num_tiles, uint32_t digits,
+                                                          uint32_t* __restrict__ totals) {
+  __shared__ uint32_t sums[kScanStretches][kScanDigits + 1];
+  const uint32_t d = blockIdx.x * kScanDigits + (threadIdx.x & (kScanDigits - 1));
+  const int s = threadIdx.x / kScanDigits;
+  const int64_t per = (num_tiles + kScanStretches - 1) / kScanStretches;
+  const int64_t lo = min(num_tiles, s * per), hi = min(num_tiles, lo + per);
+  const bool live = d < digits;
+  constexpr int kBurst = 16;
+  uint32_t v[kBurst];
+  auto load = [&](int64_t t) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = (at + k < num_tiles) ? row[at + k] : 0u;
-    const uint32_t own = v[0] + v[1] + v[2] + v[3];
+    for (int u = 0; u < kBurst; ++u) v[u] = (live && t + u < hi) ? counts[(t + u) * digits + d] : 0u;
+  };
+  uint32_t sum = 0;
+  for (int64_t t = lo; t < hi; t += kBurst) {
+    load(t);
+#pragma unroll
+    for (int u = 0; u < kBurst; ++u) sum += v[u];
+  }
+  sums[s][threadIdx.x & (kScanDigits - 1)] = sum;
+  __syncthreads();
+  {                                              // wave w: the stretches of digit w
+    static_assert(kScanStretches == 64 && kScanDigits == 16, "sixteen waves, a lane per stretch");
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t own = sums[lane][w];
     const uint32_t incl = wave_inclusive(own, lane);
-    if (lane == 63) wave_sum[turn][wave] = incl;
-    __syncthreads();
-    uint32_t run = carry + incl - own;
+    sums[lane][w] = incl - own;
+    if (lane == 63 && blockIdx.x * kScanDigits + w < digits) totals[blockIdx.x * kScanDigits + w] = incl;
+  }
+  __syncthreads();
+  uint32_t run = sums[s][threadIdx.x & (kScanDigits - 1)];
+  for (int64_t t = lo; t < hi; t += kBurst) {
+    if (per > kBurst) load(t);                   // (else still there)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w < wave) run += wave_sum[turn][w];
-      carry += wave_sum[turn][w];
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (at + k < num_tiles) row[at + k] = run;
-      run += v[k];
+    for (int u = 0; u < kBurst; ++u) {
+      if (live && t + u < hi) counts[(t + u) * digits + d] = run;
+      run += v[u];
     }
   }
-  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-template <typename K, typename V, bool kValues, int ITEMS>
-__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
+template <typename K, typename V, bool kValues, int ITEMS, int BITS>
+__global__ __launch_bounds__(kSortThreads, 4) void radix_scatter_kernel(
     const K* __restrict__ keys, const V* __restrict__ vals, K* __restrict__ keys_out,
-    V* __restrict__ vals_out, int64_t n, K limit, int shift, uint32_t mask, int64_t num_tiles,
+    V* __restrict__ vals_out, int64_t n, K limit, int shift, uint32_t mask, int64_t num_tiles, int64_t tiles_per_xcd,
     const uint32_t* __restrict__ counts, const uint32_t* __restrict__ totals) {
   constexpr int kTile = kSortThreads * ITEMS;
-  // the tile in digit order: its keys, then its values
+  constexpr int kD = 1 << BITS;
+  constexpr int kOwn = kD > kSortThreads ? kD / kSortThreads : 1;       // consecutive digits per lane
+  static_assert(kTile <= 65535, "places in a tile have 16 bits");
+  // the tile in digit order: its keys, then its values; before that the waves' counters of the digits
   constexpr size_t kRecord = kValues && sizeof(V) > sizeof(K) ? sizeof(V) : sizeof(K);
-  __shared__ __align__(16) unsigned char stage_bytes[kTile * kRecord];
-  K* stage = reinterpret_cast<K*>(stage_bytes);
-  __shared__ uint32_t wave_count[kSortWaves][kDigits];
-  __shared__ uint32_t tile_start[kDigits];            // first place of a digit in the tile
-  __shared__ uint32_t out_start[kDigits];             // first place of the tile's run of a digit in the output, minus tile_start
-  __shared__ uint32_t part[2][kDigits / 64];
+  constexpr size_t kCounters = sizeof(uint16_t) * kSortWaves * kD;
+  constexpr size_t kBytes = kTile * kRecord > kCounters ? kTile * kRecord : kCounters;
+  __shared__ __align__(16) unsigned char bytes[kBytes];
+  __shared__ uint32_t out_start[kD];                  // first place of the tile's run of a digit in the output, minus its place in the tile
+  __shared__ uint32_t part[2][kSortWaves];
+  uint32_t* pairs = reinterpret_cast<uint32_t*>(bytes);            // two counters each
+  uint16_t* wave_count = reinterpret_cast<uint16_t*>(bytes);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t* flat = &wave_count[0][0];
-  for (int i = tid; i < kSortWaves * kDigits; i += kSortThreads) flat[i] = 0u;
-  const int64_t base = (int64_t)blockIdx.x * kTile;
+  const int64_t tile = sort_tile(tiles_per_xcd);
+  if (tile >= num_tiles) return;
+  for (int i = tid; i < kSortWaves * kD / 2; i += kSortThreads) pairs[i] = 0u;
+  const int64_t base = tile * kTile;
   const int64_t first = base + (int64_t)wave * (64 * ITEMS) + lane;
   const int live = (int)min((int64_t)kTile, n - base);
   K key[ITEMS];
@@ -245,7 +271,13 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   for (int c = 0; c < ITEMS; ++c) {
     const int64_t i = first + c * 64;
     key[c] = (i < n) ? keys[i] : (K)0;
-    if (kValues && i < n) val[c] = vals[i];
+  }
+  uint32_t below_all[kOwn], below_tile[kOwn];
+#pragma unroll
+  for (int o = 0; o < kOwn; ++o) {
+    const uint32_t d = (uint32_t)(tid * kOwn + o);
+    below_all[o] = d <= mask ? totals[d] : 0u;
+    below_tile[o] = d <= mask ? counts[tile * (mask + 1u) + d] : 0u;
   }
   __syncthreads();
   // rank of every record among the wave's records of its digit, in index order
@@ -255,50 +287,65 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     const uint32_t d = digit_of(key[c], limit, shift, mask);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < kDigitBits; ++b) {
+    for (int b = 0; b < BITS; ++b) {
       const bool one = (d >> b) & 1u;
       const uint64_t vote = __ballot(one);
       peers &= one ? vote : ~vote;
     }
     const int leader = peers != 0ull ? __ffsll((unsigned long long)peers) - 1 : lane;
+    const int half = 16 * (int)(d & 1u);
     uint32_t before = 0;
-    if (valid && lane == leader) before = atomicAdd(&wave_count[wave][d], (uint32_t)__popcll(peers));
-    before = __shfl(before, leader, 64);
+    if (valid && lane == leader) before = atomicAdd(&pairs[(wave * kD + d) >> 1], (uint32_t)__popcll(peers) << half) >> half;
+    before = __shfl(before, leader, 64) & 0xffffu;
     rank[c] = before + (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
   }
   __syncthreads();
-  // per digit: the waves' counts become offsets inside the digit's run; digit runs follow each other
-  if (tid < kDigits) {
-    uint32_t run = 0;
+  // per digit: the waves' counts become places in the tile; digit runs follow each other, in the tile and in the output
+  const bool owns = tid * kOwn < kD;
+  uint32_t own = 0, all = 0;
+  if (owns) {
 #pragma unroll
-    for (int w = 0; w < kSortWaves; ++w) {
-      const uint32_t mine = wave_count[w][tid];
-      wave_count[w][tid] = run;
-      run += mine;
+    for (int o = 0; o < kOwn; ++o) {
+      all += below_all[o];
+#pragma unroll
+      for (int w = 0; w < kSortWaves; ++w) own += wave_count[w * kD + tid * kOwn + o];
     }
-    const uint32_t all = ((uint32_t)tid <= mask) ? totals[tid] : 0u;
-    const uint32_t incl = wave_inclusive(run, lane), incl_all = wave_inclusive(all, lane);
-    if (lane == 63) { part[0][wave] = incl; part[1][wave] = incl_all; }
-    tile_start[tid] = incl - run;
-    out_start[tid] = incl_all - all + (((uint32_t)tid <= mask) ? counts[(int64_t)tid * num_tiles + blockIdx.x] : 0u);
+  }
+  const uint32_t incl = wave_inclusive(own, lane), incl_all = wave_inclusive(all, lane);
+  if (lane == 63) { part[0][wave] = incl; part[1][wave] = incl_all; }
+  __syncthreads();
+  if (owns) {
+    uint32_t run = incl - own, run_all = incl_all - all;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w)
+      if (w < wave) { run += part[0][w]; run_all += part[1][w]; }
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+      out_start[tid * kOwn + o] = run_all + below_tile[o] - run;
+      run_all += below_all[o];
+#pragma unroll
+      for (int w = 0; w < kSortWaves; ++w) {
+        const int at = w * kD + tid * kOwn + o;
+        const uint32_t mine = wave_count[at];
+        wave_count[at] = (uint16_t)run;
+        run += mine;
+      }
+    }
   }
   __syncthreads();
-  if (tid < kDigits) {
-    uint32_t a = 0, b = 0;
 #pragma unroll
-    for (int w = 0; w < kDigits / 64; ++w)
-      if (w < wave) { a += part[0][w]; b += part[1][w]; }
-    const uint32_t start = tile_start[tid] + a;
-    tile_start[tid] = start;
-    out_start[tid] += b - start;
-  }
+  for (int c = 0; c < ITEMS; ++c) rank[c] += wave_count[wave * kD + digit_of(key[c], limit, shift, mask)];
   __syncthreads();
+  K* stage = reinterpret_cast<K*>(bytes);
 #pragma unroll
-  for (int c = 0; c < ITEMS; ++c) {
-    const uint32_t d = digit_of(key[c], limit, shift, mask);
-    rank[c] += tile_start[d] + wave_count[wave][d];
+  for (int c = 0; c < ITEMS; ++c)
     if (first + c * 64 < n) stage[rank[c]] = key[c];
-  }
+  if constexpr (kValues)
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) {
+      const int64_t i = first + c * 64;
+      if (i < n) val[c] = vals[i];
+    }
   __syncthreads();
   uint32_t dest[ITEMS];
 #pragma unroll
@@ -310,8 +357,8 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
       keys_out[dest[c]] = k;
     }
   }
-  if (kValues) {
-    V* vstage = reinterpret_cast<V*>(stage_bytes);
+  if constexpr (kValues) {
+    V* vstage = reinterpret_cast<V*>(bytes);
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c)
@@ -325,70 +372,100 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   }
 }
 
-template <typename K, typename V, bool kValues, int ITEMS>
+template <typename K, typename V, bool kValues, int ITEMS, int BITS>
 static int32_t radix_pass(const K* keys, const V* vals, K* keys_out, V* vals_out, int64_t n, K limit,
                           int shift, int bits, uint32_t* counts, uint32_t* totals, hipStream_t stream) {
-  const int64_t tiles = ceil_div(n, kSortThreads * ITEMS);
+  const int64_t tiles = ceil_div(n, kSortThreads * ITEMS), per_xcd = ceil_div(tiles, 8);
   const uint32_t mask = (1u << bits) - 1u;
-  radix_count_kernel<K, ITEMS><<<(unsigned)tiles, kSortThreads, 0, stream>>>(keys, n, limit, shift, mask, tiles, counts);
+  radix_count_kernel<K, ITEMS, BITS><<<(unsigned)tiles, kSortThreads, 0, stream>>>(keys, n, limit, shift, mask, counts);
   GS_LAUNCH_CHECK();
-  radix_scan_kernel<<<1u << bits, 256, 0, stream>>>(counts, tiles, totals);
+  radix_scan_kernel<<<(unsigned)ceil_div(mask + 1, kScanDigits), 1024, 0, stream>>>(counts, tiles, mask + 1u, totals);
   GS_LAUNCH_CHECK();
-  radix_scatter_kernel<K, V, kValues, ITEMS><<<(unsigned)tiles, kSortThreads, 0, stream>>>(
-      keys, vals, keys_out, vals_out, n, limit, shift, mask, tiles, counts, totals);
+  radix_scatter_kernel<K, V, kValues, ITEMS, BITS><<<(unsigned)(8 * per_xcd), kSortThreads, 0, stream>>>(
+      keys, vals, keys_out, vals_out, n, limit, shift, mask, tiles, per_xcd, counts, totals);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
 
-// Records per lane: a tile of 8192 records makes runs of 32 records per digit on average (256 bytes
-// of 8-byte keys); while that leaves compute units without a tile (256 of them, so below 2^21
-// records), tiles of 2048.
-constexpr int kSortItemsLarge = 16, kSortItemsSmall = 4;
-constexpr int64_t kSortLarge = (int64_t)1 << 21;
+// Digits of up to 10 bits, that is, as few passes as those take, all of about the same width; of up to 8 for few records, which the
+// narrower count table of their one or two tiles serves as well, and where the caller's scratch memory holds no more.
+constexpr int kWideBits = 10, kNarrowBits = 8;
+constexpr int64_t kWideMin = (int64_t)1 << 13;
+// Records per lane.  Long runs per digit want large tiles, which leave compute units idle while there are few records.  Whole sorts, us, with
+// 4 / 8 / 16: 20-bit keys of 4 + 8 bytes, 0.7 M records 42 / 45 / 59, 1.5 M 57 / 56 / 64, 3 M 87 / 74 / 82, 5 M 126 / 110 / 117, 8 M
+// 201 / 175 / 152; 40-bit keys of 8 + 4 bytes 89 / 91 / 119, 111 / 107 / 122, 171 / 159 / 162, 242 / 229 / 213, 370 / 325 / 302.
+constexpr int64_t kMidTiles = (int64_t)3 << 19, kLargeTiles = (int64_t)5 << 20;
+constexpr int64_t kLargeTilesNarrow = (int64_t)1 << 21;
 
-// (never less than a shorter sort takes: a caller's workspace for its largest batch serves every batch)
-size_t radix_sort_scratch_bytes(int64_t n) {
-  const int64_t small = std::max((int64_t)1, std::min(n, kSortLarge - 1));
-  const size_t tiles = (size_t)std::max(ceil_div(small, kSortThreads * kSortItemsSmall),
-                                   n >= kSortLarge ? ceil_div(n, kSortThreads * kSortItemsLarge) : (int64_t)0);
-  return align_up(tiles * kDigits * sizeof(uint32_t)) + align_up(kDigits * sizeof(uint32_t));
+static SortPlan sort_plan_of(int64_t n, int nbits, bool wide) {
+  SortPlan p;
+  const int most = wide ? kWideBits : kNarrowBits;
+  p.passes = (nbits + most - 1) / most;
+  p.width = (nbits + p.passes - 1) / p.passes;
+  if (wide) p.items = n >= kLargeTiles ? 16 : (n >= kMidTiles ? 8 : 4);
+  else p.items = n >= kLargeTilesNarrow ? 16 : 4;
+  return p;
+}
+static size_t sort_scratch(int64_t n, const SortPlan& p) {
+  return align_up((size_t)ceil_div(std::max((int64_t)1, n), kSortThreads * p.items) * sizeof(uint32_t) << p.width) +
+         align_up(sizeof(uint32_t) << p.width);
 }
 
-int radix_sort_passes(int nbits) { return (nbits + kDigitBits - 1) / kDigitBits; }
+// (for any width of keys; never less than a shorter sort takes: a caller's workspace for its largest batch serves every batch)
+size_t radix_sort_scratch_bytes(int64_t n, bool wide) {
+  size_t bytes = 0;
+  for (const int64_t border : {kWideMin, kMidTiles, kLargeTiles, kLargeTilesNarrow, n + 1}) {
+    const int64_t m = std::min(n, border - 1);
+    const bool w = wide && m >= kWideMin;
+    bytes = std::max(bytes, sort_scratch(m, sort_plan_of(m, w ? kWideBits : kNarrowBits, w)));
+  }
+  return bytes;
+}
+
+SortPlan radix_sort_plan(int64_t n, int nbits, size_t scratch_bytes) {
+  const SortPlan wide = sort_plan_of(n, nbits, true);
+  return n >= kWideMin && sort_scratch(n, wide) <= scratch_bytes ? wide : sort_plan_of(n, nbits, false);
+}
+
+template <typename K, typename V, bool kValues, int ITEMS>
+static int32_t radix_pass_of(int bits, const K* keys, const V* vals, K* keys_out, V* vals_out, int64_t n, K limit,
+                             int shift, uint32_t* counts, uint32_t* totals, hipStream_t stream) {
+  if (bits <= kNarrowBits)
+    return radix_pass<K, V, kValues, ITEMS, kNarrowBits>(keys, vals, keys_out, vals_out, n, limit, shift, bits, counts, totals, stream);
+  return radix_pass<K, V, kValues, ITEMS, kWideBits>(keys, vals, keys_out, vals_out, n, limit, shift, bits, counts, totals, stream);
+}
 
 template <typename K, typename V>
-int32_t radix_sort(const K* keys_in, const V* vals_in, K* keys_out, V* vals_out, K* keys_alt, V* vals_alt, int64_t n,
-                   K limit, int nbits, void* scratch, hipStream_t stream) {
+int32_t radix_sort(const SortPlan& plan, const K* keys_in, const V* vals_in, K* keys_out, V* vals_out, K* keys_alt, V* vals_alt,
+                   int64_t n, K limit, int nbits, void* scratch, hipStream_t stream) {
   if (n <= 0) return GS_OK;
   if (n > (int64_t)UINT32_MAX) return GS_EOVERFLOW;      // (places are 32-bit)
-  const bool large = n >= kSortLarge;
   Carver cv(scratch);
-  const int64_t tile = kSortThreads * (large ? kSortItemsLarge : kSortItemsSmall);
-  uint32_t* counts = cv.take<uint32_t>((size_t)ceil_div(n, tile) * kDigits);
-  uint32_t* totals = cv.take<uint32_t>(kDigits);
-  auto pass = vals_in != nullptr ? (large ? radix_pass<K, V, true, kSortItemsLarge> : radix_pass<K, V, true, kSortItemsSmall>)
-                                 : (large ? radix_pass<K, V, false, kSortItemsLarge> : radix_pass<K, V, false, kSortItemsSmall>);
-  const int passes = radix_sort_passes(nbits);
-  const int width = (nbits + passes - 1) / passes;
+  uint32_t* counts = cv.take<uint32_t>((size_t)ceil_div(n, kSortThreads * plan.items) << plan.width);
+  uint32_t* totals = cv.take<uint32_t>((size_t)1 << plan.width);
+  auto pass = radix_pass_of<K, V, true, 4>;
+  if (vals_in != nullptr) pass = plan.items == 16 ? radix_pass_of<K, V, true, 16> : (plan.items == 8 ? radix_pass_of<K, V, true, 8> : pass);
+  else pass = plan.items == 16 ? radix_pass_of<K, V, false, 16> : (plan.items == 8 ? radix_pass_of<K, V, false, 8> : radix_pass_of<K, V, false, 4>);
   const K* k_from = keys_in;
   const V* v_from = vals_in;
-  for (int p = 0; p < passes; ++p) {
-    const bool to_alt = (passes - 1 - p) & 1;              // the last pass ends in the output
+  for (int p = 0; p < plan.passes; ++p) {
+    const bool to_alt = (plan.passes - 1 - p) & 1;         // the last pass ends in the output
     K* k_to = to_alt ? keys_alt : keys_out;
     V* v_to = to_alt ? vals_alt : vals_out;
-    const int32_t rc = pass(k_from, v_from, k_to, v_to, n, limit, p * width, std::min(width, nbits - p * width), counts,
-                            totals, stream);
+    const int32_t rc = pass(std::min(plan.width, nbits - p * plan.width), k_from, v_from, k_to, v_to, n, limit, p * plan.width,
+                            counts, totals, stream);
     if (rc != GS_OK) return rc;
     k_from = k_to;
     v_from = v_to;
   }
   return GS_OK;
 }
-template int32_t radix_sort(const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*, int64_t,
+template int32_t radix_sort(const SortPlan&, const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*, int64_t,
                             uint32_t, int, void*, hipStream_t);
-template int32_t radix_sort(const uint32_t*, const uint2*, uint32_t*, uint2*, uint32_t*, uint2*, int64_t, uint32_t,
+template int32_t radix_sort(const SortPlan&, const uint32_t*, const uint2*, uint32_t*, uint2*, uint32_t*, uint2*, int64_t, uint32_t,
                             int, void*, hipStream_t);
-template int32_t radix_sort(const uint64_t*, const uint32_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*, int64_t,
+template int32_t radix_sort(const SortPlan&, const uint64_t*, const uint32_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*, int64_t,
                             uint64_t, int, void*, hipStream_t);
+
 
 }  // namespace gs

@@ -1835,6 +1835,7 @@ struct SgnsPlan {
   uint32_t* term_key[2] = {nullptr, nullptr};      // [0] holds the sorted ones
   uint2* term_src[2] = {nullptr, nullptr};
   void* sort_scratch = nullptr;
+  size_t sort_bytes = 0;
   int64_t stage_base = 0, stage_long_base = 0;
   size_t bytes;
 };
@@ -1927,7 +1928,8 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
     p.term_key[i] = cv.take<uint32_t>(terms);
     p.term_src[i] = cv.take<uint2>(terms);
   }
-  p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)terms));
+  p.sort_bytes = radix_sort_scratch_bytes((int64_t)terms, true);
+  p.sort_scratch = cv.take<char>(p.sort_bytes);
   p.cnt = cv.take<uint32_t>((size_t)p.cnt_last + 1 + 3);                   // cleared 16 bytes at a time
   p.key_table = p.table_places > 0 ? cv.take<uint32_t>((size_t)p.table_places) : nullptr;
   p.tile_sums = cv.take<uint32_t>((size_t)ceil_div(p.cnt_last + 1, kScanTile));
@@ -1942,7 +1944,7 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
 }
 static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
   const int64_t terms = num_pairs * (int64_t)(k + 1);
-  if (radix_sort_passes(bits_for_rows(num_nodes)) <= 2) return terms >= (k >= 2 ? kSortedMinTermsTwoPasses : 2 * kSortedMinTermsTwoPasses);
+  if (bits_for_rows(num_nodes) <= 16) return terms >= (k >= 2 ? kSortedMinTermsTwoPasses : 2 * kSortedMinTermsTwoPasses);
   return terms >= (num_nodes <= kSortedFewRows ? kSortedMinTermsFewRows : kSortedMinTerms);
 }
 
@@ -2161,7 +2163,8 @@ template <typename T, int VPL, int RB>
 static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStream_t stream) {
   SgnsArgs a = unsorted;
   const int bits = bits_for_rows(a.num_nodes);
-  const int made = radix_sort_passes(bits) & 1;              // the passes end in buffer 0
+  const SortPlan sort = radix_sort_plan(a.num_terms, bits, p.sort_bytes);
+  const int made = sort.passes & 1;                          // the passes end in buffer 0
   a.term_key = p.term_key[made];
   a.term_src = p.term_src[made];
   int32_t rc = launch_clear(a, stream);
@@ -2172,7 +2175,7 @@ static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStr
   if (rc != GS_OK) return rc;
   sgns_place_kernel<<<(unsigned)ceil_div(a.num_pairs, 256), 256, 0, stream>>>(a, a.num_terms);
   GS_LAUNCH_CHECK();
-  rc = radix_sort(a.term_key, a.term_src, p.term_key[0], p.term_src[0], p.term_key[1], p.term_src[1], a.num_terms,
+  rc = radix_sort(sort, a.term_key, a.term_src, p.term_key[0], p.term_src[0], p.term_key[1], p.term_src[1], a.num_terms,
                   ~0u, bits, p.sort_scratch, stream);
   if (rc != GS_OK) return rc;
   a.term_key = p.term_key[0];

@@ -314,7 +314,8 @@ struct UniquePlan {
   uint32_t *keys, *keys_alt;
   uint32_t *index, *index_alt;
   int64_t *head, *scan_scratch;
-  void* sort_scratch;
+  void* sort_scratch;            // (in the place of head, which is written when the ids are sorted)
+  size_t sort_bytes;
   size_t bytes;
 };
 
@@ -326,9 +327,10 @@ UniquePlan plan_unique(void* ws, int64_t n) {
   p.keys_alt = cv.take<uint32_t>(m);
   p.index = cv.take<uint32_t>(m);
   p.index_alt = cv.take<uint32_t>(m);
-  p.head = cv.take<int64_t>(m);
+  p.sort_bytes = std::max(m * sizeof(int64_t), radix_sort_scratch_bytes((int64_t)m, true));
+  p.sort_scratch = cv.take<char>(p.sort_bytes);
+  p.head = static_cast<int64_t*>(p.sort_scratch);
   p.scan_scratch = cv.take<int64_t>(scan_scratch_elems((int64_t)m));
-  p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)m));
   p.bytes = cv.used;
   return p;
 }
@@ -336,16 +338,18 @@ UniquePlan plan_unique(void* ws, int64_t n) {
 struct SortPairsPlan {
   uint32_t *keys_alt, *vals_alt;
   void* sort_scratch;
+  size_t before_sort;            // bytes in front of the sort's scratch memory, which comes last
   size_t bytes;
 };
 
-SortPairsPlan plan_sort_pairs(void* ws, int64_t n) {
+SortPairsPlan plan_sort_pairs(void* ws, int64_t n, bool wide) {
   Carver cv(ws);
   SortPairsPlan p;
   const size_t m = (size_t)(n > 0 ? n : 1);
   p.keys_alt = cv.take<uint32_t>(m);
   p.vals_alt = cv.take<uint32_t>(m);
-  p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)m));
+  p.before_sort = cv.used;
+  p.sort_scratch = cv.take<char>(radix_sort_scratch_bytes((int64_t)m, wide));
   p.bytes = cv.used;
   return p;
 }
@@ -428,10 +432,11 @@ extern "C" int32_t gs_unique_ids(const int32_t* ids, int64_t n, int64_t num_node
   const unsigned blocks = (unsigned)ceil_div(n, 256);
   if (n > 0) {
     const int nbits = bits_for((uint64_t)num_nodes);
-    uint32_t* index = (radix_sort_passes(nbits) & 1) ? p.index_alt : p.index;
+    const SortPlan sort = radix_sort_plan(n, nbits, p.sort_bytes);
+    uint32_t* index = (sort.passes & 1) ? p.index_alt : p.index;
     index_kernel<<<blocks, 256, 0, stream>>>(n, index);
     GS_LAUNCH_CHECK();
-    const int32_t rc = radix_sort<uint32_t>(reinterpret_cast<const uint32_t*>(ids), index, p.keys, p.index, p.keys_alt,
+    const int32_t rc = radix_sort<uint32_t>(sort, reinterpret_cast<const uint32_t*>(ids), index, p.keys, p.index, p.keys_alt,
                                             p.index_alt, n, (uint32_t)num_nodes, nbits, p.sort_scratch, stream);
     if (rc != GS_OK) return rc;
     unique_heads_kernel<<<blocks, 256, 0, stream>>>(p.keys, n, num_nodes, p.head);
@@ -531,7 +536,7 @@ extern "C" int32_t gs_table_mult_add(void* dst, const void* src, int64_t num_nod
 
 extern "C" size_t gs_sort_pairs_workspace_bytes(int64_t n) {
   if (n < 0) return 0;
-  return plan_sort_pairs(nullptr, n).bytes;
+  return plan_sort_pairs(nullptr, n, true).bytes;
 }
 
 extern "C" int32_t gs_sort_pairs(const int32_t* centers, const int32_t* contexts, int64_t n,
@@ -543,12 +548,12 @@ extern "C" int32_t gs_sort_pairs(const int32_t* centers, const int32_t* contexts
   if (n > 0 && (!centers || !contexts || !centers_out || !contexts_out)) return GS_EINVAL;
   if (n > 0 && (centers_out == centers || contexts_out == contexts)) return GS_EINVAL;
   if (!ws || !aligned(ws, 256)) return GS_EINVAL;
-  SortPairsPlan p = plan_sort_pairs(ws, n);
+  const SortPairsPlan p = plan_sort_pairs(ws, n, false);
   if (ws_bytes < p.bytes) return GS_EWORKSPACE;
   if (n == 0) return GS_OK;
   // the pair itself is the record: a source id that is not a row sorts as num_nodes, i.e. last
-  return radix_sort<uint32_t>(reinterpret_cast<const uint32_t*>(centers), reinterpret_cast<const uint32_t*>(contexts),
+  const int nbits = bits_for((uint64_t)num_nodes);
+  return radix_sort<uint32_t>(radix_sort_plan(n, nbits, ws_bytes - p.before_sort), reinterpret_cast<const uint32_t*>(centers), reinterpret_cast<const uint32_t*>(contexts),
                               reinterpret_cast<uint32_t*>(centers_out), reinterpret_cast<uint32_t*>(contexts_out),
-                              p.keys_alt, p.vals_alt, n, (uint32_t)num_nodes, bits_for((uint64_t)num_nodes),
-                              p.sort_scratch, stream);
+                              p.keys_alt, p.vals_alt, n, (uint32_t)num_nodes, nbits, p.sort_scratch, stream);
 }

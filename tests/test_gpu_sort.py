@@ -36,6 +36,25 @@ def test_sort_pairs_sizes(gs, n, num_nodes):
     np.testing.assert_array_equal(got_c.cpu().numpy(), c[at])
 
 
+@pytest.mark.parametrize("n", [8191, 8192, (3 << 19) - 1, (3 << 19) + 4095, (5 << 20) - 1, (5 << 20) + 1])
+@pytest.mark.parametrize("num_nodes", [(1 << 18) - 1, (1 << 20) - 1])                # two passes of 9 and of 10 bits
+def test_sort_pairs_in_wide_digits(gs, n, num_nodes):
+    """Both sides of every size of tile, and digits of 8 bits where the workspace leaves room for no more."""
+    rng = np.random.default_rng(n + num_nodes)
+    c = rng.integers(0, num_nodes, n).astype(np.int32)
+    c[rng.integers(0, n, n // 3)] = c[0]
+    c[rng.integers(0, n, n // 50)] = num_nodes + 3
+    o = np.arange(n, dtype=np.int32)
+    at = np.argsort(np.minimum(c, num_nodes), kind="stable")
+    size = gs.gs_sort_pairs_workspace_bytes(n)
+    tiles = max(min(n, (1 << 21) - 1) // 2048, n // 8192) + 1
+    narrow = 2 * (-(-4 * n // 256) * 256) + 1024 * tiles + 1024
+    for room in {size, min(size, narrow)}:
+        got_c, got_o = gs.gs_sort_pairs(_t(c), _t(o), num_nodes, ws=torch.empty(room, dtype=torch.uint8, device=DEV))
+        np.testing.assert_array_equal(got_o.cpu().numpy(), o[at])
+        np.testing.assert_array_equal(got_c.cpu().numpy(), c[at])
+
+
 @pytest.mark.parametrize("m,num_nodes", [(1, 1), (1023, 9), (1024, 300), (40_000, 5000), (40_001, 70_000),
                                          ((1 << 20) + 17, 3_000_000)])     # 1, 2, 3, 4, 5 and 6 passes
 @pytest.mark.parametrize("weighted", [False, True])
