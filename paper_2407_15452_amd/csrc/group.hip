@@ -1,0 +1,590 @@
+// Grouping of the terms of a large training batch by their row (see sgns.hip): records into the order of their
+// rows, the records of a row in any order.
+//
+// Without stability one pass over memory and one over LDS do what three passes of the radix sort do.  The records are brought into
+// a few thousand buckets of consecutive rows (count, prefix sums, scatter; a record's rank in its tile is an LDS atomic's answer), and a
+// bucket, of about 6000 records where there are many, fits the registers and the LDS of a workgroup, which counts its
+// rows and puts it in order.  12 million records on 4 M rows take 175 us (count 20, prefix sums 14, scatter 76, buckets 62)
+// against 296 for the stable sort in three passes; 2.4 million 46 (79 in two), 1.6 million 41 (57).
+//
+// Two kinds of rows are grouped together: rows of the first kind come as records (row; 8 bytes), rows of the second kind as a list of
+// rows with gaps (-1: no record), whose 8 bytes are the place in the list and a constant.  The gaps are left out on the way, so the number of
+// records of the second kind need not be known to the host.
+//
+// Buckets of more records than a workgroup takes (a single row may have any number) are split: the prefix sums enter them in a list,
+// in pieces, the bucket kernel adds up the counts of their rows in global memory, and one more launch, which otherwise looks at the length of
+// the list and returns, moves their records.  All 12 million records in one row: 0.32 ms.
+#include "group.h"
+
+namespace gs {
+
+constexpr int kBucketThreads = 1024, kBucketWaves = kBucketThreads / 64;
+constexpr int kBucketItems = 9, kBucketItemsMost = 16;         // records per lane: two workgroups, or one, share a compute unit's LDS
+constexpr int kBucketRowBits = 14;             // rows of a bucket: their counters fit a workgroup's LDS
+constexpr int64_t kBuckets = 2048, kSecondBuckets = 1024;      // most buckets of either kind of rows
+// Records per bucket, which leave a bucket of 9216 room for uneven rows; fewer where that keeps compute units busy.
+constexpr int64_t kBucketMean = 6000, kBucketMeanLeast = 1024, kBusyBuckets = 256, kBucketMeanMost = 7000;
+constexpr int kSplitBlocks = 256;
+// Records of a tile.  us with 2048 / 4096 / 8192: 0.8 M records 35.9 / 36.9 / 41.2, 1.6 M 40.6 / 40.7 / 42.4, 2.4 M 54 / 50 / 54, 3 M
+// 65 / 60 / 62, 6 M 108 / 97 / 90; 16,384 instead of 8192 (half the counts): prefix sums of 12 million records 23 -> 15, the scatter the same
+constexpr int64_t kMidTiles = (int64_t)3 << 19, kLargeTiles = (int64_t)1 << 22, kLargestTiles = (int64_t)1 << 23;
+
+// inclusive prefix sum over the lanes of a wave
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, int lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t up = __shfl_up(v, d, 64);
+    if (lane >= d) v += up;
+  }
+  return v;
+}
+
+// ---- into the buckets -----------------------------------------------------------------------
+// Tiles [0, first_tiles) hold records of the first kind, the others entries of the list of the second kind.
+struct TileOf {
+  bool second;
+  int64_t base;                  // first record, or first entry of the list
+  int live;                      // records or entries
+  int row_bits;
+  uint32_t digits;               // buckets of the kind
+  uint32_t* counts;              // of the tile, per bucket
+  uint32_t *totals, *starts;     // of the kind, per bucket: records, and the first of them in the result
+};
+__device__ __forceinline__ TileOf tile_of(const GroupArgs& a, int64_t tile, int size) {
+  TileOf t;
+  t.second = tile >= a.first_tiles;
+  t.base = (t.second ? tile - a.first_tiles : tile) * size;
+  t.live = (int)min((int64_t)size, (t.second ? a.second_n : a.n) - t.base);
+  t.row_bits = t.second ? a.second_row_bits : a.row_bits;
+  t.digits = t.second ? a.digits - a.buckets : a.buckets;
+  t.counts = a.counts + (t.second ? a.first_tiles * a.buckets + (tile - a.first_tiles) * t.digits : tile * t.digits);
+  t.totals = a.totals + (t.second ? a.buckets : 0u);
+  t.starts = a.starts + (t.second ? a.buckets : 0u);
+  return t;
+}
+
+template <int kTileThreads, int ITEMS, int DIGITS>
+__global__ __launch_bounds__(kTileThreads) void group_count_kernel(GroupArgs a) {
+  constexpr int kCopies = DIGITS <= 256 ? 4 : 2;          // (the waves share them)
+  __shared__ uint32_t hist[kCopies][DIGITS];
+  uint32_t* flat = &hist[0][0];
+  for (int i = threadIdx.x; i < kCopies * DIGITS; i += kTileThreads) flat[i] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x < kGroupCounters) a.counters[threadIdx.x] = 0u;
+  const TileOf t = tile_of(a, blockIdx.x, kTileThreads * ITEMS);
+  const uint32_t* rows = t.second ? reinterpret_cast<const uint32_t*>(a.second) : a.rows;
+  uint32_t row[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int i = c * kTileThreads + threadIdx.x;
+    row[c] = i < t.live ? rows[t.base + i] : kNoGroupRow;
+  }
+  __syncthreads();
+  uint32_t* mine = hist[(threadIdx.x >> 6) % kCopies];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (row[c] != kNoGroupRow) atomicAdd(&mine[row[c] >> t.row_bits], 1u);
+  __syncthreads();
+  for (uint32_t d = threadIdx.x; d < t.digits; d += kTileThreads) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int w = 0; w < kCopies; ++w) sum += hist[w][d];
+    t.counts[d] = sum;
+  }
+}
+
+// Exclusive prefix sums of the counts of a bucket over the tiles, and their total: a workgroup takes kScanDigits buckets, a
+// lane one bucket of a stretch of tiles.  Buckets of more than a.most records are entered in the list.
+constexpr int kScanDigits = 16, kScanStretches = 1024 / kScanDigits;
+__global__ __launch_bounds__(1024) void group_scan_kernel(GroupArgs a) {
+  __shared__ uint32_t sums[kScanStretches][kScanDigits + 1];
+  __shared__ uint32_t total_s[kScanDigits];
+  __shared__ uint32_t at_s[3];
+  const bool second = blockIdx.x >= a.first_scans;
+  const uint32_t digits = second ? a.digits - a.buckets : a.buckets, first_digit = second ? a.buckets : 0u;
+  const uint32_t d0 = (second ? blockIdx.x - a.first_scans : blockIdx.x) * kScanDigits;       // among the kind's buckets
+  const uint32_t d = d0 + (threadIdx.x & (kScanDigits - 1));
+  uint32_t* counts = a.counts + (second ? a.first_tiles * a.buckets : 0);
+  const int64_t tiles = second ? a.tiles - a.first_tiles : a.first_tiles;
+  const int s = threadIdx.x / kScanDigits;
+  const int64_t per = (tiles + kScanStretches - 1) / kScanStretches;
+  const int64_t lo = min(tiles, s * per), hi = min(tiles, lo + per);
+  const bool live = d < digits;
+  constexpr int kBurst = 8;
+  uint32_t v[kBurst];
+  auto load = [&](int64_t t) {
+#pragma unroll
+    for (int u = 0; u < kBurst; ++u) v[u] = (live && t + u < hi) ? counts[(t + u) * digits + d] : 0u;
+  };
+  uint32_t sum = 0;
+  for (int64_t t = lo; t < hi; t += kBurst) {
+    load(t);
+#pragma unroll
+    for (int u = 0; u < kBurst; ++u) sum += v[u];
+  }
+  sums[s][threadIdx.x & (kScanDigits - 1)] = sum;
+  __syncthreads();
+  {                                              // wave w: the stretches of bucket w
+    static_assert(kScanStretches == 64 && kScanDigits == 16, "sixteen waves, a lane per stretch");
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t own = sums[lane][w];
+    const uint32_t incl = wave_inclusive(own, lane);
+    sums[lane][w] = incl - own;
+    if (lane == 63) {
+      total_s[w] = incl;
+      if (d0 + w < digits) a.totals[first_digit + d0 + w] = incl;
+    }
+  }
+  __syncthreads();
+  uint32_t run = sums[s][threadIdx.x & (kScanDigits - 1)];
+  for (int64_t t = lo; t < hi; t += kBurst) {
+    if (per > kBurst) load(t);                   // (else still there)
+#pragma unroll
+    for (int u = 0; u < kBurst; ++u) {
+      if (live && t + u < hi) counts[(t + u) * digits + d] = run;
+      run += v[u];
+    }
+  }
+  for (int w = 0; w < kScanDigits; ++w) {        // (buckets behind the last have no records)
+    const uint32_t total = total_s[w];
+    if (total <= a.most) continue;
+    const uint32_t pieces = (total + a.most - 1) / a.most, bucket = first_digit + d0 + (uint32_t)w;
+    const uint32_t rows = 1u << (second ? a.second_row_bits : a.row_bits);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      at_s[0] = atomicAdd(a.counters + kGroupPieces, pieces);
+      at_s[1] = atomicAdd(a.counters + kGroupSplitRows, rows);
+      at_s[2] = atomicAdd(a.counters + kGroupSplit, 1u);
+      a.pieces_left[at_s[2]] = pieces;
+    }
+    __syncthreads();
+    const uint32_t first = at_s[0], rows_at = at_s[1], number = at_s[2];
+    for (uint32_t i = threadIdx.x; i < pieces; i += 1024u) a.pieces[first + i] = make_uint4(bucket, rows_at, i, number);
+    for (uint32_t r = threadIdx.x; r < rows; r += 1024u) a.row_next[rows_at + r] = 0u;
+  }
+}
+
+template <int kTileThreads, int ITEMS, int DIGITS>
+__global__ __launch_bounds__(kTileThreads, 4) void group_scatter_kernel(GroupArgs a) {
+  constexpr int kTile = kTileThreads * ITEMS, kTileWaves = kTileThreads / 64;
+  constexpr int kOwn = DIGITS > kTileThreads ? DIGITS / kTileThreads : 1;
+  constexpr size_t kBytes = kTile * sizeof(uint2) > sizeof(uint32_t) * DIGITS ? kTile * sizeof(uint2) : sizeof(uint32_t) * DIGITS;
+  __shared__ __align__(16) unsigned char bytes[kBytes];          // the buckets' counters, then the tile's rows, then its values
+  __shared__ uint32_t out_start[DIGITS];                         // first place of the tile's run of a bucket, minus its place in the tile
+  __shared__ uint32_t part[2][kTileWaves];
+  uint32_t* count = reinterpret_cast<uint32_t*>(bytes);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // each XCD (workgroups go to the 8 of them in turn) takes one contiguous eighth, so that the runs of a bucket that share a cache
+  // line meet in one L2
+  const int64_t tile = (int64_t)(blockIdx.x & 7u) * a.tiles_per_xcd + (blockIdx.x >> 3);
+  if (tile >= a.tiles) return;
+  const TileOf t = tile_of(a, tile, kTile);
+  const uint32_t* rows = (t.second ? reinterpret_cast<const uint32_t*>(a.second) : a.rows) + t.base;
+  for (int i = tid; i < DIGITS; i += kTileThreads) count[i] = 0u;
+  uint32_t row[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) row[c] = c * kTileThreads + tid < t.live ? rows[c * kTileThreads + tid] : kNoGroupRow;
+  uint32_t below_all[kOwn], below_tile[kOwn];
+#pragma unroll
+  for (int o = 0; o < kOwn; ++o) {
+    const uint32_t d = (uint32_t)(tid * kOwn + o);
+    below_all[o] = d < t.digits ? t.totals[d] : 0u;
+    below_tile[o] = d < t.digits ? t.counts[d] : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (row[c] != kNoGroupRow) rank[c] = atomicAdd(&count[row[c] >> t.row_bits], 1u);
+  __syncthreads();
+  const bool owns = tid * kOwn < DIGITS;
+  uint32_t mine[kOwn], own = 0, all = 0;
+#pragma unroll
+  for (int o = 0; o < kOwn; ++o) {
+    mine[o] = owns ? count[tid * kOwn + o] : 0u;
+    own += mine[o];
+    all += below_all[o];
+  }
+  const uint32_t incl = wave_inclusive(own, lane), incl_all = wave_inclusive(all, lane);
+  if (lane == 63) { part[0][wave] = incl; part[1][wave] = incl_all; }
+  __syncthreads();
+  int live = 0;                                                  // records of the tile
+  uint32_t run = incl - own, run_all = incl_all - all + (t.second ? (uint32_t)a.n : 0u);
+#pragma unroll
+  for (int w = 0; w < kTileWaves; ++w) {
+    live += (int)part[0][w];
+    if (w < wave) { run += part[0][w]; run_all += part[1][w]; }
+  }
+  if (owns) {
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+      count[tid * kOwn + o] = run;
+      out_start[tid * kOwn + o] = run_all + below_tile[o] - run;
+      if (t.base == 0 && (uint32_t)(tid * kOwn + o) < t.digits) t.starts[tid * kOwn + o] = run_all;
+      run += mine[o];
+      run_all += below_all[o];
+    }
+  }
+  if (tile == a.first_tiles && tid == kTileThreads - 1) a.counters[kGroupRecords] = run_all + (owns ? 0u : all);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (row[c] != kNoGroupRow) rank[c] += count[row[c] >> t.row_bits];
+  __syncthreads();
+  uint32_t* stage = reinterpret_cast<uint32_t*>(bytes);
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    if (row[c] != kNoGroupRow) stage[rank[c]] = row[c];
+    else rank[c] = kNoGroupRow;
+  }
+  uint2 val[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    if (rank[c] == kNoGroupRow) continue;
+    const int i = c * kTileThreads + tid;
+    val[c] = t.second ? make_uint2((uint32_t)(t.base + i), a.second_word) : a.vals[t.base + i];
+  }
+  __syncthreads();
+  uint32_t dest[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int at = c * kTileThreads + tid;
+    if (at < live) {
+      const uint32_t r = stage[at];
+      dest[c] = out_start[r >> t.row_bits] + (uint32_t)at;
+      a.rows_mid[dest[c]] = r;
+    }
+  }
+  uint2* vstage = reinterpret_cast<uint2*>(bytes);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (rank[c] != kNoGroupRow) vstage[rank[c]] = val[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int at = c * kTileThreads + tid;
+    if (at < live) a.vals_mid[dest[c]] = vstage[at];
+  }
+}
+
+// ---- inside the buckets ----------------------------------------------------------------------
+struct BucketOf {
+  int64_t base;                  // first record
+  int row_bits;
+  uint32_t first_row;            // of the rows of its kind
+  uint32_t key;                  // of the first row
+  uint32_t named;                // the first row's mark
+};
+__device__ __forceinline__ BucketOf bucket_of(const GroupArgs& a, uint32_t b) {
+  BucketOf o;
+  o.base = (int64_t)a.starts[b];
+  const bool second = b >= a.buckets;
+  o.row_bits = second ? a.second_row_bits : a.row_bits;
+  o.first_row = (second ? b - a.buckets : b) << o.row_bits;
+  o.key = o.first_row + (second ? a.second_key : 0u);
+  o.named = o.first_row + (second ? a.buckets << a.row_bits : 0u);
+  return o;
+}
+
+// counts of rows into exclusive prefix sums, by the whole workgroup; each(row, its count, the records before it) on the way
+template <typename Each>
+__device__ __forceinline__ void bucket_scan(uint32_t* count, int rows, uint32_t* part, Each each) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int per = max(1, rows / kBucketThreads), first = (int)threadIdx.x * per;
+  uint32_t own = 0;
+  if (first < rows)
+    for (int o = 0; o < per; ++o) own += count[first + o];
+  const uint32_t incl = wave_inclusive(own, lane);
+  if (lane == 63) part[wave] = incl;
+  __syncthreads();
+  if (first < rows) {
+    uint32_t run = incl - own;
+#pragma unroll
+    for (int w = 0; w < kBucketWaves; ++w)
+      if (w < wave) run += part[w];
+    for (int o = 0; o < per; ++o) {
+      const uint32_t c = count[first + o];
+      count[first + o] = run;
+      each(first + o, c, run);
+      run += c;
+    }
+  }
+  __syncthreads();
+}
+
+// A row of more than one segment: entered in the list of long rows.
+__device__ __forceinline__ void enter_long_row(const GroupArgs& a, uint32_t key, uint32_t slot) {
+  const uint32_t at = atomicAdd(a.counters + kGroupLong, 1u);
+  a.long_rows[at] = make_uint2(key, slot);
+}
+
+// The pieces in the list of buckets to split: the counts of their rows are added up in global memory, and who adds the last of a bucket's
+// turns them into the rows' first places.
+template <int kMost>
+__device__ __forceinline__ void count_pieces(const GroupArgs& a, uint32_t first_piece, uint32_t stride, uint32_t* count, uint32_t* part,
+                                             uint32_t* last_s) {
+  const int tid = threadIdx.x;
+  const uint32_t pieces = a.counters[kGroupPieces];
+  for (uint32_t j = first_piece; j < pieces; j += stride) {
+    const uint4 piece = a.pieces[j];
+    const BucketOf b = bucket_of(a, piece.x);
+    const int rows = 1 << b.row_bits;
+    const uint32_t* piece_rows = a.rows_mid + b.base + (int64_t)piece.z * kMost;
+    uint32_t* row_next = a.row_next + piece.y;
+    const int live = (int)min((uint32_t)kMost, a.totals[piece.x] - piece.z * (uint32_t)kMost);
+    for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < live; i += kBucketThreads) atomicAdd(&count[piece_rows[i] & (uint32_t)(rows - 1)], 1u);
+    __syncthreads();
+    for (int r = tid; r < rows; r += kBucketThreads)
+      if (count[r] != 0u) atomicAdd(row_next + r, count[r]);
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) *last_s = atomicSub(a.pieces_left + piece.w, 1u);
+    __syncthreads();
+    if (*last_s == 1u) {
+      __threadfence();
+      for (int r = tid; r < rows; r += kBucketThreads) count[r] = __hip_atomic_load(row_next + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      bucket_scan(count, rows, part, [&](int r, uint32_t c, uint32_t before) {
+        row_next[r] = before;
+        if (a.named != nullptr) a.named[b.named + r] = c != 0u ? 1 : 0;
+        if (c > 1u << a.seg_shift) {
+          const uint32_t slot = (uint32_t)((b.base + before) >> a.seg_shift);
+          enter_long_row(a, b.key + (uint32_t)r, slot);
+          for (int x = 0; x < a.dim; ++x) a.long_acc[(int64_t)slot * a.dim + x] = 0;
+        }
+      });
+    }
+    __syncthreads();
+  }
+}
+
+// A workgroup per bucket; those in the list of buckets to split are left to the workgroups behind them.
+template <int ITEMS>
+__global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void group_bucket_kernel(GroupArgs a) {
+  constexpr int kMost = kBucketThreads * ITEMS;
+  static_assert(kMost * sizeof(uint2) >= sizeof(uint32_t) << kBucketRowBits, "the counters lie where the records are put in order");
+  constexpr int kLongMost = kMost >> kGroupLeastSegment;         // rows of more than one segment in a bucket
+  __shared__ __align__(16) unsigned char bytes[kMost * sizeof(uint2)];
+  __shared__ uint32_t part[kBucketWaves];
+  __shared__ uint32_t long_s[kLongMost], long_n;
+  uint32_t* count = reinterpret_cast<uint32_t*>(bytes);
+  const int tid = threadIdx.x;
+  if (blockIdx.x >= a.digits) {
+    count_pieces<kMost>(a, blockIdx.x - a.digits, gridDim.x - a.digits, count, part, &long_n);
+    return;
+  }
+  const uint32_t total = a.totals[blockIdx.x];
+  if (total > (uint32_t)kMost) return;
+  const int live = (int)total;
+  const bool second = blockIdx.x >= a.buckets;
+  const int rows = 1 << (second ? a.second_row_bits : a.row_bits);
+  const uint32_t mask = (uint32_t)rows - 1u;
+  for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
+  if (tid == 0) long_n = 0u;
+  const BucketOf b = bucket_of(a, blockIdx.x);
+  __syncthreads();
+  if (total == 0u) {
+    if (a.named != nullptr)
+      for (int r = tid; r < rows; r += kBucketThreads) a.named[b.named + r] = 0;
+    return;
+  }
+  const uint32_t* my_rows = a.rows_mid + b.base;
+  const uint2* my_vals = a.vals_mid + b.base;
+  uint32_t* keys_to = a.keys_out + b.base;
+  uint2* vals_to = a.vals_out + b.base;
+  // a record's row in the bucket, and above it its rank in the row, then its place in the bucket
+  static_assert(kMost <= 1 << (32 - kBucketRowBits), "both fit 32 bits");
+  constexpr uint32_t kRowMask = (1u << kBucketRowBits) - 1u;
+  uint32_t at[ITEMS];
+  uint2 val[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) at[c] = my_rows[c * kBucketThreads + tid] & mask;
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) val[c] = my_vals[c * kBucketThreads + tid];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) at[c] |= atomicAdd(&count[at[c]], 1u) << kBucketRowBits;
+  __syncthreads();
+  bucket_scan(count, rows, part, [&](int r, uint32_t c, uint32_t before) {
+    if (a.named != nullptr) a.named[b.named + r] = c != 0u ? 1 : 0;
+    if (c > 1u << a.seg_shift) {
+      const uint32_t slot = (uint32_t)((b.base + before) >> a.seg_shift);
+      long_s[atomicAdd(&long_n, 1u)] = slot;
+      enter_long_row(a, b.key + (uint32_t)r, slot);
+    }
+  });
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) at[c] += count[at[c] & kRowMask] << kBucketRowBits;
+  __syncthreads();
+  uint2* vstage = reinterpret_cast<uint2*>(bytes);
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) vstage[at[c] >> kBucketRowBits] = val[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) vals_to[c * kBucketThreads + tid] = vstage[c * kBucketThreads + tid];
+  __syncthreads();
+  uint32_t* stage = reinterpret_cast<uint32_t*>(bytes);
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) stage[at[c] >> kBucketRowBits] = b.key + (at[c] & kRowMask);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c * kBucketThreads + tid < live) keys_to[c * kBucketThreads + tid] = stage[c * kBucketThreads + tid];
+  for (uint32_t l = 0; l < long_n; ++l)
+    for (int x = tid; x < a.dim; x += kBucketThreads) a.long_acc[(int64_t)long_s[l] * a.dim + x] = 0;
+}
+
+// The pieces in the list: a piece takes the next places of its rows and moves its records there.
+template <int ITEMS>
+__global__ __launch_bounds__(kBucketThreads) void group_split_kernel(GroupArgs a) {
+  constexpr int kMost = kBucketThreads * ITEMS;
+  __shared__ uint32_t count[1 << kBucketRowBits];
+  const int tid = threadIdx.x;
+  const uint32_t pieces = a.counters[kGroupPieces];
+  for (uint32_t j = blockIdx.x; j < pieces; j += gridDim.x) {
+    const uint4 piece = a.pieces[j];
+    const BucketOf b = bucket_of(a, piece.x);
+    const int rows = 1 << b.row_bits;
+    const uint32_t mask = (uint32_t)rows - 1u;
+    const int64_t base = b.base + (int64_t)piece.z * kMost;
+    const int live = (int)min((uint32_t)kMost, a.totals[piece.x] - piece.z * (uint32_t)kMost);
+    for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
+    uint32_t row[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c)
+      if (c * kBucketThreads + tid < live) row[c] = a.rows_mid[base + c * kBucketThreads + tid] & mask;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c)
+      if (c * kBucketThreads + tid < live) rank[c] = atomicAdd(&count[row[c]], 1u);
+    __syncthreads();
+    for (int r = tid; r < rows; r += kBucketThreads)
+      if (count[r] != 0u) count[r] = atomicAdd(a.row_next + piece.y + r, count[r]);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c)
+      if (c * kBucketThreads + tid < live) {
+        const int64_t at = b.base + count[row[c]] + rank[c];
+        a.keys_out[at] = b.key + row[c];
+        a.vals_out[at] = a.vals_mid[base + c * kBucketThreads + tid];
+      }
+    __syncthreads();
+  }
+}
+
+// ---- host side -------------------------------------------------------------------------------
+struct GroupPlan {
+  int row_bits, second_row_bits;
+  int64_t buckets, second_buckets;
+  int tile;                      // records of a tile
+  int bucket_items;              // records per lane of a bucket's workgroup
+  int64_t first_tiles, tiles;
+};
+
+// the fewest buckets of a power of two of rows that hold about kBucketMean records each
+static int row_bits_for(int64_t n, int64_t rows, int64_t most_buckets) {
+  const int64_t mean = std::min(kBucketMean, std::max(kBucketMeanLeast, ceil_div(n, kBusyBuckets)));
+  int bits = kBucketRowBits;
+  while (bits > 0 && ceil_div(n, ceil_div(rows, (int64_t)1 << bits)) > mean &&
+         ceil_div(rows, (int64_t)1 << (bits - 1)) <= most_buckets)
+    --bits;
+  return bits;
+}
+
+static GroupPlan plan_group(int64_t n, int64_t second_n, int64_t rows) {
+  GroupPlan p;
+  p.row_bits = row_bits_for(n, rows, kBuckets);
+  p.second_row_bits = row_bits_for(second_n, rows, kSecondBuckets);
+  p.buckets = ceil_div(rows, (int64_t)1 << p.row_bits);
+  p.second_buckets = ceil_div(rows, (int64_t)1 << p.second_row_bits);
+  p.tile = n >= kLargestTiles ? 16384 : (n >= kLargeTiles ? 8192 : (n >= kMidTiles ? 4096 : 2048));
+  p.bucket_items = ceil_div(n, p.buckets) > kBucketMeanMost ? kBucketItemsMost : kBucketItems;
+  p.first_tiles = ceil_div(n, p.tile);
+  p.tiles = p.first_tiles + ceil_div(second_n, p.tile);
+  return p;
+}
+
+bool can_group(int64_t rows) { return ceil_div(rows, (int64_t)1 << kBucketRowBits) <= kSecondBuckets; }
+
+// (no array is smaller for more records: a caller's workspace for its largest batch serves every batch)
+void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t rows, int32_t seg_shift, bool marks) {
+  const GroupPlan p = plan_group(n, second_n, rows);
+  a.digits = (uint32_t)(p.buckets + p.second_buckets);
+  size_t counts = 0;                             // (there are fewer tiles where they are larger)
+  for (const int64_t m : {n, std::min(n, kMidTiles - 1), std::min(n, kLargeTiles - 1), std::min(n, kLargestTiles - 1)}) {
+    const GroupPlan q = plan_group(m, second_n, rows);
+    counts = std::max(counts, (size_t)q.first_tiles * (size_t)q.buckets + (size_t)(q.tiles - q.first_tiles) * (size_t)q.second_buckets);
+  }
+  const size_t records = (size_t)(n + second_n);
+  const size_t split = records / (size_t)(kBucketThreads * kBucketItems) + 1;        // (each has more records than that)
+  const size_t all_rows = 2 * ((size_t)rows + ((size_t)1 << kBucketRowBits));        // of the buckets of both kinds
+  // rows of the buckets to split: of at most kBucketMean / (kBucketThreads * kBucketItems) of a kind's buckets (< 2 / 3) where there are as
+  // many buckets as their mean size wants
+  auto split_rows_of = [&](int64_t m, int64_t buckets) {
+    const size_t most = (size_t)(m / (kBucketThreads * kBucketItems) + 1) << kBucketRowBits;
+    const size_t all = (size_t)rows + ((size_t)1 << kBucketRowBits);
+    return std::min(most, ceil_div(m, buckets) > kBucketMean ? all : all / 3 * 2 + ((size_t)1 << kBucketRowBits));
+  };
+  const size_t split_rows = split_rows_of(n, p.buckets) + split_rows_of(second_n, p.second_buckets);
+  // (the marks are written when the counts have been read for the last time)
+  a.counts = cv.take<uint32_t>(marks ? std::max(counts, all_rows / sizeof(uint32_t)) : counts);
+  a.named = marks ? reinterpret_cast<uint8_t*>(a.counts) : nullptr;
+  a.totals = cv.take<uint32_t>((size_t)(kBuckets + kSecondBuckets));
+  a.starts = cv.take<uint32_t>((size_t)(kBuckets + kSecondBuckets));
+  a.counters = cv.take<uint32_t>(kGroupCounters);
+  a.pieces = cv.take<uint4>(2 * split);
+  a.pieces_left = cv.take<uint32_t>(split);
+  a.row_next = cv.take<uint32_t>(split_rows);
+  a.long_rows = cv.take<uint2>((records >> seg_shift) + 1);
+  a.second_named = (uint32_t)(p.buckets << p.row_bits);
+}
+
+template <int kTileThreads, int ITEMS, int DIGITS>
+static int32_t launch_scatter(const GroupArgs& a, hipStream_t stream) {
+  group_count_kernel<kTileThreads, ITEMS, DIGITS><<<(unsigned)a.tiles, kTileThreads, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  group_scan_kernel<<<a.first_scans + (unsigned)ceil_div(a.digits - a.buckets, kScanDigits), 1024, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  group_scatter_kernel<kTileThreads, ITEMS, DIGITS><<<(unsigned)(8 * a.tiles_per_xcd), kTileThreads, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+template <int ITEMS>
+static int32_t launch_buckets(const GroupArgs& a, hipStream_t stream) {
+  group_bucket_kernel<ITEMS><<<a.digits + kSplitBlocks, kBucketThreads, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  group_split_kernel<ITEMS><<<kSplitBlocks, kBucketThreads, 0, stream>>>(a);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+
+int32_t group_rows(GroupArgs a, int64_t rows, hipStream_t stream) {
+  const GroupPlan p = plan_group(a.n, a.second_n, rows);
+  a.row_bits = p.row_bits;
+  a.second_row_bits = p.second_row_bits;
+  a.buckets = (uint32_t)p.buckets;
+  a.first_tiles = p.first_tiles;
+  a.first_scans = (uint32_t)ceil_div(p.buckets, kScanDigits);
+  a.tiles = p.tiles;
+  a.tiles_per_xcd = ceil_div(p.tiles, 8);
+  a.most = (uint32_t)(kBucketThreads * p.bucket_items);
+  auto scatter = launch_scatter<512, 4, 256>;
+  const int64_t digits = std::max(p.buckets, p.second_buckets);
+  if (p.tile == 2048) scatter = digits <= 256 ? scatter : (digits <= 1024 ? launch_scatter<512, 4, 1024> : launch_scatter<512, 4, 2048>);
+  else if (p.tile == 4096) scatter = digits <= 256 ? launch_scatter<512, 8, 256> : (digits <= 1024 ? launch_scatter<512, 8, 1024> : launch_scatter<512, 8, 2048>);
+  else if (p.tile == 8192) scatter = digits <= 256 ? launch_scatter<512, 16, 256> : (digits <= 1024 ? launch_scatter<512, 16, 1024> : launch_scatter<512, 16, 2048>);
+  else scatter = digits <= 1024 ? launch_scatter<1024, 16, 1024> : launch_scatter<1024, 16, 2048>;
+  const int32_t rc = scatter(a, stream);
+  if (rc != GS_OK) return rc;
+  return p.bucket_items == kBucketItems ? launch_buckets<kBucketItems>(a, stream) : launch_buckets<kBucketItemsMost>(a, stream);
+}
+
+}  // namespace gs

@@ -36,7 +36,7 @@
 //              extra block sums the per-block loss partials in a fixed order
 //
 // Small batches take two launches instead (forward, and one kernel for the rest): see
-// sgns_small_update_kernel.  Large ones sort their context-table terms instead of counting and
+// sgns_small_update_kernel.  Large ones write their terms as records that are grouped by row instead of counting and
 // placing them: see sgns_sorted_update_kernel.
 //
 // delta is accumulated exactly: every product coef * element is rounded once to
@@ -61,10 +61,12 @@
 // kept, because that kernel then writes rows of the table it would read.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <type_traits>
 
 #include "common.h"
+#include "group.h"
 
 namespace gs {
 
@@ -80,6 +82,7 @@ constexpr int kStageSlice = 8;     // staged gradients per 16-lane group in the 
 // first term >> seg_shift).  Long segments keep the side-buffer traffic low; small batches take
 // short ones, so that the few waves of a launch do not wait for one that sums a long segment.
 constexpr int kSegShiftLarge = 8, kSegShiftSmall = 6;
+constexpr int kLongRowBlocks = 512;   // launch over the list of long rows
 constexpr int kScanThreads = 256;
 constexpr int kScanPerThread = 16;
 constexpr int kScanTile = kScanThreads * kScanPerThread;
@@ -196,6 +199,11 @@ struct SgnsArgs {
   int64_t stage_long_base;  // first side-buffer slot of the input-table rows
   uint32_t* term_key;       // large batches: [num_terms] row of the context table and
   uint2* term_src;          // (source row, coefficient) of every term; after the sort: in order of the rows
+  const uint32_t* num_records;   // grouped batches: records of both kinds of rows,
+  const uint2* long_rows;        // (key, side-buffer slot) of the long rows
+  const uint32_t* num_long_rows;
+  const uint8_t* named;          // optimizers on grouped batches: which rows of the context table the batch names, and from named_in on of
+  uint32_t named_in;             // the input table; else null
   long long* long_acc;      // [long_slots][dim] exact sums of the long rows
   int32_t* stage_center;    // [num_pairs], -1 = unused slot
   uint32_t* stage_rank;     // [num_pairs] rank of the slot among the slots of its centre
@@ -476,7 +484,9 @@ __global__ void sgns_clear_kernel(uint4* __restrict__ cnt4, int64_t n4, uint4* _
 }
 
 // ---- forward ------------------------------------------------------------------------------
-enum : int { kByCounter, kBySort, kInLds };
+enum : int { kByCounter, kBySort, kGrouped, kInLds };
+// whether an earlier kernel has cleared the flag of bad ids (else the block's loss partial reports them)
+constexpr bool has_flag(int group) { return group == kByCounter || group == kBySort; }
 // Staged centre-row gradient of one run of equal centres, in natural element
 // order.  Slot numbers are fixed by position (first pair of the chunk + flush
 // number), so no counter is shared between groups; unused slots of a chunk are
@@ -486,7 +496,7 @@ __device__ __forceinline__ void stage_flush(const SgnsArgs& a, int64_t slot, int
                                             const float4 (&du)[VPL]) {
   if (l16 == 0) {
     a.stage_center[slot] = center;
-    if constexpr (kGroup != kInLds) a.stage_rank[slot] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)a.num_nodes + (uint32_t)center), 1u);
+    if constexpr (has_flag(kGroup)) a.stage_rank[slot] = atomicAdd(a.cnt + claim_slot(a, (uint32_t)a.num_nodes + (uint32_t)center), 1u);
   }
   float4* out = reinterpret_cast<float4*>(a.stage_delta + slot * (int64_t)a.dim);
   const int dim4 = a.dim >> 2;
@@ -510,9 +520,10 @@ __device__ __forceinline__ float row_peak(const float4 (&r)[VPL]) {
 // kGroup: how the terms of a row come together afterwards.
 //   kByCounter  every term takes a rank from its row's counter (for the place kernel)
 //   kBySort     every term is written as a record for the sort; only staging slots are counted
-//   kInLds      the step of a small batch, whose update kernel groups the terms itself: nothing is
-//               counted, and a bad id or an out-of-range product turns the block's loss partial into
+//   kGrouped    every term is written as a record for the grouping, which takes the staging slots as well:
+//               nothing is counted, and a bad id or an out-of-range product turns the block's loss partial into
 //               NaN (there is no flag that an earlier kernel would have cleared)
+//   kInLds      the step of a small batch, whose update kernel groups the terms itself: the same
 // kWaves: waves per SIMD that the registers have to leave room for (0: no say); see launch_forward.
 template <typename T, int VPL, int RB, int kGroup, int kThreads, int kWaves = 0>
 __global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs a) {
@@ -529,13 +540,13 @@ __global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs
   __shared__ uint32_t hot_base[kGroup == kByCounter ? kHotSlots : 1];
   bool bad = false;
   auto row_of = [&](int32_t id) -> int32_t {
-    if constexpr (kGroup != kInLds) return checked_row(a, id);
+    if constexpr (has_flag(kGroup)) return checked_row(a, id);
     if ((uint32_t)id < (uint32_t)a.num_nodes) return id;
     bad = true;
     return 0;
   };
   auto report = [&]() {
-    if constexpr (kGroup != kInLds) *a.bad_ids = 1u;
+    if constexpr (has_flag(kGroup)) *a.bad_ids = 1u;
     else bad = true;
   };
   const T* __restrict__ w_in = static_cast<const T*>(a.w_in);
@@ -721,7 +732,7 @@ __global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs
       for (int b = 0; b < RB; ++b)
         if (j0 + b <= K) axpy<VPL>(du, __shfl(g_mine, b, kGroupLanes), vv[b]);
       if (mine) {
-        if constexpr (kGroup == kBySort) {
+        if constexpr (kGroup == kBySort || kGroup == kGrouped) {
           const int32_t src = a.snap != nullptr ? (int32_t)(first + flushes) : c;
           a.term_key[e0 + my_j] = (uint32_t)prow[my_j];
           a.term_src[e0 + my_j] = make_uint2((uint32_t)src, __float_as_uint(-a.lr * g_mine));
@@ -737,7 +748,7 @@ __global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs
   }
   if (l16 >= flushes && l16 < count) a.stage_center[first + l16] = -1;
   if (!(peak * fabsf(a.lr) < kFixPeak)) report();   // (also taken for NaN)
-  if (kGroup == kInLds && bad) loss = __uint_as_float(0x7fc00000u);
+  if (!has_flag(kGroup) && bad) loss = __uint_as_float(0x7fc00000u);
 
   loss = row_sum16(loss);
   if (l16 == 0) loss_s[group_in_block] = loss;
@@ -898,7 +909,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(uint32_t* __re
 // move 16 bytes at a time, eight independent loads in flight per thread: `data` is 16-byte
 // aligned and allocated up to a multiple of four entries; the padding is read (it holds
 // zeros) and written.
-constexpr int64_t kScanSmallMax = 1 << 17;
+constexpr int64_t kScanSmallMax = 24 << 10;      // (20,000 entries 7 us, 100,000 47; the two kernels 10 to 11)
 __global__ __launch_bounds__(1024) void scan_small_kernel(uint32_t* __restrict__ data, int64_t n) {
   __shared__ uint32_t wave_tot[16];
   constexpr int kBurst = 8;
@@ -1149,7 +1160,7 @@ __device__ __forceinline__ void update_range(const SgnsArgs& a, const Term* __re
   auto flush_long = [&]() {
     const int64_t row_first = seg_first - ((int64_t)cur_seg << a.seg_shift);
     unsigned long long* dst = reinterpret_cast<unsigned long long*>(a.long_acc) +
-                              ((row_first >> a.seg_shift) + (kStage ? a.stage_long_base : 0)) * a.dim;
+                              ((row_first >> a.seg_shift) + (kStage && !kSorted ? a.stage_long_base : 0)) * a.dim;
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
       if (piece_ok[p]) {
@@ -1358,48 +1369,9 @@ template <typename T, if_16bit<T> = 0>
 __device__ __forceinline__ void elem_store(T* row, int e, float v) { row[e].bits = (uint16_t)T::round(v); }
 
 // ---- finish: table[row] = round(old + side buffer) for the long rows ------------------------
-// Side-buffer slot s belongs to the long row (more than one segment of S = 2^seg_shift terms)
-// whose first term lies in [s * S, (s+1) * S): that row then also owns the last position of
-// the window.  The last block of the launch adds up the per-block
-// loss partials instead (in a fixed order, so the loss is reproducible); a bad id
-// or an out-of-range product seen by an earlier kernel turns it into NaN.
-// which: 0 = long rows of both tables and the loss; 1 = context-table keys only, no loss;
-// 2 = input-table keys and the loss.  With one table on both sides a row can be long under
-// both of its keys, and its two read-modify-writes must not overlap: the context-table keys
-// are then finished before the input-table keys are summed.
+// one long row, by 16 lanes
 template <typename T, int kOpt>
-__global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, int which) {
-  if (blockIdx.x == gridDim.x - 1) {
-    if (which == 1) return;
-    __shared__ double sum_s[kSgnsThreads];
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < a.forward_blocks; i += kSgnsThreads) acc += a.loss_partials[i];
-    sum_s[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = kSgnsThreads / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) sum_s[threadIdx.x] += sum_s[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0)
-      *a.loss_out = (*a.bad_ids != 0u) ? __longlong_as_double(0x7ff8000000000000ll) : sum_s[0];
-    return;
-  }
-  const int l16 = threadIdx.x & (kGroupLanes - 1);
-  const int64_t s = ((int64_t)blockIdx.x * kSgnsThreads + threadIdx.x) / kGroupLanes;
-  const int64_t last_pos = ((s + 1) << a.seg_shift) - 1;
-  const int64_t total = (int64_t)a.cnt[a.cnt_last];
-  if (last_pos >= total) return;
-  const Term t = a.sorted[last_pos];
-  const int64_t first_pos = last_pos - (int64_t)t.pos;
-  if ((first_pos >> a.seg_shift) != s) return;
-  // long: the row has a term at position S
-  const int64_t second = first_pos + ((int64_t)1 << a.seg_shift);
-  if (second >= total || a.sorted[second].row != t.row) return;
-  const bool input_row = (int64_t)t.row >= a.num_nodes;
-  if (which != 0 && input_row != (which == 2)) return;
-  const int64_t row = input_row ? (int64_t)t.row - a.num_nodes : (int64_t)t.row;
-  const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.long_acc) +
-                                  (s + (input_row ? a.stage_long_base : 0)) * (int64_t)a.dim;
+__device__ __forceinline__ void finish_row(const SgnsArgs& a, bool input_row, int64_t row, const unsigned long long* src, int l16) {
   T* dst = static_cast<T*>(input_row ? a.dst_in : a.dst_out) + row * (int64_t)a.dim;
   if constexpr (kOpt != kPlain) {
     T* model = static_cast<T*>(input_row ? a.w_in : a.w_out) + row * (int64_t)a.dim;
@@ -1422,24 +1394,98 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, i
     elem_store(dst, e, (float)((double)elem_load(dst, e) + fix_value(src[e])));
 }
 
-// ---- large batches: the context-table terms as sorted records -------------------------------
-// With many terms the counters cost more than a sort: a random atomic per term in the forward
+// the per-block loss partials, in a fixed order, by one workgroup
+__device__ __forceinline__ double sum_of_losses(const SgnsArgs& a) {
+  __shared__ double sum_s[kSgnsThreads];
+  double acc = 0.0;
+  for (int64_t i = threadIdx.x; i < a.forward_blocks; i += kSgnsThreads) acc += a.loss_partials[i];
+  sum_s[threadIdx.x] = acc;
+  __syncthreads();
+  for (int w = kSgnsThreads / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) sum_s[threadIdx.x] += sum_s[threadIdx.x + w];
+    __syncthreads();
+  }
+  return sum_s[0];
+}
+
+// Side-buffer slot s belongs to the long row (more than one segment of S = 2^seg_shift terms)
+// whose first term lies in [s * S, (s+1) * S): that row then also owns the last position of
+// the window.  The last block of the launch adds up the per-block
+// loss partials instead (in a fixed order, so the loss is reproducible); a bad id
+// or an out-of-range product seen by an earlier kernel turns it into NaN.
+// which: 0 = long rows of both tables and the loss; 1 = context-table keys only, no loss;
+// 2 = input-table keys and the loss.  With one table on both sides a row can be long under
+// both of its keys, and its two read-modify-writes must not overlap: the context-table keys
+// are then finished before the input-table keys are summed.
+template <typename T, int kOpt>
+__global__ __launch_bounds__(kSgnsThreads) void sgns_finish_kernel(SgnsArgs a, int which) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (which == 1) return;
+    const double sum = sum_of_losses(a);
+    if (threadIdx.x == 0)
+      *a.loss_out = (*a.bad_ids != 0u) ? __longlong_as_double(0x7ff8000000000000ll) : sum;
+    return;
+  }
+  const int l16 = threadIdx.x & (kGroupLanes - 1);
+  const int64_t s = ((int64_t)blockIdx.x * kSgnsThreads + threadIdx.x) / kGroupLanes;
+  const int64_t last_pos = ((s + 1) << a.seg_shift) - 1;
+  const int64_t total = (int64_t)a.cnt[a.cnt_last];
+  if (last_pos >= total) return;
+  const Term t = a.sorted[last_pos];
+  const int64_t first_pos = last_pos - (int64_t)t.pos;
+  if ((first_pos >> a.seg_shift) != s) return;
+  // long: the row has a term at position S
+  const int64_t second = first_pos + ((int64_t)1 << a.seg_shift);
+  if (second >= total || a.sorted[second].row != t.row) return;
+  const bool input_row = (int64_t)t.row >= a.num_nodes;
+  if (which != 0 && input_row != (which == 2)) return;
+  const int64_t row = input_row ? (int64_t)t.row - a.num_nodes : (int64_t)t.row;
+  const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.long_acc) +
+                                  (s + (input_row ? a.stage_long_base : 0)) * (int64_t)a.dim;
+  finish_row<T, kOpt>(a, input_row, row, src, l16);
+}
+
+// The same for grouped batches, whose long rows are in a list (which: as above; a bad id or an out-of-range product has made a
+// partial NaN).
+template <typename T, int kOpt>
+__global__ __launch_bounds__(kSgnsThreads) void sgns_long_rows_kernel(SgnsArgs a, int which) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (which == 1) return;
+    const double sum = sum_of_losses(a);
+    if (threadIdx.x == 0) *a.loss_out = sum;
+    return;
+  }
+  const int l16 = threadIdx.x & (kGroupLanes - 1);
+  const uint32_t rows = *a.num_long_rows;
+  for (uint32_t i = (blockIdx.x * kSgnsThreads + threadIdx.x) / kGroupLanes; i < rows; i += (gridDim.x - 1) * kGroupsPerBlock) {
+    const uint2 r = a.long_rows[i];
+    const bool input_row = (int64_t)r.x >= a.num_nodes;
+    if (which != 0 && input_row != (which == 2)) continue;
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.long_acc) + (int64_t)r.y * a.dim;
+    finish_row<T, kOpt>(a, input_row, input_row ? (int64_t)r.x - a.num_nodes : (int64_t)r.x, src, l16);
+  }
+}
+
+// ---- large batches: the terms as records in the order of their rows --------------------------
+// With many terms the counters cost more than bringing records together: a random atomic per term in the forward
 // kernel, and in the place kernel a random read and a random 16-byte write per term, all of them whole
 // cache lines.  The forward kernel writes each term as a record (row; source row, coefficient)
-// instead, the radix sort (a pass per 8 bits of the row numbers, two to four of them) brings the records into
-// row order in streams, and the update kernel reads them as they lie.  The few input-table terms keep their counters.
-// 12 million terms, 128 fp32 columns, 4 M nodes: forward 1016 -> 827 us, place and scan 420 -> three
-// passes of 106 us (count 28, prefix sums 5, scatter 73), update 944 -> 1000 us.
+// instead, and the update kernels read the records as they lie in the order of their rows.
+//   Up to 2^24 rows: grouped (group.hip), the records of both tables at once; the staging slots are the list with gaps.  Nothing is
+//   cleared, counted per row or scanned; the grouping also says which rows have more than one segment and, for the optimizers, which rows
+//   have any records.  12 million terms, 128 fp32 columns, 4 M nodes: a step takes 2256 us (2579 with the counters, 2411 with the
+//   records of the context table through the stable sort in three passes); 65,536 pairs, 64 columns on 10 k nodes 90 (104 with the counters).
+//   More rows: the radix sort brings the records of the context table into order; the few input-table terms keep their counters.
 
-// First position >= p (and <= num_terms) that starts a segment of its row, and the row's first
-// position.  back and ahead: the keys of the 64 positions before p (lane l: p - 1 - l) and of the 64
+// First position >= p (and <= hi) that starts a segment of its row, and the row's first
+// position, among the records [lo, hi).  back and ahead: the keys of the 64 positions before p (lane l: p - 1 - l) and of the 64
 // from p on (kNoRow outside), loaded by the caller so that the loads of both ends of a slice are
 // under way together; almost always they decide.
 __device__ __forceinline__ int64_t sorted_segment_start(const SgnsArgs& a, int64_t p, int lane, uint32_t back,
-                                                        uint32_t ahead, int64_t& first_row) {
+                                                        uint32_t ahead, int64_t lo, int64_t hi, int64_t& first_row) {
   const uint32_t* __restrict__ keys = a.term_key;
   first_row = p;
-  if (p == 0 || p >= a.num_terms) return p;
+  if (p == lo || p >= hi) return p;
   const uint32_t key = uniform_u32(ahead);
   const unsigned long long other_back = __builtin_amdgcn_ballot_w64(back != key);
   if (other_back & 1ull) return p;                                   // a row starts at p
@@ -1448,27 +1494,42 @@ __device__ __forceinline__ int64_t sorted_segment_start(const SgnsArgs& a, int64
   if (other_back != 0ull) {
     first = p - __builtin_ctzll(other_back);
   } else {
-    int64_t lo = 0, hi = max((int64_t)0, p - 64);                     // (keys[hi] == key)
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (uniform_u32(keys[mid]) < key) lo = mid + 1; else hi = mid;
+    // the row goes back further: 64 positions at a time, 64 apart, then 4096 apart and so on until one lies in front of the row, and
+    // back down (21 dependent reads of a binary search over a million records instead: a batch of 800,000 pairs on 10,000 rows 397 us)
+    first = max(lo, p - 64);                                          // (keys[first] == key)
+    int shift = 6;
+    auto before = [&]() {                                             // of the 64 positions in front of `first`, how many are the row's
+      const int64_t q = first - ((int64_t)(lane + 1) << shift);
+      const unsigned long long other = __builtin_amdgcn_ballot_w64(q < lo || keys[max(lo, q)] != key);
+      return other != 0ull ? __builtin_ctzll(other) : 64;
+    };
+    int n = before();
+    while (n == 64) {
+      first -= (int64_t)64 << shift;
+      shift += 6;
+      n = before();
     }
-    first = lo;
+    for (;;) {
+      first -= (int64_t)n << shift;
+      if (shift == 0) break;
+      shift -= 6;
+      n = before();
+    }
   }
   const int64_t segment = (int64_t)1 << a.seg_shift;
   const int64_t next = first + ((p - first + segment - 1) & ~(segment - 1));      // the row's next segment, if it gets there
-  int64_t row_end = a.num_terms;                                     // first position behind the row, as far as it matters
+  int64_t row_end = hi;                                              // first position behind the row, as far as it matters
   if (other_ahead != 0ull) {
     row_end = p + __builtin_ctzll(other_ahead);
   } else {
-    for (int64_t x = p + 64; x < min(next, a.num_terms); x += 64) {
-      const unsigned long long mask = __builtin_amdgcn_ballot_w64(x + lane >= a.num_terms || keys[min(x + lane, a.num_terms - 1)] != key);
+    for (int64_t x = p + 64; x < min(next, hi); x += 64) {
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(x + lane >= hi || keys[min(x + lane, hi - 1)] != key);
       if (mask == 0ull) continue;
       row_end = x + __builtin_ctzll(mask);
       break;
     }
   }
-  if (next < row_end && next < a.num_terms) {
+  if (next < row_end && next < hi) {
     // (next may lie behind the last key looked at: the row's own segment only if it gets there)
     if (uniform_u32(keys[next]) == key) {
       first_row = first;
@@ -1480,21 +1541,28 @@ __device__ __forceinline__ int64_t sorted_segment_start(const SgnsArgs& a, int64
   return row_end;
 }
 
-template <typename T, int WPP, int PPL, int UB>
+// kStage: the records of the input-table rows, which follow those of the context table (grouped batches); their number is on
+// the device, so the launch is sized for the few that a batch normally has and its waves stride over the slices.
+template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage>
 __global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_update_kernel(SgnsArgs a) {
   const uint32_t* __restrict__ keys = a.term_key;
   const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t)blockIdx.x * (kSgnsThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t p0 = wave * a.slice_terms;
-  if (p0 >= a.num_terms) return;
-  const int64_t p1 = min(p0 + a.slice_terms, a.num_terms);
-  auto key_at = [&](int64_t p) { return p >= 0 && p < a.num_terms ? keys[p] : kNoRow; };
-  const uint32_t back0 = key_at(p0 - 1 - lane), ahead0 = key_at(p0 + lane);
-  const uint32_t back1 = key_at(p1 - 1 - lane), ahead1 = key_at(p1 + lane);
-  int64_t first_row, unused;
-  const int64_t begin = sorted_segment_start(a, p0, lane, back0, ahead0, first_row);
-  const int64_t end = sorted_segment_start(a, p1, lane, back1, ahead1, unused);
-  update_range<T, WPP, PPL, UB, kPlain, false, true, true>(a, nullptr, begin, end, a.num_terms, lane, first_row);
+  const int64_t first_wave = (int64_t)blockIdx.x * (kSgnsThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t lo = kStage ? a.num_terms : 0, hi = kStage ? (int64_t)uniform_u32(*a.num_records) : a.num_terms;
+  const int64_t slice = kStage ? kStageSlice : a.slice_terms;
+  for (int64_t wave = first_wave;; wave += (int64_t)gridDim.x * (kSgnsThreads / 64)) {
+    const int64_t p0 = lo + wave * slice;
+    if (p0 >= hi) return;
+    const int64_t p1 = min(p0 + slice, hi);
+    auto key_at = [&](int64_t p) { return p >= lo && p < hi ? keys[p] : kNoRow; };
+    const uint32_t back0 = key_at(p0 - 1 - lane), ahead0 = key_at(p0 + lane);
+    const uint32_t back1 = key_at(p1 - 1 - lane), ahead1 = key_at(p1 + lane);
+    int64_t first_row, unused;
+    const int64_t begin = sorted_segment_start(a, p0, lane, back0, ahead0, lo, hi, first_row);
+    const int64_t end = sorted_segment_start(a, p1, lane, back1, ahead1, lo, hi, unused);
+    update_range<T, WPP, PPL, UB, kOpt, kStage, true, true>(a, nullptr, begin, end, hi, lane, first_row);
+    if constexpr (!kStage) return;               // (one slice per wave)
+  }
 }
 
 // The long rows (more than one segment) of the sorted terms, 16 lanes per side-buffer slot: slot s
@@ -1831,7 +1899,9 @@ struct SgnsPlan {
   bool small = false;       // the two-launch step of a small batch, which keeps copies of the input rows
   void* snap = nullptr;
   int32_t* pair_slot = nullptr;
-  bool by_sort = false;     // the context-table terms as sorted records (large batches)
+  bool by_sort = false;     // the context-table terms as sorted records (large batches on very many rows)
+  bool grouped = false;     // records of both tables, grouped by row (large batches)
+  GroupArgs group = {};
   uint32_t* term_key[2] = {nullptr, nullptr};      // [0] holds the sorted ones
   uint2* term_src[2] = {nullptr, nullptr};
   void* sort_scratch = nullptr;
@@ -1886,19 +1956,10 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
   return p;
 }
 
-// Batches of at least this many terms take the sorted records: fewer where two passes sort them (up to
-// 2^16 rows), because few rows also mean busy counters.  Times of the counters over those of the records, batches of
-// walks and negatives on R-MAT graphs, 16 to 256 columns (least and most of them):
-//   two passes    0.65 M terms: 10 k rows, k = 1 0.85 to 0.94, k = 5 0.90 to 1.07
-//                 1.05 M terms: 5 k to 60 k rows, k = 1 0.96 to 1.05, 2 0.99 to 1.07, 5 1.04 to 1.12, 10 1.05 to 1.16
-//                 2.0 M terms: the same rows, k = 1 0.99 to 1.11, 5 1.05 to 1.23
-//   three passes  4.8 M terms: 100 k rows, k = 1 0.90 to 1.07, 5 0.99 to 1.06; 400 k 0.99 to 1.11; 1 M and 4 M 1.01 to 1.15
-//                 8 M terms: 100 k rows 1.02 to 1.21, 4 M 1.03 to 1.23
-//   four passes   4.8 M terms: 18 M rows 1.02 to 1.14, 16 M terms 1.06 to 1.16; 25 M rows of 256 bf16 columns, 22 M
-//                 terms 8697 / 7879 us; 100 M rows of 128 fp32 columns, 24 M terms 11866 / 10166 us
-// (Ids drawn one by one, evenly, on 4 M rows of 128 fp32 columns: 0.98 to 0.99 at 4.7 M to 6.6 M terms, 1.04 at 12 M.)
-constexpr int64_t kSortedMinTerms = (int64_t)9 << 19, kSortedMinTermsFewRows = (int64_t)3 << 21, kSortedFewRows = (int64_t)1 << 17;
-constexpr int64_t kSortedMinTermsTwoPasses = (int64_t)1 << 20;
+// Batches of at least this many terms on more rows than can be grouped take the sorted records.  Times of the counters over those
+// of the records (in four passes of 8 bits; three of 9 are faster): 4.8 M terms on 18 M rows 1.02 to 1.14, 16 M terms 1.06 to 1.16; 25 M rows of 256
+// bf16 columns, 22 M terms 8697 / 7879 us; 100 M rows of 128 fp32 columns, 24 M terms 11866 / 10166 us
+constexpr int64_t kSortedMinTerms = (int64_t)9 << 19;
 // Sorted terms per wave of the update: the ends of a slice cost four loads of keys (256 against 128 terms:
 // 2407 / 2425 us for 12 million terms on 4 M rows), and a short batch has to make enough waves.
 static int sorted_slice_for(int64_t num_terms) { return num_terms >= ((int64_t)1 << 22) ? 256 : 128; }
@@ -1942,10 +2003,44 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
   p.bytes = cv.used;
   return p;
 }
+
+// Records of both kinds of rows, grouped.
+static SgnsPlan plan_grouped(void* ws, int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim) {
+  Carver cv(ws);
+  SgnsPlan p = {};
+  const size_t b = (size_t)num_pairs, terms = b * (size_t)(k + 1);
+  p.grouped = true;
+  p.seg_shift = seg_shift_for(num_pairs);
+  p.long_slots = (int64_t)((terms + b) >> p.seg_shift) + 1;
+  p.loss_partials = cv.take<double>((size_t)forward_blocks_for(num_pairs));
+  for (int i = 0; i < 2; ++i) {
+    p.term_key[i] = cv.take<uint32_t>(terms + b);
+    p.term_src[i] = cv.take<uint2>(terms + b);
+  }
+  group_take(p.group, cv, (int64_t)terms, num_pairs, num_nodes, p.seg_shift, true);
+  p.long_acc = cv.take<long long>((size_t)p.long_slots * (size_t)dim);
+  p.stage_center = cv.take<int32_t>(b);
+  p.stage_delta = cv.take<float>(b * (size_t)dim);
+  p.bytes = cv.used;
+  return p;
+}
+// Batches of at least this many terms are grouped: fewer on few rows, whose counters are busy.  Times of the counters over those of the
+// records, batches of walks and negatives on R-MAT graphs, 16 to 400 columns (least and most of them):
+//   5 k and 10 k rows   0.3 M terms 0.96 to 1.17, 0.4 M 0.97 to 1.15, 0.6 M 1.01 to 1.18, 1.2 M 0.95 (one negative) to 1.17, 4 M 1.01 to 1.35
+//   100 k rows          0.3 M 0.93 to 1.07, 0.4 M 0.94 to 1.08, 0.6 M 0.99 to 1.08, 1.2 M 0.98 to 1.11, 4 M 1.01 to 1.20
+//   1 M rows            0.3 M 0.89 to 1.05, 0.4 M 0.87 to 1.05, 0.6 M 0.95 to 1.07, 1.2 M 1.03 to 1.08, 4 M 1.08 to 1.22
+constexpr int64_t kGroupedMinTerms = (int64_t)5 << 17, kGroupedMinTermsFewRows = (int64_t)5 << 16, kGroupedFewRows = (int64_t)1 << 16;
+static bool grouped_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
+  return num_pairs * (int64_t)(k + 1) >= (num_nodes <= kGroupedFewRows ? kGroupedMinTermsFewRows : kGroupedMinTerms) && can_group(num_nodes);
+}
+// Records per wave of the update (us with 32 / 64 / 128 / 256): 0.4 M terms on 10 k rows of 64 columns 108 / 99 / 102 / 117, on 1 M rows of 128 151 /
+// 156 / 166 / 209, 1.6 M 387 / 376 / 383 / 406, 2.4 M 591 / 563 / 554 / 555, 6 M 1210 / 1127 / 1095 / 1100, 12 M 2472 / 2345 / 2282 / 2256
+static int grouped_slice_for(int64_t num_terms) {
+  return num_terms >= ((int64_t)1 << 23) ? 256 : (num_terms >= ((int64_t)1 << 21) ? 128 : 64);
+}
+
 static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
-  const int64_t terms = num_pairs * (int64_t)(k + 1);
-  if (bits_for_rows(num_nodes) <= 16) return terms >= (k >= 2 ? kSortedMinTermsTwoPasses : 2 * kSortedMinTermsTwoPasses);
-  return terms >= (num_nodes <= kSortedFewRows ? kSortedMinTermsFewRows : kSortedMinTerms);
+  return num_pairs * (int64_t)(k + 1) >= kSortedMinTerms && !can_group(num_nodes);
 }
 
 // Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every
@@ -1992,16 +2087,20 @@ static SgnsPlan plan_small(void* ws, int64_t num_pairs, int32_t k, int32_t dim, 
 // The plan of a step in a workspace of ws_bytes, of which the call's own arrays take `extra` bytes
 // behind the plan; false: too small.  Every call needs room for the counters' plan, whatever its
 // batch takes; with more room, the two-launch step where the batch is small (two_launches: the call can take
-// it) and the sorted records where it is large.
+// it) and records where it is large (sort_records: the call can take sorted ones).
 static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int64_t num_pairs, int64_t num_nodes,
-                      int32_t k, int32_t dim, int32_t dtype, bool two_launches = true, bool force_compact = false) {
+                      int32_t k, int32_t dim, int32_t dtype, bool two_launches = true, bool force_compact = false,
+                      bool sort_records = true) {
   const SgnsPlan counters = plan_sgns(ws, num_pairs, num_nodes, k, dim, force_compact);
   if (counters.bytes + extra > ws_bytes) return false;
   if (two_launches && small_batch(num_pairs, num_nodes, k, dim, dtype)) {
     p = plan_small(ws, num_pairs, k, dim, dtype);
     if (p.bytes + extra <= ws_bytes) return true;
   }
-  if (sorted_batch(num_pairs, num_nodes, k)) {
+  if (grouped_batch(num_pairs, num_nodes, k)) {
+    p = plan_grouped(ws, num_pairs, num_nodes, k, dim);
+    if (p.bytes + extra <= ws_bytes) return true;
+  } else if (sort_records && sorted_batch(num_pairs, num_nodes, k)) {
     p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
     if (p.bytes + extra <= ws_bytes) return true;
   }
@@ -2013,7 +2112,8 @@ static size_t plan_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
   if (two_launches && small_batch(num_pairs, num_nodes, k, dim, dtype))
     bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
-  if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  if (grouped_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_grouped(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  else if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
   return bytes;
 }
 // The same over all batches of up to num_pairs: the workspace of a program's largest batch serves every
@@ -2128,7 +2228,7 @@ static int32_t launch_sorted_updates(const SgnsArgs& a, hipStream_t stream) {
   const unsigned in_blocks = (unsigned)std::min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
   const unsigned long_blocks = (unsigned)ceil_div(a.stage_long_base, kGroupsPerBlock);
   sgns_sorted_long_kernel<T, true><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
-  sgns_sorted_update_kernel<T, WPP, PPL, UB><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_sorted_update_kernel<T, WPP, PPL, UB, kPlain, false><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
   sgns_sorted_long_kernel<T, false><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
   sgns_update_kernel<T, WPP, PPL, UB, kPlain, true><<<in_blocks, kSgnsThreads, 0, stream>>>(a);
   GS_LAUNCH_CHECK();
@@ -2193,6 +2293,71 @@ static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStr
   return GS_OK;
 }
 
+template <typename T, int WPP, int PPL, int UB, int kOpt>
+static int32_t launch_grouped_updates(const SgnsArgs& a, hipStream_t stream) {
+  constexpr int kWaves = kSgnsThreads / 64;
+  const unsigned out_blocks = (unsigned)ceil_div(ceil_div(a.num_terms, a.slice_terms), kWaves);
+  const unsigned in_blocks = (unsigned)std::min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
+  const unsigned long_blocks = (unsigned)std::min((int64_t)kLongRowBlocks, ceil_div(a.long_slots, kGroupsPerBlock)) + 1;
+  sgns_sorted_update_kernel<T, WPP, PPL, UB, kOpt, false><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
+  const bool one_table = a.dst_in == a.dst_out;
+  if constexpr (kOpt == kPlain)
+    if (one_table) sgns_long_rows_kernel<T, kOpt><<<long_blocks, kSgnsThreads, 0, stream>>>(a, 1);
+  sgns_sorted_update_kernel<T, WPP, PPL, UB, kOpt, true><<<in_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_long_rows_kernel<T, kOpt><<<long_blocks, kSgnsThreads, 0, stream>>>(a, one_table ? 2 : 0);
+  GS_LAUNCH_CHECK();
+  return GS_OK;
+}
+
+template <typename T, int kOpt>
+static int32_t launch_grouped_rows(const SgnsArgs& a, hipStream_t stream) {
+  const int row_bytes = a.dim * (int)sizeof(T);
+  int32_t rc;
+  if (row_bytes <= 256) rc = launch_grouped_updates<T, 1, 1, 16, kOpt>(a, stream);
+  else if (row_bytes <= 512) rc = launch_grouped_updates<T, 2, 1, 16, kOpt>(a, stream);
+  else if (row_bytes <= 1024) rc = launch_grouped_updates<T, 4, 1, 8, kOpt>(a, stream);
+  else if (row_bytes <= 2048) rc = launch_grouped_updates<T, 4, 2, 4, kOpt>(a, stream);
+  else rc = launch_grouped_updates<T, 4, 4, 2, kOpt>(a, stream);
+  if (rc != GS_OK) return rc;
+  if constexpr (kOpt != kPlain) return launch_dense_rest<T, kOpt>(a, true, stream);
+  return GS_OK;
+}
+
+template <typename T, int VPL, int RB>
+static int32_t launch_grouped(const SgnsArgs& ungrouped, const SgnsPlan& p, int opt, hipStream_t stream) {
+  SgnsArgs a = ungrouped;
+  a.term_key = p.term_key[0];
+  a.term_src = p.term_src[0];
+  launch_forward<T, VPL, RB, kGrouped>(a, stream);
+  GS_LAUNCH_CHECK();
+  GroupArgs g = p.group;
+  g.rows = g.keys_out = p.term_key[0];
+  g.vals = g.vals_out = p.term_src[0];
+  g.n = a.num_terms;
+  g.second = a.stage_center;
+  g.second_n = a.num_pairs;
+  const float coef = -a.lr;
+  std::memcpy(&g.second_word, &coef, sizeof(coef));
+  g.second_key = (uint32_t)a.num_nodes;
+  g.rows_mid = p.term_key[1];
+  g.vals_mid = p.term_src[1];
+  g.seg_shift = a.seg_shift;
+  g.dim = a.dim;
+  g.long_acc = a.long_acc;
+  if (opt == kPlain) g.named = nullptr;
+  const int32_t rc = group_rows(g, a.num_nodes, stream);
+  if (rc != GS_OK) return rc;
+  a.num_records = g.counters + kGroupRecords;
+  a.num_long_rows = g.counters + kGroupLong;
+  a.long_rows = g.long_rows;
+  a.named = g.named;
+  a.named_in = g.second_named;
+  if (opt == kMomentum) return launch_grouped_rows<T, kMomentum>(a, stream);
+  if constexpr (std::is_same<T, float>::value)
+    if (opt == kAdam) return launch_grouped_rows<T, kAdam>(a, stream);
+  return launch_grouped_rows<T, kPlain>(a, stream);
+}
+
 template <typename T, int VPL, int RB>
 static int32_t launch_sgns(const SgnsArgs& a, const SgnsPlan& p, int opt, hipStream_t stream) {
   if (p.small) {
@@ -2200,6 +2365,7 @@ static int32_t launch_sgns(const SgnsArgs& a, const SgnsPlan& p, int opt, hipStr
     if constexpr (VPL * 64 * sizeof(T) <= (size_t)kSmallMaxRowBytes) return launch_small<T, VPL, RB>(a, stream);
     return GS_EINVAL;
   }
+  if (p.grouped) return launch_grouped<T, VPL, RB>(a, p, opt, stream);
   if (p.by_sort) return launch_sorted<T, VPL, RB>(a, p, stream);
   int32_t rc = launch_clear(a, stream);
   if (rc != GS_OK) return rc;
@@ -2270,6 +2436,7 @@ __global__ __launch_bounds__(256) void table_axpy16_kernel(uint4* __restrict__ w
 // Whether the batch named the row of `key`: its counter slot holds terms, or the key is in the table of
 // the batch's keys.
 __device__ __forceinline__ bool row_named(const SgnsArgs& a, uint32_t key) {
+  if (a.named != nullptr) return a.named[key >= (uint32_t)a.num_nodes ? key - (uint32_t)a.num_nodes + a.named_in : key] != 0;
   const KeyRegion r = key_region(a, key);
   if (r.bits == 0) return a.cnt[r.slot_base + r.vertex] != a.cnt[r.slot_base + r.vertex + 1u];
   const uint32_t mask = (1u << r.bits) - 1u;
@@ -2490,12 +2657,17 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
   a.stage_long_base = p.stage_long_base;
   a.term_key = nullptr;
   a.term_src = nullptr;
+  a.num_records = nullptr;
+  a.long_rows = nullptr;
+  a.num_long_rows = nullptr;
+  a.named = nullptr;
+  a.named_in = 0;
   a.long_acc = p.long_acc;
   a.stage_center = p.stage_center;
   a.stage_rank = p.stage_rank;
   a.stage_delta = p.stage_delta;
   a.chunk_pairs = p.small ? kSmallChunkPairs : chunk_pairs_for(num_pairs);
-  a.slice_terms = p.by_sort ? sorted_slice_for(a.num_terms) : slice_terms_for(num_pairs);
+  a.slice_terms = p.grouped ? grouped_slice_for(a.num_terms) : (p.by_sort ? sorted_slice_for(a.num_terms) : slice_terms_for(num_pairs));
   a.loss_partials = p.loss_partials;
   a.forward_blocks = p.small ? small_forward_blocks(num_pairs) : forward_blocks_for(num_pairs);
   a.forward_blocks_per_xcd = ceil_div(a.forward_blocks, 8);
@@ -2760,7 +2932,7 @@ extern "C" int32_t gs_sgns_momentum_step(void* w_in, void* w_out, void* m_in, vo
   if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype)) return GS_EWORKSPACE;
   const int64_t table_bytes = num_nodes * (int64_t)dim * (dtype == GS_F32 ? 4 : 2);
   if (num_pairs > 0 && !(p.small && table_bytes <= kSeparatePassBytes)) {
-    p = plan_sgns(ws, num_pairs, num_nodes, k, dim);       // (fits: every plan_step needs it to)
+    if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, dtype, false, false, false)) return GS_EWORKSPACE;
     SgnsExtras x;
     x.opt = kMomentum;
     x.rates.decay1 = mu;
@@ -2825,8 +2997,8 @@ extern "C" int32_t gs_sgns_adam_step(float* w_in, float* w_out, float* m_in, flo
   }
   if (t < 1 || !(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f) || !(eps >= 0.f))
     return GS_EINVAL;
-  SgnsPlan p = plan_sgns(ws, num_pairs, num_nodes, k, dim);
-  if (ws_bytes < p.bytes) return GS_EWORKSPACE;
+  SgnsPlan p;
+  if (!plan_step(p, ws, ws_bytes, 0, num_pairs, num_nodes, k, dim, GS_F32, false, false, false)) return GS_EWORKSPACE;
   SgnsExtras x;
   x.opt = kAdam;
   x.sq_in = v_in;

@@ -1,0 +1,102 @@
+"""Steps whose terms are grouped as records: the borders of the dispatch, one and few rows, buckets of more records than a workgroup
+takes, long rows in both tables, every or no centre its own run, the optimizers' marks of the rows of a batch and the one-table step."""
+import numpy as np
+import pytest
+import torch
+
+from tolerances import EMB_ATOL, LOSS_RTOL, assert_emb_close, assert_half_close
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(DEV)
+
+
+def _batch(kind, n, b, k, rng):
+    c = np.repeat(rng.integers(0, n, b // 5 + 1), 5)[:b].astype(np.int32)
+    o, neg = rng.integers(0, n, b).astype(np.int32), rng.integers(0, n, (b, k)).astype(np.int32)
+    if kind == "hub":                       # half of all terms and of all runs in one row
+        o[rng.random(b) < 0.5] = n - 1
+        neg[rng.random((b, k)) < 0.5] = n - 1
+        c[(np.arange(b) // 5) % 2 == 0] = n // 2
+    elif kind == "runs of one":
+        c = rng.permutation(np.arange(b) % n).astype(np.int32)
+    elif kind == "one run":
+        c[:] = n // 3
+    return c, o, neg
+
+
+def _tables(n, dim, count, seed, scale=0.3):
+    g = torch.Generator().manual_seed(seed)
+    return [(torch.rand((n, dim), generator=g) - 0.5) * scale for _ in range(count)]
+
+
+# terms: 5 * 2^16 and one less on 2^16 rows, 5 * 2^17 on one row more; 1 to 32 rows; up to 256, 1024 and 2048 buckets; tiles of 2048,
+# 4096 and 8192 records; a row per bucket with more records than a workgroup takes
+@pytest.mark.parametrize("kind,n,b,k", [
+    ("even", 65_536, 54_614, 5), ("even", 65_536, 54_613, 5), ("even", 65_537, 109_227, 5), ("even", 65_537, 109_226, 5),
+    ("even", 1, 65_536, 4), ("even", 2, 70_001, 4), ("even", 33, 70_001, 4), ("even", 5_000, 350_003, 0), ("hub", 20_000, 120_000, 5),
+    ("hub", 300_000, 262_145, 5), ("runs of one", 70_000, 400_000, 1), ("one run", 70_000, 131_073, 7), ("hub", 3_000_001, 699_051, 6),
+    ("even", (1 << 24) - 5, 131_101, 4)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16"])
+def test_step(oracle, kind, n, b, k, fmt):
+    from paper_2407_15452_amd import binding as gs
+    dim = 8 if n > 1_000_000 else 24
+    c, o, neg = _batch(kind, n, b, k, np.random.default_rng(n + b))
+    tabs = [t.to(torch.float32 if fmt == "f32" else torch.bfloat16) for t in _tables(n, dim, 2, n)]
+    host = [t.numpy().copy() if fmt == "f32" else t.view(torch.int16).numpy().view(np.uint16).copy() for t in tabs]
+    dev = [t.to(DEV) for t in tabs]
+    lr = 1e-5 if n < 100 else 1e-4          # (rows of 10^5 terms)
+    want = oracle.sgns_step(*host, c, o, neg, lr, dtype=oracle.F32 if fmt == "f32" else oracle.BF16)
+    loss = gs.gs_sgns_step(*dev, _dev(c), _dev(o), _dev(neg), lr)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for d, h in zip(dev, host):
+        if fmt == "f32":
+            assert_emb_close(d.cpu().numpy(), h)
+        else:                               # (tables of a few rows: one element that rounds the other way is more than the share)
+            assert_half_close(d.view(torch.int16).cpu().numpy().view(np.uint16), h, fmt,
+                              flip_fraction=None if h.size > 20_000 else 2.0 / h.size)
+
+
+@pytest.mark.parametrize("kind,n,b,k", [("even", 65_536, 54_614, 5), ("hub", 40_000, 60_000, 5), ("hub", 700_000, 110_000, 5)])
+@pytest.mark.parametrize("call", ["momentum", "adam", "line1"])
+def test_optimizers_and_one_table(oracle, call, kind, n, b, k):
+    from paper_2407_15452_amd import binding as gs
+    dim, lr = 12, 1e-3
+    c, o, neg = _batch(kind, n, b, k, np.random.default_rng(n))
+    tabs = _tables(n, dim, 4, n)
+    if call == "line1":
+        tabs = tabs[:1]
+    elif call == "adam":
+        tabs += [t.abs() + 0.01 for t in _tables(n, dim, 2, n + 1, 0.1)]          # (denominators well above zero)
+    host, dev = [t.numpy().copy() for t in tabs], [t.to(DEV) for t in tabs]
+    ids = (_dev(c), _dev(o), _dev(neg))
+    if call == "momentum":
+        want, loss = oracle.sgns_momentum_step(*host, c, o, neg, lr, 0.875), gs.gs_sgns_momentum_step(*dev, *ids, lr, 0.875)
+    elif call == "adam":
+        rates = (lr, 0.9, 0.999, 1e-8, 5)
+        want, loss = oracle.sgns_adam_step(*host, c, o, neg, *rates), gs.gs_sgns_adam_step(*dev, *ids, *rates)
+    else:
+        want, loss = oracle.line1_step(*host, c, o, neg, lr), gs.gs_line1_step(*dev, *ids, lr)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for i, (d, h) in enumerate(zip(dev, host)):
+        got = d.cpu().numpy()
+        if call == "adam" and i < 2:
+            assert np.abs(got - h).max() <= EMB_ATOL
+        elif call == "adam":
+            assert (np.abs(got - h) <= 1e-6 + 1e-5 * np.abs(h)).all()
+        else:
+            assert_emb_close(got, h)
+
+
+def test_bad_ids_and_products_out_of_range():
+    """Both turn the loss into NaN; the ids are read as row 0."""
+    from paper_2407_15452_amd import binding as gs
+    n, b, k = 60_000, 60_000, 5
+    c, o, neg = _batch("even", n, b, k, np.random.default_rng(1))
+    for ids, lr in (((c, o, np.where(neg == neg[7, 2], n, neg)), 1e-3), ((np.where(c == c[5], -1, c), o, neg), 1e-3), ((c, o, neg), 1e6)):
+        dev = [t.to(DEV) for t in _tables(n, 8, 2, 3)]
+        assert np.isnan(float(gs.gs_sgns_step(*dev, *(_dev(x.astype(np.int32)) for x in ids), lr).item()))

@@ -202,3 +202,27 @@ def test_long_segments_among_very_many(launches, segments):
     got, rc = launches("p = [C.c_void_p(1 << (20 + i)) for i in range(6)]\nprint(json.dumps({'rc': lib.gs_alias_build(p[0], C.c_int32(64), "
                        "C.c_int64(%d), C.c_int64(1 << 33), *p[1:5], C.c_size_t(1 << 45), None)}))\n" % segments)
     assert rc == [0] and "alias_build_rows_kernel" in got[-1][0]
+
+
+@pytest.mark.parametrize("call,pairs,nodes,k,how", [
+    ("gs_sgns_step", 54_613, 65_536, 5, "place"), ("gs_sgns_step", 54_614, 65_536, 5, "group"), ("gs_sgns_step", 54_614, 65_537, 5, "place"),
+    ("gs_sgns_step", 109_226, 65_537, 5, "place"), ("gs_sgns_step", 109_227, 65_537, 5, "group"), ("gs_sgns_step", 2_000_000, 1 << 24, 5, "group"),
+    ("gs_sgns_step", 786_431, (1 << 24) + 1, 5, "place"), ("gs_sgns_step", 786_432, (1 << 24) + 1, 5, "radix"),
+    ("gs_sgns_momentum_step", 109_227, 70_000, 5, "group"), ("gs_sgns_momentum_step", 786_432, (1 << 24) + 1, 5, "place"),
+    ("gs_sgns_adam_step", 109_227, 70_000, 5, "group"), ("gs_sgns_adam_step", 109_226, 70_000, 5, "place")])
+def test_ways_of_large_steps(launches, call, pairs, nodes, k, how):
+    """Counters, grouped records (up to 2^24 rows) and sorted ones (beyond; without an optimizer)."""
+    got, rc = launches(STEP + "print(json.dumps({'rc': step('%s', %d, %d, 64, 0, %d)}))\n" % (call, pairs, nodes, k))
+    assert rc == [0]
+    names = " ".join(x[0] for x in got)
+    assert ("group_bucket_kernel" in names, "radix_scatter_kernel" in names, "sgns_clear_kernel" in names) == (
+        how == "group", how == "radix", how != "group")
+
+
+def test_workspaces_grow_with_the_batch(launches):
+    """Also where a larger batch takes fewer and larger tiles, or fewer rows per bucket."""
+    got, rc = launches("f = lib.gs_sgns_step_workspace_bytes\nf.restype = C.c_size_t\nfor n in (10000, 1000000, 4000000, 1 << 24):\n"
+                       "  last = 0\n  for i in range(2000):\n    b = int(2000 * 1.0045 ** i)\n"
+                       "    now = f(C.c_int64(b), C.c_int64(n), C.c_int32(5), C.c_int32(64), C.c_int32(0))\n"
+                       "    if now < last: print(json.dumps({'rc': [n, b]}))\n    last = now\n")
+    assert rc == []
