@@ -100,3 +100,22 @@ def test_bad_ids_and_products_out_of_range():
     for ids, lr in (((c, o, np.where(neg == neg[7, 2], n, neg)), 1e-3), ((np.where(c == c[5], -1, c), o, neg), 1e-3), ((c, o, neg), 1e6)):
         dev = [t.to(DEV) for t in _tables(n, 8, 2, 3)]
         assert np.isnan(float(gs.gs_sgns_step(*dev, *(_dev(x.astype(np.int32)) for x in ids), lr).item()))
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("dim", [8, 120, 136, 248, 264, 504, 520, 1016])
+@pytest.mark.parametrize("n,b,k", [(100_000, 1_500, 6), (20_000, 9_000, 3), (30_000, 30_000, 10)])
+def test_short_16bit_rows(oracle, fmt, dim, n, b, k):
+    """Rows that leave lanes of the forward kernel without a piece, and terms that do not fill its blocks of rows: two launches (or, of
+    wide rows, counters over the keys of the batch), counters, grouped records."""
+    from paper_2407_15452_amd import binding as gs
+    dtype = torch.bfloat16 if fmt == "bf16" else torch.float16
+    c, o, neg = _batch("even", n, b, k, np.random.default_rng(dim))
+    tabs = [t.to(dtype) for t in _tables(n, dim, 2, dim)]
+    host = [t.view(torch.int16).numpy().view(np.uint16).copy() for t in tabs]
+    dev = [t.to(DEV) for t in tabs]
+    want = oracle.sgns_step(*host, c, o, neg, 0.01, dtype=oracle.BF16 if fmt == "bf16" else oracle.F16)
+    loss = gs.gs_sgns_step(*dev, _dev(c), _dev(o), _dev(neg), 0.01)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for d, h in zip(dev, host):
+        assert_half_close(d.view(torch.int16).cpu().numpy().view(np.uint16), h, fmt)
