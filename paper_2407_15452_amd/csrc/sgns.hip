@@ -319,7 +319,7 @@ __device__ __forceinline__ RawRow<T, VPL> inside_row(const RawRow<T, VPL>& x, in
   return y;
 }
 
-// an input row, widened
+// an input row, widened; zeros behind its end, where an infinity of the last piece would meet the zeros of inside_row
 template <int VPL>
 __device__ __forceinline__ void load_center(const float* __restrict__ table, int64_t row, int dim, int l16, float4 (&u)[VPL]) {
   RawRow<float, VPL> x;
@@ -331,6 +331,7 @@ template <int VPL, typename T, if_16bit<T> = 0>
 __device__ __forceinline__ void load_center(const T* __restrict__ table, int64_t row, int dim, int l16, float4 (&u)[VPL]) {
   RawRow<T, VPL> x;
   load_raw<VPL>(table, row, dim, l16, x);
+  x = inside_row<VPL>(x, dim, l16);
 #pragma unroll
   for (int w = 0; w < VPL / 2; ++w) {
     const uint4 q = x.r[w];

@@ -119,3 +119,27 @@ def test_short_16bit_rows(oracle, fmt, dim, n, b, k):
     assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
     for d, h in zip(dev, host):
         assert_half_close(d.view(torch.int16).cpu().numpy().view(np.uint16), h, fmt)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("table", [0, 1])
+@pytest.mark.parametrize("n,b,k", [(100_000, 1_500, 6), (20_000, 9_000, 3), (30_000, 30_000, 10)])
+def test_infinity_in_the_last_piece(fmt, table, n, b, k):
+    """An infinity among the last columns of a row that leaves lanes of the forward kernel without a piece: the rows come out as
+    the same rows do with zeros up to the columns that fill the lanes."""
+    from paper_2407_15452_amd import binding as gs
+    dtype = torch.bfloat16 if fmt == "bf16" else torch.float16
+    c, o, neg = (_dev(x) for x in _batch("even", n, b, k, np.random.default_rng(b)))
+    wide = [torch.zeros((n, 256), dtype=dtype) for _ in range(2)]
+    for w, t in zip(wide, _tables(n, 200, 2, n)):
+        w[:, :200] = t.to(dtype)
+    wide[table][(c if table == 0 else o)[17].item(), 197] = float("inf")
+    short = [w[:, :200].contiguous().to(DEV) for w in wide]
+    wide = [w.to(DEV) for w in wide]
+    for tabs in (short, wide):
+        assert np.isnan(float(gs.gs_sgns_step(*tabs, c, o, neg, 0.01).item()))
+    for s, w in zip(short, wide):
+        # (NaN may carry any bits)
+        s, w = s.cpu(), w[:, :200].cpu()
+        assert torch.equal(s.isnan(), w.isnan())
+        assert torch.equal(s.nan_to_num(nan=0.0), w.nan_to_num(nan=0.0))
