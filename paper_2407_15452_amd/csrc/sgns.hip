@@ -1972,8 +1972,12 @@ static SgnsPlan plan_sgns(void* ws, int64_t num_pairs, int64_t num_nodes, int32_
 
 // Batches of at least this many terms on more rows than can be grouped take the sorted records.  Times of the counters over those
 // of the records (in four passes of 8 bits; three of 9 are faster): 4.8 M terms on 18 M rows 1.02 to 1.14, 16 M terms 1.06 to 1.16; 25 M rows of 256
-// bf16 columns, 22 M terms 8697 / 7879 us; 100 M rows of 128 fp32 columns, 24 M terms 11866 / 10166 us
-constexpr int64_t kSortedMinTerms = (int64_t)9 << 19;
+// bf16 columns, 22 M terms 8697 / 7879 us; 100 M rows of 128 fp32 columns, 24 M terms 11866 / 10166 us.  On fewer rows the records are grouped; in a workspace
+// that has no room for that but for the sorted ones, which take up to 3 % less, these still beat the counters (2 M pairs, 128 fp32 columns, 4 M
+// nodes 2411 / 2579 us).  Few rows with busy counters: from fewer terms on (batches of walks, counters over records: 65,536 rows and less,
+// 2.0 M terms 0.99 to 1.23; 100 k rows, 4.8 M terms 0.90 to 1.07, 8 M 1.02 to 1.21).
+constexpr int64_t kSortedMinTerms = (int64_t)9 << 19, kSortedMinTermsFewRows = (int64_t)3 << 21, kSortedFewRows = (int64_t)1 << 17;
+constexpr int64_t kSortedMinTermsFewest = (int64_t)1 << 20, kSortedFewestRows = (int64_t)1 << 16;
 // Sorted terms per wave of the update: the ends of a slice cost four loads of keys (256 against 128 terms:
 // 2407 / 2425 us for 12 million terms on 4 M rows), and a short batch has to make enough waves.
 static int sorted_slice_for(int64_t num_terms) { return num_terms >= ((int64_t)1 << 22) ? 256 : 128; }
@@ -1984,7 +1988,8 @@ static int bits_for_rows(int64_t num_nodes) {
   return b;
 }
 
-static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim) {
+// wide: with room for the fewest passes of the sort
+static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int32_t k, int32_t dim, bool wide) {
   Carver cv(ws);
   SgnsPlan p = {};
   const size_t b = (size_t)num_pairs, terms = b * (size_t)(k + 1), nodes = (size_t)num_nodes;
@@ -2003,7 +2008,7 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
     p.term_key[i] = cv.take<uint32_t>(terms);
     p.term_src[i] = cv.take<uint2>(terms);
   }
-  p.sort_bytes = radix_sort_scratch_bytes((int64_t)terms, true);
+  p.sort_bytes = radix_sort_scratch_bytes((int64_t)terms, wide);
   p.sort_scratch = cv.take<char>(p.sort_bytes);
   p.cnt = cv.take<uint32_t>((size_t)p.cnt_last + 1 + 3);                   // cleared 16 bytes at a time
   p.key_table = p.table_places > 0 ? cv.take<uint32_t>((size_t)p.table_places) : nullptr;
@@ -2054,7 +2059,9 @@ static int grouped_slice_for(int64_t num_terms) {
 }
 
 static bool sorted_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
-  return num_pairs * (int64_t)(k + 1) >= kSortedMinTerms && !can_group(num_nodes);
+  const int64_t terms = num_pairs * (int64_t)(k + 1);
+  if (num_nodes <= kSortedFewestRows) return terms >= (k >= 2 ? kSortedMinTermsFewest : 2 * kSortedMinTermsFewest);
+  return terms >= (num_nodes <= kSortedFewRows ? kSortedMinTermsFewRows : kSortedMinTerms);
 }
 
 // Batches of at most this many ids (contexts, negatives, centres) take the two-launch step: every
@@ -2101,7 +2108,7 @@ static SgnsPlan plan_small(void* ws, int64_t num_pairs, int32_t k, int32_t dim, 
 // The plan of a step in a workspace of ws_bytes, of which the call's own arrays take `extra` bytes
 // behind the plan; false: too small.  Every call needs room for the counters' plan, whatever its
 // batch takes; with more room, the two-launch step where the batch is small (two_launches: the call can take
-// it) and records where it is large (sort_records: the call can take sorted ones).
+// it) and records where it is large, grouped or, where there is less room, sorted (sort_records: the call can take those).
 static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int64_t num_pairs, int64_t num_nodes,
                       int32_t k, int32_t dim, int32_t dtype, bool two_launches = true, bool force_compact = false,
                       bool sort_records = true) {
@@ -2114,10 +2121,12 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
   if (grouped_batch(num_pairs, num_nodes, k)) {
     p = plan_grouped(ws, num_pairs, num_nodes, k, dim);
     if (p.bytes + extra <= ws_bytes) return true;
-  } else if (sort_records && sorted_batch(num_pairs, num_nodes, k)) {
-    p = plan_sorted(ws, num_pairs, num_nodes, k, dim);
-    if (p.bytes + extra <= ws_bytes) return true;
   }
+  if (sort_records && sorted_batch(num_pairs, num_nodes, k))
+    for (const bool wide : {true, false}) {
+      p = plan_sorted(ws, num_pairs, num_nodes, k, dim, wide);
+      if (p.bytes + extra <= ws_bytes) return true;
+    }
   p = counters;
   return true;
 }
@@ -2127,7 +2136,7 @@ static size_t plan_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_
   if (two_launches && small_batch(num_pairs, num_nodes, k, dim, dtype))
     bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
   if (grouped_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_grouped(nullptr, num_pairs, num_nodes, k, dim).bytes);
-  else if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  else if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim, true).bytes);
   return bytes;
 }
 // The same over all batches of up to num_pairs: the workspace of a program's largest batch serves every

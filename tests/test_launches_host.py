@@ -136,14 +136,14 @@ def test_width_of_positions(launches, walks):
 
 
 STEP = """
-def step(call, pairs, nodes, dim, dtype=0, k=5):
+def step(call, pairs, nodes, dim, dtype=0, k=5, ws=1 << 50):
     p = [C.c_void_p(1 << (20 + i)) for i in range(12)]
     head = p[:{'gs_sgns_step': 2, 'gs_sgns_momentum_step': 4, 'gs_sgns_adam_step': 6}[call]]
     rates = {'gs_sgns_step': [0.1], 'gs_sgns_momentum_step': [0.1, 0.9], 'gs_sgns_adam_step': [0.1, 0.9, 0.999, 1e-8]}[call]
     tail = [C.c_int64(3)] if call == 'gs_sgns_adam_step' else []
     form = [C.c_int32(dtype)] if call != 'gs_sgns_adam_step' else []
     return getattr(lib, call)(*head, C.c_int64(nodes), C.c_int32(dim), *form, *p[6:9], C.c_int64(pairs), C.c_int32(k),
-                              *[C.c_float(r) for r in rates], *tail, p[9], p[10], C.c_size_t(1 << 50), None)
+                              *[C.c_float(r) for r in rates], *tail, p[9], p[10], C.c_size_t(ws), None)
 """
 
 
@@ -217,6 +217,19 @@ def test_ways_of_large_steps(launches, call, pairs, nodes, k, how):
     names = " ".join(x[0] for x in got)
     assert ("group_bucket_kernel" in names, "radix_scatter_kernel" in names, "sgns_clear_kernel" in names) == (
         how == "group", how == "radix", how != "group")
+
+
+@pytest.mark.parametrize("pairs,nodes,k,dim,bytes", [
+    (2_000_000, 4_000_000, 5, 128, 1_448_071_680), (200_000, 60_000, 5, 64, 96_867_840), (1_100_000, 5_000, 1, 32, 224_405_248),
+    (1_100_000, 100_000, 5, 64, 483_285_504)])
+def test_ways_of_large_steps_in_smaller_workspaces(launches, pairs, nodes, k, dim, bytes):
+    """A workspace that holds no grouped records holds sorted ones: the sizes are those that these records took before
+    there were others, with counts of 8-bit digits."""
+    for ws, how in ((1 << 50, "group"), (bytes, "radix")):
+        got, rc = launches(STEP + "print(json.dumps({'rc': step('gs_sgns_step', %d, %d, %d, 0, %d, %d)}))\n" % (pairs, nodes, dim, k, ws))
+        assert rc == [0]
+        names = " ".join(x[0] for x in got)
+        assert ("group_bucket_kernel" in names, "radix_scatter_kernel" in names) == (how == "group", how == "radix"), how
 
 
 def test_workspaces_grow_with_the_batch(launches):
