@@ -6,9 +6,8 @@
 namespace gs {
 
 constexpr uint32_t kNoGroupRow = 0xffffffffu;  // (rows are below 2^31)
-constexpr int kGroupLeastSegment = 6;          // segments of rows have at least 2^6 records
-// device counters: pieces of split buckets, split buckets, their rows, long rows, records of both kinds
-enum : int { kGroupPieces, kGroupSplit, kGroupSplitRows, kGroupLong, kGroupRecords, kGroupCounters };
+// device counters: pieces of split buckets, rows of split buckets, long rows, records of both kinds
+enum : int { kGroupPieces, kGroupSplitRows, kGroupLong, kGroupRecords, kGroupCounters };
 
 struct GroupArgs {
   // records of the first kind (rows below 2^31) and the list of rows of the second kind (-1: no record)
@@ -35,9 +34,9 @@ struct GroupArgs {
   uint32_t second_named;         // the same of the second kind
   uint32_t* counts;              // [tiles][buckets] of one kind, then of the other
   uint32_t *totals, *starts;     // [digits] records of a bucket, and the first of them
-  uint4* pieces;                 // of the buckets to split: bucket, place of its rows in row_next, piece, number of the bucket
-  uint32_t* pieces_left;         // [buckets to split] pieces whose rows have not been counted
-  uint32_t* row_next;            // of the rows of the buckets to split: their counts, then the places of their next records
+  uint4* pieces;                 // of the buckets to split: bucket, place of its rows in the next two, piece, pieces of the bucket
+  uint32_t* row_counts;          // of the rows of the buckets to split: their records, and
+  uint32_t* row_taken;           // those that pieces have taken places for
   uint32_t digits;               // buckets of both kinds
   // set by group_rows
   int row_bits, second_row_bits;
@@ -48,6 +47,8 @@ struct GroupArgs {
 };
 
 bool can_group(int64_t rows);
+constexpr int kBucketRowBits = 14;             // rows of a bucket: their counters fit a workgroup's LDS
+int64_t group_border(int64_t rows, bool second, int bits);
 void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t rows, int32_t seg_shift, bool marks);
 int32_t group_rows(GroupArgs a, int64_t rows, hipStream_t stream);       // n >= 1, n + second_n < 2^32
 

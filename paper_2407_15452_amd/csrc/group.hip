@@ -13,14 +13,17 @@
 //
 // Buckets of more records than a workgroup takes (a single row may have any number) are split: the prefix sums enter them in a list,
 // in pieces, the bucket kernel adds up the counts of their rows in global memory, and one more launch, which otherwise looks at the length of
-// the list and returns, moves their records.  All 12 million records in one row: 0.32 ms.
+// the list and returns, moves their records: every piece sums the counts of its bucket's rows by itself, so that no workgroup waits for what
+// another of the same launch has written.  (With the last piece of a bucket summing them in the same launch, the release and acquire around that took 50 to
+// 90 us where other workgroups were writing: 4 million records of a batch of walks on 5000 nodes, 64 buckets split, bucket kernel 121 -> 36 us and the
+// launch behind it 17 -> 18; without fences 521 -> 437 us the step.)  All 12 million records in one row, 128 fp32 columns: a step of
+// 2.84 ms (3.24).
 #include "group.h"
 
 namespace gs {
 
 constexpr int kBucketThreads = 1024, kBucketWaves = kBucketThreads / 64;
 constexpr int kBucketItems = 9, kBucketItemsMost = 16;         // records per lane: two workgroups, or one, share a compute unit's LDS
-constexpr int kBucketRowBits = 14;             // rows of a bucket: their counters fit a workgroup's LDS
 constexpr int64_t kBuckets = 2048, kSecondBuckets = 1024;      // most buckets of either kind of rows
 // Records per bucket, which leave a bucket of 9216 room for uneven rows; fewer where that keeps compute units busy.
 constexpr int64_t kBucketMean = 6000, kBucketMeanLeast = 1024, kBusyBuckets = 256, kBucketMeanMost = 7000;
@@ -98,7 +101,6 @@ constexpr int kScanDigits = 16, kScanStretches = 1024 / kScanDigits;
 __global__ __launch_bounds__(1024) void group_scan_kernel(GroupArgs a) {
   __shared__ uint32_t sums[kScanStretches][kScanDigits + 1];
   __shared__ uint32_t total_s[kScanDigits];
-  __shared__ uint32_t at_s[3];
   const bool second = blockIdx.x >= a.first_scans;
   const uint32_t digits = second ? a.digits - a.buckets : a.buckets, first_digit = second ? a.buckets : 0u;
   const uint32_t d0 = (second ? blockIdx.x - a.first_scans : blockIdx.x) * kScanDigits;       // among the kind's buckets
@@ -144,22 +146,21 @@ __global__ __launch_bounds__(1024) void group_scan_kernel(GroupArgs a) {
       run += v[u];
     }
   }
-  for (int w = 0; w < kScanDigits; ++w) {        // (buckets behind the last have no records)
+  {                                              // wave w: bucket w, if it is to be split (those behind the last have no records)
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t total = total_s[w];
-    if (total <= a.most) continue;
-    const uint32_t pieces = (total + a.most - 1) / a.most, bucket = first_digit + d0 + (uint32_t)w;
+    if (total <= a.most) return;
+    const uint32_t pieces = (total + a.most - 1) / a.most;
     const uint32_t rows = 1u << (second ? a.second_row_bits : a.row_bits);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      at_s[0] = atomicAdd(a.counters + kGroupPieces, pieces);
-      at_s[1] = atomicAdd(a.counters + kGroupSplitRows, rows);
-      at_s[2] = atomicAdd(a.counters + kGroupSplit, 1u);
-      a.pieces_left[at_s[2]] = pieces;
+    uint32_t first = 0, rows_at = 0;
+    if (lane == 0) {
+      first = atomicAdd(a.counters + kGroupPieces, pieces);
+      rows_at = atomicAdd(a.counters + kGroupSplitRows, rows);
     }
-    __syncthreads();
-    const uint32_t first = at_s[0], rows_at = at_s[1], number = at_s[2];
-    for (uint32_t i = threadIdx.x; i < pieces; i += 1024u) a.pieces[first + i] = make_uint4(bucket, rows_at, i, number);
-    for (uint32_t r = threadIdx.x; r < rows; r += 1024u) a.row_next[rows_at + r] = 0u;
+    first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+    rows_at = (uint32_t)__builtin_amdgcn_readfirstlane((int)rows_at);
+    for (uint32_t i = lane; i < pieces; i += 64u) a.pieces[first + i] = make_uint4(first_digit + d0 + (uint32_t)w, rows_at, i, pieces);
+    for (uint32_t r = lane; r < rows; r += 64u) a.row_counts[rows_at + r] = a.row_taken[rows_at + r] = 0u;
   }
 }
 
@@ -285,9 +286,33 @@ __device__ __forceinline__ BucketOf bucket_of(const GroupArgs& a, uint32_t b) {
   return o;
 }
 
-// counts of rows into exclusive prefix sums, by the whole workgroup; each(row, its count, the records before it) on the way
-template <typename Each>
-__device__ __forceinline__ void bucket_scan(uint32_t* count, int rows, uint32_t* part, Each each) {
+// count[row] += 1 for the live lanes, and how many came before.  Lanes that name one row are served one after the other (17 cycles each), so rows that
+// many lanes of the wave name are added once.
+__device__ __forceinline__ uint32_t count_row(uint32_t* count, uint32_t row, bool live) {
+  constexpr int kMany = 8;
+  const int lane = threadIdx.x & 63;
+  unsigned long long todo = __ballot(live);
+  uint32_t add = live ? 1u : 0u, before = 0u;
+  int adds = lane;
+  while (todo != 0ull) {
+    const int l = __builtin_ctzll(todo);
+    const bool same = live && row == (uint32_t)__builtin_amdgcn_readlane((int)row, l);
+    const unsigned long long peers = __ballot(same);
+    if (__popcll(peers) < kMany) break;
+    if (same) {
+      adds = l;
+      add = lane == l ? (uint32_t)__popcll(peers) : 0u;
+      before = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
+    }
+    todo &= ~peers;
+  }
+  uint32_t at = 0u;
+  if (add != 0u) at = atomicAdd(&count[row], add);
+  return (uint32_t)__shfl((int)at, adds, 64) + before;
+}
+
+// counts of rows into exclusive prefix sums, by the whole workgroup
+__device__ __forceinline__ void bucket_scan(uint32_t* count, int rows, uint32_t* part) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int per = max(1, rows / kBucketThreads), first = (int)threadIdx.x * per;
   uint32_t own = 0;
@@ -304,24 +329,42 @@ __device__ __forceinline__ void bucket_scan(uint32_t* count, int rows, uint32_t*
     for (int o = 0; o < per; ++o) {
       const uint32_t c = count[first + o];
       count[first + o] = run;
-      each(first + o, c, run);
       run += c;
     }
   }
   __syncthreads();
 }
 
-// A row of more than one segment: entered in the list of long rows.
-__device__ __forceinline__ void enter_long_row(const GroupArgs& a, uint32_t key, uint32_t slot) {
-  const uint32_t at = atomicAdd(a.counters + kGroupLong, 1u);
-  a.long_rows[at] = make_uint2(key, slot);
+// What the grouping says of the rows of a bucket of `total` records besides their order, from the rows' first places in it: marks, long rows.  A wave
+// takes 64 rows at a time, and of those every pieces-th one (the pieces of a split bucket share them); a long row's slot is cleared by its lanes
+// together.
+__device__ __forceinline__ void tell_of_rows(const GroupArgs& a, const BucketOf& b, const uint32_t* first, uint32_t total, uint32_t piece,
+                                             uint32_t pieces) {
+  const uint32_t rows = 1u << b.row_bits;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  for (uint32_t r0 = (wave * pieces + piece) * 64u; r0 < rows; r0 += kBucketThreads * pieces) {
+    const uint32_t r = r0 + lane;
+    const uint32_t before = r < rows ? first[r] : total, behind = r + 1u < rows ? first[r + 1u] : total;
+    if (a.named != nullptr && r < rows) a.named[b.named + r] = behind != before ? 1 : 0;
+    const bool is_long = behind - before > 1u << a.seg_shift;
+    const uint32_t slot = (uint32_t)((b.base + before) >> a.seg_shift);
+    unsigned long long longs = __ballot(is_long);
+    if (longs == 0ull) continue;
+    uint32_t at = 0;
+    if (lane == 0u) at = atomicAdd(a.counters + kGroupLong, (uint32_t)__popcll(longs));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (is_long) a.long_rows[at + (uint32_t)__popcll(longs & ((1ull << lane) - 1ull))] = make_uint2(b.key + r, slot);
+    for (; longs != 0ull; longs &= longs - 1ull) {
+      const int64_t s = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)slot, __builtin_ctzll(longs));
+      for (int x = (int)lane; x < a.dim; x += 64) a.long_acc[s * a.dim + x] = 0;
+    }
+  }
 }
 
-// The pieces in the list of buckets to split: the counts of their rows are added up in global memory, and who adds the last of a bucket's
-// turns them into the rows' first places.
-template <int kMost>
-__device__ __forceinline__ void count_pieces(const GroupArgs& a, uint32_t first_piece, uint32_t stride, uint32_t* count, uint32_t* part,
-                                             uint32_t* last_s) {
+// The pieces in the list of buckets to split: the counts of their rows are added up in global memory.
+template <int ITEMS>
+__device__ __forceinline__ void count_pieces(const GroupArgs& a, uint32_t first_piece, uint32_t stride, uint32_t* count) {
+  constexpr int kMost = kBucketThreads * ITEMS;
   const int tid = threadIdx.x;
   const uint32_t pieces = a.counters[kGroupPieces];
   for (uint32_t j = first_piece; j < pieces; j += stride) {
@@ -329,33 +372,18 @@ __device__ __forceinline__ void count_pieces(const GroupArgs& a, uint32_t first_
     const BucketOf b = bucket_of(a, piece.x);
     const int rows = 1 << b.row_bits;
     const uint32_t* piece_rows = a.rows_mid + b.base + (int64_t)piece.z * kMost;
-    uint32_t* row_next = a.row_next + piece.y;
     const int live = (int)min((uint32_t)kMost, a.totals[piece.x] - piece.z * (uint32_t)kMost);
     for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
+    uint32_t row[ITEMS];
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c)
+      row[c] = c * kBucketThreads + tid < live ? piece_rows[c * kBucketThreads + tid] & (uint32_t)(rows - 1) : 0u;
     __syncthreads();
-#pragma unroll 4
-    for (int i = tid; i < live; i += kBucketThreads) atomicAdd(&count[piece_rows[i] & (uint32_t)(rows - 1)], 1u);
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) count_row(count, row[c], c * kBucketThreads + tid < live);
     __syncthreads();
     for (int r = tid; r < rows; r += kBucketThreads)
-      if (count[r] != 0u) atomicAdd(row_next + r, count[r]);
-    __threadfence();
-    __syncthreads();
-    if (tid == 0) *last_s = atomicSub(a.pieces_left + piece.w, 1u);
-    __syncthreads();
-    if (*last_s == 1u) {
-      __threadfence();
-      for (int r = tid; r < rows; r += kBucketThreads) count[r] = __hip_atomic_load(row_next + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __syncthreads();
-      bucket_scan(count, rows, part, [&](int r, uint32_t c, uint32_t before) {
-        row_next[r] = before;
-        if (a.named != nullptr) a.named[b.named + r] = c != 0u ? 1 : 0;
-        if (c > 1u << a.seg_shift) {
-          const uint32_t slot = (uint32_t)((b.base + before) >> a.seg_shift);
-          enter_long_row(a, b.key + (uint32_t)r, slot);
-          for (int x = 0; x < a.dim; ++x) a.long_acc[(int64_t)slot * a.dim + x] = 0;
-        }
-      });
-    }
+      if (count[r] != 0u) atomicAdd(a.row_counts + piece.y + r, count[r]);
     __syncthreads();
   }
 }
@@ -365,14 +393,12 @@ template <int ITEMS>
 __global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void group_bucket_kernel(GroupArgs a) {
   constexpr int kMost = kBucketThreads * ITEMS;
   static_assert(kMost * sizeof(uint2) >= sizeof(uint32_t) << kBucketRowBits, "the counters lie where the records are put in order");
-  constexpr int kLongMost = kMost >> kGroupLeastSegment;         // rows of more than one segment in a bucket
   __shared__ __align__(16) unsigned char bytes[kMost * sizeof(uint2)];
   __shared__ uint32_t part[kBucketWaves];
-  __shared__ uint32_t long_s[kLongMost], long_n;
   uint32_t* count = reinterpret_cast<uint32_t*>(bytes);
   const int tid = threadIdx.x;
   if (blockIdx.x >= a.digits) {
-    count_pieces<kMost>(a, blockIdx.x - a.digits, gridDim.x - a.digits, count, part, &long_n);
+    count_pieces<ITEMS>(a, blockIdx.x - a.digits, gridDim.x - a.digits, count);
     return;
   }
   const uint32_t total = a.totals[blockIdx.x];
@@ -382,7 +408,6 @@ __global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void
   const int rows = 1 << (second ? a.second_row_bits : a.row_bits);
   const uint32_t mask = (uint32_t)rows - 1u;
   for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
-  if (tid == 0) long_n = 0u;
   const BucketOf b = bucket_of(a, blockIdx.x);
   __syncthreads();
   if (total == 0u) {
@@ -409,14 +434,8 @@ __global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void
   for (int c = 0; c < ITEMS; ++c)
     if (c * kBucketThreads + tid < live) at[c] |= atomicAdd(&count[at[c]], 1u) << kBucketRowBits;
   __syncthreads();
-  bucket_scan(count, rows, part, [&](int r, uint32_t c, uint32_t before) {
-    if (a.named != nullptr) a.named[b.named + r] = c != 0u ? 1 : 0;
-    if (c > 1u << a.seg_shift) {
-      const uint32_t slot = (uint32_t)((b.base + before) >> a.seg_shift);
-      long_s[atomicAdd(&long_n, 1u)] = slot;
-      enter_long_row(a, b.key + (uint32_t)r, slot);
-    }
-  });
+  bucket_scan(count, rows, part);
+  tell_of_rows(a, b, count, total, 0u, 1u);
 #pragma unroll
   for (int c = 0; c < ITEMS; ++c)
     if (c * kBucketThreads + tid < live) at[c] += count[at[c] & kRowMask] << kBucketRowBits;
@@ -438,36 +457,40 @@ __global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void
 #pragma unroll
   for (int c = 0; c < ITEMS; ++c)
     if (c * kBucketThreads + tid < live) keys_to[c * kBucketThreads + tid] = stage[c * kBucketThreads + tid];
-  for (uint32_t l = 0; l < long_n; ++l)
-    for (int x = tid; x < a.dim; x += kBucketThreads) a.long_acc[(int64_t)long_s[l] * a.dim + x] = 0;
 }
 
 // The pieces in the list: a piece takes the next places of its rows and moves its records there.
 template <int ITEMS>
 __global__ __launch_bounds__(kBucketThreads) void group_split_kernel(GroupArgs a) {
   constexpr int kMost = kBucketThreads * ITEMS;
-  __shared__ uint32_t count[1 << kBucketRowBits];
+  __shared__ uint32_t first[1 << kBucketRowBits];                // of a row of the bucket: the records before it,
+  __shared__ uint32_t count[1 << kBucketRowBits];                // those of this piece, then the place of the first of them
+  __shared__ uint32_t part[kBucketWaves];
   const int tid = threadIdx.x;
   const uint32_t pieces = a.counters[kGroupPieces];
   for (uint32_t j = blockIdx.x; j < pieces; j += gridDim.x) {
     const uint4 piece = a.pieces[j];
     const BucketOf b = bucket_of(a, piece.x);
     const int rows = 1 << b.row_bits;
-    const uint32_t mask = (uint32_t)rows - 1u;
+    const uint32_t mask = (uint32_t)rows - 1u, total = a.totals[piece.x];
     const int64_t base = b.base + (int64_t)piece.z * kMost;
-    const int live = (int)min((uint32_t)kMost, a.totals[piece.x] - piece.z * (uint32_t)kMost);
-    for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
+    const int live = (int)min((uint32_t)kMost, total - piece.z * (uint32_t)kMost);
+    for (int r = tid; r < rows; r += kBucketThreads) {
+      first[r] = a.row_counts[piece.y + r];
+      count[r] = 0u;
+    }
     uint32_t row[ITEMS], rank[ITEMS];
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c)
-      if (c * kBucketThreads + tid < live) row[c] = a.rows_mid[base + c * kBucketThreads + tid] & mask;
+      row[c] = c * kBucketThreads + tid < live ? a.rows_mid[base + c * kBucketThreads + tid] & mask : 0u;
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c)
-      if (c * kBucketThreads + tid < live) rank[c] = atomicAdd(&count[row[c]], 1u);
-    __syncthreads();
+      rank[c] = count_row(count, row[c], c * kBucketThreads + tid < live);
+    bucket_scan(first, rows, part);
     for (int r = tid; r < rows; r += kBucketThreads)
-      if (count[r] != 0u) count[r] = atomicAdd(a.row_next + piece.y + r, count[r]);
+      if (count[r] != 0u) count[r] = first[r] + atomicAdd(a.row_taken + piece.y + r, count[r]);
+    tell_of_rows(a, b, first, total, piece.z, piece.w);
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c)
@@ -514,7 +537,14 @@ static GroupPlan plan_group(int64_t n, int64_t second_n, int64_t rows) {
 
 bool can_group(int64_t rows) { return ceil_div(rows, (int64_t)1 << kBucketRowBits) <= kSecondBuckets; }
 
-// (no array is smaller for more records: a caller's workspace for its largest batch serves every batch)
+// The most records of a kind that are grouped in buckets of 2^bits rows or more (behind it, there are more buckets of fewer rows); 0: no border.
+int64_t group_border(int64_t rows, bool second, int bits) {
+  if (bits <= 0 || bits > kBucketRowBits || ceil_div(rows, (int64_t)1 << (bits - 1)) > (second ? kSecondBuckets : kBuckets)) return 0;
+  const int64_t buckets = ceil_div(rows, (int64_t)1 << bits);
+  return buckets * (buckets >= kBusyBuckets ? kBucketMean : kBucketMeanLeast);
+}
+
+// (but for the rows of the buckets to split, which are fewer behind a border, no array is smaller for more records)
 void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t rows, int32_t seg_shift, bool marks) {
   const GroupPlan p = plan_group(n, second_n, rows);
   a.digits = (uint32_t)(p.buckets + p.second_buckets);
@@ -526,14 +556,10 @@ void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t r
   const size_t records = (size_t)(n + second_n);
   const size_t split = records / (size_t)(kBucketThreads * kBucketItems) + 1;        // (each has more records than that)
   const size_t all_rows = 2 * ((size_t)rows + ((size_t)1 << kBucketRowBits));        // of the buckets of both kinds
-  // rows of the buckets to split: of at most kBucketMean / (kBucketThreads * kBucketItems) of a kind's buckets (< 2 / 3) where there are as
-  // many buckets as their mean size wants
-  auto split_rows_of = [&](int64_t m, int64_t buckets) {
-    const size_t most = (size_t)(m / (kBucketThreads * kBucketItems) + 1) << kBucketRowBits;
-    const size_t all = (size_t)rows + ((size_t)1 << kBucketRowBits);
-    return std::min(most, ceil_div(m, buckets) > kBucketMean ? all : all / 3 * 2 + ((size_t)1 << kBucketRowBits));
+  auto split_rows_of = [&](int64_t m, int64_t buckets, int row_bits) {
+    return (size_t)std::min(m / (kBucketThreads * kBucketItems) + 1, buckets) << row_bits;
   };
-  const size_t split_rows = split_rows_of(n, p.buckets) + split_rows_of(second_n, p.second_buckets);
+  const size_t split_rows = split_rows_of(n, p.buckets, p.row_bits) + split_rows_of(second_n, p.second_buckets, p.second_row_bits);
   // (the marks are written when the counts have been read for the last time)
   a.counts = cv.take<uint32_t>(marks ? std::max(counts, all_rows / sizeof(uint32_t)) : counts);
   a.named = marks ? reinterpret_cast<uint8_t*>(a.counts) : nullptr;
@@ -541,8 +567,8 @@ void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t r
   a.starts = cv.take<uint32_t>((size_t)(kBuckets + kSecondBuckets));
   a.counters = cv.take<uint32_t>(kGroupCounters);
   a.pieces = cv.take<uint4>(2 * split);
-  a.pieces_left = cv.take<uint32_t>(split);
-  a.row_next = cv.take<uint32_t>(split_rows);
+  a.row_counts = cv.take<uint32_t>(split_rows);
+  a.row_taken = cv.take<uint32_t>(split_rows);
   a.long_rows = cv.take<uint2>((records >> seg_shift) + 1);
   a.second_named = (uint32_t)(p.buckets << p.row_bits);
 }

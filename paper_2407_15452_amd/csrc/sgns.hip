@@ -2154,6 +2154,9 @@ static size_t step_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_
                           small_ids / (k + 2)};           // of those with two launches
   for (const int64_t pairs : last)
     if (pairs > 0 && pairs < num_pairs) bytes = std::max(bytes, plan_bytes(pairs, num_nodes, k, dim, dtype, two_launches));
+  for (int bits = kBucketRowBits; bits > 0; --bits)       // of grouped ones with more rows per bucket
+    for (const int64_t pairs : {group_border(num_nodes, false, bits) / (k + 1), group_border(num_nodes, true, bits)})
+      if (pairs < num_pairs && grouped_batch(pairs, num_nodes, k)) bytes = std::max(bytes, plan_bytes(pairs, num_nodes, k, dim, dtype, two_launches));
   return bytes;
 }
 

@@ -239,3 +239,13 @@ def test_workspaces_grow_with_the_batch(launches):
                        "    now = f(C.c_int64(b), C.c_int64(n), C.c_int32(5), C.c_int32(64), C.c_int32(0))\n"
                        "    if now < last: print(json.dumps({'rc': [n, b]}))\n    last = now\n")
     assert rc == []
+
+
+@pytest.mark.parametrize("nodes", [7, 3_000, 20_000, 300_000, 3_000_000])
+def test_workspaces_grow_past_the_borders_of_buckets(launches, nodes):
+    """Behind a border there are more buckets of fewer rows, and less room for the rows of those that are split."""
+    got, rc = launches("f = lib.gs_sgns_step_workspace_bytes\nf.restype = C.c_size_t\nfor k in (0, 1, 5, 10):\n"
+                       "  last, b = 0, 20000\n  while b < 1 << 23:\n"
+                       "    now = f(C.c_int64(b), C.c_int64(%d), C.c_int32(k), C.c_int32(4), C.c_int32(0))\n"
+                       "    if now < last: print(json.dumps({'rc': [k, b]}))\n    last, b = now, b + b // 500 + 1\n" % nodes)
+    assert rc == []
