@@ -29,6 +29,8 @@ struct GroupArgs {
   long long* long_acc;           // [((n + second_n) >> seg_shift) + 1][dim]
   // taken from the caller's memory by group_take
   uint2* long_rows;
+  uint2* further;                // [((n + second_n) >> seg_shift) + 2] entry w: the one position of [w << seg_shift, (w + 1) << seg_shift) at which a
+                                 // segment of a row other than its first starts, and the row's first position; else kNoGroupRow
   uint32_t* counters;            // [kGroupCounters]
   uint8_t* named;                // null, or marks: entry r is 1 if row r of the first kind has a record, entry second_named + r
   uint32_t second_named;         // the same of the second kind

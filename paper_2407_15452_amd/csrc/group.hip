@@ -73,6 +73,9 @@ __global__ __launch_bounds__(kTileThreads) void group_count_kernel(GroupArgs a) 
   uint32_t* flat = &hist[0][0];
   for (int i = threadIdx.x; i < kCopies * DIGITS; i += kTileThreads) flat[i] = 0u;
   if (blockIdx.x == 0 && threadIdx.x < kGroupCounters) a.counters[threadIdx.x] = 0u;
+  const int64_t windows = ((a.n + a.second_n) >> a.seg_shift) + 2, windows_each = (windows + gridDim.x - 1) / gridDim.x;
+  for (int64_t w = blockIdx.x * windows_each + threadIdx.x; w < min(windows, (blockIdx.x + 1) * windows_each); w += kTileThreads)
+    a.further[w] = make_uint2(kNoGroupRow, 0u);
   const TileOf t = tile_of(a, blockIdx.x, kTileThreads * ITEMS);
   const uint32_t* rows = t.second ? reinterpret_cast<const uint32_t*>(a.second) : a.rows;
   uint32_t row[ITEMS];
@@ -335,9 +338,9 @@ __device__ __forceinline__ void bucket_scan(uint32_t* count, int rows, uint32_t*
   __syncthreads();
 }
 
-// What the grouping says of the rows of a bucket of `total` records besides their order, from the rows' first places in it: marks, long rows.  A wave
-// takes 64 rows at a time, and of those every pieces-th one (the pieces of a split bucket share them); a long row's slot is cleared by its lanes
-// together.
+// What the grouping says of the rows of a bucket of `total` records besides their order, from the rows' first places in it: marks, long rows and
+// their segments.  A wave takes 64 rows at a time, and of those every pieces-th one (the pieces of a split bucket share them); its lanes clear a long
+// row's slot and enter its segments together.
 __device__ __forceinline__ void tell_of_rows(const GroupArgs& a, const BucketOf& b, const uint32_t* first, uint32_t total, uint32_t piece,
                                              uint32_t pieces) {
   const uint32_t rows = 1u << b.row_bits;
@@ -355,8 +358,13 @@ __device__ __forceinline__ void tell_of_rows(const GroupArgs& a, const BucketOf&
     at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
     if (is_long) a.long_rows[at + (uint32_t)__popcll(longs & ((1ull << lane) - 1ull))] = make_uint2(b.key + r, slot);
     for (; longs != 0ull; longs &= longs - 1ull) {
-      const int64_t s = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)slot, __builtin_ctzll(longs));
+      const int l = __builtin_ctzll(longs);
+      const int64_t s = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)slot, l);
       for (int x = (int)lane; x < a.dim; x += 64) a.long_acc[s * a.dim + x] = 0;
+      const uint32_t row_first = (uint32_t)b.base + (uint32_t)__builtin_amdgcn_readlane((int)before, l);
+      const uint32_t records = (uint32_t)__builtin_amdgcn_readlane((int)(behind - before), l);
+      for (uint32_t i = (lane + 1u) << a.seg_shift; i < records; i += 64u << a.seg_shift)
+        a.further[(row_first + i) >> a.seg_shift] = make_uint2(row_first + i, row_first);
     }
   }
 }
@@ -570,6 +578,7 @@ void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t r
   a.row_counts = cv.take<uint32_t>(split_rows);
   a.row_taken = cv.take<uint32_t>(split_rows);
   a.long_rows = cv.take<uint2>((records >> seg_shift) + 1);
+  a.further = cv.take<uint2>((records >> seg_shift) + 2);
   a.second_named = (uint32_t)(p.buckets << p.row_bits);
 }
 

@@ -1491,74 +1491,42 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_long_rows_kernel(SgnsArgs a
 //   records of the context table through the stable sort in three passes); 65,536 pairs, 64 columns on 10 k nodes 90 (104 with the counters).
 //   More rows: the radix sort brings the records of the context table into order; the few input-table terms keep their counters.
 
-// First position >= p (and <= hi) that starts a segment of its row, and the row's first
-// position, among the records [lo, hi).  back and ahead: the keys of the 64 positions before p (lane l: p - 1 - l) and of the 64
-// from p on (kNoRow outside), loaded by the caller so that the loads of both ends of a slice are
-// under way together; almost always they decide.
-__device__ __forceinline__ int64_t sorted_segment_start(const SgnsArgs& a, int64_t p, int lane, uint32_t back,
-                                                        uint32_t ahead, int64_t lo, int64_t hi, int64_t& first_row) {
-  const uint32_t* __restrict__ keys = a.term_key;
-  first_row = p;
-  if (p == lo || p >= hi) return p;
-  const uint32_t key = uniform_u32(ahead);
-  const unsigned long long other_back = __builtin_amdgcn_ballot_w64(back != key);
-  if (other_back & 1ull) return p;                                   // a row starts at p
-  const unsigned long long other_ahead = __builtin_amdgcn_ballot_w64(ahead != key);
-  int64_t first;
-  if (other_back != 0ull) {
-    first = p - __builtin_ctzll(other_back);
-  } else {
-    // the row goes back further: 64 positions at a time, 64 apart, then 4096 apart and so on until one lies in front of the row, and
-    // back down (21 dependent reads of a binary search over a million records instead: a batch of 800,000 pairs on 10,000 rows 397 us)
-    first = max(lo, p - 64);                                          // (keys[first] == key)
-    int shift = 6;
-    auto before = [&]() {                                             // of the 64 positions in front of `first`, how many are the row's
-      const int64_t q = first - ((int64_t)(lane + 1) << shift);
-      const unsigned long long other = __builtin_amdgcn_ballot_w64(q < lo || keys[max(lo, q)] != key);
-      return other != 0ull ? __builtin_ctzll(other) : 64;
-    };
-    int n = before();
-    while (n == 64) {
-      first -= (int64_t)64 << shift;
-      shift += 6;
-      n = before();
-    }
-    for (;;) {
-      first -= (int64_t)n << shift;
-      if (shift == 0) break;
-      shift -= 6;
-      n = before();
-    }
+// First position >= p (p < hi; at most hi) that starts a segment of its row, and the row's first position, among the records [lo, hi).  keys: those of
+// the 64 positions from p - 1 on (kNoRow outside); here and next: the entries of p's window and of the one behind it.  The caller loads them, so
+// that the loads of both ends of a slice are under way together.  A row's first segment starts where the keys change; where its further ones
+// do, whoever brought the records together has written down.  (Searching for the row's first record instead, 64 reads of 64 cache lines, several times, at
+// both ends of every slice in a long row: 7.3 M terms of walks on 5000 nodes, 20 columns 322 us for the context table, now 306; 1.2 M with one negative,
+// 104 columns 103 and, for the input table, 47, now 96 and 45; 12 M on 4 M nodes, 128 columns 964 and 72, now 962 and 71.)
+__device__ __forceinline__ int64_t sorted_segment_start(const SgnsArgs& a, int64_t p, int lane, uint32_t keys, uint2 here, uint2 next,
+                                                        int64_t hi, int64_t& first_row) {
+  const int64_t none = (int64_t)1 << 62;
+  int64_t further = none;                                            // a further segment of p's row
+  if (uniform_u32(here.x) != kNoRow && (int64_t)uniform_u32(here.x) >= p) {
+    further = (int64_t)uniform_u32(here.x);
+    first_row = (int64_t)uniform_u32(here.y);
+  } else if (uniform_u32(next.x) != kNoRow) {
+    further = (int64_t)uniform_u32(next.x);
+    first_row = (int64_t)uniform_u32(next.y);
   }
-  const int64_t segment = (int64_t)1 << a.seg_shift;
-  const int64_t next = first + ((p - first + segment - 1) & ~(segment - 1));      // the row's next segment, if it gets there
-  int64_t row_end = hi;                                              // first position behind the row, as far as it matters
-  if (other_ahead != 0ull) {
-    row_end = p + __builtin_ctzll(other_ahead);
-  } else {
-    for (int64_t x = p + 64; x < min(next, hi); x += 64) {
-      const unsigned long long mask = __builtin_amdgcn_ballot_w64(x + lane >= hi || keys[min(x + lane, hi - 1)] != key);
-      if (mask == 0ull) continue;
-      row_end = x + __builtin_ctzll(mask);
-      break;
-    }
+  for (int64_t q = p;; q += 63) {
+    if (q > further) return further;
+    if (q != p) keys = q - 1 + lane < hi ? a.term_key[q - 1 + lane] : kNoRow;
+    const uint32_t before = (uint32_t)__shfl_up((int)keys, 1, 64);   // (by every lane: lane 1 wants lane 0's)
+    const unsigned long long changes = __builtin_amdgcn_ballot_w64(keys != before) & ~1ull;
+    if (changes == 0ull) continue;                                   // (a segment has at most 2^seg_shift records, and behind hi there is none)
+    const int64_t row = q - 1 + __builtin_ctzll(changes);
+    if (further < row) return further;
+    first_row = row;
+    return row;
   }
-  if (next < row_end && next < hi) {
-    // (next may lie behind the last key looked at: the row's own segment only if it gets there)
-    if (uniform_u32(keys[next]) == key) {
-      first_row = first;
-      return next;
-    }
-  }
-  row_end = min(row_end, next < row_end ? next : row_end);
-  first_row = row_end;
-  return row_end;
 }
 
 // kStage: the records of the input-table rows, which follow those of the context table (grouped batches); their number is on
-// the device, so the launch is sized for the few that a batch normally has and its waves stride over the slices.
+// the device, so the launch is sized for the few that a batch normally has and its waves stride over the slices.  further (behind SgnsArgs: one more
+// field in there costs the forward kernel of narrow rows 12 %): entry w tells of the records [w << seg_shift, (w + 1) << seg_shift) the one that starts
+// a segment of a row other than its first, and the row's first record; else kNoRow.
 template <typename T, int WPP, int PPL, int UB, int kOpt, bool kStage>
-__global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_update_kernel(SgnsArgs a) {
+__global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_update_kernel(SgnsArgs a, const uint2* __restrict__ further) {
   const uint32_t* __restrict__ keys = a.term_key;
   const int lane = threadIdx.x & 63;
   const int64_t first_wave = (int64_t)blockIdx.x * (kSgnsThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1569,11 +1537,12 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_update_kernel(SgnsAr
     if (p0 >= hi) return;
     const int64_t p1 = min(p0 + slice, hi);
     auto key_at = [&](int64_t p) { return p >= lo && p < hi ? keys[p] : kNoRow; };
-    const uint32_t back0 = key_at(p0 - 1 - lane), ahead0 = key_at(p0 + lane);
-    const uint32_t back1 = key_at(p1 - 1 - lane), ahead1 = key_at(p1 + lane);
+    const uint32_t keys0 = key_at(p0 - 1 + lane), keys1 = key_at(p1 - 1 + lane);
+    const uint2 here0 = further[p0 >> a.seg_shift], next0 = further[(p0 >> a.seg_shift) + 1];
+    const uint2 here1 = further[p1 >> a.seg_shift], next1 = further[(p1 >> a.seg_shift) + 1];
     int64_t first_row, unused;
-    const int64_t begin = sorted_segment_start(a, p0, lane, back0, ahead0, lo, hi, first_row);
-    const int64_t end = sorted_segment_start(a, p1, lane, back1, ahead1, lo, hi, unused);
+    const int64_t begin = sorted_segment_start(a, p0, lane, keys0, here0, next0, hi, first_row);
+    const int64_t end = p1 < hi ? sorted_segment_start(a, p1, lane, keys1, here1, next1, hi, unused) : hi;
     update_range<T, WPP, PPL, UB, kOpt, kStage, true, true>(a, nullptr, begin, end, hi, lane, first_row);
     if constexpr (!kStage) return;               // (one slice per wave)
   }
@@ -1581,13 +1550,40 @@ __global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_update_kernel(SgnsAr
 
 // The long rows (more than one segment) of the sorted terms, 16 lanes per side-buffer slot: slot s
 // belongs to the row whose first term lies in positions [s * S, (s + 1) * S), if that row goes on for more
-// than S terms.  kZero: clears the slot; else table[row] = round(old + slot).
+// than S terms.  kZero: clears the slot, and writes down where a further segment of a row starts in those positions; else table[row] =
+// round(old + slot).
 template <typename T, bool kZero>
-__global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_long_kernel(SgnsArgs a) {
+__global__ __launch_bounds__(kSgnsThreads) void sgns_sorted_long_kernel(SgnsArgs a, uint2* __restrict__ further) {
   const uint32_t* __restrict__ keys = a.term_key;
   const int l16 = threadIdx.x & (kGroupLanes - 1);
   const int64_t s = ((int64_t)blockIdx.x * kSgnsThreads + threadIdx.x) / kGroupLanes;
   const int64_t low = s << a.seg_shift, after = (s + 1) << a.seg_shift;
+  if constexpr (kZero) {
+    if (s > a.stage_long_base) return;
+    uint2 start_and_row = make_uint2(kNoRow, 0u);
+    if (low > 0 && low < a.num_terms && keys[low - 1] == keys[low]) {
+      // the row goes back: if it has more than S records, half a segment away on one side or the other are some of them
+      const uint32_t key = keys[low];
+      const int64_t half = (int64_t)1 << (a.seg_shift - 1);
+      if ((low >= half && keys[low - half] == key) || (low + half < a.num_terms && keys[low + half] == key)) {
+        int64_t hi = low - 1, step = half;                             // (keys[hi] == key)
+        int64_t lo = max((int64_t)0, hi - step);
+        while (lo > 0 && keys[lo] == key) {
+          hi = lo;
+          step *= 2;
+          lo = max((int64_t)0, hi - step);
+        }
+        while (lo < hi) {
+          const int64_t mid = (lo + hi) >> 1;
+          if (keys[mid] < key) lo = mid + 1; else hi = mid;
+        }
+        const int64_t segment = (int64_t)1 << a.seg_shift;
+        const int64_t start = lo + ((low - lo + segment - 1) & ~(segment - 1));
+        if (start < a.num_terms && keys[start] == key) start_and_row = make_uint2((uint32_t)start, (uint32_t)lo);
+      }
+    }
+    if (l16 == 0) further[s] = start_and_row;
+  }
   if (after >= a.num_terms) return;
   const uint32_t key = keys[after];
   if (keys[after - 1] != key) return;
@@ -2008,7 +2004,8 @@ static SgnsPlan plan_sorted(void* ws, int64_t num_pairs, int64_t num_nodes, int3
     p.term_key[i] = cv.take<uint32_t>(terms);
     p.term_src[i] = cv.take<uint2>(terms);
   }
-  p.sort_bytes = radix_sort_scratch_bytes((int64_t)terms, wide);
+  // (behind the sort, its scratch memory holds `further`)
+  p.sort_bytes = std::max(radix_sort_scratch_bytes((int64_t)terms, wide), ((terms >> p.seg_shift) + 2) * sizeof(uint2));
   p.sort_scratch = cv.take<char>(p.sort_bytes);
   p.cnt = cv.take<uint32_t>((size_t)p.cnt_last + 1 + 3);                   // cleared 16 bytes at a time
   p.key_table = p.table_places > 0 ? cv.take<uint32_t>((size_t)p.table_places) : nullptr;
@@ -2248,14 +2245,14 @@ static int32_t launch_scan(const SgnsArgs& a, hipStream_t stream) {
 // everything behind the sort but the long input-table rows: the context-table keys from the records, their
 // long rows before and after, then the input-table keys
 template <typename T, int WPP, int PPL, int UB>
-static int32_t launch_sorted_updates(const SgnsArgs& a, hipStream_t stream) {
+static int32_t launch_sorted_updates(const SgnsArgs& a, uint2* further, hipStream_t stream) {
   constexpr int kWaves = kSgnsThreads / 64;
   const unsigned out_blocks = (unsigned)ceil_div(ceil_div(a.num_terms, a.slice_terms), kWaves);
   const unsigned in_blocks = (unsigned)std::min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
-  const unsigned long_blocks = (unsigned)ceil_div(a.stage_long_base, kGroupsPerBlock);
-  sgns_sorted_long_kernel<T, true><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
-  sgns_sorted_update_kernel<T, WPP, PPL, UB, kPlain, false><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
-  sgns_sorted_long_kernel<T, false><<<long_blocks, kSgnsThreads, 0, stream>>>(a);
+  const unsigned long_blocks = (unsigned)ceil_div(a.stage_long_base + 1, kGroupsPerBlock);
+  sgns_sorted_long_kernel<T, true><<<long_blocks, kSgnsThreads, 0, stream>>>(a, further);
+  sgns_sorted_update_kernel<T, WPP, PPL, UB, kPlain, false><<<out_blocks, kSgnsThreads, 0, stream>>>(a, further);
+  sgns_sorted_long_kernel<T, false><<<long_blocks, kSgnsThreads, 0, stream>>>(a, nullptr);
   sgns_update_kernel<T, WPP, PPL, UB, kPlain, true><<<in_blocks, kSgnsThreads, 0, stream>>>(a);
   GS_LAUNCH_CHECK();
   return GS_OK;
@@ -2306,12 +2303,13 @@ static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStr
   if (rc != GS_OK) return rc;
   a.term_key = p.term_key[0];
   a.term_src = p.term_src[0];
+  uint2* further = static_cast<uint2*>(p.sort_scratch);
   const int row_bytes = a.dim * (int)sizeof(T);
-  if (row_bytes <= 256) rc = launch_sorted_updates<T, 1, 1, 16>(a, stream);
-  else if (row_bytes <= 512) rc = launch_sorted_updates<T, 2, 1, 16>(a, stream);
-  else if (row_bytes <= 1024) rc = launch_sorted_updates<T, 4, 1, 8>(a, stream);
-  else if (row_bytes <= 2048) rc = launch_sorted_updates<T, 4, 2, 4>(a, stream);
-  else rc = launch_sorted_updates<T, 4, 4, 2>(a, stream);
+  if (row_bytes <= 256) rc = launch_sorted_updates<T, 1, 1, 16>(a, further, stream);
+  else if (row_bytes <= 512) rc = launch_sorted_updates<T, 2, 1, 16>(a, further, stream);
+  else if (row_bytes <= 1024) rc = launch_sorted_updates<T, 4, 1, 8>(a, further, stream);
+  else if (row_bytes <= 2048) rc = launch_sorted_updates<T, 4, 2, 4>(a, further, stream);
+  else rc = launch_sorted_updates<T, 4, 4, 2>(a, further, stream);
   if (rc != GS_OK) return rc;
   // long rows of the input table; one more block sums the loss
   sgns_finish_kernel<T, kPlain><<<(unsigned)ceil_div(a.long_slots, kGroupsPerBlock) + 1, kSgnsThreads, 0, stream>>>(a, 2);
@@ -2320,30 +2318,30 @@ static int32_t launch_sorted(const SgnsArgs& unsorted, const SgnsPlan& p, hipStr
 }
 
 template <typename T, int WPP, int PPL, int UB, int kOpt>
-static int32_t launch_grouped_updates(const SgnsArgs& a, hipStream_t stream) {
+static int32_t launch_grouped_updates(const SgnsArgs& a, const uint2* further, hipStream_t stream) {
   constexpr int kWaves = kSgnsThreads / 64;
   const unsigned out_blocks = (unsigned)ceil_div(ceil_div(a.num_terms, a.slice_terms), kWaves);
   const unsigned in_blocks = (unsigned)std::min((int64_t)kStageMaxBlocks, ceil_div(ceil_div(a.num_pairs, kStageSlice), kWaves));
   const unsigned long_blocks = (unsigned)std::min((int64_t)kLongRowBlocks, ceil_div(a.long_slots, kGroupsPerBlock)) + 1;
-  sgns_sorted_update_kernel<T, WPP, PPL, UB, kOpt, false><<<out_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_sorted_update_kernel<T, WPP, PPL, UB, kOpt, false><<<out_blocks, kSgnsThreads, 0, stream>>>(a, further);
   const bool one_table = a.dst_in == a.dst_out;
   if constexpr (kOpt == kPlain)
     if (one_table) sgns_long_rows_kernel<T, kOpt><<<long_blocks, kSgnsThreads, 0, stream>>>(a, 1);
-  sgns_sorted_update_kernel<T, WPP, PPL, UB, kOpt, true><<<in_blocks, kSgnsThreads, 0, stream>>>(a);
+  sgns_sorted_update_kernel<T, WPP, PPL, UB, kOpt, true><<<in_blocks, kSgnsThreads, 0, stream>>>(a, further);
   sgns_long_rows_kernel<T, kOpt><<<long_blocks, kSgnsThreads, 0, stream>>>(a, one_table ? 2 : 0);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
 
 template <typename T, int kOpt>
-static int32_t launch_grouped_rows(const SgnsArgs& a, hipStream_t stream) {
+static int32_t launch_grouped_rows(const SgnsArgs& a, const uint2* further, hipStream_t stream) {
   const int row_bytes = a.dim * (int)sizeof(T);
   int32_t rc;
-  if (row_bytes <= 256) rc = launch_grouped_updates<T, 1, 1, 16, kOpt>(a, stream);
-  else if (row_bytes <= 512) rc = launch_grouped_updates<T, 2, 1, 16, kOpt>(a, stream);
-  else if (row_bytes <= 1024) rc = launch_grouped_updates<T, 4, 1, 8, kOpt>(a, stream);
-  else if (row_bytes <= 2048) rc = launch_grouped_updates<T, 4, 2, 4, kOpt>(a, stream);
-  else rc = launch_grouped_updates<T, 4, 4, 2, kOpt>(a, stream);
+  if (row_bytes <= 256) rc = launch_grouped_updates<T, 1, 1, 16, kOpt>(a, further, stream);
+  else if (row_bytes <= 512) rc = launch_grouped_updates<T, 2, 1, 16, kOpt>(a, further, stream);
+  else if (row_bytes <= 1024) rc = launch_grouped_updates<T, 4, 1, 8, kOpt>(a, further, stream);
+  else if (row_bytes <= 2048) rc = launch_grouped_updates<T, 4, 2, 4, kOpt>(a, further, stream);
+  else rc = launch_grouped_updates<T, 4, 4, 2, kOpt>(a, further, stream);
   if (rc != GS_OK) return rc;
   if constexpr (kOpt != kPlain) return launch_dense_rest<T, kOpt>(a, true, stream);
   return GS_OK;
@@ -2378,10 +2376,10 @@ static int32_t launch_grouped(const SgnsArgs& ungrouped, const SgnsPlan& p, int 
   a.long_rows = g.long_rows;
   a.named = g.named;
   a.named_in = g.second_named;
-  if (opt == kMomentum) return launch_grouped_rows<T, kMomentum>(a, stream);
+  if (opt == kMomentum) return launch_grouped_rows<T, kMomentum>(a, g.further, stream);
   if constexpr (std::is_same<T, float>::value)
-    if (opt == kAdam) return launch_grouped_rows<T, kAdam>(a, stream);
-  return launch_grouped_rows<T, kPlain>(a, stream);
+    if (opt == kAdam) return launch_grouped_rows<T, kAdam>(a, g.further, stream);
+  return launch_grouped_rows<T, kPlain>(a, g.further, stream);
 }
 
 template <typename T, int VPL, int RB>

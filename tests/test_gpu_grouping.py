@@ -61,6 +61,36 @@ def test_step(oracle, kind, n, b, k, fmt):
                               flip_fraction=None if h.size > 20_000 else 2.0 / h.size)
 
 
+@pytest.mark.parametrize("b,k,mean", [(100_000, 4, 64), (1_400_000, 0, 256), (300_000, 3, 256)])
+@pytest.mark.parametrize("less", [0, 256])
+def test_rows_of_whole_segments(oracle, b, k, mean, less):
+    """Rows of a few records more and less than one, two and seventeen segments of 64 or 256, in both tables, so that further segments start
+    everywhere; also as the sorted records (or counters) that a little less room leaves."""
+    from paper_2407_15452_amd import binding as gs
+    rng = np.random.default_rng(b)
+
+    def ids(count):
+        sizes = rng.choice([1, mean - 1, mean, mean + 1, 2 * mean, 2 * mean + 1, 17 * mean + 3], count // mean + 200, p=[.3, .1, .2, .2, .1, .05, .05])
+        rows = np.repeat(rng.permutation(sizes.size), sizes)[:count]
+        assert rows.size == count
+        return rows.astype(np.int32), sizes.size
+
+    terms, n_out = ids(b * (k + 1))
+    terms = rng.permutation(terms).reshape(b, k + 1)
+    c, n_in = ids(b)
+    c = rng.permutation(c)                  # (nearly every centre its own run)
+    n, dim, lr = max(n_out, n_in), 8, 1e-4
+    o, neg = np.ascontiguousarray(terms[:, 0]), np.ascontiguousarray(terms[:, 1:])
+    tabs = _tables(n, dim, 2, n)
+    host, dev = [t.numpy().copy() for t in tabs], [t.to(DEV) for t in tabs]
+    want = oracle.sgns_step(*host, c, o, neg, lr)
+    ws = torch.empty(gs.gs_sgns_step_workspace_bytes(b, n, k, dim, gs.GS_F32) - less, dtype=torch.uint8, device=DEV)
+    loss = gs.gs_sgns_step(*dev, _dev(c), _dev(o), _dev(neg), lr, ws=ws)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for d, h in zip(dev, host):
+        assert_emb_close(d.cpu().numpy(), h)
+
+
 @pytest.mark.parametrize("kind,n,b,k", [("even", 65_536, 54_614, 5), ("hub", 40_000, 60_000, 5), ("hub", 700_000, 110_000, 5)])
 @pytest.mark.parametrize("call", ["momentum", "adam", "line1"])
 def test_optimizers_and_one_table(oracle, call, kind, n, b, k):

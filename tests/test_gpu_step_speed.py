@@ -21,8 +21,9 @@ def _batch(n, b, k, window):
     return c[:b], o[:b], gs.gs_sample_negatives(noise, n, b, k, 7)
 
 
-# buckets of rows that are split among workgroups
-@pytest.mark.parametrize("n,b,k,window,dim", [(5_000, 666_666, 5, 10, 52), (8_000, 600_000, 5, 10, 20)])
+# buckets of rows that are split among workgroups; slices of long rows, of which many start nothing
+@pytest.mark.parametrize("n,b,k,window,dim", [(5_000, 666_666, 5, 10, 52), (8_000, 600_000, 5, 10, 20),
+                                              (5_000, 666_666, 10, 10, 20), (5_000, 600_000, 1, 10, 104)])
 def test_no_slower_than_with_less_room(n, b, k, window, dim):
     from paper_2407_15452_amd import binding as gs, inputs
     batch = _batch(n, b, k, window)
