@@ -27,7 +27,8 @@ constexpr int kBucketItems = 9, kBucketItemsMost = 16;         // records per la
 constexpr int64_t kBuckets = 2048, kSecondBuckets = 1024;      // most buckets of either kind of rows
 // Records per bucket, which leave a bucket of 9216 room for uneven rows; fewer where that keeps compute units busy.
 constexpr int64_t kBucketMean = 6000, kBucketMeanLeast = 1024, kBusyBuckets = 256, kBucketMeanMost = 7000;
-constexpr int kSplitBlocks = 256;
+// Buckets to split: records per lane of a piece, workgroups for the pieces, rows of a bucket whose counters leave room for two of them in a compute unit.
+constexpr int kPieceItems = 4, kPiece = kBucketThreads * kPieceItems, kSplitBlocks = 512, kFewRowBits = 12;
 // Records of a tile.  us with 2048 / 4096 / 8192: 0.8 M records 35.9 / 36.9 / 41.2, 1.6 M 40.6 / 40.7 / 42.4, 2.4 M 54 / 50 / 54, 3 M
 // 65 / 60 / 62, 6 M 108 / 97 / 90; 16,384 instead of 8192 (half the counts): prefix sums of 12 million records 23 -> 15, the scatter the same
 constexpr int64_t kMidTiles = (int64_t)3 << 19, kLargeTiles = (int64_t)1 << 22, kLargestTiles = (int64_t)1 << 23;
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(1024) void group_scan_kernel(GroupArgs a) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t total = total_s[w];
     if (total <= a.most) return;
-    const uint32_t pieces = (total + a.most - 1) / a.most;
+    const uint32_t pieces = (total + kPiece - 1) / kPiece;
     const uint32_t rows = 1u << (second ? a.second_row_bits : a.row_bits);
     uint32_t first = 0, rows_at = 0;
     if (lane == 0) {
@@ -370,25 +371,23 @@ __device__ __forceinline__ void tell_of_rows(const GroupArgs& a, const BucketOf&
 }
 
 // The pieces in the list of buckets to split: the counts of their rows are added up in global memory.
-template <int ITEMS>
 __device__ __forceinline__ void count_pieces(const GroupArgs& a, uint32_t first_piece, uint32_t stride, uint32_t* count) {
-  constexpr int kMost = kBucketThreads * ITEMS;
   const int tid = threadIdx.x;
   const uint32_t pieces = a.counters[kGroupPieces];
   for (uint32_t j = first_piece; j < pieces; j += stride) {
     const uint4 piece = a.pieces[j];
     const BucketOf b = bucket_of(a, piece.x);
     const int rows = 1 << b.row_bits;
-    const uint32_t* piece_rows = a.rows_mid + b.base + (int64_t)piece.z * kMost;
-    const int live = (int)min((uint32_t)kMost, a.totals[piece.x] - piece.z * (uint32_t)kMost);
+    const uint32_t* piece_rows = a.rows_mid + b.base + (int64_t)piece.z * kPiece;
+    const int live = (int)min((uint32_t)kPiece, a.totals[piece.x] - piece.z * (uint32_t)kPiece);
     for (int r = tid; r < rows; r += kBucketThreads) count[r] = 0u;
-    uint32_t row[ITEMS];
+    uint32_t row[kPieceItems];
 #pragma unroll
-    for (int c = 0; c < ITEMS; ++c)
+    for (int c = 0; c < kPieceItems; ++c)
       row[c] = c * kBucketThreads + tid < live ? piece_rows[c * kBucketThreads + tid] & (uint32_t)(rows - 1) : 0u;
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < ITEMS; ++c) count_row(count, row[c], c * kBucketThreads + tid < live);
+    for (int c = 0; c < kPieceItems; ++c) count_row(count, row[c], c * kBucketThreads + tid < live);
     __syncthreads();
     for (int r = tid; r < rows; r += kBucketThreads)
       if (count[r] != 0u) atomicAdd(a.row_counts + piece.y + r, count[r]);
@@ -406,7 +405,7 @@ __global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void
   uint32_t* count = reinterpret_cast<uint32_t*>(bytes);
   const int tid = threadIdx.x;
   if (blockIdx.x >= a.digits) {
-    count_pieces<ITEMS>(a, blockIdx.x - a.digits, gridDim.x - a.digits, count);
+    count_pieces(a, blockIdx.x - a.digits, gridDim.x - a.digits, count);
     return;
   }
   const uint32_t total = a.totals[blockIdx.x];
@@ -468,11 +467,11 @@ __global__ __launch_bounds__(kBucketThreads, ITEMS <= kBucketItems ? 8 : 4) void
 }
 
 // The pieces in the list: a piece takes the next places of its rows and moves its records there.
-template <int ITEMS>
+// ROW_BITS: the most of either kind of buckets.
+template <int ROW_BITS>
 __global__ __launch_bounds__(kBucketThreads) void group_split_kernel(GroupArgs a) {
-  constexpr int kMost = kBucketThreads * ITEMS;
-  __shared__ uint32_t first[1 << kBucketRowBits];                // of a row of the bucket: the records before it,
-  __shared__ uint32_t count[1 << kBucketRowBits];                // those of this piece, then the place of the first of them
+  __shared__ uint32_t first[1 << ROW_BITS];                // of a row of the bucket: the records before it,
+  __shared__ uint32_t count[1 << ROW_BITS];                // those of this piece, then the place of the first of them
   __shared__ uint32_t part[kBucketWaves];
   const int tid = threadIdx.x;
   const uint32_t pieces = a.counters[kGroupPieces];
@@ -481,19 +480,23 @@ __global__ __launch_bounds__(kBucketThreads) void group_split_kernel(GroupArgs a
     const BucketOf b = bucket_of(a, piece.x);
     const int rows = 1 << b.row_bits;
     const uint32_t mask = (uint32_t)rows - 1u, total = a.totals[piece.x];
-    const int64_t base = b.base + (int64_t)piece.z * kMost;
-    const int live = (int)min((uint32_t)kMost, total - piece.z * (uint32_t)kMost);
+    const int64_t base = b.base + (int64_t)piece.z * kPiece;
+    const int live = (int)min((uint32_t)kPiece, total - piece.z * (uint32_t)kPiece);
     for (int r = tid; r < rows; r += kBucketThreads) {
       first[r] = a.row_counts[piece.y + r];
       count[r] = 0u;
     }
-    uint32_t row[ITEMS], rank[ITEMS];
+    uint32_t row[kPieceItems], rank[kPieceItems];
+    uint2 val[kPieceItems];                                            // (asked for here: between the stores below each would be waited for)
 #pragma unroll
-    for (int c = 0; c < ITEMS; ++c)
+    for (int c = 0; c < kPieceItems; ++c)
       row[c] = c * kBucketThreads + tid < live ? a.rows_mid[base + c * kBucketThreads + tid] & mask : 0u;
+#pragma unroll
+    for (int c = 0; c < kPieceItems; ++c)
+      if (c * kBucketThreads + tid < live) val[c] = a.vals_mid[base + c * kBucketThreads + tid];
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < ITEMS; ++c)
+    for (int c = 0; c < kPieceItems; ++c)
       rank[c] = count_row(count, row[c], c * kBucketThreads + tid < live);
     bucket_scan(first, rows, part);
     for (int r = tid; r < rows; r += kBucketThreads)
@@ -501,11 +504,11 @@ __global__ __launch_bounds__(kBucketThreads) void group_split_kernel(GroupArgs a
     tell_of_rows(a, b, first, total, piece.z, piece.w);
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < ITEMS; ++c)
+    for (int c = 0; c < kPieceItems; ++c)
       if (c * kBucketThreads + tid < live) {
         const int64_t at = b.base + count[row[c]] + rank[c];
         a.keys_out[at] = b.key + row[c];
-        a.vals_out[at] = a.vals_mid[base + c * kBucketThreads + tid];
+        a.vals_out[at] = val[c];
       }
     __syncthreads();
   }
@@ -574,7 +577,7 @@ void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t r
   a.totals = cv.take<uint32_t>((size_t)(kBuckets + kSecondBuckets));
   a.starts = cv.take<uint32_t>((size_t)(kBuckets + kSecondBuckets));
   a.counters = cv.take<uint32_t>(kGroupCounters);
-  a.pieces = cv.take<uint4>(2 * split);
+  a.pieces = cv.take<uint4>(records / kPiece + split);
   a.row_counts = cv.take<uint32_t>(split_rows);
   a.row_taken = cv.take<uint32_t>(split_rows);
   a.long_rows = cv.take<uint2>((records >> seg_shift) + 1);
@@ -596,7 +599,8 @@ template <int ITEMS>
 static int32_t launch_buckets(const GroupArgs& a, hipStream_t stream) {
   group_bucket_kernel<ITEMS><<<a.digits + kSplitBlocks, kBucketThreads, 0, stream>>>(a);
   GS_LAUNCH_CHECK();
-  group_split_kernel<ITEMS><<<kSplitBlocks, kBucketThreads, 0, stream>>>(a);
+  if (std::max(a.row_bits, a.second_row_bits) <= kFewRowBits) group_split_kernel<kFewRowBits><<<kSplitBlocks, kBucketThreads, 0, stream>>>(a);
+  else group_split_kernel<kBucketRowBits><<<kSplitBlocks, kBucketThreads, 0, stream>>>(a);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
