@@ -2705,16 +2705,19 @@ static int32_t run_sgns(void* w_in, void* w_out, void* dst_in, void* dst_out, in
     if (vpl <= 8) return launch_sgns<float, 8, 2>(a, p, x.opt, stream);
     return launch_sgns<float, 16, 1>(a, p, x.opt, stream);
   }
-  // 16-bit rows: a 16-byte piece is 8 elements = two float4, so the register count is even
+  // 16-bit rows: a 16-byte piece is 8 elements = two float4, so the register count is even.  With one negative, whose pairs have two terms, blocks of
+  // two rows, since a block's reads are all made: 120,000 pairs on 1 M nodes, 400 and 512 bf16 columns 219 and 236 us with blocks of four (212
+  // and 228 with a branch in front of every read), now 193 and 207; 200 fp16 and 256 bf16 columns with six 137 and 139 (136, 138), now 130 and 134;
+  // 128 columns 110 (112) and 106: not worth the kernels.  With two negatives the blocks of four and six are no slower than the branches were.
   if (dtype == GS_BF16) {
     if (vpl <= 2) return launch_sgns<bf16_t, 2, 6>(a, p, x.opt, stream);
-    if (vpl <= 4) return launch_sgns<bf16_t, 4, 6>(a, p, x.opt, stream);
-    if (vpl <= 8) return launch_sgns<bf16_t, 8, 4>(a, p, x.opt, stream);
+    if (vpl <= 4) return k <= 1 ? launch_sgns<bf16_t, 4, 2>(a, p, x.opt, stream) : launch_sgns<bf16_t, 4, 6>(a, p, x.opt, stream);
+    if (vpl <= 8) return k <= 1 ? launch_sgns<bf16_t, 8, 2>(a, p, x.opt, stream) : launch_sgns<bf16_t, 8, 4>(a, p, x.opt, stream);
     return launch_sgns<bf16_t, 16, 2>(a, p, x.opt, stream);
   }
   if (vpl <= 2) return launch_sgns<f16_t, 2, 6>(a, p, x.opt, stream);
-  if (vpl <= 4) return launch_sgns<f16_t, 4, 6>(a, p, x.opt, stream);
-  if (vpl <= 8) return launch_sgns<f16_t, 8, 4>(a, p, x.opt, stream);
+  if (vpl <= 4) return k <= 1 ? launch_sgns<f16_t, 4, 2>(a, p, x.opt, stream) : launch_sgns<f16_t, 4, 6>(a, p, x.opt, stream);
+  if (vpl <= 8) return k <= 1 ? launch_sgns<f16_t, 8, 2>(a, p, x.opt, stream) : launch_sgns<f16_t, 8, 4>(a, p, x.opt, stream);
   return launch_sgns<f16_t, 16, 2>(a, p, x.opt, stream);
 }
 

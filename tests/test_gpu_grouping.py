@@ -152,6 +152,14 @@ def test_short_16bit_rows(oracle, fmt, dim, n, b, k):
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("dim", [136, 256, 264, 512])
+@pytest.mark.parametrize("n,b,k", [(100_000, 1_500, 1), (30_000, 30_000, 1), (30_000, 180_001, 1), (30_000, 330_001, 0)])
+def test_16bit_rows_with_one_negative_or_none(oracle, fmt, dim, n, b, k):
+    """Blocks of two rows: two launches, counters, grouped records."""
+    test_short_16bit_rows(oracle, fmt, dim, n, b, k)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
 @pytest.mark.parametrize("table", [0, 1])
 @pytest.mark.parametrize("n,b,k", [(100_000, 1_500, 6), (20_000, 9_000, 3), (30_000, 30_000, 10)])
 def test_infinity_in_the_last_piece(fmt, table, n, b, k):

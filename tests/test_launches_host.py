@@ -159,6 +159,18 @@ def test_forward_waves(launches, dtype, dim, pairs, more):
     assert len(forward) == 1 and ("Li256ELi%dEEEv" % (0 if not more else (4 if dim <= 256 else 3))) in forward[0], forward
 
 
+@pytest.mark.parametrize("pairs", [2_000, 100_000, 500_000])
+@pytest.mark.parametrize("dtype,dim,k,rows", [(1, 256, 1, 2), (1, 136, 0, 2), (2, 200, 1, 2), (1, 256, 2, 6), (1, 512, 1, 2), (2, 264, 1, 2), (1, 512, 2, 4),
+                                              (1, 128, 1, 6), (0, 256, 1, 3), (1, 520, 1, 2)])
+def test_forward_rows_in_flight(launches, pairs, dtype, dim, k, rows):
+    """16-bit rows: no block of rows much longer than the terms of a pair, all of whose reads are made."""
+    got, rc = launches(STEP + "print(json.dumps({'rc': step('gs_sgns_step', %d, 100000, %d, %d, %d)}))\n" % (pairs, dim, dtype, k))
+    assert rc == [0]
+    (name,) = [x[0] for x in got if "sgns_forward_kernel" in x[0]]
+    vpl = -(-dim // 64) if dim <= 64 else 2 if dim <= 128 else 4 if dim <= 256 else 8 if dim <= 512 else 16
+    assert "Li%dELi%dE" % (vpl, rows) in name, name
+
+
 @pytest.mark.parametrize("call,nodes,dim,dtype,once", [
     ("gs_sgns_momentum_step", 131_072, 128, 0, 0), ("gs_sgns_momentum_step", 131_073, 128, 0, 1),
     ("gs_sgns_momentum_step", 262_144, 128, 1, 0), ("gs_sgns_momentum_step", 262_145, 128, 2, 1),
