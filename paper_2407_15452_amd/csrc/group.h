@@ -49,6 +49,7 @@ struct GroupArgs {
 };
 
 bool can_group(int64_t rows);
+bool group_crowded(int64_t n, int64_t rows);                              // whether sorting is faster, since most buckets are split
 constexpr int kBucketRowBits = 14;             // rows of a bucket: their counters fit a workgroup's LDS
 int64_t group_border(int64_t rows, bool second, int bits);
 void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t rows, int32_t seg_shift, bool marks);

@@ -548,6 +548,14 @@ static GroupPlan plan_group(int64_t n, int64_t second_n, int64_t rows) {
 
 bool can_group(int64_t rows) { return ceil_div(rows, (int64_t)1 << kBucketRowBits) <= kSecondBuckets; }
 
+// Buckets of more records than a workgroup takes, all of which are split, and of more rows than let two workgroups of the splitting launch share a
+// compute unit.  Steps, us, grouped / sorted: 16 M rows 30 M records 2992 / 3268, 34 M 3861 / 3666, 72 M 7796 / 7114; 8 M rows 36 M 3651 /
+// 3708, 60 M 5922 / 5832; 4 M rows 36 M 3360 / 3526, 120 M 10641 / 10953; 100 k rows 48 M 3882 / 3868.
+bool group_crowded(int64_t n, int64_t rows) {
+  const int bits = row_bits_for(n, rows, kBuckets);
+  return bits > kFewRowBits && ceil_div(n, ceil_div(rows, (int64_t)1 << bits)) > kBucketThreads * kBucketItemsMost;
+}
+
 // The most records of a kind that are grouped in buckets of 2^bits rows or more (behind it, there are more buckets of fewer rows); 0: no border.
 int64_t group_border(int64_t rows, bool second, int bits) {
   if (bits <= 0 || bits > kBucketRowBits || ceil_div(rows, (int64_t)1 << (bits - 1)) > (second ? kSecondBuckets : kBuckets)) return 0;

@@ -2041,10 +2041,14 @@ static SgnsPlan plan_grouped(void* ws, int64_t num_pairs, int64_t num_nodes, int
   return p;
 }
 // Batches of at least this many terms are grouped: fewer on few rows, whose counters are busy.  Times of the counters over those of the
-// records, batches of walks and negatives on R-MAT graphs, 16 to 400 columns (least and most of them):
-//   5 k and 10 k rows   0.3 M terms 0.96 to 1.17, 0.4 M 0.97 to 1.15, 0.6 M 1.01 to 1.18, 1.2 M 0.95 (one negative) to 1.17, 4 M 1.01 to 1.35
-//   100 k rows          0.3 M 0.93 to 1.07, 0.4 M 0.94 to 1.08, 0.6 M 0.99 to 1.08, 1.2 M 0.98 to 1.11, 4 M 1.01 to 1.20
-//   1 M rows            0.3 M 0.89 to 1.05, 0.4 M 0.87 to 1.05, 0.6 M 0.95 to 1.07, 1.2 M 1.03 to 1.08, 4 M 1.08 to 1.22
+// records, 755 batches of walks and negatives (windows of 2 to 10) and of LINE on R-MAT graphs, momentum and Adam among them, 16 to 256 columns (least and most
+// of them; with one negative, with more):
+//   5 k and 10 k rows    0.33 M terms 1.06 to 1.13, 1.04 to 1.12; 0.5 M 1.00 to 1.24, 1.08 to 1.24; 1.2 M 0.98 to 1.16, 1.03 to 1.28; 3 M and more 1.15 to 1.46
+//   20 k to 2^16         0.33 M 0.99 to 1.12, 1.01 to 1.13; 0.5 M 0.97 to 1.13, 1.01 to 1.18; 1.2 M 0.96 to 1.07, 1.01 to 1.27; 3 M 1.09 to 1.38
+//   2^16 to 100 k        0.4 M 0.94 to 1.05, 0.94 to 1.06; 0.66 M 1.01 to 1.08, 0.98 to 1.11; 1.2 M 1.00, 1.01 to 1.12; 3 M 1.05 to 1.31
+//   300 k                0.4 M 0.96 to 1.00, 0.99 to 1.08; 0.66 M 1.03, 0.99 to 1.12; 1.2 M 0.97 to 1.11, 0.99 to 1.09; 3 M 1.07 to 1.19
+//   1 M and 2 M          0.4 M 1.00 to 1.09, 0.92 to 1.06; 0.66 M 1.11 to 1.29, 0.98 to 1.19; 1.2 M 1.01 to 1.10, 1.07 to 1.15; 3 M 1.09 to 1.39
+// (Below 0.98 of those that are grouped: five of 607, four of them of one negative on rows of 32 to 48 bytes.)
 constexpr int64_t kGroupedMinTerms = (int64_t)5 << 17, kGroupedMinTermsFewRows = (int64_t)5 << 16, kGroupedFewRows = (int64_t)1 << 16;
 static bool grouped_batch(int64_t num_pairs, int64_t num_nodes, int32_t k) {
   return num_pairs * (int64_t)(k + 1) >= (num_nodes <= kGroupedFewRows ? kGroupedMinTermsFewRows : kGroupedMinTerms) && can_group(num_nodes);
@@ -2115,11 +2119,12 @@ static bool plan_step(SgnsPlan& p, void* ws, size_t ws_bytes, size_t extra, int6
     p = plan_small(ws, num_pairs, k, dim, dtype);
     if (p.bytes + extra <= ws_bytes) return true;
   }
-  if (grouped_batch(num_pairs, num_nodes, k)) {
+  const bool sorted = sort_records && sorted_batch(num_pairs, num_nodes, k);
+  if (grouped_batch(num_pairs, num_nodes, k) && !(sorted && group_crowded(num_pairs * (int64_t)(k + 1), num_nodes))) {
     p = plan_grouped(ws, num_pairs, num_nodes, k, dim);
     if (p.bytes + extra <= ws_bytes) return true;
   }
-  if (sort_records && sorted_batch(num_pairs, num_nodes, k))
+  if (sorted)
     for (const bool wide : {true, false}) {
       p = plan_sorted(ws, num_pairs, num_nodes, k, dim, wide);
       if (p.bytes + extra <= ws_bytes) return true;
@@ -2132,8 +2137,9 @@ static size_t plan_bytes(int64_t num_pairs, int64_t num_nodes, int32_t k, int32_
   size_t bytes = plan_sgns(nullptr, num_pairs, num_nodes, k, dim).bytes;
   if (two_launches && small_batch(num_pairs, num_nodes, k, dim, dtype))
     bytes = std::max(bytes, plan_small(nullptr, num_pairs, k, dim, dtype).bytes);
-  if (grouped_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_grouped(nullptr, num_pairs, num_nodes, k, dim).bytes);
-  else if (sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim, true).bytes);
+  const bool grouped = grouped_batch(num_pairs, num_nodes, k);
+  if (grouped) bytes = std::max(bytes, plan_grouped(nullptr, num_pairs, num_nodes, k, dim).bytes);
+  if ((!grouped || group_crowded(num_pairs * (int64_t)(k + 1), num_nodes)) && sorted_batch(num_pairs, num_nodes, k)) bytes = std::max(bytes, plan_sorted(nullptr, num_pairs, num_nodes, k, dim, true).bytes);
   return bytes;
 }
 // The same over all batches of up to num_pairs: the workspace of a program's largest batch serves every

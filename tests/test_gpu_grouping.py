@@ -91,6 +91,30 @@ def test_rows_of_whole_segments(oracle, b, k, mean, less):
         assert_emb_close(d.cpu().numpy(), h)
 
 
+@pytest.mark.parametrize("n,b,k", [(700, 1_500_000, 5), (5_000, 6_000_000, 5), (3_000_000, 5_800_000, 5), (9_000_000, 5_600_000, 5)])
+def test_more_records_than_buckets_hold(n, b, k):
+    """Tiles of 16,384 records and few buckets, and every bucket split (or, of more than 2^23 rows, sorted records): bit for bit what sorted
+    records and counters in less room give (the sums are exact, and chunks of a forward group the same)."""
+    from paper_2407_15452_amd import binding as gs
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    ids = [(torch.rand(m, generator=gen, device=DEV) ** 2 * n).to(torch.int32).clamp_(0, n - 1) for m in (b // 4, b, b * k)]
+    c, o, neg = ids[0].repeat_interleave(4), ids[1], ids[2].view(b, k)
+    assert c.numel() == b
+    tabs = [t.to(DEV) for t in _tables(n, 4, 2, n)]
+    size = gs.gs_sgns_step_workspace_bytes(b, n, k, 4, gs.GS_F32)
+    ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+    results = []
+    for room in (size, size - 256, size // 256 * 256 * 3 // 4):
+        mine = [t.clone() for t in tabs]
+        try:
+            loss = gs.gs_sgns_step(*mine, c, o, neg, 1e-7, ws=ws[:room])
+        except gs.GsError as e:
+            assert e.status == gs.GS_EWORKSPACE and room < size - 256
+            continue
+        results.append((loss, *mine))
+    assert all(torch.equal(x, y) for r in results[1:] for x, y in zip(r, results[0])) and np.isfinite(float(results[0][0].item()))
+
+
 @pytest.mark.parametrize("kind,n,b,k", [("even", 65_536, 54_614, 5), ("hub", 40_000, 60_000, 5), ("hub", 700_000, 110_000, 5)])
 @pytest.mark.parametrize("call", ["momentum", "adam", "line1"])
 def test_optimizers_and_one_table(oracle, call, kind, n, b, k):

@@ -231,6 +231,17 @@ def test_ways_of_large_steps(launches, call, pairs, nodes, k, how):
         how == "group", how == "radix", how != "group")
 
 
+@pytest.mark.parametrize("call,pairs,nodes,how", [
+    ("gs_sgns_step", 5_592_405, 1 << 24, "group"), ("gs_sgns_step", 5_592_406, 1 << 24, "radix"), ("gs_sgns_step", 20_000_000, 1 << 23, "group"),
+    ("gs_sgns_step", 20_000_000, (1 << 23) + 1, "radix"), ("gs_sgns_step", 20_000_000, 5_000, "group"), ("gs_sgns_momentum_step", 5_592_406, 1 << 24, "group")])
+def test_steps_beyond_the_buckets(launches, call, pairs, nodes, how):
+    """More than 2^25 terms on more than 2^23 rows are sorted: each of the most buckets that there are would be split."""
+    got, rc = launches(STEP + "print(json.dumps({'rc': step('%s', %d, %d, 8)}))\n" % (call, pairs, nodes))
+    assert rc == [0]
+    names = " ".join(x[0] for x in got)
+    assert ("group_bucket_kernel" in names, "radix_scatter_kernel" in names) == (how == "group", how == "radix")
+
+
 @pytest.mark.parametrize("pairs,nodes,k,dim,bytes", [
     (2_000_000, 4_000_000, 5, 128, 1_448_071_680), (200_000, 60_000, 5, 64, 96_867_840), (1_100_000, 5_000, 1, 32, 224_405_248),
     (1_100_000, 100_000, 5, 64, 483_285_504)])
