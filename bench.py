@@ -64,7 +64,7 @@ def stored_record(workload_name: str, hash_field: str, *sources: str):
 
 
 def traffic_record(workload_name: str):
-    return stored_record(workload_name, "sgns_code_sha256", "sgns.hip", "scan_sort.hip", "common.h")
+    return stored_record(workload_name, "sgns_code_sha256", "sgns.hip", "group.hip", "group.h", "scan_sort.hip", "common.h")
 
 
 def walk_record(workload_name: str):
