@@ -198,6 +198,16 @@ __device__ __forceinline__ int64_t load_off(const void* offsets, int64_t i) {
   return (int64_t) static_cast<const OffT*>(offsets)[i];
 }
 
+// inclusive prefix sum over the lanes of a wave
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, int lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t up = __shfl_up(v, d, 64);
+    if (lane >= d) v += up;
+  }
+  return v;
+}
+
 #endif  // __HIPCC__
 
 }  // namespace gs

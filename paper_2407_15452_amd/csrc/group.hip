@@ -31,17 +31,7 @@ constexpr int64_t kBucketMean = 6000, kBucketMeanLeast = 1024, kBusyBuckets = 25
 constexpr int kPieceItems = 4, kPiece = kBucketThreads * kPieceItems, kSplitBlocks = 512, kFewRowBits = 12;
 // Records of a tile.  us with 2048 / 4096 / 8192: 0.8 M records 35.9 / 36.9 / 41.2, 1.6 M 40.6 / 40.7 / 42.4, 2.4 M 54 / 50 / 54, 3 M
 // 65 / 60 / 62, 6 M 108 / 97 / 90; 16,384 instead of 8192 (half the counts): prefix sums of 12 million records 23 -> 15, the scatter the same
-constexpr int64_t kMidTiles = (int64_t)3 << 19, kLargeTiles = (int64_t)1 << 22, kLargestTiles = (int64_t)1 << 23;
-
-// inclusive prefix sum over the lanes of a wave
-__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t up = __shfl_up(v, d, 64);
-    if (lane >= d) v += up;
-  }
-  return v;
-}
+constexpr int64_t kMidGroupTiles = (int64_t)3 << 19, kLargeGroupTiles = (int64_t)1 << 22, kLargestGroupTiles = (int64_t)1 << 23;
 
 // ---- into the buckets -----------------------------------------------------------------------
 // Tiles [0, first_tiles) hold records of the first kind, the others entries of the list of the second kind.
@@ -539,7 +529,7 @@ static GroupPlan plan_group(int64_t n, int64_t second_n, int64_t rows) {
   p.second_row_bits = row_bits_for(second_n, rows, kSecondBuckets);
   p.buckets = ceil_div(rows, (int64_t)1 << p.row_bits);
   p.second_buckets = ceil_div(rows, (int64_t)1 << p.second_row_bits);
-  p.tile = n >= kLargestTiles ? 16384 : (n >= kLargeTiles ? 8192 : (n >= kMidTiles ? 4096 : 2048));
+  p.tile = n >= kLargestGroupTiles ? 16384 : (n >= kLargeGroupTiles ? 8192 : (n >= kMidGroupTiles ? 4096 : 2048));
   p.bucket_items = ceil_div(n, p.buckets) > kBucketMeanMost ? kBucketItemsMost : kBucketItems;
   p.first_tiles = ceil_div(n, p.tile);
   p.tiles = p.first_tiles + ceil_div(second_n, p.tile);
@@ -568,7 +558,7 @@ void group_take(GroupArgs& a, Carver& cv, int64_t n, int64_t second_n, int64_t r
   const GroupPlan p = plan_group(n, second_n, rows);
   a.digits = (uint32_t)(p.buckets + p.second_buckets);
   size_t counts = 0;                             // (there are fewer tiles where they are larger)
-  for (const int64_t m : {n, std::min(n, kMidTiles - 1), std::min(n, kLargeTiles - 1), std::min(n, kLargestTiles - 1)}) {
+  for (const int64_t m : {n, std::min(n, kMidGroupTiles - 1), std::min(n, kLargeGroupTiles - 1), std::min(n, kLargestGroupTiles - 1)}) {
     const GroupPlan q = plan_group(m, second_n, rows);
     counts = std::max(counts, (size_t)q.first_tiles * (size_t)q.buckets + (size_t)(q.tiles - q.first_tiles) * (size_t)q.second_buckets);
   }

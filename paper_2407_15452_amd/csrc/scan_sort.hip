@@ -184,16 +184,6 @@ __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(const K* __re
   }
 }
 
-// inclusive prefix sum over the lanes of a wave
-__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t up = __shfl_up(v, d, 64);
-    if (lane >= d) v += up;
-  }
-  return v;
-}
-
 // Exclusive prefix sums of the counts of a digit over the tiles, and their total: a workgroup takes kScanDigits digits, a
 // lane one digit of a stretch of tiles.
 constexpr int kScanDigits = 16, kScanStretches = 1024 / kScanDigits;
@@ -443,9 +433,11 @@ int32_t radix_sort(const SortPlan& plan, const K* keys_in, const V* vals_in, K* 
   Carver cv(scratch);
   uint32_t* counts = cv.take<uint32_t>((size_t)ceil_div(n, kSortThreads * plan.items) << plan.width);
   uint32_t* totals = cv.take<uint32_t>((size_t)1 << plan.width);
-  auto pass = radix_pass_of<K, V, true, 4>;
-  if (vals_in != nullptr) pass = plan.items == 16 ? radix_pass_of<K, V, true, 16> : (plan.items == 8 ? radix_pass_of<K, V, true, 8> : pass);
-  else pass = plan.items == 16 ? radix_pass_of<K, V, false, 16> : (plan.items == 8 ? radix_pass_of<K, V, false, 8> : radix_pass_of<K, V, false, 4>);
+  auto pass = plan.items == 16 ? radix_pass_of<K, V, true, 16> : (plan.items == 8 ? radix_pass_of<K, V, true, 8> : radix_pass_of<K, V, true, 4>);
+  if constexpr (sizeof(K) == 8) {                          // (64-bit keys alone come without values)
+    if (vals_in == nullptr)
+      pass = plan.items == 16 ? radix_pass_of<K, V, false, 16> : (plan.items == 8 ? radix_pass_of<K, V, false, 8> : radix_pass_of<K, V, false, 4>);
+  }
   const K* k_from = keys_in;
   const V* v_from = vals_in;
   for (int p = 0; p < plan.passes; ++p) {

@@ -146,6 +146,25 @@ def test_optimizers_and_one_table(oracle, call, kind, n, b, k):
             assert_emb_close(got, h)
 
 
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("call,n,b,k,dim", [("momentum", 40_000, 60_000, 5, 24), ("momentum", 40_000, 60_000, 5, 136), ("momentum", 300_000, 110_000, 5, 264),
+                                            ("line1", 40_000, 60_000, 5, 24), ("line1", 300_000, 110_000, 5, 264)])
+def test_16bit_momentum_and_one_table(oracle, call, fmt, n, b, k, dim):
+    from paper_2407_15452_amd import binding as gs
+    dtype, code, lr = torch.bfloat16 if fmt == "bf16" else torch.float16, oracle.BF16 if fmt == "bf16" else oracle.F16, 5e-3
+    c, o, neg = _batch("hub", n, b, k, np.random.default_rng(dim))
+    tabs = [t.to(dtype) for t in _tables(n, dim, 4 if call == "momentum" else 1, dim)]
+    host = [t.view(torch.int16).numpy().view(np.uint16).copy() for t in tabs]
+    dev, ids = [t.to(DEV) for t in tabs], (_dev(c), _dev(o), _dev(neg))
+    if call == "momentum":
+        want, loss = oracle.sgns_momentum_step(*host, c, o, neg, lr, 0.875, dtype=code), gs.gs_sgns_momentum_step(*dev, *ids, lr, 0.875)
+    else:
+        want, loss = oracle.line1_step(*host, c, o, neg, lr, dtype=code), gs.gs_line1_step(*dev, *ids, lr)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for d, h in zip(dev, host):             # (one table: a row is rounded with its context terms, then with its source terms)
+        assert_half_close(d.view(torch.int16).cpu().numpy().view(np.uint16), h, fmt, steps=2 if call == "line1" else 1)
+
+
 def test_bad_ids_and_products_out_of_range():
     """Both turn the loss into NaN; the ids are read as row 0."""
     from paper_2407_15452_amd import binding as gs

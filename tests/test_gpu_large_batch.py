@@ -1,6 +1,7 @@
-"""The step on sorted records (batches of at least 9 * 2^19 terms, 2^20 or, with at most one negative, 2^21 on at
-most 2^16 rows) and just below, against the CPU reference: a handful of rows with everything in them, rows around the segment length (256 terms) and around slice borders,
-rows of a few terms on a large table, both table types and the one-table step."""
+"""Large steps against the CPU reference.  Up to 2^24 rows their terms are records that are grouped by row (test_gpu_grouping.py has that way's
+borders): a handful of rows with everything in them, rows around the segment length (256 terms) and around slice borders, rows of a few terms on a
+large table, both table types and the one-table step.  On more rows the records are sorted (at least 9 * 2^19 terms): rows of whole segments and
+long ones, every width of rows, both tables or one, negatives drawn and pairs made in the call."""
 import numpy as np
 import pytest
 import torch
@@ -90,3 +91,78 @@ def test_reports_bad_ids_and_repeats_the_bits():
     assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
     neg[b // 2, 1] = n
     assert np.isnan(float(gs.gs_sgns_step(*runs[0], _dev(c), _dev(o), _dev(neg), 1e-3).item()))
+
+
+SORTED_ROWS = (1 << 24) + 1                 # the fewest that are not grouped
+
+
+def _whole_segments(rows, count, rng):
+    """Ids in any order, of which each has up to three terms, or up to two more or less than one, two or seventeen segments of 256."""
+    sizes = rng.choice([1, 2, 3, 254, 255, 256, 257, 258, 511, 512, 513, 4352, 4355], count // 100 + 200,
+                       p=[.3, .2, .1, .04, .06, .06, .06, .04, .03, .04, .03, .02, .02])
+    ids = np.repeat(rng.permutation(rows[:sizes.size]), sizes)[:count]
+    assert sizes.size <= rows.size and ids.size == count
+    return rng.permutation(ids).astype(np.int32)
+
+
+@pytest.mark.parametrize("call,fmt,dim", [("step", "f32", 4), ("step", "f32", 132), ("step", "f16", 264), ("step", "bf16", 520), ("step", "f32", 516),
+                                          ("line1", "f32", 8), ("line1", "bf16", 264)])
+def test_sorted_records(oracle, call, fmt, dim):
+    """Rows of up to 256, 1024, 2048 and 4096 bytes.  The reference's tables hold the rows that the batch names; all others
+    have to come out as they went in."""
+    from paper_2407_15452_amd import binding as gs
+    n, k, b = SORTED_ROWS, 5, 786_433
+    rng = np.random.default_rng(dim)
+    named = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 60_000)]))
+    rows = rng.permutation(named.size)                     # rows of the reference's tables
+    terms = _whole_segments(rows, b * (k + 1), rng).reshape(b, k + 1)
+    o, neg = np.ascontiguousarray(terms[:, 0]), np.ascontiguousarray(terms[:, 1:])
+    c = np.repeat(_whole_segments(rows, b // 3 + 1, rng), 3)[:b]
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt]
+
+    def table(seed):
+        return torch.rand((n, dim), generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV).sub_(0.5).mul_(0.6).to(tdt)
+
+    tabs = [table(i) for i in range(1 if call == "line1" else 2)]
+    at = _dev(named)
+    host = [t[at].cpu().numpy() if fmt == "f32" else t[at].view(torch.int16).cpu().numpy().view(np.uint16) for t in tabs]
+    ids = [_dev(named[x].astype(np.int32)) for x in (c, o, neg)]
+    lr, code = 0.02, {"f32": oracle.F32, "bf16": oracle.BF16, "f16": oracle.F16}[fmt]
+    if call == "line1":
+        want, loss = oracle.line1_step(*host, c, o, neg, lr, dtype=code), gs.gs_line1_step(*tabs, *ids, lr)
+    else:
+        want, loss = oracle.sgns_step(*host, c, o, neg, lr, dtype=code), gs.gs_sgns_step(*tabs, *ids, lr)
+    assert abs(float(loss.item()) - want) <= LOSS_RTOL * abs(want)
+    for i, (t, h) in enumerate(zip(tabs, host)):
+        got = t[at].cpu()
+        if fmt == "f32":
+            assert_emb_close(got.numpy(), h)
+        else:               # (one table: a row is rounded with its context terms, then with its source terms)
+            assert_half_close(got.view(torch.int16).numpy().view(np.uint16), h, fmt, steps=2 if call == "line1" else 1)
+        as_before = table(i)
+        as_before[at] = t[at]
+        assert torch.equal(t, as_before)
+
+
+@pytest.mark.parametrize("call", ["fused", "from_walks"])
+def test_sorted_records_of_pairs_made_in_the_call(call):
+    """Negatives drawn and pairs made in the call: the bits of the step on the same ones made before it."""
+    from paper_2407_15452_amd import binding as gs
+    n, k, dim, length, window, first = SORTED_ROWS, 7, 8, 20, 5, 3
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    walks = (torch.rand((4_000, length), generator=gen, device=DEV) ** 4 * n).to(torch.int32).clamp_(0, n - 1)
+    walks[::7, 13:] = -1
+    noise = gs.gs_alias_build(torch.tensor([0, n], dtype=torch.int64, device=DEV), torch.rand(n, generator=gen, device=DEV) ** 8)
+    c, o, pairs = gs.gs_make_pairs(walks, window)
+    b = ((9 << 19) + k) // (k + 1) + 1
+    assert pairs >= first + b
+    c, o = c[first:first + b].clone(), o[first:first + b].clone()
+    tabs = [torch.rand((n, dim), generator=gen, device=DEV).sub_(0.5) for _ in range(2)]
+    mine = [t.clone() for t in tabs]
+    loss = gs.gs_sgns_step(*tabs, c, o, gs.gs_sample_negatives(noise, n, b, k, 9, pair_index_base=77), 0.01)
+    if call == "fused":
+        own = gs.gs_sgns_step_fused(*mine, c, o, noise, k, 9, 0.01, pair_index_base=77)
+    else:
+        own = gs.gs_sgns_step_from_walks(*mine, walks, window, gs.gs_pair_offsets(walks, window), first, b, noise, k, 9, 0.01, pair_index_base=77)
+    assert float(own.item()) == float(loss.item()) and np.isfinite(float(loss.item()))
+    assert all(torch.equal(x, y) for x, y in zip(mine, tabs))

@@ -1,5 +1,5 @@
-"""The ways of one training step (two launches, counters per row or per key of the batch, sorted records)
-against the CPU reference where other files do not: every row width and storage type of the sorted records, the calls
+"""The ways of one training step (two launches, counters per row or per key of the batch, grouped records)
+against the CPU reference where other files do not: every row width and storage type of the grouped records, the calls
 that draw their negatives or make their pairs on them, counters over the keys of a batch that is too
 large or too wide for two launches, and each way against the counters in a workspace that only holds those."""
 import numpy as np
@@ -64,7 +64,7 @@ def _step(oracle, n, b, k, dim, fmt, flip_fraction=None):
 
 @pytest.mark.parametrize("dim,fmt", [(132, "f32"), (260, "f32"), (516, "f32"), (8, "f16"), (264, "f16"), (264, "bf16"),
                                      (520, "bf16")])
-def test_sorted_records_of_every_width(oracle, dim, fmt):
+def test_grouped_records_of_every_width(oracle, dim, fmt):
     """Rows of up to 512, 1024, 2048 and 4096 bytes; 2^20 terms and a few on 40,000 rows."""
     _step(oracle, 40_000, 32_769, 31, dim, fmt)
 
@@ -79,7 +79,7 @@ def test_counters_over_the_keys_of_a_batch(oracle, n, b, k, dim, fmt):
 
 
 @pytest.mark.parametrize("call", ["fused", "from_walks"])
-def test_sorted_records_made_in_the_call(oracle, call):
+def test_grouped_records_made_in_the_call(oracle, call):
     from paper_2407_15452_amd import binding as gs
     n, k, dim, length, window = 40_000, 5, 12, 20, 5
     rng = np.random.default_rng(3)
@@ -110,7 +110,7 @@ def test_sorted_records_made_in_the_call(oracle, call):
 @pytest.mark.parametrize("call,n,b,k,dim", [(call, 20_000, 1_500, 5, 256) for call in ("step", "fused", "from_walks", "momentum")] +
                          [(call, 30_000, 17_200, 60, 8) for call in ("step", "fused", "from_walks", "line1")])
 def test_smaller_workspace(call, n, b, k, dim):
-    """Two launches, and sorted records, against the counters that the least workspace leaves.  The row sums are
+    """Two launches, and grouped records, against the counters that the least workspace leaves.  The row sums are
     exact and a row is rounded at the same places, so the tables agree bit for bit, but for the centre rows of the
     two launches: their gradients are summed in fp32 over two pairs of a run at a time instead of four."""
     from paper_2407_15452_amd import binding as gs
