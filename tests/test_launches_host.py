@@ -242,6 +242,16 @@ def test_steps_beyond_the_buckets(launches, call, pairs, nodes, how):
     assert ("group_bucket_kernel" in names, "radix_scatter_kernel" in names) == (how == "group", how == "radix")
 
 
+@pytest.mark.parametrize("n,nodes,few", [(1 << 20, 60_000, 1), ((1 << 20) + 1, 60_000, 0), (1 << 19, (1 << 20) - 1, 1), ((1 << 19) + 1, (1 << 20) - 1, 0),
+                                         (9_000, 1, 0), (9_000, 3, 1)])
+def test_scans_of_a_sort(launches, n, nodes, few):
+    got, rc = launches("p = [C.c_void_p(1 << (20 + i)) for i in range(5)]\nrc = lib.gs_sort_pairs(*p[:2], C.c_int64(%d), C.c_int64(%d), *p[2:], C.c_size_t(1 << 50), None)\n"
+                       "print(json.dumps({'rc': rc}))\n" % (n, nodes))
+    assert rc == [0]
+    scans = [x for x in got if "radix_scan" in x[0]]
+    assert scans and all(("radix_scan_few_kernel" in x[0], x[4]) == ((True, 256) if few else (False, 1024)) for x in scans), scans
+
+
 @pytest.mark.parametrize("pairs,nodes,k,dim,bytes", [
     (2_000_000, 4_000_000, 5, 128, 1_448_071_680), (200_000, 60_000, 5, 64, 96_867_840), (1_100_000, 5_000, 1, 32, 224_405_248),
     (1_100_000, 100_000, 5, 64, 483_285_504)])
