@@ -319,17 +319,15 @@ __device__ __forceinline__ RawRow<T, VPL> inside_row(const RawRow<T, VPL>& x, in
   return y;
 }
 
-// an input row, widened; zeros behind its end, where an infinity of the last piece would meet the zeros of inside_row
+// an input row, widened, and as it is stored; zeros behind its end, where an infinity of the last piece would meet the zeros of inside_row
 template <int VPL>
-__device__ __forceinline__ void load_center(const float* __restrict__ table, int64_t row, int dim, int l16, float4 (&u)[VPL]) {
-  RawRow<float, VPL> x;
+__device__ __forceinline__ void load_center(const float* __restrict__ table, int64_t row, int dim, int l16, RawRow<float, VPL>& x, float4 (&u)[VPL]) {
   load_raw<VPL>(table, row, dim, l16, x);
 #pragma unroll
   for (int v = 0; v < VPL; ++v) u[v] = x.r[v];
 }
 template <int VPL, typename T, if_16bit<T> = 0>
-__device__ __forceinline__ void load_center(const T* __restrict__ table, int64_t row, int dim, int l16, float4 (&u)[VPL]) {
-  RawRow<T, VPL> x;
+__device__ __forceinline__ void load_center(const T* __restrict__ table, int64_t row, int dim, int l16, RawRow<T, VPL>& x, float4 (&u)[VPL]) {
   load_raw<VPL>(table, row, dim, l16, x);
   x = inside_row<VPL>(x, dim, l16);
 #pragma unroll
@@ -684,13 +682,11 @@ __global__ __launch_bounds__(kThreads, kWaves) void sgns_forward_kernel(SgnsArgs
         peak = fmaxf(peak, row_peak<VPL>(du));
         stage_flush<T, VPL, kGroup>(a, first + flushes++, cur_c, l16, du);
       }
-      load_center<VPL>(w_in, c, a.dim, l16, u);
+      RawRow<T, VPL> keep;
+      load_center<VPL>(w_in, c, a.dim, l16, keep, u);
       peak = fmaxf(peak, row_peak<VPL>(u));
-      if (a.snap != nullptr) {              // one-table mode: keep the row as it is now
-        RawRow<T, VPL> keep;
-        load_raw<VPL>(w_in, c, a.dim, l16, keep);
-        store_raw<VPL>(static_cast<T*>(a.snap), first + flushes, a.dim, l16, keep);
-      }
+      // one-table mode: keep the row as it is now
+      if (a.snap != nullptr) store_raw<VPL>(static_cast<T*>(a.snap), first + flushes, a.dim, l16, keep);
       zero<VPL>(du);
       cur_c = c;
     }
