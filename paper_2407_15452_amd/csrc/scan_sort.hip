@@ -234,10 +234,10 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__
 }
 
 // The same for few tiles, where a launch takes as long as its chain of reads, sums and writes: a workgroup takes four digits, a lane those of one
-// or two tiles.  us, against the kernel above: 256 digits of 40 tiles 3.2 / 4.0, of 290 3.9 / 5.3, of 490 4.5 / 5.3; 1024 digits of 150
+// to three tiles.  us, against the kernel above: 256 digits of 40 tiles 3.2 / 4.0, of 290 3.9 / 5.3, of 490 4.5 / 5.3; 1024 digits of 150
 // tiles 3.9 / 5.4, of 680 6.3 / 5.4.  With the tiles above, which were slower for a million records and less than counts by digit and tiles in turn: CSR of
 // 300,000 edges 122 -> 116 us (115 then).
-constexpr int kFewEach = 2, kFewThreads = 256;
+constexpr int kFewEach = 3, kFewThreads = 256;
 constexpr int64_t kFewCounts = 1 << 18;
 __global__ __launch_bounds__(kFewThreads) void radix_scan_few_kernel(uint32_t* __restrict__ counts, int num_tiles, uint32_t digits,
                                                                      uint32_t* __restrict__ totals) {

@@ -55,10 +55,10 @@ def test_sort_pairs_in_wide_digits(gs, n, num_nodes):
         np.testing.assert_array_equal(got_c.cpu().numpy(), c[at])
 
 
-@pytest.mark.parametrize("n,num_nodes", [(1 << 20, 60_000), ((1 << 20) + 1, 60_000), (1 << 19, (1 << 20) - 1), ((1 << 19) + 1, (1 << 20) - 1),
+@pytest.mark.parametrize("n,num_nodes", [(1 << 20, 60_000), ((1 << 20) + 1, 60_000), ((3 << 19) - 1, 60_000), (3 << 20, 60_000), ((3 << 20) + 1, 60_000), (1 << 19, (1 << 20) - 1), ((1 << 19) + 1, (1 << 20) - 1),
                                          (300_001, 60_000), (300_001, 3), (40_000, 2)])
 def test_sort_pairs_of_few_tiles(gs, n, num_nodes):
-    """Both sides of the most counts that the scan for few tiles takes: 512 tiles of 256 digits, 256 of 1024; digits of one and two bits."""
+    """Both sides of the most counts that the scan for few tiles takes: 768 tiles of 256 digits, 256 of 1024; digits of one and two bits."""
     test_sort_pairs_sizes(gs, n, num_nodes)
 
 

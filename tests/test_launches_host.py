@@ -242,7 +242,7 @@ def test_steps_beyond_the_buckets(launches, call, pairs, nodes, how):
     assert ("group_bucket_kernel" in names, "radix_scatter_kernel" in names) == (how == "group", how == "radix")
 
 
-@pytest.mark.parametrize("n,nodes,few", [(1 << 20, 60_000, 1), ((1 << 20) + 1, 60_000, 0), (1 << 19, (1 << 20) - 1, 1), ((1 << 19) + 1, (1 << 20) - 1, 0),
+@pytest.mark.parametrize("n,nodes,few", [((3 << 19) - 1, 60_000, 1), (3 << 19, 60_000, 1), (3 << 20, 60_000, 1), ((3 << 20) + 1, 60_000, 0), (1 << 19, (1 << 20) - 1, 1), ((1 << 19) + 1, (1 << 20) - 1, 0),
                                          (9_000, 1, 0), (9_000, 3, 1)])
 def test_scans_of_a_sort(launches, n, nodes, few):
     got, rc = launches("p = [C.c_void_p(1 << (20 + i)) for i in range(5)]\nrc = lib.gs_sort_pairs(*p[:2], C.c_int64(%d), C.c_int64(%d), *p[2:], C.c_size_t(1 << 50), None)\n"
